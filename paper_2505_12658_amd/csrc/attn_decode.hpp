@@ -1,0 +1,371 @@
+// Attention of decode steps over the paged KV cache (gfx950): few rows, long contexts, HBM-bound.
+//
+// All (new token, query head) pairs of one (request, KV head) form ONE tile of at most 16 rows, so the context
+// is read once per KV head.  The waves of a workgroup split the keys: wave w takes the blocks of 32 keys
+// w, w + W, w + 2 W, ... of the workgroup's share, and the partial results (row maximum, row sum, unnormalised
+// output) are merged through LDS at the end.
+//
+// The contractions are
+//   S^T[key, row] = K Q^T        v_mfma_f32_16x16x32_bf16, A = K, B = Q
+//   O^T[c, row]  += V^T P^T      the same instruction, A = V^T, B = P^T
+// and both K and V come from memory in load instructions that cover whole rows (4 rows of 256 bytes at head_dim 128):
+//   - K goes through a stage of the wave's own in LDS, where it is read back in the layout of the A operand, lane
+//     (m, h) = (lane % 16, lane / 16) holding 16-byte piece 4 s + h of key m in step s.
+//   - V stays in registers.  Lane (m, h) loads, for each of the eight keys it contributes to a block of 32, its D / 16
+//     columns m D/16 .., and one v_perm_b32 per register turns that 8 x (D / 16) block of bf16 into the
+//     eight-keys-per-column order of the A operand.  The matrix instruction that takes column u of every lane's block
+//     yields output columns m D/16 + u.
+// In the result layout of the first contraction lane (m, h) has row m and keys 4 h .. 4 h + 3 of both halves of 16; as
+// the B operand of the second a lane owns eight keys of its row, and which eight is free as long as V uses the same:
+// so P stays where it is.
+//
+// What bounds it: memory.  Reading rows of 256 bytes, scattered in pages of 16, this chip gives 6.4 TB/s with
+// non-temporal loads and 5.7 without; 16 rows x 64 bytes per instruction (K straight in the operand layout, no LDS)
+// gave 5.5 and 4.9, and was built first.  A compute unit gets at most 48 GB/s of a stream that comes from HBM, four
+// waves with one block of 32 keys (16 KB) in flight each are enough for that, and a second block in flight per wave
+// made the whole chip slower (5.2 - 5.7 TB/s).  So a wave keeps one block in flight: the K registers are refilled as soon as
+// they are staged, the V registers as soon as the product is out.
+// Against the form for up to 32 rows (32 x 32 tiles, in attn_paged.hpp), us: 96 requests of 128 .. 1782 tokens, 28 / 4
+// heads of 128, 41.5 -> 35.7 (150 MB); 33 requests of 600 .. 1100 tokens, 32 / 32 heads, 83.8 -> 79.7 (475 MB, 5.9 TB/s);
+// 4 requests of 300 .. 1200 tokens 12.3 -> 5.5, in 16 shares instead of 2.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "attn_tiles.hpp"
+#include "paged_args.hpp"
+
+namespace hydra {
+namespace paged {
+
+constexpr int kDecodeRows = 16;  // rows (new tokens x grouped heads) of a decode tile
+constexpr int kDecodeKeys = 32;  // keys per step
+
+// Floats of LDS per wave and row of partial output (padded: the rows of a wave start in different banks).
+template <int D>
+constexpr int kDecodeRowFloats = D + 4;
+
+// A wave's slot in LDS: its stage of 32 rows of K during the loop, its partial output for the merge.
+template <int D>
+constexpr int kDecodeSlotFloats = kDecodeRows * kDecodeRowFloats<D> > kDecodeKeys * D / 2 ? kDecodeRows * kDecodeRowFloats<D> : kDecodeKeys * D / 2;
+template <int D>
+constexpr size_t kDecodeLdsPerWave = (kDecodeSlotFloats<D> + 2 * kDecodeRows) * sizeof(float);
+
+#if defined(__HIP_DEVICE_COMPILE__)
+
+typedef const __attribute__((address_space(4))) int32_t* const_table_t;
+
+// The same value of all four lanes l, l ^ 16, l ^ 32, l ^ 48 combined with `op`.
+template <typename Op>
+__device__ __forceinline__ float over_row_lanes(float x, Op op) {
+  float r0, r1;
+  own_and_other_half(x, r0, r1);
+  x = op(r0, r1);
+  // (as own_and_other_half, between the odd and the even rows of 16 lanes)
+  float a = x, b = x;
+  asm volatile("s_nop 3\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 3" : "+v"(a), "+v"(b));
+  return op(a, b);
+}
+
+// A wave's state for one tile of up to 16 rows, and its walk over keys.
+template <int D>
+struct DecodeWave {
+  static constexpr int KS = D / 32;          // 32-wide steps of the QK contraction
+  static constexpr int CW = D / 16;          // columns of V per lane, units of the PV contraction
+  static constexpr int VW = CW / 2;          // registers per V row of a lane
+  static constexpr int RL = D / 8;           // lanes per K row (16 bytes each)
+  static constexpr int KL = 16 * RL / 64;    // load instructions per 16 rows of K
+  static constexpr int ROWB = D * 2;
+  typedef __attribute__((ext_vector_type(VW))) uint32_t vrow_t;
+
+  bf16x8_t q[KS];
+  f32x4_t o[CW];
+  float row_max, row_sum;  // maximum over all lanes of the row, this lane's part of the sum
+  u32x4_t kreg[2][KL];     // [half of 16 keys]: rows lane / RL + u 64 / RL, piece lane % RL
+  vrow_t vreg[2][4];       // [half of 16 keys][key 4 h + j]
+  uint64_t k_base, v_base; // this KV head's part of cache row 0
+  uint32_t row_bytes, k_off, v_off;
+  int k_chunk, k_row;
+  uint32_t k_put, k_get[KS]; // LDS addresses of this lane's pieces of the wave's K stage
+  int kv_len, block_shift, last_block;
+
+  __device__ __forceinline__ void init(const uint16_t* k_cache, const uint16_t* v_cache, int n_kv_heads, int kv_head, int kv_len_, int block_shift_,
+                                       int num_blocks, const uint16_t* q_row, uint32_t stage, int lane) {
+    const int m = lane & 15, h = lane >> 4;
+    k_base = (uint64_t)(uintptr_t)(k_cache + (int64_t)kv_head * D);
+    v_base = (uint64_t)(uintptr_t)(v_cache + (int64_t)kv_head * D);
+    row_bytes = (uint32_t)n_kv_heads * (D * 2);
+    const int kr = lane / RL, kc = lane % RL;
+    k_off = (uint32_t)kr * row_bytes + kc * 16;
+    k_put = stage + kr * ROWB;
+    k_chunk = kc;
+    k_row = kr;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) k_get[s] = stage + m * ROWB + k_swizzle<D>(m, 4 * s + h) * 16;
+    v_off = (uint32_t)(4 * h) * row_bytes + m * (CW * 2);
+    kv_len = kv_len_;
+    block_shift = block_shift_;
+    last_block = num_blocks - 1;
+    row_max = -3.0e38f;
+    row_sum = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) q[s] = *reinterpret_cast<const bf16x8_t*>(q_row + (4 * s + h) * 8);
+#pragma unroll
+    for (int u = 0; u < CW; ++u) o[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  // Descriptor of the 16 rows that start at key `key` (a multiple of 16), which lie in cache block `block`: it ends
+  // with the last row of the context, so rows past it (and whole groups past it) arrive as zeros.
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows16(uint64_t base, int block, int key) const {
+    const uint32_t slot = ((uint32_t)block << block_shift) + ((uint32_t)key & ((1u << block_shift) - 1u));
+    int valid = kv_len - key;
+    valid = valid > 16 ? 16 : valid;
+    const uint32_t bytes = valid > 0 ? (uint32_t)(valid - 1) * row_bytes + D * 2 : 0u;
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base + (uint64_t)slot * row_bytes), 0, (int)bytes, 0x00020000);
+  }
+  // (nt: every key of a context is read by one wave only)
+  __device__ __forceinline__ void load_k(int half, int block, int key) {
+    const __amdgpu_buffer_rsrc_t r = rows16(k_base, block, key);
+#pragma unroll
+    for (int u = 0; u < KL; ++u) kreg[half][u] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)k_off, u * (64 / RL) * (int)row_bytes, 2);
+  }
+  __device__ __forceinline__ void stage_k() const {
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int u = 0; u < KL; ++u) {
+        const int row = 16 * half + u * (64 / RL);
+        *reinterpret_cast<u32x4_t*>(HYDRA_LDS_BYTE(k_put + row * ROWB + k_swizzle<D>(row + k_row, k_chunk) * 16)) = kreg[half][u];
+      }
+  }
+  __device__ __forceinline__ void load_v(int half, int block, int key) {
+    const __amdgpu_buffer_rsrc_t r = rows16(v_base, block, key);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (VW == 4) vreg[half][j] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)v_off, j * (int)row_bytes, 2);
+      else vreg[half][j] = __builtin_amdgcn_raw_buffer_load_b64(r, (int)v_off, j * (int)row_bytes, 2);
+    }
+  }
+
+  // S^T of the block of 32 keys in kreg: s[half], keys 16 half + 4 h + r of row m
+  __device__ __forceinline__ void scores(f32x4_t (&s)[2]) const {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) s[half] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+        {
+        const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(HYDRA_LDS_BYTE(k_get[st] + half * 16 * ROWB));
+        s[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, q[st], s[half], 0, 0, 0);
+      }
+  }
+  // Online softmax of the block whose first key is key0: P in bf16, O and the sums rescaled.
+  __device__ __forceinline__ bf16x8_t softmax(f32x4_t (&s)[2], int key0, int lim, float c, int h) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (key0 + 16 * half + 4 * h + r > lim) s[half][r] = -__builtin_inff();
+    float top = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    top = over_row_lanes(top, [](float x, float y) { return fmaxf(x, y); });
+    // (a row whose keys are all masked so far keeps the initial, very negative maximum: its exponentials are 0)
+    const float m_new = fmaxf(row_max, top);
+    const float alpha = fast_exp2((row_max - m_new) * c);
+    row_max = m_new;
+    const float mc = m_new * c;
+    bf16x8_t p;
+    float sum = 0.f;
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int r = 0; r < 4; r += 2) {
+        const f32x2_t e = {fast_exp2(__builtin_fmaf(s[half][r], c, -mc)), fast_exp2(__builtin_fmaf(s[half][r + 1], c, -mc))};
+        sum += e[0];
+        sum += e[1];
+        const bf16x2_t b = __builtin_convertvector(e, bf16x2_t);
+        p[4 * half + r] = b[0];
+        p[4 * half + r + 1] = b[1];
+      }
+    row_sum = row_sum * alpha + sum;
+#pragma unroll
+    for (int u = 0; u < CW; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[u][r] *= alpha;
+    return p;
+  }
+  // O^T += V^T P^T for the block in vreg
+  __device__ __forceinline__ void product(const bf16x8_t& p) {
+#pragma unroll
+    for (int u = 0; u < CW; ++u) {
+      // column u of the lane's block: low or high halves of register u / 2 of the eight rows, two rows per register
+      const uint32_t sel = u % 2 ? 0x07060302u : 0x05040100u;
+      u32x4_t a;
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) a[2 * half + j / 2] = __builtin_amdgcn_perm(vreg[half][j + 1][u / 2], vreg[half][j][u / 2], sel);
+      o[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), p, o[u], 0, 0, 0);
+    }
+  }
+};
+
+// One workgroup's share of one (request, KV head): all of it, its output included, when the context fits one share,
+// otherwise a partial result for the combine kernel.  Called by all n_waves waves; lds: n_waves * kDecodeLdsPerWave<D>
+// bytes, 16-byte aligned.  Does nothing for a request that has no new tokens or more than kDecodeRows rows.
+template <int D>
+__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int b, int kv_head, int split) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, h = lane >> 4;
+  float* s_max = lds;
+  float* s_sum = s_max + n_waves * kDecodeRows;
+  float* s_slots = s_sum + n_waves * kDecodeRows;
+
+  const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
+  const int q_start = cu[b];
+  const int q_len = cu[b + 1] - q_start;
+  int kv_len = lens[b];
+  const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;
+  if (kv_len > table_keys) kv_len = (int)table_keys;
+  if (q_len <= 0 || kv_len < q_len || q_len * a.group > kDecodeRows) return;
+  const int n_rows = q_len * a.group;
+
+  const int n_halves = (kv_len + kDecodeKeys - 1) / kDecodeKeys;
+  int begin, end, per_share, n_shares;
+  share_plan(n_halves, a.halves_per_split, per_share, n_shares);
+  split_range(n_halves, per_share, split, begin, end);
+  if (begin >= end) return;  // past the context's last share: the combine kernel knows and skips it
+
+  // this lane's row
+  const int row = m < n_rows ? m : n_rows - 1;
+  const int token = row / a.group;
+  const int head = kv_head * a.group + (row - token * a.group);
+  const int lim = kv_len - q_len + token;  // largest visible key
+  const float c = a.scale_log2;
+
+  const int steps = begin + wave < end ? (end - begin - wave + n_waves - 1) / n_waves : 0;
+  DecodeWave<D> w;
+  w.init(a.k_cache, a.v_cache, a.n_kv_heads, kv_head, kv_len, a.block_shift, a.num_blocks, a.q + (int64_t)(q_start + token) * a.q_stride + head * D,
+         (uint32_t)(uintptr_t)HYDRA_LDS_PTR(s_slots + wave * kDecodeSlotFloats<D>), lane);
+  if (steps > 0) {
+    // Block-table entries of the wave's next 32 steps: lane 2 i + half has the entry of that half of step i
+    // (one load; the loop takes them from there lane by lane).  Ids are clamped to the cache, so that a corrupt
+    // table cannot make the loads leave it; entries past the context are not read.
+    const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
+    const int last_entry = (kv_len - 1) >> a.block_shift;
+    auto entries = [&](int first_step) {
+      const int key = (begin + wave + n_waves * (first_step + (lane >> 1))) * kDecodeKeys + 16 * (lane & 1);
+      int e = key >> a.block_shift;
+      e = e < last_entry ? e : last_entry;
+      const int id = table[e];
+      return id < 0 ? 0 : (id > w.last_block ? w.last_block : id);
+    };
+    int ids = entries(0);
+    auto key_of = [&](int i) { return (begin + wave + n_waves * i) * kDecodeKeys; };
+    auto id_of = [&](int i, int half) { return __builtin_amdgcn_readlane(ids, 2 * (i & 31) + half); };
+#pragma unroll
+    for (int half = 0; half < 2; ++half) w.load_k(half, id_of(0, half), key_of(0) + 16 * half);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) w.load_v(half, id_of(0, half), key_of(0) + 16 * half);
+    for (int i = 0; i < steps; ++i) {
+      f32x4_t s[2];
+      w.stage_k();
+      // (the loads of a step that does not exist are issued all the same, with nothing in range: a branch around
+      // them would make the compiler wait for everything in flight where the paths meet again)
+      if ((i & 31) == 31) ids = entries(i + 1);
+      const int b0 = id_of(i + 1, 0), b1 = id_of(i + 1, 1), next = i + 1 < steps ? key_of(i + 1) : kv_len;
+      w.load_k(0, b0, next);
+      w.load_k(1, b1, next + 16);
+      __builtin_amdgcn_sched_barrier(0);
+      w.scores(s);
+      const bf16x8_t p = w.softmax(s, key_of(i), lim, c, h);
+      __builtin_amdgcn_sched_barrier(0);
+      w.product(p);
+      __builtin_amdgcn_sched_barrier(0);
+      w.load_v(0, b0, next);
+      w.load_v(1, b1, next + 16);
+    }
+  }
+
+  // ---- merge: every wave leaves its rows' maximum, sum and unnormalised output ----
+  constexpr int RF = kDecodeRowFloats<D>;
+  constexpr int CW = DecodeWave<D>::CW;
+  __builtin_amdgcn_sched_barrier(0);
+  const float total_own = over_row_lanes(w.row_sum, [](float x, float y) { return x + y; });
+  if (h == 0) {
+    s_max[wave * kDecodeRows + m] = w.row_max;
+    s_sum[wave * kDecodeRows + m] = total_own;
+  }
+  if (m < n_rows) {
+    float* mine = s_slots + wave * kDecodeSlotFloats<D> + m * RF;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int u = 0; u < CW; u += 4)  // columns (4 h + r) CW + u ..
+        *reinterpret_cast<f32x4_t*>(mine + (4 * h + r) * CW + u) = f32x4_t{w.o[u][r], w.o[u + 1][r], w.o[u + 2][r], w.o[u + 3][r]};
+  }
+  __syncthreads();
+  const bool whole = n_halves <= a.halves_per_split;  // the context fits one share: this workgroup writes the output
+  constexpr int kCols = D / 4;
+  for (int i = threadIdx.x; i < n_rows * kCols; i += 64 * n_waves) {
+    const int r = i / kCols, col = (i - r * kCols) * 4;
+    float top = s_max[r];
+    for (int o = 1; o < n_waves; ++o) top = fmaxf(top, s_max[o * kDecodeRows + r]);
+    float total = 0.f;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < n_waves; ++o) {
+      // (a wave that saw no key of this row still holds the initial maximum: weight 0)
+      const float weight = fast_exp2((s_max[o * kDecodeRows + r] - top) * c);
+      total += weight * s_sum[o * kDecodeRows + r];
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(s_slots + o * kDecodeSlotFloats<D> + r * RF + col);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += weight * v[e];
+    }
+    if (whole) {
+      const int tok = r / a.group, hd = kv_head * a.group + (r - tok * a.group);
+      const float inv = 1.0f / total;
+      const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
+      const u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
+                          __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2_t))};
+      *reinterpret_cast<u32x2_t*>(a.out + ((int64_t)(q_start + tok) * a.n_q_heads + hd) * D + col) = pk;
+    } else {
+      float* rec = a.partials + (((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits + split) * kPartialFloats<D>;
+      if (col == 0) {
+        rec[r] = top;
+        rec[kRows + r] = total;
+      }
+      *reinterpret_cast<f32x4_t*>(rec + 2 * kRows + r * D + col) = acc;
+    }
+  }
+}
+
+#endif  // __HIP_DEVICE_COMPILE__
+
+// Whether requests of `rows` rows take this form (the 16 keys of half a step lie in one cache block).
+template <int D>
+constexpr bool kDecodeForm = D == 64 || D == 128;
+constexpr int kDecodeMinBlock = 16;
+
+// Waves per SIMD the kernel is built for (168 registers each).
+constexpr int kDecodeWavesPerSimd = 3;
+constexpr int kDecodeMaxWaves = 8;
+
+// grid = batch * n_kv_heads * n_splits workgroups, share-major (the first shares of all pairs, which every request
+// has, then the second shares, ...); dynamic LDS: waves * kDecodeLdsPerWave<D> bytes.
+template <int D>
+__global__ __launch_bounds__(64 * kDecodeMaxWaves) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd, kDecodeWavesPerSimd))) void attn_decode_kernel(
+    const PagedArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) float s_decode[];
+  const int pairs = a.batch * a.n_kv_heads;
+  const int split = (int)blockIdx.x / pairs, pair = (int)blockIdx.x - split * pairs;
+  const int b = pair / a.n_kv_heads;
+  run_decode<D>(a, s_decode, (int)blockDim.x >> 6, b, pair - b * a.n_kv_heads, split);
+#else
+  (void)a;
+#endif
+}
+
+}  // namespace paged
+}  // namespace hydra

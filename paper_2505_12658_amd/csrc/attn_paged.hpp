@@ -16,8 +16,9 @@
 // fetched while tile t is used.  Scores are kept transposed (S^T = K Q^T, O^T += V^T P^T, as in the
 // packed kernel) and the softmax is the textbook online one: running maximum and rescaling at every
 // tile.  Two workgroups per compute unit.
-// Requests with few new tokens (decode steps above all) take a second form, in which the rows of ALL the
-// query heads of a KV head share one tile and the four waves split the keys: see run_packed_rows.
+// Requests with few new tokens (decode steps above all) take another form, in which the rows of ALL the query heads of
+// a KV head share one tile and the four waves split the keys: attn_decode.hpp where there are at most 16 rows and the
+// cache layout allows, run_packed_rows otherwise.
 // When the batch is small for the chip or its contexts are long, the packed-rows form also splits a context
 // over several workgroups and a second, small kernel merges their partial results (see n_splits).
 // Groups of wave tiles run on the packed kernel's software pipeline where the cache layout allows (PagedSource);
@@ -27,60 +28,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_decode.hpp"
 #include "attn_fwd.hpp"
 #include "attn_tiles.hpp"
+#include "paged_args.hpp"
 
 namespace hydra {
 namespace paged {
-
-constexpr int kRows = 32;          // new tokens (or packed rows) per wave tile
-constexpr int kWavesPerGroup = 4;  // wave tiles per workgroup
-
-struct PagedArgs {
-  const uint16_t* q;        // [total_q, n_q_heads, D] with token stride
-  uint16_t* out;            // [total_q, n_q_heads, D] contiguous
-  int64_t q_stride;         // elements per token
-  const uint16_t* k_cache;  // [num_blocks, block_size, n_kv_heads, D]
-  const uint16_t* v_cache;
-  const int32_t* block_tables;  // [batch, max_blocks_per_seq]
-  const int32_t* cu_seqlens_q;  // [batch + 1]
-  const int32_t* kv_lens;       // [batch]
-  int32_t max_blocks_per_seq;
-  int32_t num_blocks;
-  int32_t block_shift;  // log2(block_size)
-  int32_t n_q_heads;
-  int32_t n_kv_heads;
-  int32_t group;     // n_q_heads / n_kv_heads
-  float scale_log2;  // softmax_scale * log2(e)
-  // Packed-rows form, long contexts split over workgroups: a context of more than halves_per_split half tiles
-  // (32 keys each) is cut into the fewest shares that fit that size, all of (nearly) the same length (share_plan);
-  // n_splits workgroups per (request, KV head), one per share.  A context that fits one share is done by its first
-  // workgroup, which writes `out` itself (the others leave at once); of a longer one every share leaves a partial
-  // result in `partials`, and the combine kernel merges them.  n_splits == 1: never split.
-  int32_t n_splits;
-  int32_t halves_per_split;
-  float* partials;  // [batch, n_kv_heads, n_splits] records of kPartialFloats<D> floats
-  int32_t batch;
-  int32_t n_tile_wgs;  // workgroups of the wave-tile form at the end of the grid (an upper bound from the host)
-};
-
-// One partial result of the packed-rows form: per row (32 rows) the maximum and the sum, then the
-// unnormalised output rows [32][D] (only the first q_len * group rows are written and read).
-template <int D>
-constexpr int kPartialFloats = 2 * kRows + kRows * D;
-
-// How a context of n_halves half tiles is cut: `shares` shares of `per` half tiles (the last one may be shorter);
-// one share when it fits halves_per_split.
-__device__ __forceinline__ void share_plan(int n_halves, int halves_per_split, int& per, int& shares) {
-  const int k = (n_halves + halves_per_split - 1) / halves_per_split;
-  per = k > 1 ? (n_halves + k - 1) / k : n_halves;
-  shares = per > 0 ? (n_halves + per - 1) / per : 0;
-}
-// half tiles [begin, end) of share s (empty past the last share)
-__device__ __forceinline__ void split_range(int n_halves, int per, int s, int& begin, int& end) {
-  begin = s * per < n_halves ? s * per : n_halves;
-  end = begin + per < n_halves ? begin + per : n_halves;
-}
 
 template <int D>
 struct StageGeom : RowGeom<D> {
@@ -642,6 +596,9 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
 // Both forms live in one kernel so that the decode requests and the prefill chunks of a batch run side by
 // side on the chip; two workgroups per compute unit (a wave keeps within 256 registers, a workgroup within
 // half of the LDS).
+constexpr int kFirstLayer = 256;  // compute units: workgroups i and i + 256 of a grid share one
+constexpr int kLongChain = 8;     // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
+
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_paged_kernel(const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -649,6 +606,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int kLds = G::kLdsBytes > TileGeom<D>::kLdsBytes ? G::kLdsBytes : TileGeom<D>::kLdsBytes;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
   __shared__ float s_stats[2 * kWavesPerGroup * 64];
+  if constexpr (kDecodeForm<D>) static_assert(kWavesPerGroup * kDecodeLdsPerWave<D> <= (size_t)kLds, "the decode form fits the tile stages");
 
   // new tokens and context of request b (context cut to what the table can describe; q_len 0: nothing to do,
   // also for a context shorter than its new tokens, which is invalid)
@@ -661,8 +619,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   int b, kv_head, f0 = 0;
   const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;
-  if ((int)blockIdx.x < n_rows_wgs) {
-    const int r = (int)blockIdx.x;
+  // This workgroup's place in the order above.  Where the decode steps fill the first layer of the chip (256 units) and
+  // part of the second, the second layer's remaining slots go to the longest chunk chains, and a chain that shares its
+  // unit with a decode step crawls: the decode step keeps the unit's memory path full (a key tile takes the chain 2.2 us
+  // instead of 1.5).  When the batch has long chains, those slots are moved: c chains end the first layer and c lie
+  // above them in the second, so that chains share units with chains and decode steps with decode steps (96 decode
+  // steps and 4 chunks of 512 with up to 3 chunks behind them: 71.3 -> 62 us; over 48 mixes +5 %, from +17 to -3).
+  // Without long chains the decode steps are what the kernel waits for, and they stay in front.
+  int place = (int)blockIdx.x;
+  {
+    const int c = ((kFirstLayer * 2 - n_rows_wgs) / 2) & ~7;  // (a multiple of 8: KV heads keep their dies)
+    const int id = (int)blockIdx.x;
+    if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
+      bool far = false;
+      for (int r = (int)threadIdx.x; r < a.batch; r += 256) {
+        int q_len, kv_len;
+        lengths_of(r, q_len, kv_len);
+        far = far || (q_len * a.group > kRows && kv_len > kLongChain * kKvTileRows);
+      }
+      if (__syncthreads_or(far)) place = id < kFirstLayer ? n_rows_wgs + id - (kFirstLayer - c) : id - c;
+    }
+  }
+  if (place < n_rows_wgs) {
+    const int r = place;
     // (share-major: the workgroups of the first shares, which every request has, lie next to each other and are dealt
     // to all dies alike; the further shares, some of them empty when contexts differ in length, come behind them)
     const int pairs = a.batch * a.n_kv_heads;
@@ -672,14 +651,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int q_len, kv_len;
     lengths_of(b, q_len, kv_len);
     if (q_len == 0 || q_len * a.group > kRows) return;
+    if constexpr (kDecodeForm<D>) {
+      if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
+        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, split);
+        return;
+      }
+    }
     run_packed_rows<D>(a, smem, s_stats, a.block_tables + (int64_t)b * a.max_blocks_per_seq, a.cu_seqlens_q[b], q_len, kv_len, kv_head, b, split);
     return;
   }
   {
     // which group of which request: see above.  Thread i adds up requests [i * per, (i + 1) * per).
     int* s_scan = reinterpret_cast<int*>(s_stats);  // [0..3] the waves' groups, [4..7] the waves' requests, [256] = request, [257] = group
-    const int target = ((int)blockIdx.x - n_rows_wgs) / a.n_kv_heads;
-    kv_head = ((int)blockIdx.x - n_rows_wgs) - target * a.n_kv_heads;
+    const int target = (place - n_rows_wgs) / a.n_kv_heads;
+    kv_head = (place - n_rows_wgs) - target * a.n_kv_heads;
     const int per = (a.batch + 255) / 256;
     auto groups_of = [&](int r, int& kv_len) {
       int q_len;
@@ -870,22 +855,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #endif
 }
 
-// Merges the partial results of the packed-rows form when contexts were split over workgroups
-// (n_splits > 1).  grid = (n_kv_heads, batch), 256 threads.  Requests that took the wave-tile form, have
-// no new tokens, or whose context fits one share (already finished by one workgroup) are skipped.
-// First the shares' row statistics go to LDS and every row's weights (exp2 of its maximum's distance to the
-// overall maximum, divided by the overall sum) are formed there; then every thread adds up 4 output
-// columns of one row over the shares.
+// Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch), kCombineThreads threads.
+// Requests that took the wave-tile form, have no new tokens, or whose context fits one share (already finished by one
+// workgroup) are skipped.  A thread adds up 4 output columns of one row over the shares; it asks for everything it
+// needs (every share's row statistics and columns) before it uses any of it, so that behind the two lengths the kernel
+// is one round trip to memory long: it runs on an idle chip, and latency is all it costs (3.8 us after a decode of 4
+// requests, 4.6 us after one of 8 x 16 384 keys, most of it launch and instruction fetch).
 constexpr int kMaxSplits = 16;
+constexpr int kCombineThreads = 256;
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_paged_combine_kernel(const PagedArgs a) {
+__global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ float s_max[kMaxSplits][kRows], s_weight[kMaxSplits][kRows];
   const int b = blockIdx.y, kv_head = blockIdx.x;
-  const int64_t q_start = a.cu_seqlens_q[b];
-  const int q_len = a.cu_seqlens_q[b + 1] - (int)q_start;
-  int kv_len = a.kv_lens[b];
+  const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
+  const int q_start = cu[b];
+  const int q_len = cu[b + 1] - q_start;
+  int kv_len = lens[b];
   const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;
   if (kv_len > table_keys) kv_len = (int)table_keys;
   if (q_len <= 0 || kv_len < q_len || q_len * a.group > kRows) return;
@@ -895,48 +881,38 @@ __global__ __launch_bounds__(256) void attn_paged_combine_kernel(const PagedArgs
   int per_share, n_shares;
   share_plan(n_halves, a.halves_per_split, per_share, n_shares);
   const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
-  // share s, row r: maximum -> s_max, sum -> s_weight (for now)
-  for (int i = threadIdx.x; i < n_shares * kRows; i += 256) {
-    const int s = i / kRows, r = i - s * kRows;
-    const bool live = r < n_rows;
-    s_max[s][r] = live ? recs[(int64_t)s * kPartialFloats<D> + r] : 0.f;
-    s_weight[s][r] = live ? recs[(int64_t)s * kPartialFloats<D> + kRows + r] : 0.f;
-  }
-  __syncthreads();
-  if (threadIdx.x < kRows) {
-    const int r = threadIdx.x;
-    float top = s_max[0][r];
-    for (int s = 1; s < n_shares; ++s) top = fmaxf(top, s_max[s][r]);
-    float total = 0.f;
-    for (int s = 0; s < n_shares; ++s) {
-      const float w = fast_exp2((s_max[s][r] - top) * a.scale_log2);
-      total += w * s_weight[s][r];
-      s_max[s][r] = w;
-    }
-    const float inv = r < n_rows ? 1.0f / total : 0.f;
-    for (int s = 0; s < n_shares; ++s) s_weight[s][r] = s_max[s][r] * inv;
-  }
-  __syncthreads();
   constexpr int kColGroups = D / 4;
-  for (int i = threadIdx.x; i < n_rows * kColGroups; i += 256) {
+  for (int i = threadIdx.x; i < n_rows * kColGroups; i += kCombineThreads) {
     const int row = i / kColGroups, col = (i - row * kColGroups) * 4;
-    const float* src = recs + 2 * kRows + row * D + col;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int s = 0; s < n_shares; ++s) {
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + (int64_t)s * kPartialFloats<D>);
-      const float w = s_weight[s][row];
-      acc[0] += w * v[0];
-      acc[1] += w * v[1];
-      acc[2] += w * v[2];
-      acc[3] += w * v[3];
+    f32x4_t v[kMaxSplits];
+    float top[kMaxSplits], sum[kMaxSplits];
+    // (shares past the last one re-read it, with weight 0: no branch between the loads)
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+      const float* rec = recs + (int64_t)(s < n_shares ? s : n_shares - 1) * kPartialFloats<D>;
+      top[s] = rec[row];
+      sum[s] = rec[kRows + row];
+      v[s] = *reinterpret_cast<const f32x4_t*>(rec + 2 * kRows + row * D + col);
     }
+    float best = top[0];
+#pragma unroll
+    for (int s = 1; s < kMaxSplits; ++s) best = fmaxf(best, top[s]);
+    float total = 0.f;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+      const float w = s < n_shares ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
+      total += w * sum[s];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += w * v[s][e];
+    }
+    const float inv = 1.0f / total;
     const int token = row / a.group;
     const int head = kv_head * a.group + (row - token * a.group);
-    f32x2_t a0 = {acc[0], acc[1]}, a1 = {acc[2], acc[3]};
+    const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
     u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
                   __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2_t))};
-    *reinterpret_cast<u32x2_t*>(a.out + ((q_start + token) * a.n_q_heads + head) * D + col) = pk;
+    *reinterpret_cast<u32x2_t*>(a.out + ((int64_t)(q_start + token) * a.n_q_heads + head) * D + col) = pk;
   }
 #else
   (void)a;

@@ -23,15 +23,19 @@ bool head_dim_supported(int d) { return d == 64 || d == 80 || d == 128; }
 // Enqueues one kernel and returns the status of THIS launch (the runtime's sticky last-error slot
 // is shared by every caller of the process and may hold somebody else's failure).
 template <typename... Params, typename... Args>
-hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, const Args&... args) {
+hipError_t launch_lds(void (*kernel)(Params...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t stream, const Args&... args) {
   static_assert(sizeof...(Params) == sizeof...(Args), "one argument per kernel parameter");
   std::tuple<Params...> vals(args...);
   return std::apply(
       [&](auto&... v) {
         void* ptrs[] = {static_cast<void*>(&v)...};
-        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, 0, stream);
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds_bytes, stream);
       },
       vals);
+}
+template <typename... Params, typename... Args>
+hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, const Args&... args) {
+  return launch_lds(kernel, grid, block, 0, stream, args...);
 }
 
 // Compute units of the current device (0 if the runtime cannot tell).  Looked up on every call:
@@ -61,21 +65,60 @@ hipError_t launch_attn(bool causal, const hydra::AttnArgs& args, unsigned comput
 // Bytes of one partial result of the paged kernel's packed-rows form.
 size_t paged_partial_bytes(int head_dim) { return (size_t)(2 * hydra::paged::kRows + hydra::paged::kRows * head_dim) * sizeof(float); }
 
-// Workgroups per (request, KV head) over which the packed-rows form of the paged kernel splits a context.
-// A function of the launch sizes alone (both the workspace-size query and the launch use it): as many as
-// fit the chip's 512 workgroup slots together (a batch that already brings 256 (request, KV head) pairs or
-// more is not split: measured, the extra workgroups and the merge then cost more than the imbalance they
-// remove), at least 512 keys per share of the longest context the block table can describe, at most 16, and
-// no more than the workspace holds.
-int paged_splits(int32_t batch, int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks_per_seq, int32_t block_size, size_t workspace_bytes) {
-  const int64_t pairs = (int64_t)batch * n_kv_heads;
-  int64_t want = 512 / pairs;
-  const int64_t by_length = ((int64_t)max_blocks_per_seq * block_size) / 512;
-  if (want > by_length) want = by_length;
-  if (want > hydra::paged::kMaxSplits) want = hydra::paged::kMaxSplits;
+// Workgroups per (request, KV head) pair over which the paged kernels split a context: of the two numbers that fill the
+// chip's 256 compute units once (first) and twice (second) with the pairs' shares, 1 each where splitting does not pay.
+// A function of the launch sizes alone: the workspace query and the launch both use it.
+//   - One compute unit fetches at most 48 GB/s of a stream from HBM, whatever its waves keep in flight, so one workgroup
+//     needs 2.7 us per 256 keys of a KV head (512 bytes each at head_dim 128), and the combine kernel costs 2.5 us: a
+//     split pays from about 600 keys saved on.
+//   - The keys per compute unit are what counts: 48 pairs of up to 3731 keys take 15.1 us in 5 shares (240 workgroups),
+//     17.5 in 6 (288: some units get two shares), 15.8 in 10 (480).
+//   - More than 256 pairs are not split: the extra workgroups and the merge cost more than the imbalance they remove.
+struct PagedSplits {
+  int once, twice;
+};
+PagedSplits paged_splits(int32_t batch, int32_t n_kv_heads, int32_t max_blocks_per_seq, int32_t block_size) {
+  constexpr int64_t kUnits = 256, kSavedKeys = 600;
+  const int64_t pairs = (int64_t)batch * n_kv_heads, keys = (int64_t)max_blocks_per_seq * block_size;
+  auto fill = [&](int64_t layers) {
+    int64_t n = layers * kUnits / pairs;
+    if (n > hydra::paged::kMaxSplits) n = hydra::paged::kMaxSplits;
+    return n < 2 || pairs > kUnits || keys - keys / n < kSavedKeys ? 1 : (int)n;
+  };
+  return {fill(1), fill(2)};
+}
+// The number of the two that leaves fewer keys to the busiest compute unit (the larger one only where it is 10 % fewer),
+// as far as the workspace holds that many partial results.
+int choose_splits(const PagedSplits& s, int64_t pairs, int32_t head_dim, size_t workspace_bytes) {
+  auto layers = [&](int64_t n) { return (pairs * n + 255) / 256; };  // shares on the busiest unit, of 1 / n of a context
+  int64_t n = layers(s.twice) * s.once * 10 < layers(s.once) * s.twice * 9 ? s.twice : s.once;
   const int64_t fits = (int64_t)(workspace_bytes / (paged_partial_bytes(head_dim) * (size_t)pairs));
-  if (want > fits) want = fits;
-  return want < 2 ? 1 : (int)want;
+  if (n > fits) n = fits;
+  return n < 2 ? 1 : (int)n;
+}
+
+// Launches of attn_paged_fwd for one head dimension: the decode kernel when no request of the batch has more rows than
+// its form takes, otherwise the kernel that holds all forms; then the merge of split contexts.
+template <int D>
+hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, unsigned rows_wgs, unsigned tile_wgs, hipStream_t s) {
+  hipError_t err;
+  bool launched = false;
+  if constexpr (hydra::paged::kDecodeForm<D>) {
+    if (decode_only) {
+      // Waves per workgroup: 4 keep a compute unit's memory path full.  With one to two workgroups per unit and long
+      // contexts 8, of which a unit holds one at a time: units that are done early then take the remaining pairs
+      // instead of some units holding two long contexts from the start (96 requests of 128 .. 1782 tokens, 4 KV heads:
+      // 39.7 -> 35.7 us; 195 of at most 407: 16.4 -> 20.4, hence the length).
+      const int64_t keys = (int64_t)args.max_blocks_per_seq << args.block_shift;
+      const int waves = rows_wgs > 256 && rows_wgs <= 512 && args.n_splits == 1 && keys >= 768 ? hydra::paged::kDecodeMaxWaves : 4;
+      err = launch_lds(hydra::paged::attn_decode_kernel<D>, dim3(rows_wgs), dim3(64 * waves), waves * hydra::paged::kDecodeLdsPerWave<D>, s, args);
+      launched = true;
+    }
+  }
+  if (!launched) err = launch(hydra::paged::attn_paged_kernel<D>, dim3(rows_wgs + tile_wgs), dim3(256), s, args);
+  if (err == hipSuccess && args.n_splits > 1)
+    err = launch(hydra::paged::attn_paged_combine_kernel<D>, dim3((unsigned)args.n_kv_heads, (unsigned)args.batch), dim3(hydra::paged::kCombineThreads), s, args);
+  return err;
 }
 
 }  // namespace
@@ -355,7 +398,7 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   const int64_t tok_tiles = ((int64_t)max_q_len + hydra::paged::kRows - 1) / hydra::paged::kRows;
   int64_t groups = (tok_tiles * args.group + hydra::paged::kWavesPerGroup - 1) / hydra::paged::kWavesPerGroup;
   if ((int64_t)max_q_len * args.group <= hydra::paged::kRows) groups = 0;  // every request takes the packed-rows form
-  const int splits = paged_splits(batch, n_kv_heads, head_dim, max_blocks_per_seq, block_size, workspace_bytes);
+  const int splits = choose_splits(paged_splits(batch, n_kv_heads, max_blocks_per_seq, block_size), (int64_t)batch * n_kv_heads, head_dim, workspace_bytes);
   args.n_splits = splits;
   {
     const int64_t max_halves = ((int64_t)max_blocks_per_seq * block_size + 31) / 32;
@@ -371,31 +414,21 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   const int64_t rows_wgs = (int64_t)batch * n_kv_heads * splits;
   if (tile_wgs + rows_wgs > (int64_t)0x7fffffff) return HYDRA_ERR_UNSUPPORTED;
   args.n_tile_wgs = (int32_t)tile_wgs;
-  const dim3 grid((unsigned)(tile_wgs + rows_wgs), 1, 1);
-  const dim3 combine_grid((unsigned)n_kv_heads, (unsigned)batch);
+  const bool decode_only = (int64_t)max_q_len * args.group <= hydra::paged::kDecodeRows && block_size >= hydra::paged::kDecodeMinBlock;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
   switch (head_dim) {
-    case 64:
-      err = launch(hydra::paged::attn_paged_kernel<64>, grid, dim3(256), s, args);
-      if (err == hipSuccess && splits > 1) err = launch(hydra::paged::attn_paged_combine_kernel<64>, combine_grid, dim3(256), s, args);
-      break;
-    case 80:
-      err = launch(hydra::paged::attn_paged_kernel<80>, grid, dim3(256), s, args);
-      if (err == hipSuccess && splits > 1) err = launch(hydra::paged::attn_paged_combine_kernel<80>, combine_grid, dim3(256), s, args);
-      break;
-    default:
-      err = launch(hydra::paged::attn_paged_kernel<128>, grid, dim3(256), s, args);
-      if (err == hipSuccess && splits > 1) err = launch(hydra::paged::attn_paged_combine_kernel<128>, combine_grid, dim3(256), s, args);
-      break;
+    case 64: err = launch_paged<64>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    case 80: err = launch_paged<80>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    default: err = launch_paged<128>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
   }
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }
 
 size_t hydra_attn_paged_workspace_bytes(int32_t batch, int32_t n_kv_heads, int32_t head_dim, int32_t max_blocks_per_seq, int32_t block_size) {
   if (batch <= 0 || n_kv_heads <= 0 || !head_dim_supported(head_dim) || max_blocks_per_seq < 1 || block_size < 1) return 0;
-  const int splits = paged_splits(batch, n_kv_heads, head_dim, max_blocks_per_seq, block_size, ~(size_t)0);
-  return splits > 1 ? paged_partial_bytes(head_dim) * (size_t)splits * (size_t)batch * (size_t)n_kv_heads : 0;
+  const PagedSplits splits = paged_splits(batch, n_kv_heads, max_blocks_per_seq, block_size);
+  return splits.twice > 1 ? paged_partial_bytes(head_dim) * (size_t)splits.twice * (size_t)batch * (size_t)n_kv_heads : 0;
 }
 
 int hydra_kv_cache_write(const void* k, const void* v, int64_t k_token_stride, int64_t v_token_stride, void* k_cache, void* v_cache,

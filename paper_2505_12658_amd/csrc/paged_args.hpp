@@ -1,0 +1,59 @@
+// Arguments of the paged attention kernels, and how long contexts are cut into shares.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace hydra {
+namespace paged {
+
+constexpr int kRows = 32;          // new tokens (or packed rows) per wave tile
+constexpr int kWavesPerGroup = 4;  // wave tiles per workgroup
+
+struct PagedArgs {
+  const uint16_t* q;        // [total_q, n_q_heads, D] with token stride
+  uint16_t* out;            // [total_q, n_q_heads, D] contiguous
+  int64_t q_stride;         // elements per token
+  const uint16_t* k_cache;  // [num_blocks, block_size, n_kv_heads, D]
+  const uint16_t* v_cache;
+  const int32_t* block_tables;  // [batch, max_blocks_per_seq]
+  const int32_t* cu_seqlens_q;  // [batch + 1]
+  const int32_t* kv_lens;       // [batch]
+  int32_t max_blocks_per_seq;
+  int32_t num_blocks;
+  int32_t block_shift;  // log2(block_size)
+  int32_t n_q_heads;
+  int32_t n_kv_heads;
+  int32_t group;     // n_q_heads / n_kv_heads
+  float scale_log2;  // softmax_scale * log2(e)
+  // Packed-rows form, long contexts split over workgroups: a context of more than halves_per_split half tiles
+  // (32 keys each) is cut into the fewest shares that fit that size, all of (nearly) the same length (share_plan);
+  // n_splits workgroups per (request, KV head), one per share.  A context that fits one share is done by its first
+  // workgroup, which writes `out` itself (the others leave at once); of a longer one every share leaves a partial
+  // result in `partials`, and the combine kernel merges them.  n_splits == 1: never split.
+  int32_t n_splits;
+  int32_t halves_per_split;
+  float* partials;  // [batch, n_kv_heads, n_splits] records of kPartialFloats<D> floats
+  int32_t batch;
+  int32_t n_tile_wgs;  // workgroups of the wave-tile form at the end of the grid (an upper bound from the host)
+};
+
+// One partial result of the packed-rows form: per row (32 rows) the maximum and the sum, then the
+// unnormalised output rows [32][D] (only the first q_len * group rows are written and read).
+template <int D>
+constexpr int kPartialFloats = 2 * kRows + kRows * D;
+
+// How a context of n_halves half tiles is cut: `shares` shares of `per` half tiles (the last one may be shorter);
+// one share when it fits halves_per_split.
+__device__ __forceinline__ void share_plan(int n_halves, int halves_per_split, int& per, int& shares) {
+  const int k = (n_halves + halves_per_split - 1) / halves_per_split;
+  per = k > 1 ? (n_halves + k - 1) / k : n_halves;
+  shares = per > 0 ? (n_halves + per - 1) / per : 0;
+}
+// half tiles [begin, end) of share s (empty past the last share)
+__device__ __forceinline__ void split_range(int n_halves, int per, int s, int& begin, int& end) {
+  begin = s * per < n_halves ? s * per : n_halves;
+  end = begin + per < n_halves ? begin + per : n_halves;
+}
+
+}  // namespace paged
+}  // namespace hydra

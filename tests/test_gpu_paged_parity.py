@@ -302,3 +302,25 @@ def test_requests_pages_move_to_another_cache():
     _check(after, _want(h, q, kc, vc, tables))
     untouched = np.setdiff1d(np.arange(n_dst), dst)
     assert (kc2[torch.from_numpy(untouched).to(dev)] == sentinel).all() and (vc2[torch.from_numpy(untouched).to(dev)] == -sentinel).all()
+
+
+DECODE_CASES = [
+    # q_lens, kv_lens, Hq, Hkv, d, block_size: requests of at most 16 rows (new tokens x grouped heads)
+    ([1] * 9, [1, 15, 16, 17, 31, 32, 33, 127, 129], 4, 4, 128, 16),          # edges of a block of keys, of the waves' turns
+    ([1, 2, 1, 0, 2], [700, 2, 64, 5, 33], 14, 2, 64, 16),                    # 14 rows, an empty request
+    ([16, 3, 1], [16, 500, 40], 1, 1, 128, 64),                               # 16 rows of one head, causal limits inside the last keys
+    ([1, 1], [4129, 9000], 16, 1, 64, 256),                                   # more than 32 steps per wave: a second load of table entries
+    ([1, 2, 1], [16, 300, 9], 16, 2, 128, 32),
+    ([1] * 258, [9000, 8193] + [5 + 3 * i for i in range(256)], 7, 1, 128, 16),  # more requests than compute units, long table: eight waves
+]
+
+
+@pytest.mark.parametrize("case", DECODE_CASES, ids=lambda c: f"n{len(c[0])}-kv{max(c[1])}-h{c[2]}k{c[3]}-d{c[4]}-b{c[5]}")
+def test_decode_form(case):
+    """Batches of requests with at most 16 rows each (the decode kernel), unsplit and split, whole output against the oracle."""
+    q_lens, kv_lens, hq, hkv, d, bs = case
+    h = si.HybridBatch("decode", q_lens, kv_lens, hq, hkv, d, block_size=bs, seed=3 * len(q_lens) + bs)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    want = _want(h, q, kc, vc, tables)
+    _check(_run_gpu(h, q, kc, vc, tables, use_workspace=False), want)
+    _check(_run_gpu(h, q, kc, vc, tables), want)
