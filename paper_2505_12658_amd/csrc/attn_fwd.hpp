@@ -171,44 +171,69 @@ __device__ __forceinline__ void s_results_to_valu(f32x16_t (&S)[2]) { asm volati
 // Scheduling hints: keep the listed instruction classes in this order inside the current region.
 #define HYDRA_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// Every workgroup of the grid ends up making exactly ONE failing claim on every queue: on its own when that
-// runs dry, on each of the others while it looks for work to steal (a queue found empty is not asked again).
-// A queue of n items has therefore been asked n + (workgroups) times when the kernel ends, and the workgroup
-// whose claim returns position n + (workgroups) - 1 is the last that will ever touch that head in this call: it
-// puts the head back to zero, so that the next attention call on the same work list (the next layer of the same
-// batch) finds a clean control block.  No counter of finished workgroups is needed, and no launch to tidy up.
-// Called by the lane that holds the position.
-__device__ __forceinline__ void reset_head_if_last(WorkControl* ctrl, int y, int pos, int n_items) {
-  if (pos == n_items + (int)gridDim.x - 1) atomicExch(&ctrl->queue_head[y * kHeadStride], 0);
+// How the items of a call are shared out.  Workgroup id w belongs to die w % 8 (the hardware deals ids to the dies
+// round-robin: measured, always; nothing but locality depends on it) and is number w / 8 there.  The first entries of a
+// queue go to the die's workgroups by their number, without an atomic; the rest are claimed one by one from the queue's
+// head.  When a die's queue has run out, its workgroups look at the other dies' heads, all at once, and claim from one
+// that has entries left.
+// What this avoids: a few hundred atomics on one address take tens of microseconds, from all dies together, and the end
+// of a kernel is where all workgroups would meet.  (It was: every workgroup made one failing claim on every queue, one
+// round trip after the other, and the last failing claim on a queue put its head back to zero.  For one image of 577
+// tokens that was 6 - 8 us of 18.7; polling all heads with claims at once made every batch 10 - 30 us longer.)
+//
+// Before the kernel ends the heads have to be zero again for the next call on the same work list (the next layer of
+// the same batch).  The last workgroup of a die to leave is known from a count per die, and the last die from a count of
+// dies, so no address sees more than a die's workgroups; the last of all clears everything.  Where no queue is longer
+// than its die's workgroups are many, no head is ever touched and nothing is counted.
+
+// Workgroups of die y in a grid of n.
+__device__ __forceinline__ int queue_wgs(int y, int n) { return (n - y + kXcds - 1) / kXcds; }
+
+// The claimed part of queue y: entries past those that belong to the die's workgroups.
+__device__ __forceinline__ int claimable(const WorkControl* ctrl, int y) {
+  return ctrl->xcd_start[y + 1] - ctrl->xcd_start[y] - queue_wgs(y, (int)gridDim.x);
 }
 
-// Claims the next unclaimed entry of queue y.  Called by all lanes of ONE wave; returns the list
-// index, or -1 when the queue is empty.
-__device__ __forceinline__ int claim_from(WorkControl* ctrl, int y, int lane) {
-  const int begin = ctrl->xcd_start[y], end = ctrl->xcd_start[y + 1];
-  int pos = 0;
-  if (lane == 0) {
-    pos = atomicAdd(&ctrl->queue_head[y * kHeadStride], 1);
-    reset_head_if_last(ctrl, y, pos, end - begin);
-  }
-  pos = __builtin_amdgcn_readfirstlane(pos);
-  return pos < end - begin ? begin + pos : -1;
-}
-
-// A workgroup whose own die's queue is empty helps the other dies: one claim attempt per queue it
-// has not yet found empty (`empty_mask`, kept by the caller), starting at a different neighbour for
-// different workgroups.  Heads only grow, so a queue found empty stays empty and every workgroup
-// makes at most seven failing attempts in its life: no polling, no storm of atomics at the end of
-// the kernel.  Returns the list index or -1 when all queues are empty.
-__device__ __forceinline__ int steal_item(WorkControl* ctrl, int xcc, int first, int lane, uint32_t& empty_mask) {
-  for (int k = 0; k < kXcds - 1; ++k) {
-    const int y = (xcc + 1 + (first + k) % (kXcds - 1)) & (kXcds - 1);
-    if (empty_mask & (1u << y)) continue;
-    const int idx = claim_from(ctrl, y, lane);
-    if (idx >= 0) return idx;
-    empty_mask |= 1u << y;
+// An item of another die's queue, for a workgroup whose own has run out.  Called by all lanes of ONE wave.  Returns the
+// list index, or -1 when all queues are empty.  Heads only grow, so a queue seen empty stays so: every round either
+// returns an item or leaves fewer queues to look at.
+__device__ __forceinline__ int steal_item(WorkControl* ctrl, int own, int first) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // (keeps what follows from the lane number out of the hot loop's registers)
+  uint32_t open = 0xffu & ~(1u << own);
+  while (open != 0) {
+    bool left = false;
+    if (lane < kXcds && (open >> lane & 1)) {
+      const int n = claimable(ctrl, lane);
+      left = n > 0 && __hip_atomic_load(&ctrl->queue_head[lane * kHeadStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n;
+    }
+    open = (uint32_t)__builtin_amdgcn_ballot_w64(left);
+    if (open == 0) break;
+    int y = own;
+    for (int k = 0; k < kXcds - 1; ++k) {  // (a different neighbour first for different workgroups)
+      y = (own + 1 + (first + k) % (kXcds - 1)) & (kXcds - 1);
+      if (open >> y & 1) break;
+    }
+    const int n = claimable(ctrl, y);
+    int pos = 0;
+    if (lane == 0) pos = atomicAdd(&ctrl->queue_head[y * kHeadStride], 1);
+    pos = __builtin_amdgcn_readfirstlane(pos);
+    if (pos < n) return ctrl->xcd_start[y + 1] - n + pos;
+    open &= ~(1u << y);
   }
   return -1;
+}
+
+// The last thing a workgroup does in a call that claims (one thread; its claims have returned).
+__device__ __forceinline__ void leave(WorkControl* ctrl) {
+  const int n = (int)gridDim.x, die = (int)blockIdx.x % kXcds, dies = n < kXcds ? n : kXcds;
+  if (atomicAdd(&ctrl->queue_head[die * kHeadStride + kLeftAt], 1) != queue_wgs(die, n) - 1) return;
+  if (atomicAdd(&ctrl->queues_left, 1) != dies - 1) return;
+  for (int y = 0; y < kXcds; ++y) {
+    atomicExch(&ctrl->queue_head[y * kHeadStride], 0);
+    atomicExch(&ctrl->queue_head[y * kHeadStride + kLeftAt], 0);
+  }
+  atomicExch(&ctrl->queues_left, 0);
 }
 
 constexpr int kKeyBlock = 32;         // keys per pipeline step
@@ -263,8 +288,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
 
   const int lane_id = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // die this workgroup runs on (hardware id register XCC_ID, bits 3:0)
-  const int xcc = (int)__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & (kXcds - 1);
+  const int die = (int)blockIdx.x % kXcds;  // the die this workgroup runs on, whose queue is its own
   // s_redo: an item whose exponentials left the fast path's range: {flag, first token, length, first wave tile, KV
   // head}, posted by the waves that noticed, acted upon by the whole workgroup at the top of its next round.
   if (threadIdx.x == 0) s_redo[0] = 0;
@@ -293,10 +317,10 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
       s_claim[3] = it.w;
     }
   };
-  int own_begin = 0, own_count = 0;
+  int own_claimed_at = 0, own_count = 0;  // the claimed part of the own queue: first entry, entries
   if constexpr (!Src::kPaged) {
-    own_begin = a.ctrl->xcd_start[xcc];
-    own_count = a.ctrl->xcd_start[xcc + 1] - own_begin;
+    own_count = claimable(a.ctrl, die);
+    own_claimed_at = a.ctrl->xcd_start[die + 1] - own_count;
   }
   // Q: a wave's 32 rows come in with direct-to-LDS loads that cover whole rows (loaded straight
   // into the B-operand register layout, one instruction would touch 32 different rows: one address
@@ -329,10 +353,12 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     }
   };
   bool q_ahead = false;      // the current item's Q loads were issued at the end of the previous round
-  bool own_empty = false;    // this die's queue has run out (same value in all waves)
-  uint32_t empty_mask = 0;   // wave 0: other dies' queues found empty
+  bool own_empty = own_count <= 0;  // nothing is left to claim from this die's queue (same value in all waves)
   if constexpr (!Src::kPaged) {
-    if (wave == 0) post_claim(claim_from(a.ctrl, xcc, lane_id));
+    if (wave == 0) {
+      const int idx = a.ctrl->xcd_start[die] + (int)blockIdx.x / kXcds;
+      post_claim(idx < a.ctrl->xcd_start[die + 1] ? idx : -1);
+    }
   }
 
   for (;;) {  // one work item per round
@@ -366,7 +392,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     // from the own queue.  Every wave has seen the empty claim before wave 0 overwrites it.
     own_empty = true;
     __syncthreads();
-    if (wave == 0) post_claim(steal_item(a.ctrl, xcc, (int)(blockIdx.x >> 3), lane_id, empty_mask));
+    if (wave == 0) post_claim(steal_item(a.ctrl, die, (int)(blockIdx.x / kXcds)));
     __syncthreads();
   }
   // The item: `seq_len` query rows that start at packed token `seq_start`, and `kv_len` keys; query row i sees
@@ -400,7 +426,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // the hot loop makes it wait for ALL loads there, which would undo the tile prefetch.)
   int pending_claim = 0x7fffffff;
   if constexpr (!Src::kPaged) {
-    if (threadIdx.x == 0 && !own_empty) pending_claim = atomicAdd(&a.ctrl->queue_head[xcc * kHeadStride], 1);
+    if (threadIdx.x == 0 && !own_empty) pending_claim = atomicAdd(&a.ctrl->queue_head[die * kHeadStride], 1);
   }
   const int n_tok_tiles = (seq_len + kWaveTileRows - 1) / kWaveTileRows;
   const int n_wave_tiles = n_tok_tiles * a.group;
@@ -770,8 +796,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   if constexpr (!Src::kPaged)
   if (wave == 0) {
     // (own queue empty: an empty claim is posted, and the top of the next round goes stealing)
-    const int idx = pos < own_count ? own_begin + pos : -1;
-    if (lane == 0) reset_head_if_last(a.ctrl, xcc, pos, own_count);
+    const int idx = pos < own_count ? own_claimed_at + pos : -1;
     // The item itself travels memory -> LDS on its own (one more direct-to-LDS load, lane 0 only):
     // it is complete when this wave's last wait of the round (for zero loads in flight) has
     // passed, and the barrier after that wait makes it visible to the other waves.  Every wave
@@ -951,6 +976,13 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   if constexpr (Src::kPaged) {
     __syncthreads();
     return s_redo[0] != 0;
+  }
+  if constexpr (!Src::kPaged) {
+    if (wave == 0) {
+      int y = threadIdx.x & (kXcds - 1);
+      asm volatile("" : "+v"(y));
+      if (__builtin_amdgcn_ballot_w64(claimable(a.ctrl, y) > 0) != 0 && threadIdx.x == 0) leave(a.ctrl);
+    }
   }
   return false;
 }

@@ -43,16 +43,19 @@ typedef int4 WorkItem;
 constexpr int kXcds = 8;  // accelerator dies; workgroup ids are dealt to them round-robin, each die has its own L2
 
 // Control block at the start of the workspace.  The work list is one array; the entries
-// [xcd_start[x], xcd_start[x + 1]) form the queue of die x and queue_head[x] counts how many of
-// them have been claimed in the current attention call.
+// [xcd_start[x], xcd_start[x + 1]) form the queue of die x.  The first entries of a queue belong to the die's
+// workgroups by their number; queue_head[x] counts how many of the others have been claimed in the current attention
+// call (see queue_wgs and the item loop).
 // Every queue head has a 128-byte line of its own: the heads are the only words of the workspace
 // that many workgroups update during the kernel, and claims of different dies must not collide.
 constexpr int kHeadStride = 32;  // int32 words between queue heads
+constexpr int kLeftAt = 16;      // on a head's line: workgroups of that die that have left the kernel
 struct WorkControl {
   int32_t n_items;
   int32_t xcd_start[kXcds + 1];
-  int32_t reserved[22];
-  int32_t queue_head[kXcds * kHeadStride];  // head of queue x at [x * kHeadStride]; zero between calls
+  int32_t queues_left;  // dies all of whose workgroups have left; zero between calls
+  int32_t reserved[21];
+  int32_t queue_head[kXcds * kHeadStride];  // head of queue x at [x * kHeadStride], its count at + kLeftAt; zero between calls
 };
 static_assert(sizeof(WorkControl) == 128 + kXcds * 128, "control block layout");
 

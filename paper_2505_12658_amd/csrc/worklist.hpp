@@ -106,7 +106,8 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   // out over the grid (step 3), and workgroup x < 8 also orders the tail of queue x (step 4).  Workgroup 0
   // writes the control block.
   const bool leader = blockIdx.x == 0;
-  if (leader && tid < kXcds) ctrl->queue_head[tid * kHeadStride] = 0;
+  if (leader && tid < kXcds) ctrl->queue_head[tid * kHeadStride] = ctrl->queue_head[tid * kHeadStride + kLeftAt] = 0;
+  if (leader && tid == kXcds) ctrl->queues_left = 0;
 
   // Small batches (the normal case) are handled entirely in LDS after one read of cu_seqlens;
   // the global arrays are only used for what does not fit.

@@ -273,6 +273,38 @@ def test_worklist_covers_every_tile_once_and_ends_with_cheap_items(hq, hkv, d, c
         assert all(a >= b for a, b in zip(t, t[1:])), (x, t)
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d", [
+    ([40] * 3, 2, 1, 64),                 # fewer items than workgroups on every die: nothing is claimed
+    ([20] * 800, 1, 1, 64),               # more items than workgroups on some dies
+    ([64] * 1024 + [1], 1, 1, 128),       # twice the workgroups everywhere and one over
+    ([3000], 8, 1, 128),                  # one queue holds everything, the other dies live off it
+])
+def test_repeated_calls_on_one_work_list(lengths, hq, hkv, d):
+    """Several attention calls on one work list, back to back and with fewer workgroups in between: every call has to
+    leave the control block as it found it (heads and counts zero), or the next one would skip items."""
+    hydra = _hydra()
+    w = si.custom(lengths, hq, hkv, d, True, seed=len(lengths))
+    q, k, v = si.make_qkv(w)
+    dev = torch.device("cuda:0")
+    cu = torch.from_numpy(w.cu_seqlens).to(dev)
+    qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+    ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, w.max_seqlen, hq, hkv, d, True)
+    first = None
+    for per_cu in (None, None, 1, None, 2):
+        out = torch.full_like(qd, float("nan"))
+        if per_cu is None:
+            hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, w.max_seqlen, True, w.softmax_scale, out, ws)
+        else:
+            hydra.hydra_attn_varlen_fwd_shared(qd, kd, vd, cu, w.max_seqlen, True, w.softmax_scale, out, ws, per_cu)
+        torch.cuda.synchronize()
+        words = ws.cpu().numpy().view(np.int32)
+        assert words[10] == 0 and (words[32:32 + 256:32] == 0).all() and (words[48:48 + 256:32] == 0).all()
+        if first is None:
+            first = out
+            _check(out, c_oracle.attn_varlen(_f64(q), _f64(k), _f64(v), w.cu_seqlens, True, w.softmax_scale))
+        assert torch.equal(out.view(torch.int16), first.view(torch.int16))
+
+
 @pytest.mark.parametrize("seed", range(48))
 def test_random_ragged_batches(seed):
     """Seeded random batches (number of sequences, lengths with zeros and tile-boundary values mixed in, head
