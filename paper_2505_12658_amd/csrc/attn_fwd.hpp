@@ -258,18 +258,27 @@ constexpr float kMaxRowSum = 1.0995116e12f;  // 2^40: largest row sum (relative 
 
 
 // Where a workgroup's items and their K/V rows come from.  The packed kernel (below) takes items from the work
-// list's queues and K/V rows from the packed batch; the paged kernel runs ONE item per call, handed over in its
-// source object, with K/V rows gathered from cache pages and queries that are the LAST q_len positions of a
-// context of kv_len keys (see attn_paged.hpp for that source).
+// list's queues and K/V rows from the packed batch; for small batches a workgroup works its one item out for itself
+// (attn_fwd_direct_kernel) and hands it over in its source object; the paged kernel does so as well, with K/V rows
+// gathered from cache pages and queries that are the LAST q_len positions of a context of kv_len keys (see
+// attn_paged.hpp for that source).
 struct PackedSource {
-  static constexpr bool kPaged = false;
+  static constexpr bool kPaged = false, kOneItem = false;
   template <int D>
   struct Gather {};  // (the paged source's K/V gatherer; the packed rows use two TileLoaders)
+};
+struct DirectSource {
+  static constexpr bool kPaged = false, kOneItem = true;
+  template <int D>
+  struct Gather {};
+  int64_t q_start;   // first token of the sequence
+  int q_len;         // its length
+  int f0, kv_head;   // first flattened wave tile of the item, KV head
 };
 
 #if defined(__HIP_DEVICE_COMPILE__)
 // The item loop of a workgroup (4 waves).  smem: TileGeom<D>::kLdsBytes bytes of LDS, 1024-aligned; s_claim: 4
-// ints, s_redo: 8 ints of LDS.  Packed source: runs until the queues are empty.  Paged source: runs the source's
+// ints, s_redo: 8 ints of LDS.  Packed source: runs until the queues are empty.  One-item sources: runs the source's
 // item and returns whether its row sums left the fast path's range (same value in every thread; the caller then
 // recomputes the item with its own careful routine).
 template <int D, bool CAUSAL, class Src>
@@ -318,7 +327,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     }
   };
   int own_claimed_at = 0, own_count = 0;  // the claimed part of the own queue: first entry, entries
-  if constexpr (!Src::kPaged) {
+  if constexpr (!Src::kOneItem) {
     own_count = claimable(a.ctrl, die);
     own_claimed_at = a.ctrl->xcd_start[die + 1] - own_count;
   }
@@ -354,7 +363,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   };
   bool q_ahead = false;      // the current item's Q loads were issued at the end of the previous round
   bool own_empty = own_count <= 0;  // nothing is left to claim from this die's queue (same value in all waves)
-  if constexpr (!Src::kPaged) {
+  if constexpr (!Src::kOneItem) {
     if (wave == 0) {
       const int idx = a.ctrl->xcd_start[die] + (int)blockIdx.x / kXcds;
       post_claim(idx < a.ctrl->xcd_start[die + 1] ? idx : -1);
@@ -363,7 +372,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
 
   for (;;) {  // one work item per round
   __syncthreads();
-  if constexpr (!Src::kPaged)
+  if constexpr (!Src::kOneItem)
   if (__builtin_expect(__builtin_amdgcn_readfirstlane(s_redo[0]) != 0, 0)) {
     // The previous round's item has to be redone carefully.  Its (wrong) output rows are already stored and are
     // overwritten by the same waves; the loads of the next item's Q, in flight into the V ring, are waited for
@@ -385,7 +394,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   asm volatile("" : "+v"(lane));
   __builtin_assume(lane >= 0 && lane < 64);  // (divisions of lane-derived indices by constants become shifts)
   const int m = lane & 31, hf = lane >> 5, sl = lane & 15, grp = (lane >> 4) & 1;
-  if constexpr (!Src::kPaged)
+  if constexpr (!Src::kOneItem)
   if (__builtin_amdgcn_readfirstlane(s_claim[1]) == 0) {
     // Nothing left in this die's queue: take an item from another die's queue.  This is done here, with
     // the workgroup idle, and synchronously (two memory round trips), not ahead of time like the claims
@@ -399,7 +408,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // keys 0 .. shift + i (causal).  Packed batch: the keys are the sequence's own rows, shift = 0.
   int64_t seq_start;
   int seq_len, f0, kv_head;
-  if constexpr (Src::kPaged) {
+  if constexpr (Src::kOneItem) {
     seq_start = src.q_start;
     seq_len = src.q_len;
     f0 = src.f0;
@@ -425,7 +434,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // operations per code path, and an atomic that is "maybe still in flight" on some path into
   // the hot loop makes it wait for ALL loads there, which would undo the tile prefetch.)
   int pending_claim = 0x7fffffff;
-  if constexpr (!Src::kPaged) {
+  if constexpr (!Src::kOneItem) {
     if (threadIdx.x == 0 && !own_empty) pending_claim = atomicAdd(&a.ctrl->queue_head[die * kHeadStride], 1);
   }
   const int n_tok_tiles = (seq_len + kWaveTileRows - 1) / kWaveTileRows;
@@ -793,7 +802,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   wait_all_loads();
   __syncthreads();
   const int pos = __builtin_amdgcn_readfirstlane(pending_claim);  // every wave: the claim has returned (see above)
-  if constexpr (!Src::kPaged)
+  if constexpr (!Src::kOneItem)
   if (wave == 0) {
     // (own queue empty: an empty claim is posted, and the top of the next round goes stealing)
     const int idx = pos < own_count ? own_claimed_at + pos : -1;
@@ -909,7 +918,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // start its Q loads now.  (When the die's queue has run out the posted claim is empty, and the
   // item stolen at the top of the next round loads its Q there.)
   q_ahead = false;
-  if constexpr (!Src::kPaged) {
+  if constexpr (!Src::kOneItem) {
     const int next_len = __builtin_amdgcn_readfirstlane(s_claim[1]);
     if (next_len != 0) {
       const int64_t next_start = __builtin_amdgcn_readfirstlane(s_claim[0]);
@@ -971,13 +980,13 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
       asm volatile("buffer_store_dwordx4 %0, %1, %2, 0 offen nt\n\ts_nop 1" : : "v"(piece), "v"(off), "s"(rsrc) : "memory");
     }
   }
-  if constexpr (Src::kPaged) break;
+  if constexpr (Src::kOneItem) break;
   }  // next work item
-  if constexpr (Src::kPaged) {
+  if constexpr (Src::kOneItem) {
     __syncthreads();
     return s_redo[0] != 0;
   }
-  if constexpr (!Src::kPaged) {
+  if constexpr (!Src::kOneItem) {
     if (wave == 0) {
       int y = threadIdx.x & (kXcds - 1);
       asm volatile("" : "+v"(y));
@@ -997,6 +1006,118 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroups
   attn_item_loop<D, CAUSAL>(a, PackedSource{}, smem, s_claim, s_redo);
 #else
   (void)a;
+#endif
+}
+
+// ---- one workgroup per item ------------------------------------------------------------------------------------
+// Batches of a few items per workgroup slot run with one workgroup per item, dealt out by the hardware as slots fall
+// free, instead of persistent workgroups that claim: at so few rounds the claims, their start and their end cost more
+// than loading the next item's Q ahead wins (7 LLaVA requests, 3 rounds: 85.0 -> 78.3 us; at 6 rounds the two are
+// level, at 13 persistent workgroups win by 2 %).
+// The item comes from the work list when there is one.  Without one (the call that would have to build it first), and
+// for at most kDirectSeqs sequences, every wave works its workgroup's item out from cu_seqlens, one round trip to memory
+// and some 300 instructions, about 1.3 us per workgroup against a prepass of 5 - 8 us.
+constexpr int kDirectSeqs = 64;
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// Sum over this lane and the lanes before it (data-parallel primitives: shifts inside the rows of 16 lanes, then the
+// rows' totals handed on; a seventh of the latency of the six LDS permutes that a shuffle would take).
+__device__ __forceinline__ int wave_scan_add(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+
+// The unit of this workgroup in a batch whose sequence of length L has units(L) units per KV head: its KV head, its
+// sequence and its number there; false for workgroups past the last one.  The order is that of the work list
+// (worklist.hpp): sequences ranked by length, longest first, their (sequence, KV head) pairs dealt to the dies in
+// serpentine order, die x taking workgroup ids x, x + 8, ...
+template <typename Units>
+__device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv_heads, Units units, int& seq_start, int& seq_len, int& kv_head, int& unit) {
+  const int lane = threadIdx.x & 63;
+  int start = 0, len = 0;
+  if (lane < batch) {
+    start = cu[lane];
+    len = cu[lane + 1] - start;
+  }
+  if (__builtin_amdgcn_ballot_w64(lane < batch && len != __builtin_amdgcn_readfirstlane(len)) != 0) {
+    // lane r gets the sequence of rank r (ranks are distinct; lanes without a sequence come last)
+    int rank = lane < batch ? 0 : lane;
+    for (int o = 0; o < batch; o += 4) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {  // (lanes past the batch hold length 0 and a larger number: they precede nobody)
+        const int other = __builtin_amdgcn_readlane(len, o + e);
+        if (lane < batch) rank += (other > len || (other == len && o + e < lane)) ? 1 : 0;
+      }
+    }
+    start = __builtin_amdgcn_ds_permute(rank * 4, start);
+    len = __builtin_amdgcn_ds_permute(rank * 4, len);
+  }
+  const int n = units(len);
+  // rows of this die's column, 64 at a time: units of each row's pair and, by a scan, of the rows before it
+  const int die = (int)blockIdx.x % kXcds, place = (int)blockIdx.x / kXcds;
+  const int pairs = batch * n_kv_heads;
+  const float per_kv = 1.0f / n_kv_heads;
+  int before = 0;
+  for (int row0 = 0; row0 * kXcds < pairs; row0 += 64) {
+    const int row = row0 + lane;
+    const int pair = row * kXcds + ((row & 1) ? kXcds - 1 - die : die);
+    const int seq = (int)((pair + 0.5f) * per_kv);  // pair / n_kv_heads (exact: fewer than 2^20 pairs)
+    int mine = __builtin_amdgcn_ds_bpermute((seq < 63 ? seq : 63) * 4, n);
+    if (pair >= pairs) mine = 0;
+    const int incl = wave_scan_add(mine);
+    const int here = __builtin_amdgcn_readlane(incl, 63);
+    if (place < before + here) {
+      const int at = place - before;
+      const int r = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > at));
+      const int pair_r = __builtin_amdgcn_readlane(pair, r), seq_r = __builtin_amdgcn_readlane(seq, r);
+      kv_head = pair_r - seq_r * n_kv_heads;
+      unit = at - __builtin_amdgcn_readlane(incl - mine, r);
+      seq_start = __builtin_amdgcn_readlane(start, seq_r);
+      seq_len = __builtin_amdgcn_readlane(len, seq_r);
+      return true;
+    }
+    before += here;
+  }
+  return false;
+}
+#endif  // __HIP_DEVICE_COMPILE__
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroupsPerCu<D>, kWorkgroupsPerCu<D>))) void attn_fwd_direct_kernel(
+    const AttnArgs a, const int batch, const int n_kv_heads) {  // batch 0: the item comes from the work list
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D>::kLdsBytes];
+  __shared__ __attribute__((aligned(16))) int s_claim[4];
+  __shared__ __attribute__((aligned(16))) int s_redo[8];
+  DirectSource src;
+  if (batch == 0) {
+    const int die = (int)blockIdx.x % kXcds, at = a.ctrl->xcd_start[die] + (int)blockIdx.x / kXcds;
+    if (at >= a.ctrl->xcd_start[die + 1]) return;
+    const WorkItem it = a.items[at];
+    src.q_start = __builtin_amdgcn_readfirstlane(it.x);
+    src.q_len = __builtin_amdgcn_readfirstlane(it.y);
+    src.f0 = __builtin_amdgcn_readfirstlane(it.z);
+    src.kv_head = __builtin_amdgcn_readfirstlane(it.w);
+  } else {
+    int start, item;
+    if (!find_unit(a.cu_seqlens, batch, n_kv_heads, [&](int len) { return items_of_sequence(len, a.group); }, start, src.q_len, src.kv_head, item)) return;
+    if (CAUSAL) item = items_of_sequence(src.q_len, a.group) - 1 - item;  // most expensive first
+    src.q_start = start;
+    src.f0 = item * kWavesPerItem;
+  }
+  if (attn_item_loop<D, CAUSAL>(a, src, smem, s_claim, s_redo)) {
+    const uint32_t lds = (uint32_t)(uintptr_t)HYDRA_LDS_PTR(smem);
+    careful::run_item<D, CAUSAL>(a, src.q_start, src.q_len, src.f0, src.kv_head, lds);
+  }
+#else
+  (void)a;
+  (void)batch;
+  (void)n_kv_heads;
 #endif
 }
 

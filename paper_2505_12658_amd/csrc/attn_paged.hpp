@@ -144,7 +144,7 @@ __device__ __forceinline__ void issue_tile_loads(const TileSlots<D, KEYS, STEP>&
 // iteration comes from the blocks its K tile came from one iteration earlier, so they are kept.
 // head_dim 80 (a row is not a whole fraction of 1024 bytes) and smaller blocks take the plain loop further down.
 struct PagedSource {
-  static constexpr bool kPaged = true;
+  static constexpr bool kPaged = true, kOneItem = true;
   const PagedArgs* args;
   const int32_t* table;  // the request's row of the block table
   int64_t q_start;       // first new token of the request in the packed q / out

@@ -100,6 +100,12 @@ __device__ __forceinline__ int v_swizzle(int row, int chunk) {
   else return chunk;
 }
 
+// Items of one (sequence, KV head).
+__device__ __forceinline__ int items_of_sequence(int len, int group) {
+  const int tok_tiles = (len + kWaveTileRows - 1) / kWaveTileRows;
+  return (tok_tiles * group + kWavesPerItem - 1) / kWavesPerItem;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Exchange between the two 32-lane halves with v_permlane32_swap, which swaps the upper half

@@ -72,11 +72,6 @@ inline WorkspaceLayout workspace_layout(int64_t batch, int64_t total_tokens, int
   return w;
 }
 
-__device__ __forceinline__ int items_of_sequence(int len, int group) {
-  const int tok_tiles = (len + kWaveTileRows - 1) / kWaveTileRows;
-  return (tok_tiles * group + kWavesPerItem - 1) / kWavesPerItem;
-}
-
 // Workgroups of the prepass: one per 1024 places of the list, at least one per queue (its tail), at most 64.
 inline unsigned prepass_workgroups(size_t capacity) {
   const size_t g = (capacity + kPrepassThreads - 1) / kPrepassThreads;

@@ -273,6 +273,41 @@ def test_worklist_covers_every_tile_once_and_ends_with_cheap_items(hq, hkv, d, c
         assert all(a >= b for a, b in zip(t, t[1:])), (x, t)
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
+    ([37], 1, 1, 64, False),                                     # one item
+    ([5 + 3 * i for i in range(64)], 16, 16, 64, True),          # as many sequences as lanes, more pairs than one scan takes
+    ([100] * 65, 2, 2, 64, False),                               # one sequence too many: the work list
+    ([0, 70, 0, 70, 33, 0], 8, 2, 80, True),                     # empty sequences in between
+    ([64] * 24, 14, 2, 128, True),                               # equal lengths (not ranked)
+    ([900, 1, 1, 32, 700, 33], 7, 1, 128, True),                 # one KV head: one pair per die and row
+])
+def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
+    """Batches that run with one workgroup per item: without a work list (the plain call) against the oracle; with one,
+    and with persistent workgroups over it, the same bits; keys out of the fast path's range as well."""
+    hydra = _hydra()
+    w = si.custom(lengths, hq, hkv, d, causal, seed=7 * len(lengths) + hq)
+    q, k, v = si.make_qkv(w)
+    dev = torch.device("cuda:0")
+    cu = torch.from_numpy(w.cu_seqlens).to(dev)
+    for planted in (False, True):
+        if planted:
+            if max(lengths) < 60:
+                continue
+            k = k.clone()
+            for b, L in enumerate(lengths):
+                if L > 50:
+                    k[w.cu_seqlens[b] + 45] = 64.0  # (see test_large_scores_take_careful_path)
+        qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+        out = _run_gpu(w, q, k, v)
+        _check(out, c_oracle.attn_varlen(_f64(q), _f64(k), _f64(v), w.cu_seqlens, causal, w.softmax_scale))
+        ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, w.max_seqlen, hq, hkv, d, causal)
+        listed, shared = torch.full_like(qd, float("nan")), torch.full_like(qd, float("nan"))
+        hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, w.max_seqlen, causal, w.softmax_scale, listed, ws)
+        hydra.hydra_attn_varlen_fwd_shared(qd, kd, vd, cu, w.max_seqlen, causal, w.softmax_scale, shared, ws, 3)
+        torch.cuda.synchronize()
+        assert torch.equal(listed.view(torch.int16), out.view(torch.int16)) and torch.equal(shared.view(torch.int16), out.view(torch.int16))
+
+
 @pytest.mark.parametrize("lengths,hq,hkv,d", [
     ([40] * 3, 2, 1, 64),                 # fewer items than workgroups on every die: nothing is claimed
     ([20] * 800, 1, 1, 64),               # more items than workgroups on some dies
@@ -290,7 +325,7 @@ def test_repeated_calls_on_one_work_list(lengths, hq, hkv, d):
     qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
     ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, w.max_seqlen, hq, hkv, d, True)
     first = None
-    for per_cu in (None, None, 1, None, 2):
+    for per_cu in (None, 3, 3, 1, None, 2, 3):
         out = torch.full_like(qd, float("nan"))
         if per_cu is None:
             hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, w.max_seqlen, True, w.softmax_scale, out, ws)
