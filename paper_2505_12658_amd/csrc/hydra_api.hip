@@ -38,6 +38,18 @@ hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t 
   return launch_lds(kernel, grid, block, 0, stream, args...);
 }
 
+// A row-copy kernel over `workgroups` workgroups: one launch, or several where a grid cannot hold them.
+template <typename Args>
+hipError_t launch_row_copy(void (*kernel)(Args), Args args, int64_t workgroups, hipStream_t stream) {
+  hipError_t err = hipSuccess;
+  for (int64_t at = 0; at < workgroups && err == hipSuccess; at += hydra::kRowCopyMostWorkgroups) {
+    args.first_wg = at;
+    const int64_t left = workgroups - at;
+    err = launch(kernel, dim3((unsigned)(left < hydra::kRowCopyMostWorkgroups ? left : hydra::kRowCopyMostWorkgroups)), dim3(hydra::kRowCopyThreads), stream, args);
+  }
+  return err;
+}
+
 // Compute units of the current device (0 if the runtime cannot tell).  Looked up on every call:
 // the library keeps no state, and the attribute query does not touch the device.
 unsigned compute_units() {
@@ -479,21 +491,17 @@ int hydra_kv_cache_write(const void* k, const void* v, int64_t k_token_stride, i
   if (k_token_stride < row || v_token_stride < row || ((k_token_stride | v_token_stride) & 7)) return HYDRA_ERR_INVALID_ARG;
 
   hydra::KvWriteArgs args;
-  args.k = static_cast<const uint4*>(k);
-  args.v = static_cast<const uint4*>(v);
-  args.k_cache = static_cast<uint4*>(k_cache);
-  args.v_cache = static_cast<uint4*>(v_cache);
+  args.k = static_cast<const hydra::piece_t*>(k);
+  args.v = static_cast<const hydra::piece_t*>(v);
+  args.k_cache = static_cast<hydra::piece_t*>(k_cache);
+  args.v_cache = static_cast<hydra::piece_t*>(v_cache);
   args.slot_mapping = slot_mapping;
   args.k_stride16 = k_token_stride / 8;
   args.v_stride16 = v_token_stride / 8;
   args.total_tokens = total_tokens;
   args.row16 = (int32_t)(row / 8);
-
-  const int64_t pieces = (int64_t)total_tokens * args.row16;
-  int64_t blocks = (pieces + hydra::kKvWriteThreads - 1) / hydra::kKvWriteThreads;
-  const int64_t max_blocks = 256 * 32;  // grid-stride beyond this
-  if (blocks > max_blocks) blocks = max_blocks;
-  const hipError_t err = launch(hydra::kv_cache_write_kernel, dim3((unsigned)blocks), dim3(hydra::kKvWriteThreads), static_cast<hipStream_t>(stream), args);
+  args.runs = hydra::runs_of_row(args.row16);
+  const hipError_t err = launch_row_copy(hydra::kv_cache_write_kernel, args, hydra::row_copy_workgroups(total_tokens, args.row16), static_cast<hipStream_t>(stream));
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }
 
@@ -514,20 +522,18 @@ int launch_page_cache(bool gather, const void* packed, int64_t packed_row_stride
   args.packed_stride16 = packed_row_stride / 8;
   args.n_rows = n_rows;
   args.row16 = row_elems / 8;
-  const int64_t pieces = (int64_t)n_rows * args.row16;
-  int64_t blocks = (pieces + hydra::kPageCacheThreads - 1) / hydra::kPageCacheThreads;
-  const int64_t max_blocks = 256 * 32;  // grid-stride beyond this
-  if (blocks > max_blocks) blocks = max_blocks;
+  args.runs = hydra::runs_of_row(args.row16);
+  const int64_t workgroups = hydra::row_copy_workgroups(n_rows, args.row16);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
   if (gather) {
-    args.src = static_cast<const uint4*>(cache);
-    args.dst = static_cast<uint4*>(const_cast<void*>(packed));
-    err = launch(hydra::page_cache_kernel<true>, dim3((unsigned)blocks), dim3(hydra::kPageCacheThreads), s, args);
+    args.src = static_cast<const hydra::piece_t*>(cache);
+    args.dst = static_cast<hydra::piece_t*>(const_cast<void*>(packed));
+    err = launch_row_copy(hydra::page_cache_kernel<true>, args, workgroups, s);
   } else {
-    args.src = static_cast<const uint4*>(packed);
-    args.dst = static_cast<uint4*>(const_cast<void*>(cache));
-    err = launch(hydra::page_cache_kernel<false>, dim3((unsigned)blocks), dim3(hydra::kPageCacheThreads), s, args);
+    args.src = static_cast<const hydra::piece_t*>(packed);
+    args.dst = static_cast<hydra::piece_t*>(const_cast<void*>(cache));
+    err = launch_row_copy(hydra::page_cache_kernel<false>, args, workgroups, s);
   }
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }

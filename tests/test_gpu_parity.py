@@ -437,6 +437,8 @@ def test_kv_write_tiny_bit_exact():
 
 def test_kv_write_strided_and_skipped():
     _kv_case(si.tiny(True), strided=True, skip_fraction=0.2)
+    _kv_case(si.custom([3, 2], 1, 1, 64, True, kv_cache=True, seed=2))               # a row smaller than one wave
+    _kv_case(si.custom([70], 9, 9, 80, True, kv_cache=True, seed=3), strided=True)  # rows of one wave and a part of another
     _kv_case(si.custom([5, 300, 1], 4, 4, 80, True, kv_cache=True, seed=4), strided=True)
 
 
@@ -476,3 +478,18 @@ def test_page_cache_write_and_gather_bit_exact(batch):
     want_out = out0.copy()
     want_out[:, 32 : 32 + batch.hidden] = reference.page_cache_gather(want_cache, slots, out0[:, 32 : 32 + batch.hidden])
     assert np.array_equal(si.bf16_bits(out), want_out)
+
+
+def test_page_cache_more_rows_than_one_grid_holds():
+    """More rows of one piece than the workgroups of one launch cover: the copy goes on in a second launch."""
+    hydra = _hydra()
+    dev = torch.device("cuda:0")
+    n = 4 * (1 << 23) + 5
+    rows = torch.arange(n * 4, dtype=torch.int32, device=dev).view(torch.bfloat16).view(n, 8)
+    slots = torch.arange(n - 1, -1, -1, dtype=torch.int64, device=dev)
+    cache = torch.zeros((n, 8), dtype=torch.bfloat16, device=dev)
+    hydra.hydra_page_cache_write(rows, cache, slots)
+    assert torch.equal(cache.view(torch.int32), rows.view(torch.int32).flip(0))
+    back = torch.zeros_like(rows)
+    hydra.hydra_page_cache_gather(cache, slots, back)
+    assert torch.equal(back.view(torch.int32), rows.view(torch.int32))
