@@ -886,7 +886,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
     const int row = i / kColGroups, col = (i - row * kColGroups) * 4;
     f32x4_t v[kMaxSplits];
     float top[kMaxSplits], sum[kMaxSplits];
-    // (shares past the last one re-read it, with weight 0: no branch between the loads)
+    // (shares past the last one re-read it and are left out below: no branch between the loads)
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) {
       const float* rec = recs + (int64_t)(s < n_shares ? s : n_shares - 1) * kPartialFloats<D>;
@@ -901,10 +901,12 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) {
-      const float w = s < n_shares ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
-      total += w * sum[s];
+      // (not by weight 0 alone: an infinite V in the last share would come out as NaN)
+      const bool live = s < n_shares;
+      const float w = live ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
+      total += w * (live ? sum[s] : 0.f);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += w * v[s][e];
+      for (int e = 0; e < 4; ++e) acc[e] += w * (live ? v[s][e] : 0.f);
     }
     const float inv = 1.0f / total;
     const int token = row / a.group;

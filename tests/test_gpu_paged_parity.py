@@ -324,3 +324,17 @@ def test_decode_form(case):
     want = _want(h, q, kc, vc, tables)
     _check(_run_gpu(h, q, kc, vc, tables, use_workspace=False), want)
     _check(_run_gpu(h, q, kc, vc, tables), want)
+
+
+def test_split_context_with_an_infinite_value():
+    """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
+    column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
+    h = si.HybridBatch("inf", [1, 1], [2000, 700], 4, 1, 128, block_size=16, seed=11)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    want = _want(h, q, kc, vc, tables)
+    vc = vc.clone()
+    vc[int(tables[1][699 // 16]), 699 % 16, 0, 3] = float("inf")
+    out = _run_gpu(h, q, kc, vc, tables).cpu()
+    assert (out[1, :, 3] == float("inf")).all()
+    out[1, :, 3] = torch.from_numpy(want[1, :, 3])
+    _check(out, want)
