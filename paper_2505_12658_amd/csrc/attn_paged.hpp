@@ -628,7 +628,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // Without long chains the decode steps are what the kernel waits for, and they stay in front.
   int place = (int)blockIdx.x;
   {
-    const int c = ((kFirstLayer * 2 - n_rows_wgs) / 2) & ~7;  // (a multiple of 8: KV heads keep their dies)
+    int c = (kFirstLayer * 2 - n_rows_wgs) / 2;
+    c = (c < a.n_tile_wgs ? c : a.n_tile_wgs) & ~7;  // (places only change hands with ids that the grid has; a multiple of 8: KV heads keep their dies)
     const int id = (int)blockIdx.x;
     if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
       bool far = false;

@@ -338,3 +338,17 @@ def test_split_context_with_an_infinite_value():
     assert (out[1, :, 3] == float("inf")).all()
     out[1, :, 3] = torch.from_numpy(want[1, :, 3])
     _check(out, want)
+
+
+def test_fewer_chunk_workgroups_than_free_slots():
+    """A workspace that holds 3 of the 5 shares asked for: 270 decode workgroups leave more of the chip's second layer free
+    than the one small chunk has workgroups, and every share still has to find a workgroup."""
+    import paper_2505_12658_amd as hydra
+
+    h = si.HybridBatch("few", [33] + [1] * 89, [1500] * 90, 1, 1, 64, block_size=16, seed=5)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    record = (2 * 32 + 32 * 64) * 4
+    assert hydra.hydra_attn_paged_workspace_bytes(90, 1, 64, tables.shape[1], 16) == 5 * 90 * record
+    ws = torch.full((3 * 90 * record // 4,), float("nan"), device="cuda:0")
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    _check(_run_gpu(h, q, kc, vc, tables, out=out, workspace=ws), _want(h, q, kc, vc, tables))
