@@ -90,7 +90,7 @@ struct DecodeWave {
   int kv_len, block_shift, last_block;
 
   __device__ __forceinline__ void init(const uint16_t* k_cache, const uint16_t* v_cache, int n_kv_heads, int kv_head, int kv_len_, int block_shift_,
-                                       int num_blocks, const uint16_t* q_row, uint32_t stage, int lane) {
+                                       int num_blocks, const uint16_t* q_row, float scale_log2, uint32_t stage, int lane) {
     const int m = lane & 15, h = lane >> 4;
     k_base = (uint64_t)(uintptr_t)(k_cache + (int64_t)kv_head * D);
     v_base = (uint64_t)(uintptr_t)(v_cache + (int64_t)kv_head * D);
@@ -106,7 +106,7 @@ struct DecodeWave {
     kv_len = kv_len_;
     block_shift = block_shift_;
     last_block = num_blocks - 1;
-    row_max = -3.0e38f;
+    row_max = lowest_reference(scale_log2);
     row_sum = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) q[s] = *reinterpret_cast<const bf16x8_t*>(q_row + (4 * s + h) * 8);
@@ -246,7 +246,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
 
   const int steps = begin + wave < end ? (end - begin - wave + n_waves - 1) / n_waves : 0;
   DecodeWave<D> w;
-  w.init(a.k_cache, a.v_cache, a.n_kv_heads, kv_head, kv_len, a.block_shift, a.num_blocks, a.q + (int64_t)(q_start + token) * a.q_stride + head * D,
+  w.init(a.k_cache, a.v_cache, a.n_kv_heads, kv_head, kv_len, a.block_shift, a.num_blocks, a.q + (int64_t)(q_start + token) * a.q_stride + head * D, c,
          (uint32_t)(uintptr_t)HYDRA_LDS_PTR(s_slots + wave * kDecodeSlotFloats<D>), lane);
   if (steps > 0) {
     // Block-table entries of the wave's next 32 steps: lane 2 i + half has the entry of that half of step i

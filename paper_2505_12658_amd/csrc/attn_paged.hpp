@@ -315,7 +315,7 @@ struct WaveTile {
     }
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
-      row_max[qs] = -3.0e38f;
+      row_max[qs] = lowest_reference(c);
       row_sum[qs] = 0.f;
 #pragma unroll
       for (int cc = 0; cc < CC; ++cc)

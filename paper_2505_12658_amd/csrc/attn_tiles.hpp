@@ -108,6 +108,10 @@ __device__ __forceinline__ int items_of_sequence(int len, int group) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The running maximum before the first visible key: as low as its product with the scale stays finite (a row whose keys
+// are all masked so far subtracts that product from -inf, and the difference has to stay -inf).
+__device__ __forceinline__ float lowest_reference(float scale_log2) { return -3.0e38f / fmaxf(scale_log2, 1.0f); }
+
 // Exchange between the two 32-lane halves with v_permlane32_swap, which swaps the upper half
 // of its first register with the lower half of its second.  Starting from two copies of x:
 //   r0 = x of the low-half lane of the pair (in both lanes), r1 = x of the high-half lane.

@@ -352,3 +352,13 @@ def test_fewer_chunk_workgroups_than_free_slots():
     ws = torch.full((3 * 90 * record // 4,), float("nan"), device="cuda:0")
     out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
     _check(_run_gpu(h, q, kc, vc, tables, out=out, workspace=ws), _want(h, q, kc, vc, tables))
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_large_scale_with_masked_blocks(d):
+    """Softmax scale 1: rows whose first keys in a wave are all masked (the early tokens of a short chunk see none of the
+    last 8 keys, which one wave has alone) keep weight 0 for them."""
+    h = si.HybridBatch("scale", [16, 3], [40, 33], 1, 1, d, block_size=16, seed=d)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    q = q * 0.125
+    _check(_run_gpu(h, q, kc, vc, tables, scale=1.0), _want(h, q, kc, vc, tables, scale=1.0))
