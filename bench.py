@@ -316,7 +316,7 @@ def paged_attention(dev, n_sets: int, steps: int):
         avg = float(t.mean())
         gbs = h.attention_min_bytes() / avg * 1e-9
         report.append({"workload": h.name, "requests": h.batch, "new_tokens": h.total_q, "context_tokens": int(sum(h.kv_lens)),
-                       "kernel": "attn_paged_kernel", "bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                       "kernel": "attn_decode_kernel" if h.max_q_len == 1 else "attn_paged_kernel", "bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                        "frac": gbs / PEAK_HBM_GBS, "avg_kernel_us": avg * 1e6, "min_kernel_us": float(t.min()) * 1e6,
                        "algorithmic_bytes": h.attention_min_bytes(), "attention_flops": h.attention_flops(),
                        "tflops": h.attention_flops() / avg * 1e-12})
