@@ -22,8 +22,10 @@ struct KvWriteArgs {
   int64_t first_wg;                // workgroups of the launches before this one
 };
 
-// The rows are on their way while the slot is looked up.  (non-temporal on both sides: the rows are not read again here,
-// and the cache lines are written whole; plain stores made the LLaVA prefill pass 168 -> 183 us)
+// Non-temporal on both sides: the rows are not read again here, and the cache lines are written whole; plain stores made
+// the LLaVA prefill pass 168 -> 183 us.  The compiler puts the row loads behind the test of the slot, one round trip to
+// memory later; held ahead of it, for launches that fit the chip at once, they won 0.0 - 0.4 us of passes of 11 - 60 us
+// (4 decode steps 10.9 -> 10.8, hybrid batch 60.6 -> 60.2), too little for a second path.
 __global__ __launch_bounds__(kRowCopyThreads) void kv_cache_write_kernel(const KvWriteArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   int32_t t, p;
