@@ -67,7 +67,8 @@ typedef enum {
  *        every token in [0, total_tokens) that belongs to a sequence is written.
  *   cu_seqlens  device int32 [batch + 1]; cu_seqlens[0] == 0, non-decreasing, cu_seqlens[batch] ==
  *        total_tokens, no sequence longer than max_seqlen.  Zero-length sequences are allowed.
- *   max_seqlen  upper bound on the sequence lengths (>= 1); only used to size and order the work.
+ *   max_seqlen  upper bound on the sequence lengths (>= 1), from which the 32-bit addressing limit is checked; a loose
+ *        bound costs nothing.
  *   head_dim    64, 80 or 128.   n_q_heads % n_kv_heads == 0.
  *   softmax_scale  finite and >= 0 (normally 1/sqrt(head_dim)).
  *   workspace   device memory, 16-byte aligned, at least hydra_attn_workspace_bytes(...) bytes.  It

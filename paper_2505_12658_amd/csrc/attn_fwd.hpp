@@ -1032,10 +1032,48 @@ __device__ __forceinline__ int wave_scan_add(int x) {
   return x;
 }
 
+// The entry that this workgroup takes from the dies' queues: workgroup t the t-th of all entries by place and, at one
+// place, by die.  While every queue has entries that is place t / 8 of the own die's queue (t % 8); dies that have run
+// out, or never had a (sequence, KV head) pair, take their part of what the others still hold, at the same place in the
+// order, so that neither the order by cost nor the grid depends on how the entries are spread over the dies.
+// n: entries of queue lane % 8.  Called by whole waves; false for workgroups past the last entry.
+// Without it (every queue done by its own die, the grid sized for the longest queue that max_seqlen allows), us: one request
+// of 8192 tokens with 28 / 4 heads of 128 800 -> 422 (half of the dies had nothing; persistent workgroups that steal 518),
+// with 8 / 1 heads 682 -> 155 (307); 12 requests of 200 .. 1047 tokens under a bound of 32 768 75.7 -> 59.7.
+__device__ __forceinline__ bool take_entry(int n, int t, int& die, int& place) {
+  die = t % kXcds;
+  place = t / kXcds;
+  if ((__builtin_amdgcn_ballot_w64(n > place) & 0xff) == 0xff) return true;
+  int count[kXcds], total = 0;
+#pragma unroll
+  for (int y = 0; y < kXcds; ++y) {
+    count[y] = __builtin_amdgcn_readlane(n, y);
+    total += count[y];
+  }
+  if (t >= total) return false;
+  auto entries_before = [&](int p) {  // at places below p
+    int sum = 0;
+#pragma unroll
+    for (int y = 0; y < kXcds; ++y) sum += count[y] < p ? count[y] : p;
+    return sum;
+  };
+  // the last place with at most t entries before it: at least t / 8, at most t; 64 candidates at a time
+  const int lane = threadIdx.x & 63;
+  for (int span = t - place + 1; span > 1;) {
+    const int step = (span + 63) / 64;
+    place += (__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane * step < span && entries_before(place + lane * step) <= t)) - 1) * step;
+    span = step;
+  }
+  uint32_t open = (uint32_t)__builtin_amdgcn_ballot_w64(n > place) & 0xff;
+  for (int skip = t - entries_before(place); skip > 0; --skip) open &= open - 1;
+  die = __builtin_ctz(open);
+  return true;
+}
+
 // The unit of this workgroup in a batch whose sequence of length L has units(L) units per KV head: its KV head, its
 // sequence and its number there; false for workgroups past the last one.  The order is that of the work list
 // (worklist.hpp): sequences ranked by length, longest first, their (sequence, KV head) pairs dealt to the dies in
-// serpentine order, die x taking workgroup ids x, x + 8, ...
+// serpentine order, and the units of a die's pairs handed out by take_entry.
 template <typename Units>
 __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv_heads, Units units, int& seq_start, int& seq_len, int& kv_head, int& unit) {
   const int lane = threadIdx.x & 63;
@@ -1058,17 +1096,30 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
     len = __builtin_amdgcn_ds_permute(rank * 4, len);
   }
   const int n = units(len);
-  // rows of this die's column, 64 at a time: units of each row's pair and, by a scan, of the rows before it
-  const int die = (int)blockIdx.x % kXcds, place = (int)blockIdx.x / kXcds;
   const int pairs = batch * n_kv_heads;
   const float per_kv = 1.0f / n_kv_heads;
+  // the pair in a row of one pair per die, its sequence, and its units (0 past the last pair)
+  auto pair_of = [&](int row, int column) { return row * kXcds + ((row & 1) ? kXcds - 1 - column : column); };
+  auto seq_of = [&](int pair) { return (int)((pair + 0.5f) * per_kv); };  // pair / n_kv_heads (exact: fewer than 2^20 pairs)
+  auto units_of = [&](int pair) {
+    const int seq = seq_of(pair);
+    const int u = __builtin_amdgcn_ds_bpermute((seq < 63 ? seq : 63) * 4, n);
+    return pair < pairs ? u : 0;
+  };
+  int die = (int)blockIdx.x % kXcds, place = (int)blockIdx.x / kXcds;
+  if (n_kv_heads % kXcds != 0) {  // (otherwise every die has the same pairs of every sequence)
+    int queue = 0;                // units of the pairs of column lane % 8
+    for (int row0 = 0; row0 * kXcds < pairs; row0 += 64 / kXcds) queue += units_of(pair_of(row0 + lane / kXcds, lane % kXcds));
+    queue += __shfl_xor(queue, 8);
+    queue += __shfl_xor(queue, 16);
+    queue += __shfl_xor(queue, 32);
+    if (!take_entry(queue, (int)blockIdx.x, die, place)) return false;
+  }
+  // rows of the die's column, 64 at a time: units of each row's pair and, by a scan, of the rows before it
   int before = 0;
   for (int row0 = 0; row0 * kXcds < pairs; row0 += 64) {
-    const int row = row0 + lane;
-    const int pair = row * kXcds + ((row & 1) ? kXcds - 1 - die : die);
-    const int seq = (int)((pair + 0.5f) * per_kv);  // pair / n_kv_heads (exact: fewer than 2^20 pairs)
-    int mine = __builtin_amdgcn_ds_bpermute((seq < 63 ? seq : 63) * 4, n);
-    if (pair >= pairs) mine = 0;
+    const int pair = pair_of(row0 + lane, die), seq = seq_of(pair);
+    const int mine = units_of(pair);
     const int incl = wave_scan_add(mine);
     const int here = __builtin_amdgcn_readlane(incl, 63);
     if (place < before + here) {
@@ -1096,9 +1147,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroups
   __shared__ __attribute__((aligned(16))) int s_redo[8];
   DirectSource src;
   if (batch == 0) {
-    const int die = (int)blockIdx.x % kXcds, at = a.ctrl->xcd_start[die] + (int)blockIdx.x / kXcds;
-    if (at >= a.ctrl->xcd_start[die + 1]) return;
-    const WorkItem it = a.items[at];
+    const int lane = threadIdx.x & 63;
+    const int first = a.ctrl->xcd_start[lane % kXcds];
+    int die, place;
+    if (!take_entry(a.ctrl->xcd_start[lane % kXcds + 1] - first, (int)blockIdx.x, die, place)) return;
+    const WorkItem it = a.items[__builtin_amdgcn_readlane(first, die) + place];
     src.q_start = __builtin_amdgcn_readfirstlane(it.x);
     src.q_len = __builtin_amdgcn_readfirstlane(it.y);
     src.f0 = __builtin_amdgcn_readfirstlane(it.z);

@@ -86,16 +86,11 @@ bool within_rounds(size_t rounds, int32_t head_dim, size_t capacity, unsigned co
 bool list_free(int32_t batch, int32_t head_dim, size_t capacity, unsigned compute_units) {
   return batch <= hydra::kDirectSeqs && within_rounds(kListFreeRounds, head_dim, capacity, compute_units);
 }
+// (grid: as many workgroups as there can be items; their order takes care of how they spread over the dies)
 template <int D>
-hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, int32_t batch, int32_t n_kv_heads, int32_t max_seqlen, size_t capacity,
-                         hipStream_t stream) {
-  // a workgroup per item of the die that has most: dealt out in rows of one pair per die by falling length, no die has
-  // more than the mean and one longest pair
-  const int64_t longest = (((int64_t)max_seqlen + hydra::kWaveTileRows - 1) / hydra::kWaveTileRows * args.group + hydra::kWavesPerItem - 1) / hydra::kWavesPerItem;
-  const int64_t per_die = ((int64_t)capacity + hydra::kXcds - 1) / hydra::kXcds + longest;
-  const unsigned grid = (unsigned)((per_die < (int64_t)capacity ? per_die : (int64_t)capacity) * hydra::kXcds);
-  return causal ? launch(hydra::attn_fwd_direct_kernel<D, true>, dim3(grid), dim3(256), stream, args, batch, n_kv_heads)
-                : launch(hydra::attn_fwd_direct_kernel<D, false>, dim3(grid), dim3(256), stream, args, batch, n_kv_heads);
+hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, int32_t batch, int32_t n_kv_heads, size_t capacity, hipStream_t stream) {
+  return causal ? launch(hydra::attn_fwd_direct_kernel<D, true>, dim3((unsigned)capacity), dim3(256), stream, args, batch, n_kv_heads)
+                : launch(hydra::attn_fwd_direct_kernel<D, false>, dim3((unsigned)capacity), dim3(256), stream, args, batch, n_kv_heads);
 }
 
 // Bytes of one partial result of the paged kernel's packed-rows form.
@@ -299,9 +294,9 @@ int launch_packed(const void* q, const void* k, const void* v, void* out, int64_
   if (workgroups_per_cu == 0 && (!with_list || within_rounds(kDirectRounds, head_dim, lay.capacity, cus))) {
     const int32_t seqs = with_list ? 0 : batch;
     switch (head_dim) {
-      case 64: err = launch_direct<64>(causal != 0, args, seqs, n_kv_heads, max_seqlen, lay.capacity, s); break;
-      case 80: err = launch_direct<80>(causal != 0, args, seqs, n_kv_heads, max_seqlen, lay.capacity, s); break;
-      default: err = launch_direct<128>(causal != 0, args, seqs, n_kv_heads, max_seqlen, lay.capacity, s); break;
+      case 64: err = launch_direct<64>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
+      case 80: err = launch_direct<80>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
+      default: err = launch_direct<128>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
     }
     return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
   }

@@ -309,6 +309,36 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
 
 
 @pytest.mark.parametrize("lengths,hq,hkv,d", [
+    ([1500], 7, 1, 128),             # one pair: seven dies have no queue of their own
+    ([900, 40], 14, 2, 64),          # four pairs of two lengths
+    ([700, 650, 30], 12, 12, 64),    # pairs in rows and a half
+    ([260] * 5, 3, 3, 80),
+    ([64] * 9, 1, 1, 64),            # nine pairs of one item: the ninth item is the second of its die
+])
+def test_items_are_handed_out_whole_for_any_bound(lengths, hq, hkv, d):
+    """Batches whose (sequence, KV head) pairs do not spread evenly over the dies, with an exact, a loose and an understated
+    max_seqlen (it limits addressing only): every item is done, with and without a work list, the same bits."""
+    hydra = _hydra()
+    w = si.custom(lengths, hq, hkv, d, True, seed=len(lengths) + hq)
+    q, k, v = si.make_qkv(w)
+    dev = torch.device("cuda:0")
+    cu = torch.from_numpy(w.cu_seqlens).to(dev)
+    qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+    want = c_oracle.attn_varlen(_f64(q), _f64(k), _f64(v), w.cu_seqlens, True, w.softmax_scale)
+    first = None
+    for bound in (w.max_seqlen, 20 * w.max_seqlen, 1):
+        ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, bound, hq, hkv, d, True)
+        plain, listed = torch.full_like(qd, float("nan")), torch.full_like(qd, float("nan"))
+        hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, bound, True, w.softmax_scale, out=plain)
+        hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, bound, True, w.softmax_scale, listed, ws)
+        torch.cuda.synchronize()
+        if first is None:
+            first = plain
+            _check(first, want)
+        assert torch.equal(plain.view(torch.int16), first.view(torch.int16)) and torch.equal(listed.view(torch.int16), first.view(torch.int16))
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d", [
     ([40] * 3, 2, 1, 64),                 # fewer items than workgroups on every die: nothing is claimed
     ([20] * 800, 1, 1, 64),               # more items than workgroups on some dies
     ([64] * 1024 + [1], 1, 1, 128),       # twice the workgroups everywhere and one over
