@@ -16,10 +16,7 @@ struct KvWriteArgs {
   piece_t* v_cache;
   const int64_t* slot_mapping;
   int64_t k_stride16, v_stride16;  // token strides in 16-byte units
-  int32_t total_tokens;
-  int32_t row16;                   // 16-byte pieces per token row (n_kv_heads * head_dim / 8)
-  int32_t runs;                    // runs_of_row(row16)
-  int64_t first_wg;                // workgroups of the launches before this one
+  RowCopyPlan rows;                // one row per token, n_kv_heads * head_dim elements
 };
 
 // Non-temporal on both sides: the rows are not read again here, and the cache lines are written whole; plain stores made
@@ -28,14 +25,14 @@ struct KvWriteArgs {
 // (4 decode steps 10.9 -> 10.8, hybrid batch 60.6 -> 60.2), too little for a second path.
 __global__ __launch_bounds__(kRowCopyThreads) void kv_cache_write_kernel(const KvWriteArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  int32_t t, p;
-  if (!piece_of_lane(a.total_tokens, a.row16, a.runs, a.first_wg, t, p)) return;
-  const int64_t slot = slot_of(a.slot_mapping, t);
+  int64_t t, slot;
+  int32_t p;
+  if (!piece_of_lane(a.rows, a.slot_mapping, t, slot, p)) return;
   const piece_t k = __builtin_nontemporal_load(a.k + t * a.k_stride16 + p);
   const piece_t v = __builtin_nontemporal_load(a.v + t * a.v_stride16 + p);
   if (slot < 0) return;
-  __builtin_nontemporal_store(k, a.k_cache + slot * a.row16 + p);
-  __builtin_nontemporal_store(v, a.v_cache + slot * a.row16 + p);
+  __builtin_nontemporal_store(k, a.k_cache + slot * a.rows.row16 + p);
+  __builtin_nontemporal_store(v, a.v_cache + slot * a.rows.row16 + p);
 #else
   (void)a;
 #endif

@@ -17,24 +17,24 @@ struct PageCacheArgs {
   piece_t* dst;                 // write: the cache, gather: packed rows
   const int64_t* slot_mapping;  // one cache slot (page * page_rows + row in page) per packed row; < 0: row skipped
   int64_t packed_stride16;      // stride of the packed rows in 16-byte units
-  int32_t n_rows;
-  int32_t row16;                // 16-byte pieces per row
-  int32_t runs;                 // runs_of_row(row16)
-  int64_t first_wg;             // workgroups of the launches before this one
+  RowCopyPlan rows;
 };
 
 // GATHER == false: cache[slot[t]] = packed[t];  GATHER == true: packed[t] = cache[slot[t]].
-template <bool GATHER>
+// KILOBYTES: the rows are whole kilobytes (rows.waves != 0).
+template <bool GATHER, bool KILOBYTES>
 __global__ __launch_bounds__(kRowCopyThreads) void page_cache_kernel(const PageCacheArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  int32_t t, p;
-  if (!piece_of_lane(a.n_rows, a.row16, a.runs, a.first_wg, t, p)) return;
-  const int64_t slot = slot_of(a.slot_mapping, t);
-  if (slot < 0) return;
-  // (non-temporal loads: nothing here is read twice; plain stores, since what is written is read by the next kernel:
-  // image cache and back 64.8 us, both non-temporal 67.2, neither 69.3)
-  const piece_t x = __builtin_nontemporal_load(a.src + (GATHER ? slot * a.row16 : t * a.packed_stride16) + p);
-  a.dst[(GATHER ? t * a.packed_stride16 : slot * a.row16) + p] = x;
+  int64_t t, slot;
+  int32_t p;
+  if (!piece_of_lane(a.rows, a.slot_mapping, t, slot, p) || slot < 0) return;
+  // Stores are plain, since what is written is read by the next kernel.  Rows of whole kilobytes are loaded non-temporally
+  // (nothing here is read twice): 14 014 rows of 7 KB into the cache and back 66.3 us, with plain loads 72.1.  Other rows
+  // end inside cache lines that the lanes of the next row read too: 50 000 rows of 1440 bytes 47.2 us with plain loads, 60.9
+  // with non-temporal ones.
+  const piece_t* src = a.src + (GATHER ? slot * a.rows.row16 : t * a.packed_stride16) + p;
+  const piece_t x = KILOBYTES ? __builtin_nontemporal_load(src) : *src;
+  a.dst[(GATHER ? t * a.packed_stride16 : slot * a.rows.row16) + p] = x;
 #else
   (void)a;
 #endif

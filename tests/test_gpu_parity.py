@@ -523,3 +523,36 @@ def test_page_cache_more_rows_than_one_grid_holds():
     back = torch.zeros_like(rows)
     hydra.hydra_page_cache_gather(cache, slots, back)
     assert torch.equal(back.view(torch.int32), rows.view(torch.int32))
+
+
+@pytest.mark.parametrize("row", [8, 16, 64, 72, 200, 504, 512, 520, 720, 1024])
+def test_rows_of_any_width(row):
+    """Row copies of rows that do and do not fill whole waves (64 pieces of 16 bytes), from strided views, with skipped rows:
+    the KV scatter and the image cache in both directions, bit for bit, and nothing else written."""
+    hydra = _hydra()
+    dev = torch.device("cuda:0")
+    gen = torch.Generator().manual_seed(row)
+    n, num = 1003, 1040
+    bits = lambda *shape: torch.randint(-2**15, 2**15, shape, generator=gen, dtype=torch.int16)  # noqa: E731
+    wide, cache0, out0 = bits(n, 2 * row + 24), bits(2, num, row), bits(n, row + 8)
+    slots = torch.randperm(num, generator=gen)[:n]
+    slots[torch.rand(n, generator=gen) < 0.1] = -1
+    kept = slots >= 0
+    k, v = wide[:, 8: 8 + row], wide[:, 16 + row: 16 + 2 * row]
+    want = cache0.clone()
+    want[0, slots[kept]], want[1, slots[kept]] = k[kept], v[kept]
+    wide_d, caches = wide.to(dev).view(torch.bfloat16), cache0.to(dev).view(torch.bfloat16)
+    kd, vd = wide_d[:, 8: 8 + row], wide_d[:, 16 + row: 16 + 2 * row]
+    hydra.hydra_kv_cache_write(kd.view(n, 2, row // 2), vd.view(n, 2, row // 2), caches[0].view(num // 16, 16, 2, row // 2),
+                               caches[1].view(num // 16, 16, 2, row // 2), slots.to(dev))
+    torch.cuda.synchronize()
+    assert torch.equal(caches.cpu().view(torch.int16), want)
+    pages = cache0[0].to(dev).view(torch.bfloat16)
+    hydra.hydra_page_cache_write(kd, pages, slots.to(dev))
+    back = out0.to(dev).view(torch.bfloat16)
+    hydra.hydra_page_cache_gather(pages, slots.to(dev), back[:, 8:])
+    torch.cuda.synchronize()
+    assert torch.equal(pages.cpu().view(torch.int16), want[0])
+    want_back = out0.clone()
+    want_back[kept, 8:] = k[kept]
+    assert torch.equal(back.cpu().view(torch.int16), want_back)
