@@ -856,12 +856,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #endif
 }
 
-// Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch), kCombineThreads threads.
+// Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch, parts), kCombineThreads threads;
+// parts: as many as give every thread 4 output columns of one row, for the most rows a request of the batch can have.
 // Requests that took the wave-tile form, have no new tokens, or whose context fits one share (already finished by one
-// workgroup) are skipped.  A thread adds up 4 output columns of one row over the shares; it asks for everything it
-// needs (every share's row statistics and columns) before it uses any of it, so that behind the two lengths the kernel
-// is one round trip to memory long: it runs on an idle chip, and latency is all it costs (3.8 us after a decode of 4
-// requests, 4.6 us after one of 8 x 16 384 keys, most of it launch and instruction fetch).
+// workgroup) are skipped.  A thread adds up its columns over the shares; it asks for everything it needs (every share's row
+// statistics and columns) before it uses any of it, so that behind the two lengths the kernel is one round trip to memory
+// long: it runs on an idle chip, and latency is all it costs (3.8 us after a decode of 4 requests, 4.6 us after one of
+// 8 x 16 384 keys, most of it launch and instruction fetch).  With one workgroup per (request, KV head) a request of more than
+// 8 rows of 128 took that trip two to four times: 30 requests of 4 new tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2,
+// 28 / 2 heads, 18.9 -> 15.9; decode steps unchanged.
 constexpr int kMaxSplits = 16;
 constexpr int kCombineThreads = 256;
 
@@ -883,7 +886,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
   share_plan(n_halves, a.halves_per_split, per_share, n_shares);
   const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
   constexpr int kColGroups = D / 4;
-  for (int i = threadIdx.x; i < n_rows * kColGroups; i += kCombineThreads) {
+  for (int i = (int)blockIdx.z * kCombineThreads + (int)threadIdx.x; i < n_rows * kColGroups; i += (int)gridDim.z * kCombineThreads) {
     const int row = i / kColGroups, col = (i - row * kColGroups) * 4;
     f32x4_t v[kMaxSplits];
     float top[kMaxSplits], sum[kMaxSplits];

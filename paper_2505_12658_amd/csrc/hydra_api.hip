@@ -134,7 +134,7 @@ int choose_splits(const PagedSplits& s, int64_t pairs, int32_t head_dim, size_t 
 // Launches of attn_paged_fwd for one head dimension: the decode kernel when no request of the batch has more rows than
 // its form takes, otherwise the kernel that holds all forms; then the merge of split contexts.
 template <int D>
-hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, unsigned rows_wgs, unsigned tile_wgs, hipStream_t s) {
+hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t max_q_len, bool decode_only, unsigned rows_wgs, unsigned tile_wgs, hipStream_t s) {
   hipError_t err;
   bool launched = false;
   if constexpr (hydra::paged::kDecodeForm<D>) {
@@ -150,8 +150,12 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, u
     }
   }
   if (!launched) err = launch(hydra::paged::attn_paged_kernel<D>, dim3(rows_wgs + tile_wgs), dim3(256), s, args);
-  if (err == hipSuccess && args.n_splits > 1)
-    err = launch(hydra::paged::attn_paged_combine_kernel<D>, dim3((unsigned)args.n_kv_heads, (unsigned)args.batch), dim3(hydra::paged::kCombineThreads), s, args);
+  if (err == hipSuccess && args.n_splits > 1) {
+    const int64_t rows = (int64_t)max_q_len * args.group;
+    const int64_t pieces = (rows < hydra::paged::kRows ? rows : hydra::paged::kRows) * (D / 4);
+    const unsigned parts = (unsigned)((pieces + hydra::paged::kCombineThreads - 1) / hydra::paged::kCombineThreads);
+    err = launch(hydra::paged::attn_paged_combine_kernel<D>, dim3((unsigned)args.n_kv_heads, (unsigned)args.batch, parts), dim3(hydra::paged::kCombineThreads), s, args);
+  }
   return err;
 }
 
@@ -463,9 +467,9 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
   switch (head_dim) {
-    case 64: err = launch_paged<64>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
-    case 80: err = launch_paged<80>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
-    default: err = launch_paged<128>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    case 64: err = launch_paged<64>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    case 80: err = launch_paged<80>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    default: err = launch_paged<128>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
   }
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }

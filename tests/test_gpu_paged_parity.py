@@ -362,3 +362,13 @@ def test_large_scale_with_masked_blocks(d):
     q, kc, vc, tables = si.make_paged_inputs(h)
     q = q * 0.125
     _check(_run_gpu(h, q, kc, vc, tables, scale=1.0), _want(h, q, kc, vc, tables, scale=1.0))
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("rows", [8, 9, 16, 17, 31, 32])
+def test_merge_of_requests_with_many_rows(d, rows):
+    """Split contexts of requests with up to 32 rows: the merge's threads, 4 columns of one row each, fill one to four workgroups
+    per (request, KV head)."""
+    h = si.HybridBatch("rows", [rows, 1, rows - 1], [2500, 2100, 1400], 2, 2, d, block_size=16, seed=rows)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    _check(_run_gpu(h, q, kc, vc, tables), _want(h, q, kc, vc, tables))
