@@ -123,9 +123,20 @@ PagedSplits paged_splits(int32_t batch, int32_t n_kv_heads, int32_t max_blocks_p
 }
 // The number of the two that leaves fewer keys to the busiest compute unit (the larger one only where it is 10 % fewer),
 // as far as the workspace holds that many partial results.
-int choose_splits(const PagedSplits& s, int64_t pairs, int32_t head_dim, size_t workspace_bytes) {
+// tile_wgs: workgroups for prefill chunks in the same batch.  Unless contexts are long, the kernel waits for the chunks'
+// chains of key tiles, and a share on a chain's unit slows it down.  So beside chunks a share has at least 512 keys, except on
+// units that the chunks leave free, and nothing is split where the decode steps alone take more than half of the units.
+// us, shares as without chunks and now: 20 decode steps of up to 800 keys and a chunk of 512 21.0 -> 15.1; 4 of up to 1000 and
+// 3 chunks of 128 16.9 -> 12.6; 10 of up to 2500 and 4 of 512 55.5 -> 50.4; 30 of up to 2000 and 2 of 512 36.0 -> 31.5.  Split in
+// two with 204 pairs 29.6 instead of 26.9; 4 of up to 2500 and a chunk of 60 in 4 shares 11.3 instead of 10.6 in 9.
+int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t tile_wgs, int32_t head_dim, size_t workspace_bytes) {
   auto layers = [&](int64_t n) { return (pairs * n + 255) / 256; };  // shares on the busiest unit, of 1 / n of a context
   int64_t n = layers(s.twice) * s.once * 10 < layers(s.once) * s.twice * 9 ? s.twice : s.once;
+  if (tile_wgs > 0) {
+    const int64_t free_units = (256 - tile_wgs) / pairs < s.once ? (256 - tile_wgs) / pairs : s.once;
+    n = s.once > 1 ? (keys / 512 < s.twice ? keys / 512 : s.twice) : 1;
+    if (n > 2 && free_units > n) n = free_units;
+  }
   const int64_t fits = (int64_t)(workspace_bytes / (paged_partial_bytes(head_dim) * (size_t)pairs));
   if (n > fits) n = fits;
   return n < 2 ? 1 : (int)n;
@@ -447,12 +458,6 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   const int64_t tok_tiles = ((int64_t)max_q_len + hydra::paged::kRows - 1) / hydra::paged::kRows;
   int64_t groups = (tok_tiles * args.group + hydra::paged::kWavesPerGroup - 1) / hydra::paged::kWavesPerGroup;
   if ((int64_t)max_q_len * args.group <= hydra::paged::kRows) groups = 0;  // every request takes the packed-rows form
-  const int splits = choose_splits(paged_splits(batch, n_kv_heads, max_blocks_per_seq, block_size), (int64_t)batch * n_kv_heads, head_dim, workspace_bytes);
-  args.n_splits = splits;
-  {
-    const int64_t max_halves = ((int64_t)max_blocks_per_seq * block_size + 31) / 32;
-    args.halves_per_split = (int32_t)((max_halves + splits - 1) / splits);
-  }
   args.partials = static_cast<float*>(workspace);
   args.batch = batch;
   // Workgroups of the wave-tile form: one per group of four wave tiles and KV head.  The request lengths are
@@ -460,6 +465,13 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   // (q / 32 + 1) * group / 4 + 1 groups.
   int64_t tile_wgs = 0;
   if (groups > 0) tile_wgs = (((int64_t)total_q / hydra::paged::kRows + batch) * args.group / hydra::paged::kWavesPerGroup + batch) * n_kv_heads;
+  const int splits = choose_splits(paged_splits(batch, n_kv_heads, max_blocks_per_seq, block_size), (int64_t)batch * n_kv_heads,
+                                   (int64_t)max_blocks_per_seq * block_size, tile_wgs, head_dim, workspace_bytes);
+  args.n_splits = splits;
+  {
+    const int64_t max_halves = ((int64_t)max_blocks_per_seq * block_size + 31) / 32;
+    args.halves_per_split = (int32_t)((max_halves + splits - 1) / splits);
+  }
   const int64_t rows_wgs = (int64_t)batch * n_kv_heads * splits;
   if (tile_wgs + rows_wgs > (int64_t)0x7fffffff) return HYDRA_ERR_UNSUPPORTED;
   args.n_tile_wgs = (int32_t)tile_wgs;

@@ -372,3 +372,22 @@ def test_merge_of_requests_with_many_rows(d, rows):
     h = si.HybridBatch("rows", [rows, 1, rows - 1], [2500, 2100, 1400], 2, 2, d, block_size=16, seed=rows)
     q, kc, vc, tables = si.make_paged_inputs(h)
     _check(_run_gpu(h, q, kc, vc, tables), _want(h, q, kc, vc, tables))
+
+
+@pytest.mark.parametrize("kv_lens,chunk,split", [
+    ([1000, 120, 430], 128, False),     # the chunk's chain of key tiles is what the kernel waits for
+    ([2500, 700, 90], 60, True),        # contexts far longer than the chunk
+    ([8200] * 16, 33, True),            # 272 shares, more than compute units, and 24 of the 26 chunk workgroups trade places with them
+    ([2000] * 170, 40, False),          # more than half of the compute units have a decode step
+])
+def test_shares_beside_chunks(kv_lens, chunk, split):
+    """Decode steps and one prefill chunk: contexts are split (partial results in the workspace) only where that pays beside a chunk."""
+    import paper_2505_12658_amd as hydra
+
+    h = si.HybridBatch("beside", [1] * len(kv_lens) + [chunk], list(kv_lens) + [chunk + 600], 2, 1, 64, block_size=16, seed=chunk)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    need = hydra.hydra_attn_paged_workspace_bytes(h.batch, 1, 64, tables.shape[1], 16)
+    ws = torch.full((max(need, 16) // 4,), float("nan"), device="cuda:0")
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    _check(_run_gpu(h, q, kc, vc, tables, out=out, workspace=ws), _want(h, q, kc, vc, tables))
+    assert bool(torch.isfinite(ws).any()) == split
