@@ -233,7 +233,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
 
   const int n_halves = (kv_len + kDecodeKeys - 1) / kDecodeKeys;
   int begin, end, per_share, n_shares;
-  share_plan(n_halves, a.halves_per_split, per_share, n_shares);
+  share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   split_range(n_halves, per_share, split, begin, end);
   if (begin >= end) return;  // past the context's last share: the combine kernel knows and skips it
 
@@ -306,7 +306,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
         *reinterpret_cast<f32x4_t*>(mine + (4 * h + r) * CW + u) = f32x4_t{w.o[u][r], w.o[u + 1][r], w.o[u + 2][r], w.o[u + 3][r]};
   }
   __syncthreads();
-  const bool whole = n_halves <= a.halves_per_split;  // the context fits one share: this workgroup writes the output
+  const bool whole = n_shares == 1;  // the context is one share: this workgroup writes the output
   constexpr int kCols = D / 4;
   for (int i = threadIdx.x; i < n_rows * kCols; i += 64 * n_waves) {
     const int r = i / kCols, col = (i - r * kCols) * 4;

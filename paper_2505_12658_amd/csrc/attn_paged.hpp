@@ -481,10 +481,10 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
   const int n_halves = (kv_len + kHalfKeys - 1) / kHalfKeys;
   int h_begin, h_end;
   int per_share, n_shares;
-  share_plan(n_halves, a.halves_per_split, per_share, n_shares);
+  share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   split_range(n_halves, per_share, split, h_begin, h_end);
   if (h_begin >= h_end) return;  // past the context's last share: the combine kernel knows and skips it
-  const bool whole = n_halves <= a.halves_per_split;  // the context fits one share: this workgroup writes the output
+  const bool whole = n_shares == 1;  // the context is one share: this workgroup writes the output
   // The rows of half tile h + 4 travel (into registers) while half tile h is computed on, and the block-table
   // look-up of half tile h + 8 travels behind them; its entries are not touched before the top of the next round.
   TileSlots<D, kHalfKeys, 1> slots;
@@ -881,9 +881,9 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
   if (q_len <= 0 || kv_len < q_len || q_len * a.group > kRows) return;
   const int n_rows = q_len * a.group;
   const int n_halves = (kv_len + kKvTileRows / 2 - 1) / (kKvTileRows / 2);
-  if (n_halves <= a.halves_per_split) return;  // done by one workgroup, which wrote the output itself
   int per_share, n_shares;
-  share_plan(n_halves, a.halves_per_split, per_share, n_shares);
+  share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
+  if (n_shares == 1) return;  // done by one workgroup, which wrote the output itself
   const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
   constexpr int kColGroups = D / 4;
   for (int i = (int)blockIdx.z * kCombineThreads + (int)threadIdx.x; i < n_rows * kColGroups; i += (int)gridDim.z * kCombineThreads) {

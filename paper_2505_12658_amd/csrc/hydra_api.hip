@@ -124,22 +124,30 @@ PagedSplits paged_splits(int32_t batch, int32_t n_kv_heads, int32_t max_blocks_p
 // The number of the two that leaves fewer keys to the busiest compute unit (the larger one only where it is 10 % fewer),
 // as far as the workspace holds that many partial results.
 // tile_wgs: workgroups for prefill chunks in the same batch.  Unless contexts are long, the kernel waits for the chunks'
-// chains of key tiles, and a share on a chain's unit slows it down.  So beside chunks a share has at least 512 keys, except on
+// chains of key tiles, and a share on a chain's unit slows it down.  So beside chunks a context has one share per 512 keys, except on
 // units that the chunks leave free, and nothing is split where the decode steps alone take more than half of the units.
 // us, shares as without chunks and now: 20 decode steps of up to 800 keys and a chunk of 512 21.0 -> 15.1; 4 of up to 1000 and
 // 3 chunks of 128 16.9 -> 12.6; 10 of up to 2500 and 4 of 512 55.5 -> 50.4; 30 of up to 2000 and 2 of 512 36.0 -> 31.5.  Split in
 // two with 204 pairs 29.6 instead of 26.9; 4 of up to 2500 and a chunk of 60 in 4 shares 11.3 instead of 10.6 in 9.
-int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t tile_wgs, int32_t head_dim, size_t workspace_bytes) {
+// *least_log2: half tiles up to which a context is not cut further (share_plan).  Beside chunks 512 keys, as above; otherwise
+// one half tile per wave, and more where shares are few and long anyway, since short contexts then only add to the merge
+// (30 requests of 100 .. 1400 tokens in 2 shares: 14.4 us with 4 half tiles, 14.0 with 16).
+int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t tile_wgs, int32_t head_dim, size_t workspace_bytes, int32_t* least_log2) {
   auto layers = [&](int64_t n) { return (pairs * n + 255) / 256; };  // shares on the busiest unit, of 1 / n of a context
   int64_t n = layers(s.twice) * s.once * 10 < layers(s.once) * s.twice * 9 ? s.twice : s.once;
+  int32_t beside_chunks = 0;
   if (tile_wgs > 0) {
     const int64_t free_units = (256 - tile_wgs) / pairs < s.once ? (256 - tile_wgs) / pairs : s.once;
     n = s.once > 1 ? (keys / 512 < s.twice ? keys / 512 : s.twice) : 1;
-    if (n > 2 && free_units > n) n = free_units;
+    if (n > 2 && free_units >= n) n = free_units;
+    else beside_chunks = 4;
   }
   const int64_t fits = (int64_t)(workspace_bytes / (paged_partial_bytes(head_dim) * (size_t)pairs));
   if (n > fits) n = fits;
-  return n < 2 ? 1 : (int)n;
+  if (n < 2) n = 1;
+  const int64_t halves = (keys < 2048 ? keys : 2048) / 32 / n;
+  *least_log2 = beside_chunks != 0 ? beside_chunks : halves < 8 ? 2 : halves < 16 ? 3 : 4;
+  return (int)n;
 }
 
 // Launches of attn_paged_fwd for one head dimension: the decode kernel when no request of the batch has more rows than
@@ -466,12 +474,8 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   int64_t tile_wgs = 0;
   if (groups > 0) tile_wgs = (((int64_t)total_q / hydra::paged::kRows + batch) * args.group / hydra::paged::kWavesPerGroup + batch) * n_kv_heads;
   const int splits = choose_splits(paged_splits(batch, n_kv_heads, max_blocks_per_seq, block_size), (int64_t)batch * n_kv_heads,
-                                   (int64_t)max_blocks_per_seq * block_size, tile_wgs, head_dim, workspace_bytes);
+                                   (int64_t)max_blocks_per_seq * block_size, tile_wgs, head_dim, workspace_bytes, &args.least_log2);
   args.n_splits = splits;
-  {
-    const int64_t max_halves = ((int64_t)max_blocks_per_seq * block_size + 31) / 32;
-    args.halves_per_split = (int32_t)((max_halves + splits - 1) / splits);
-  }
   const int64_t rows_wgs = (int64_t)batch * n_kv_heads * splits;
   if (tile_wgs + rows_wgs > (int64_t)0x7fffffff) return HYDRA_ERR_UNSUPPORTED;
   args.n_tile_wgs = (int32_t)tile_wgs;

@@ -25,13 +25,12 @@ struct PagedArgs {
   int32_t n_kv_heads;
   int32_t group;     // n_q_heads / n_kv_heads
   float scale_log2;  // softmax_scale * log2(e)
-  // Packed-rows form, long contexts split over workgroups: a context of more than halves_per_split half tiles
-  // (32 keys each) is cut into the fewest shares that fit that size, all of (nearly) the same length (share_plan);
-  // n_splits workgroups per (request, KV head), one per share.  A context that fits one share is done by its first
-  // workgroup, which writes `out` itself (the others leave at once); of a longer one every share leaves a partial
-  // result in `partials`, and the combine kernel merges them.  n_splits == 1: never split.
+  // Packed-rows form, long contexts split over workgroups: a context is cut into up to n_splits shares, all of
+  // (nearly) the same length, and no more than 1 << least_log2 half tiles (32 keys each) ask for (share_plan); n_splits
+  // workgroups per (request, KV head), one per share.  A context of one share is done by its first workgroup, which
+  // writes `out` itself (the others leave at once); of a longer one every share leaves a partial result in `partials`, and the combine kernel merges them.  n_splits == 1: never split.
   int32_t n_splits;
-  int32_t halves_per_split;
+  int32_t least_log2;
   float* partials;  // [batch, n_kv_heads, n_splits] records of kPartialFloats<D> floats
   int32_t batch;
   int32_t n_tile_wgs;  // workgroups of the wave-tile form at the end of the grid (an upper bound from the host)
@@ -42,12 +41,20 @@ struct PagedArgs {
 template <int D>
 constexpr int kPartialFloats = 2 * kRows + kRows * D;
 
-// How a context of n_halves half tiles is cut: `shares` shares of `per` half tiles (the last one may be shorter);
-// one share when it fits halves_per_split.
-__device__ __forceinline__ void share_plan(int n_halves, int halves_per_split, int& per, int& shares) {
-  const int k = (n_halves + halves_per_split - 1) / halves_per_split;
-  per = k > 1 ? (n_halves + k - 1) / k : n_halves;
-  shares = per > 0 ? (n_halves + per - 1) / per : 0;
+// How a context of n_halves half tiles is cut: `shares` shares of `per` half tiles (the last one may be shorter); as few as
+// keep a share to 1 << least_log2 half tiles, at most n_splits.
+// The context decides, not the width of the block table, which is all that the host knows and may be far wider: with the
+// share's size taken from a table of 32 768 keys 8 requests of 16 384 keys took 60.1 us instead of 45.0, 4 of 300 .. 1500 13.2
+// instead of 7.9, 12 of 1000 .. 3731 36.7 instead of 15.2.  (A size for the whole batch, from the longest of kv_lens read by
+// every workgroup, cost each of the two kernels another 0.3 us of latency.)
+__device__ __forceinline__ void share_plan(int n_halves, int n_splits, int least_log2, int& per, int& shares) {
+  per = n_halves;
+  shares = 1;
+  const int most = (n_halves + (1 << least_log2) - 1) >> least_log2;
+  const int k = n_splits < most ? n_splits : most;
+  if (k < 2) return;
+  per = (n_halves + k - 1) / k;
+  shares = (n_halves + per - 1) / per;
 }
 // half tiles [begin, end) of share s (empty past the last share)
 __device__ __forceinline__ void split_range(int n_halves, int per, int s, int& begin, int& end) {

@@ -391,3 +391,30 @@ def test_shares_beside_chunks(kv_lens, chunk, split):
     out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
     _check(_run_gpu(h, q, kc, vc, tables, out=out, workspace=ws), _want(h, q, kc, vc, tables))
     assert bool(torch.isfinite(ws).any()) == split
+
+
+@pytest.mark.parametrize("q_lens,kv_lens,hq,hkv,d,bs", [
+    ([1, 1, 1, 1], [1200, 300, 655, 1480], 28, 4, 128, 16),        # the decode kernel
+    ([1] * 8, [4096, 200, 3000, 17, 1, 33, 2222, 640], 8, 2, 64, 32),
+    ([4, 2, 1], [2500, 900, 1400], 8, 1, 80, 16),                  # up to 32 rows, blocks and head_dim of the other form
+    ([1] * 70, [2000 - 20 * i for i in range(70)], 4, 1, 128, 16), # more lengths than lanes
+    ([1, 1, 40], [3000, 2100, 200], 14, 2, 128, 16),               # beside a chunk
+])
+def test_shares_follow_the_contexts_not_the_table(q_lens, kv_lens, hq, hkv, d, bs):
+    """A block table 32 768 keys wide over contexts far shorter: split as under a table cut to the longest context; the same
+    bits without a chunk in the batch (beside one the number of shares follows the table, their least length does not)."""
+    import paper_2505_12658_amd as hydra
+
+    h = si.HybridBatch("wide", q_lens, kv_lens, hq, hkv, d, block_size=bs, seed=max(kv_lens))
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    wide = np.full((h.batch, 32768 // bs), -1, dtype=np.int32)
+    wide[:, : tables.shape[1]] = tables
+    outs = []
+    for t in (tables, wide):
+        need = hydra.hydra_attn_paged_workspace_bytes(h.batch, hkv, d, t.shape[1], bs)
+        ws = torch.full((max(need, 16) // 4,), float("nan"), device="cuda:0")
+        outs.append(_run_gpu(h, q, kc, vc, t, workspace=ws))
+        assert bool(torch.isfinite(ws).any())
+        _check(outs[-1], _want(h, q, kc, vc, tables))
+    if max(q_lens) < 32:
+        assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
