@@ -350,6 +350,9 @@ constexpr int kDecodeMinBlock = 16;
 // Waves per SIMD the kernel is built for (168 registers each).
 constexpr int kDecodeWavesPerSimd = 3;
 constexpr int kDecodeMaxWaves = 8;
+constexpr int kDecodeLongKeys = 768;   // a block table from which on asks for them
+constexpr int kDecodeShortKeys = 512;  // below which the longest context does without
+constexpr int kDecodeWideTable = 4096; // keys in a row of the block table from which on the kernel looks for that
 
 // grid = batch * n_kv_heads * n_splits workgroups, share-major (the first shares of all pairs, which every request
 // has, then the second shares, ...); dynamic LDS: waves * kDecodeLdsPerWave<D> bytes.
@@ -361,7 +364,20 @@ __global__ __launch_bounds__(64 * kDecodeMaxWaves) __attribute__((amdgpu_waves_p
   const int pairs = a.batch * a.n_kv_heads;
   const int split = (int)blockIdx.x / pairs, pair = (int)blockIdx.x - split * pairs;
   const int b = pair / a.n_kv_heads;
-  run_decode<D>(a, s_decode, (int)blockDim.x >> 6, b, pair - b * a.n_kv_heads, split);
+  int waves = (int)blockDim.x >> 6;
+  // Eight waves are for long contexts, and the host knows only that the table allows them: in a batch without one, half of
+  // the waves leave, and the unit has room for a second workgroup (195 requests of at most 407 tokens under a table of
+  // 32 768 keys 13.1 -> 11.9 us, 100 of them 13.5 -> 11.9).  Only workgroups of short contexts look for a long one, and only
+  // where the table could be wider than the contexts (125 of 128 .. 1800 tokens under a tight one 42.4 us, looking 43.2).
+  if (waves == kDecodeMaxWaves && a.kv_lens[b] < kDecodeShortKeys && ((int64_t)a.max_blocks_per_seq << a.block_shift) >= kDecodeWideTable) {
+    bool far = false;
+    for (int r = (int)threadIdx.x & 63; r < a.batch; r += 64) far = far || a.kv_lens[r] >= kDecodeShortKeys;
+    if (__builtin_amdgcn_ballot_w64(far) == 0) {
+      waves = kDecodeMaxWaves / 2;
+      if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= waves) return;
+    }
+  }
+  run_decode<D>(a, s_decode, waves, b, pair - b * a.n_kv_heads, split);
 #else
   (void)a;
 #endif

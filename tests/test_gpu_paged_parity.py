@@ -418,3 +418,19 @@ def test_shares_follow_the_contexts_not_the_table(q_lens, kv_lens, hq, hkv, d, b
         _check(outs[-1], _want(h, q, kc, vc, tables))
     if max(q_lens) < 32:
         assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("longest", [407, 511, 512])
+def test_short_contexts_under_a_wide_table(longest):
+    """Between 257 and 512 (request, KV head) pairs under a table of 8192 keys: launched with eight waves per workgroup, of which
+    four leave when no context of the batch has 512 keys."""
+    kv_lens = [1 + (37 * i) % longest for i in range(299)] + [longest]
+    h = si.HybridBatch("short", [1] * 300, kv_lens, 7, 1, 128, block_size=16, seed=longest)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    wide = np.full((h.batch, 8192 // 16), -1, dtype=np.int32)
+    wide[:, : tables.shape[1]] = tables
+    want = _want(h, q, kc, vc, tables)
+    tight, out = _run_gpu(h, q, kc, vc, tables), _run_gpu(h, q, kc, vc, wide)
+    _check(out, want)
+    # (the tight table is launched with four waves from the start: the same keys per wave, the same bits)
+    assert torch.equal(tight.view(torch.int16), out.view(torch.int16)) == (longest < 512)
