@@ -71,10 +71,12 @@ typedef enum {
  *        bound costs nothing.
  *   head_dim    64, 80 or 128.   n_q_heads % n_kv_heads == 0.
  *   softmax_scale  finite and >= 0 (normally 1/sqrt(head_dim)).
- *   workspace   device memory, 16-byte aligned, at least hydra_attn_workspace_bytes(...) bytes.  It
- *        receives the tile work list built on the device from cu_seqlens (entries of
- *        (sequence, KV head, first query tile), grouped into one queue per accelerator die) and
- *        a few counters.  It need not be initialised and may be reused by the next
+ *   workspace   device memory, 16-byte aligned, at least hydra_attn_workspace_bytes(...) bytes.  Larger
+ *        batches put the tile work list there, built on the device from cu_seqlens (entries of
+ *        (sequence, KV head, first query tile), grouped into one queue per accelerator die), and
+ *        a few counters; smaller ones run without a list and neither read nor write it.  So what the
+ *        call leaves there is not for hydra_attn_varlen_fwd_prebuilt or _shared: those take a workspace
+ *        filled by hydra_attn_build_worklist.  It need not be initialised and may be reused by the next
  *        call on the same stream.
  *
  * batch == 0 or total_tokens == 0 returns HYDRA_OK without launching.
@@ -95,8 +97,9 @@ int hydra_attn_varlen_fwd(const void* q, const void* k, const void* v, void* out
  * hydra_attn_build_worklist writes the work list for (cu_seqlens, n_q_heads, n_kv_heads, causal)
  * into `workspace` (same size rule as above).  hydra_attn_varlen_fwd_prebuilt runs the attention
  * kernel against a workspace filled by an earlier hydra_attn_build_worklist call on the same stream
- * (or one that has completed) with the SAME batch, total_tokens, head counts and causal flag.  It
- * reads the work list and uses queue counters inside the workspace (all
+ * (or one that has completed) with the SAME batch, total_tokens, head counts and causal flag (a workspace
+ * that only hydra_attn_varlen_fwd has used may hold no list).  It
+ * reads the work list and may use queue counters inside the workspace (all
  * left zero again when the call's work completes), so two attention calls that share one workspace
  * must not overlap in time.  Arguments, layouts and errors are those of hydra_attn_varlen_fwd.
  */
@@ -135,7 +138,7 @@ int hydra_attn_varlen_fwd_shared(const void* q, const void* k, const void* v, vo
 
 /*
  * hydra_attn_varlen_fwd for callers that cannot allocate device memory or have none to pass: code
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The work list,
+ * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The work list and its
  * counters live in an array of HYDRA_ATTN_STATIC_SCRATCH_BYTES that is part of the
  * library's device image (every GPU the library runs on holds its own copy until the process ends);
  * the call allocates and frees nothing, and neither does anything it calls.
@@ -147,7 +150,7 @@ int hydra_attn_varlen_fwd_shared(const void* q, const void* k, const void* v, vo
  *     4096 sequences with 262 144 tokens at 32 query heads).
  *   - All calls on one GPU share that GPU's array: two calls that overlap in time on one GPU (two
  *     streams, two threads) race on it.  Calls on one stream are ordered and safe; the array keeps
- *     the previous call's contents and every call rewrites all of what it reads.
+ *     the previous call's contents, and a call reads nothing of it that it has not written itself.
  *   - The first call on a device looks the array's address up (a runtime query, not an allocation);
  *     make that first call outside a graph capture.
  */

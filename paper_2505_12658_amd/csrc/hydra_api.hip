@@ -419,8 +419,8 @@ int hydra_attn_varlen_fwd_static(const void* q, const void* k, const void* v, vo
   if (hydra::workspace_layout(batch, total_tokens, n_q_heads, n_kv_heads).total > kStaticScratchBytes) return HYDRA_ERR_WORKSPACE;
   void* ws = nullptr;
   if (int rc = static_scratch(&ws)) return rc;
-  // The prepass rewrites every word of the work list, the counters and the flags that the attention
-  // kernels read, so whatever the previous call left in the array does not matter.
+  // Where a work list is used, the prepass rewrites every word of it, of the counters and of the flags that the attention
+  // kernels read, and otherwise nothing is read, so whatever the previous call left in the array does not matter.
   return hydra_attn_varlen_fwd(q, k, v, out, q_token_stride, k_token_stride, v_token_stride, cu_seqlens, batch, total_tokens, max_seqlen,
                                n_q_heads, n_kv_heads, head_dim, causal, softmax_scale, ws, kStaticScratchBytes, stream);
 }
