@@ -106,7 +106,7 @@ struct DecodeWave {
     kv_len = kv_len_;
     block_shift = block_shift_;
     last_block = num_blocks - 1;
-    row_max = lowest_reference(scale_log2);
+    row_max = kLowest;
     row_sum = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) q[s] = *reinterpret_cast<const bf16x8_t*>(q_row + (4 * s + h) * 8);
@@ -173,7 +173,7 @@ struct DecodeWave {
     const float m_new = fmaxf(row_max, top);
     const float alpha = fast_exp2((row_max - m_new) * c);
     row_max = m_new;
-    const float mc = m_new * c;
+    const float mc = reference_exponent(m_new, c);
     bf16x8_t p;
     float sum = 0.f;
 #pragma unroll

@@ -315,7 +315,7 @@ struct WaveTile {
     }
 #pragma unroll
     for (int qs = 0; qs < QS; ++qs) {
-      row_max[qs] = lowest_reference(c);
+      row_max[qs] = kLowest;
       row_sum[qs] = 0.f;
 #pragma unroll
       for (int cc = 0; cc < CC; ++cc)
@@ -378,7 +378,7 @@ struct WaveTile {
       const float m_new = fmaxf(row_max[qs], tmax);
       const float alpha = fast_exp2((row_max[qs] - m_new) * c);
       row_max[qs] = m_new;
-      const float mc = m_new * c;
+      const float mc = reference_exponent(m_new, c);
       float psum = 0.f;
 #pragma unroll
       for (int rb = 0; rb < RBN; ++rb) {

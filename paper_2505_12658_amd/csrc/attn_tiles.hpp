@@ -108,9 +108,11 @@ __device__ __forceinline__ int items_of_sequence(int len, int group) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// The running maximum before the first visible key: as low as its product with the scale stays finite (a row whose keys
-// are all masked so far subtracts that product from -inf, and the difference has to stay -inf).
-__device__ __forceinline__ float lowest_reference(float scale_log2) { return -3.0e38f / fmaxf(scale_log2, 1.0f); }
+// Online softmax before the first visible key: the running maximum is the lowest float, and its product with the scale, which
+// the exponents subtract, stays finite (a row whose keys are all masked so far subtracts it from -inf, and the difference
+// has to stay -inf).  At every other maximum the product is what it is.
+constexpr float kLowest = -__FLT_MAX__;
+__device__ __forceinline__ float reference_exponent(float row_max, float scale_log2) { return fmaxf(row_max * scale_log2, kLowest); }
 
 // Exchange between the two 32-lane halves with v_permlane32_swap, which swaps the upper half
 // of its first register with the lower half of its second.  Starting from two copies of x:

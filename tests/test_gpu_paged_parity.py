@@ -434,3 +434,16 @@ def test_short_contexts_under_a_wide_table(longest):
     _check(out, want)
     # (the tight table is launched with four waves from the start: the same keys per wave, the same bits)
     assert torch.equal(tight.view(torch.int16), out.view(torch.int16)) == (longest < 512)
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_scale_near_the_end_of_the_range(d):
+    """Scores of -8 under a scale whose products, 3.2e38 in units of log 2, the largest float just holds: equal weights for all
+    visible keys (nothing that stands for 'no key yet' may lie above a score).  The products are exact, so the tolerance is the usual one."""
+    h = si.HybridBatch("far", [1, 2], [100, 33], 2, 1, d, block_size=16, seed=d)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    q, kc = torch.zeros_like(q), kc.clone()
+    q[..., 0] = 1.0
+    kc[..., 0] = -8.0
+    scale = 4.0e37 / 1.44269504088896340736
+    _check(_run_gpu(h, q, kc, vc, tables, scale=scale), _want(h, q, kc, vc, tables, scale=scale))
