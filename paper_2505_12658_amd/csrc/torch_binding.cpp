@@ -52,29 +52,29 @@ const at::Tensor& tensor(PyObject* o, const char* name) {
   if (!THPVariable_Check(o)) raise(PyExc_TypeError, name, " must be a torch tensor");
   return THPVariable_Unpack(o);
 }
-int64_t integer(PyObject* o) {
-  const long long v = PyLong_Check(o) ? PyLong_AsLongLong(o) : [o] {
-    PyObject* n = PyNumber_Long(o);
-    if (!n) throw Raised{};
-    const long long x = PyLong_AsLongLong(n);
-    Py_DECREF(n);
-    return x;
-  }();
-  if (v == -1 && PyErr_Occurred()) throw Raised{};
+// The C ABI's int32 of a Python number: modulo 2^32, so that an absurd bound is what the library refuses (or not).
+// `convert`: how anything but an int becomes one.
+template <PyObject* (*convert)(PyObject*)>
+int32_t to_int32(PyObject* o) {
+  if (PyLong_Check(o)) return (int32_t)PyLong_AsUnsignedLongMask(o);
+  PyObject* n = convert(o);
+  if (!n) throw Raised{};
+  const int32_t v = (int32_t)PyLong_AsUnsignedLongMask(n);
+  Py_DECREF(n);
   return v;
 }
-int32_t integer32(PyObject* o) {
-  const int64_t v = integer(o);
-  if (v != (int32_t)v) raise(PyExc_OverflowError, "size does not fit 32 bits");
-  return (int32_t)v;
-}
+int32_t whole(PyObject* o) { return to_int32<PyNumber_Index>(o); }  // a whole number; no float, no text
+int32_t as_int(PyObject* o) { return to_int32<PyNumber_Long>(o); }  // whatever int() takes
 int32_t size32(int64_t v) {
   if (v != (int32_t)v) raise(PyExc_OverflowError, "size does not fit 32 bits");
   return (int32_t)v;
 }
-double real(PyObject* o) {
-  const double v = PyFloat_AsDouble(o);
-  if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+double real(PyObject* o) {  // whatever float() takes
+  if (PyFloat_Check(o)) return PyFloat_AS_DOUBLE(o);
+  PyObject* f = PyNumber_Float(o);
+  if (!f) throw Raised{};
+  const double v = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
   return v;
 }
 int truth(PyObject* o) {
@@ -161,16 +161,17 @@ struct Packed {
   int32_t batch, tokens, longest, n_q, n_kv, d;
   int causal;
   float scale;
-  Packed(PyObject* const* a, bool check_cu)
+  // to_int: the conversion of max_seqlen
+  Packed(PyObject* const* a, bool check_cu, int32_t (*to_int)(PyObject*) = as_int)
       : q(token_major(a[0], "q")), k(token_major(a[1], "k")), v(token_major(a[2], "v")),
         cu(check_cu ? index_array(a[3], at::kInt, "cu_seqlens") : tensor(a[3], "cu_seqlens")),
-        batch(size32(cu.numel() - 1)), tokens(size32(q.size(0))), longest(integer32(a[4])), n_q(size32(q.size(1))),
+        batch(size32(cu.numel() - 1)), tokens(size32(q.size(0))), longest(to_int(a[4])), n_q(size32(q.size(1))),
         n_kv(size32(k.size(1))), d(size32(q.size(2))), causal(truth(a[5])), scale((float)real(a[6])) {}
 };
 
 PyObject* py_attn_varlen_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded("attn_varlen_fwd", n, 10, [&] {
-    const Packed p(a, true);
+    const Packed p(a, true, whole);
     const at::Tensor out = out_like(a[7], p.q);
     const at::Tensor ws = a[8] == Py_None
                               ? bytes_on(p.q, std::max<size_t>(lib.attn_workspace_bytes(p.batch, p.tokens, p.longest, p.n_q, p.n_kv, p.d), 16))
@@ -203,8 +204,8 @@ PyObject* py_attn_varlen_fwd_static(PyObject*, PyObject* const* a, Py_ssize_t n)
 PyObject* py_attn_build_worklist(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded("attn_build_worklist", n, 9, [&] {
     const at::Tensor& cu = index_array(a[0], at::kInt, "cu_seqlens");
-    const int32_t batch = size32(cu.numel() - 1), tokens = integer32(a[1]), longest = integer32(a[2]), n_q = integer32(a[3]),
-                  n_kv = integer32(a[4]), d = integer32(a[5]);
+    const auto size = a[7] == Py_None ? whole : as_int;
+    const int32_t batch = size32(cu.numel() - 1), tokens = size(a[1]), longest = size(a[2]), n_q = whole(a[3]), n_kv = whole(a[4]), d = whole(a[5]);
     const int causal = truth(a[6]);
     const at::Tensor ws = a[7] == Py_None ? bytes_on(cu, std::max<size_t>(lib.attn_workspace_bytes(batch, tokens, longest, n_q, n_kv, d), 16))
                                           : tensor(a[7], "workspace");
@@ -231,7 +232,7 @@ PyObject* py_attn_varlen_fwd_prebuilt(PyObject*, PyObject* const* a, Py_ssize_t 
                                             ws.nbytes(), s);
       });
     } else {
-      const int32_t per_cu = integer32(a[9]);
+      const int32_t per_cu = as_int(a[9]);
       call("hydra_attn_varlen_fwd_shared", [&] {
         return lib.attn_varlen_fwd_shared(p.q.data_ptr(), p.k.data_ptr(), p.v.data_ptr(), out.data_ptr(), p.q.stride(0), p.k.stride(0),
                                           p.v.stride(0), cu, p.batch, p.tokens, p.longest, p.n_q, p.n_kv, p.d, p.causal, p.scale, ws.data_ptr(),
@@ -276,7 +277,7 @@ PyObject* py_attn_paged_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t batch64 = cu.numel() - 1;
     if (table.dim() != 2 || table.size(0) != batch64 || kv_lens.numel() != batch64 || kc.size(3) != q.size(2))
       raise(PyExc_ValueError, "shape mismatch between q, caches, block_tables, cu_seqlens_q and kv_lens");
-    const int32_t batch = size32(batch64), tokens = size32(q.size(0)), longest = integer32(a[6]), n_q = size32(q.size(1)), n_kv = size32(kc.size(2)),
+    const int32_t batch = size32(batch64), tokens = size32(q.size(0)), longest = as_int(a[6]), n_q = size32(q.size(1)), n_kv = size32(kc.size(2)),
                   d = size32(q.size(2)), block = size32(kc.size(1)), width = size32(table.size(1));
     const float scale = (float)real(a[7]);
     const at::Tensor out = out_like(a[8], q);

@@ -556,3 +556,30 @@ def test_rows_of_any_width(row):
     want_back = out0.clone()
     want_back[kept, 8:] = k[kept]
     assert torch.equal(back.cpu().view(torch.int16), want_back)
+
+
+def test_numbers_of_the_wrong_kind():
+    """Sizes that are not whole numbers are refused where they were never converted, and bounds are the C ABI's 32 bits of them."""
+    hydra = _hydra()
+    w = si.custom([40, 7], 4, 2, 64, True, seed=2)
+    q, k, v = si.make_qkv(w)
+    dev = torch.device("cuda:0")
+    cu = torch.from_numpy(w.cu_seqlens).to(dev)
+    qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+    for sizes in ((4.0, 2, 64), (4, 2.9, 64), (4, 2, "64"), (4, 2, None)):
+        with pytest.raises(TypeError):
+            hydra.hydra_attn_build_worklist(cu, 47, 40, *sizes, True)
+    for bound in (40.5, "40", None):
+        with pytest.raises(TypeError):
+            hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, bound, True, w.softmax_scale)
+        with pytest.raises(TypeError):
+            hydra.hydra_attn_build_worklist(cu, 47, bound, 4, 2, 64, True)
+    with pytest.raises(hydra.HydraError) as e:
+        hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, 2**31, True, w.softmax_scale)
+    assert e.value.status == 1
+    ws = hydra.hydra_attn_build_worklist(cu, np.int64(47), 2**32 + 40, 4, np.int32(2), 64, True)
+    want = hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, np.int64(40), True, w.softmax_scale)
+    out = torch.empty_like(qd)
+    hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, 40.0, 1, str(w.softmax_scale), out, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
