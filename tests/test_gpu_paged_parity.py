@@ -447,3 +447,27 @@ def test_scale_near_the_end_of_the_range(d):
     kc[..., 0] = -8.0
     scale = 4.0e37 / 1.44269504088896340736
     _check(_run_gpu(h, q, kc, vc, tables, scale=scale), _want(h, q, kc, vc, tables, scale=scale))
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("bs", [16, 64])
+def test_stale_rows_behind_a_context_do_not_count(d, bs):
+    """NaN in every cache row that belongs to no context (the tails of pages, pages nobody has): contexts that end at every place
+    of a block of keys, in the decode form and in the form for up to 32 rows, unsplit and split, beside a chunk."""
+    ends = [1, 2, 3, 15, 16, 17, 30, 31]
+    for kv_lens, q_lens in (([e for e in ends] + [32 + e for e in ends] + [700 + e for e in ends], None),
+                            ([1600 + e for e in (1, 3, 15, 16, 17, 31)], None),
+                            ([1600 + e for e in (3, 16, 31)], [8, 5, 1]),
+                            ([500 + e for e in (1, 15, 16, 17, 31)] + [100], [1] * 5 + [70])):
+        h = si.HybridBatch("stale", q_lens or [1] * len(kv_lens), kv_lens, 8, 2, d, block_size=bs, seed=len(kv_lens) + bs)
+        q, kc, vc, tables = si.make_paged_inputs(h)
+        owned = torch.zeros(kc.shape[:2], dtype=torch.bool)
+        for b, n in enumerate(kv_lens):
+            for at in range(0, n, bs):
+                owned[int(tables[b, at // bs]), : min(bs, n - at)] = True
+        assert not bool(owned.all())
+        want = _want(h, q, kc, vc, tables)
+        kc, vc = kc.clone(), vc.clone()
+        kc[~owned], vc[~owned] = float("nan"), float("nan")
+        _check(_run_gpu(h, q, kc, vc, tables), want)
+        _check(_run_gpu(h, q, kc, vc, tables, use_workspace=False), want)

@@ -574,9 +574,8 @@ def test_numbers_of_the_wrong_kind():
             hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, bound, True, w.softmax_scale)
         with pytest.raises(TypeError):
             hydra.hydra_attn_build_worklist(cu, 47, bound, 4, 2, 64, True)
-    with pytest.raises(hydra.HydraError) as e:
+    with pytest.raises(hydra.HydraError, match="invalid argument"):  # (nothing keeps the exception, whose frames hold device tensors)
         hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, 2**31, True, w.softmax_scale)
-    assert e.value.status == 1
     ws = hydra.hydra_attn_build_worklist(cu, np.int64(47), 2**32 + 40, 4, np.int32(2), 64, True)
     want = hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, np.int64(40), True, w.softmax_scale)
     out = torch.empty_like(qd)
