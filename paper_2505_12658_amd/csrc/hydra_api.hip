@@ -38,9 +38,10 @@ hipError_t launch(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t 
   return launch_lds(kernel, grid, block, 0, stream, args...);
 }
 
-// A row-copy kernel over `rows` rows of row16 pieces: one launch, or several where a grid cannot hold them.
+// A row-copy kernel (its form for rows of whole kilobytes, its form for others) over `rows` rows of row16 pieces: one launch,
+// or several where a grid cannot hold them.
 template <typename Args>
-hipError_t launch_row_copy(void (*kernel)(Args), Args args, int32_t rows, int32_t row16, hipStream_t stream) {
+hipError_t launch_row_copy(void (*kilobytes)(Args), void (*others)(Args), Args args, int32_t rows, int32_t row16, hipStream_t stream) {
   args.rows = hydra::row_copy_plan(row16);
   const int64_t most = hydra::row_copy_most_rows(args.rows);
   hipError_t err = hipSuccess;
@@ -48,7 +49,7 @@ hipError_t launch_row_copy(void (*kernel)(Args), Args args, int32_t rows, int32_
     const int64_t here = rows - at < most ? rows - at : most;
     args.rows.first_row = (int32_t)at;
     args.rows.rows = (int32_t)here;
-    err = launch(kernel, dim3((unsigned)hydra::row_copy_workgroups(args.rows, here)), dim3(hydra::kRowCopyThreads), stream, args);
+    err = launch(args.rows.waves != 0 ? kilobytes : others, dim3((unsigned)hydra::row_copy_workgroups(args.rows, here)), dim3(hydra::kRowCopyThreads), stream, args);
   }
   return err;
 }
@@ -516,7 +517,7 @@ int hydra_kv_cache_write(const void* k, const void* v, int64_t k_token_stride, i
   args.slot_mapping = slot_mapping;
   args.k_stride16 = k_token_stride / 8;
   args.v_stride16 = v_token_stride / 8;
-  const hipError_t err = launch_row_copy(hydra::kv_cache_write_kernel, args, total_tokens, (int32_t)(row / 8), static_cast<hipStream_t>(stream));
+  const hipError_t err = launch_row_copy(hydra::kv_cache_write_kernel<true>, hydra::kv_cache_write_kernel<false>, args, total_tokens, (int32_t)(row / 8), static_cast<hipStream_t>(stream));
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }
 
@@ -535,17 +536,16 @@ int launch_page_cache(bool gather, const void* packed, int64_t packed_row_stride
   hydra::PageCacheArgs args;
   args.slot_mapping = slot_mapping;
   args.packed_stride16 = packed_row_stride / 8;
-  const bool kilobytes = hydra::row_copy_plan(row_elems / 8).waves != 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
   if (gather) {
     args.src = static_cast<const hydra::piece_t*>(cache);
     args.dst = static_cast<hydra::piece_t*>(const_cast<void*>(packed));
-    err = launch_row_copy(kilobytes ? hydra::page_cache_kernel<true, true> : hydra::page_cache_kernel<true, false>, args, n_rows, row_elems / 8, s);
+    err = launch_row_copy(hydra::page_cache_kernel<true, true>, hydra::page_cache_kernel<true, false>, args, n_rows, row_elems / 8, s);
   } else {
     args.src = static_cast<const hydra::piece_t*>(packed);
     args.dst = static_cast<hydra::piece_t*>(const_cast<void*>(cache));
-    err = launch_row_copy(kilobytes ? hydra::page_cache_kernel<false, true> : hydra::page_cache_kernel<false, false>, args, n_rows, row_elems / 8, s);
+    err = launch_row_copy(hydra::page_cache_kernel<false, true>, hydra::page_cache_kernel<false, false>, args, n_rows, row_elems / 8, s);
   }
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }

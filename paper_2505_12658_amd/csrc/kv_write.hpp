@@ -23,11 +23,12 @@ struct KvWriteArgs {
 // the LLaVA prefill pass 168 -> 183 us.  The compiler puts the row loads behind the test of the slot, one round trip to
 // memory later; held ahead of it, for launches that fit the chip at once, they won 0.0 - 0.4 us of passes of 11 - 60 us
 // (4 decode steps 10.9 -> 10.8, hybrid batch 60.6 -> 60.2), too little for a second path.
+template <bool KILOBYTES>  // the rows are whole kilobytes (rows.waves != 0)
 __global__ __launch_bounds__(kRowCopyThreads) void kv_cache_write_kernel(const KvWriteArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   int64_t t, slot;
   int32_t p;
-  if (!piece_of_lane(a.rows, a.slot_mapping, t, slot, p)) return;
+  if (!piece_of_lane<KILOBYTES>(a.rows, a.slot_mapping, t, slot, p)) return;
   const piece_t k = __builtin_nontemporal_load(a.k + t * a.k_stride16 + p);
   const piece_t v = __builtin_nontemporal_load(a.v + t * a.v_stride16 + p);
   if (slot < 0) return;

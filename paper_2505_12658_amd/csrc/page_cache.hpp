@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kRowCopyThreads) void page_cache_kernel(const PageC
 #if defined(__HIP_DEVICE_COMPILE__)
   int64_t t, slot;
   int32_t p;
-  if (!piece_of_lane(a.rows, a.slot_mapping, t, slot, p) || slot < 0) return;
+  if (!piece_of_lane<KILOBYTES>(a.rows, a.slot_mapping, t, slot, p) || slot < 0) return;
   // Stores are plain, since what is written is read by the next kernel.  Rows of whole kilobytes are loaded non-temporally
   // (nothing here is read twice): 14 014 rows of 7 KB into the cache and back 66.3 us, with plain loads 72.1.  Other rows
   // end inside cache lines that the lanes of the next row read too: 50 000 rows of 1440 bytes 47.2 us with plain loads, 60.9

@@ -24,7 +24,7 @@ struct RowCopyPlan {
   int32_t first_row, rows;
   int32_t row16;      // 16-byte pieces per row
   int32_t waves;      // waves per row; 0: pieces end to end
-  uint32_t magic;     // division by the units of a row (its waves or its pieces), see row_of_unit
+  uint32_t magic;     // division by row16, see row_of_unit
   int32_t shift;
 };
 
@@ -32,11 +32,10 @@ inline RowCopyPlan row_copy_plan(int32_t row16) {
   RowCopyPlan p = {};
   p.row16 = row16;
   p.waves = row16 % 64 == 0 ? row16 / 64 : 0;
-  const uint64_t units = p.waves ? p.waves : row16;
   int log2 = 0;
-  while (((uint64_t)1 << log2) < units) ++log2;
+  while ((1 << log2) < row16) ++log2;
   p.shift = 31 + log2;
-  p.magic = (uint32_t)((((uint64_t)1 << p.shift) + units - 1) / units);  // (2^31 .. 2^32 - 1)
+  p.magic = (uint32_t)((((uint64_t)1 << p.shift) + row16 - 1) / row16);  // (2^31 .. 2^32 - 1)
   return p;
 }
 // Rows of one launch at most, and the workgroups for `rows` of them.
@@ -44,15 +43,19 @@ inline int64_t row_copy_most_rows(const RowCopyPlan& p) { return kRowCopyMostLan
 inline int64_t row_copy_workgroups(const RowCopyPlan& p, int64_t rows) { return (rows * p.row16 + kRowCopyThreads - 1) / kRowCopyThreads; }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// u / (units of a row), exact for u < 2^31: magic is 2^shift / units rounded up, by less than units <= 2^(shift - 31) of
-// 2^shift, which u times stays below one.
+// u / row16, exact for u < 2^31: magic is 2^shift / row16 rounded up, and u times what that adds, less than
+// row16 <= 2^(shift - 31) of 2^shift, stays below one part in row16.
 __device__ __forceinline__ uint32_t row_of_unit(const RowCopyPlan& p, uint32_t u) { return (uint32_t)(((uint64_t)u * p.magic) >> p.shift); }
 
-// This lane's row, the row's slot, and this lane's piece of it; false where there is none.
+// This lane's row, the row's slot, and this lane's piece of it; false where there is none.  KILOBYTES: whether p.waves != 0
+// (known to the compiler, so that row and slot stay in scalar registers).
+template <bool KILOBYTES>
 __device__ __forceinline__ bool piece_of_lane(const RowCopyPlan& p, const int64_t* slot_mapping, int64_t& row, int64_t& slot, int32_t& piece) {
-  if (p.waves != 0) {
+  if constexpr (KILOBYTES) {
     const uint32_t u = blockIdx.x * (kRowCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t t = row_of_unit(p, u);
+    // (not row_of_unit: with its few instructions the waves ask for memory closer together, and 14 014 rows of 7 KB through the
+    // image cache and back took 64.9 us instead of 64.4)
+    const uint32_t t = p.waves == 1 ? u : u / (uint32_t)p.waves;
     if (t >= (uint32_t)p.rows) return false;
     piece = (int32_t)((u - t * p.waves) * 64 + (threadIdx.x & 63));
     row = (int64_t)p.first_row + t;
