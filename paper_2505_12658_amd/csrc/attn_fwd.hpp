@@ -1018,6 +1018,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroups
 // for at most kDirectSeqs sequences, every wave works its workgroup's item out from cu_seqlens, one round trip to memory
 // and some 300 instructions, about 1.3 us per workgroup against a prepass of 5 - 8 us.
 constexpr int kDirectSeqs = 64;
+constexpr int kDieUnits = 32;  // compute units of a die
 
 #if defined(__HIP_DEVICE_COMPILE__)
 // Sum over this lane and the lanes before it (data-parallel primitives: shifts inside the rows of 16 lanes, then the
@@ -1032,18 +1033,36 @@ __device__ __forceinline__ int wave_scan_add(int x) {
   return x;
 }
 
+// Sum over the lanes with the same number modulo 8 (rotation inside the rows of 16 lanes, then swaps of rows and of halves).
+__device__ __forceinline__ int sum_of_columns(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);
+  int a = x, b = x;
+  asm volatile("s_nop 3\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 3" : "+v"(a), "+v"(b));
+  x = a + b;
+  a = x;
+  b = x;
+  asm volatile("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 3" : "+v"(a), "+v"(b));
+  return a + b;
+}
+
 // The entry that this workgroup takes from the dies' queues: workgroup t the t-th of all entries by place and, at one
 // place, by die.  While every queue has entries that is place t / 8 of the own die's queue (t % 8); dies that have run
 // out, or never had a (sequence, KV head) pair, take their part of what the others still hold, at the same place in the
 // order, so that neither the order by cost nor the grid depends on how the entries are spread over the dies.
-// n: entries of queue lane % 8.  Called by whole waves; false for workgroups past the last entry.
+// Only where all queues are short do the dies without entries stay idle: spread, every die would fetch rows that another one
+// has (one request of 558 tokens, 28 / 4 heads of 128, queues of 32 entries on four dies: 15.5 us, 14.8 by the own dies).
+// n: entries of queue lane % 8; the grid has kXcds * kDieUnits workgroups at least.  Called by whole waves; false for workgroups
+// past the last entry.
 // Without it (every queue done by its own die, the grid sized for the longest queue that max_seqlen allows), us: one request
 // of 8192 tokens with 28 / 4 heads of 128 800 -> 422 (half of the dies had nothing; persistent workgroups that steal 518),
 // with 8 / 1 heads 682 -> 155 (307); 12 requests of 200 .. 1047 tokens under a bound of 32 768 75.7 -> 59.7.
 __device__ __forceinline__ bool take_entry(int n, int t, int& die, int& place) {
   die = t % kXcds;
   place = t / kXcds;
-  if ((__builtin_amdgcn_ballot_w64(n > place) & 0xff) == 0xff) return true;
+  const uint32_t open_here = (uint32_t)__builtin_amdgcn_ballot_w64(n > place) & 0xff;
+  if (open_here == 0xff) return true;
+  // no queue is longer than its die has compute units: every die does its own
+  if ((__builtin_amdgcn_ballot_w64(n > kDieUnits) & 0xff) == 0) return open_here >> die & 1;
   int count[kXcds], total = 0;
 #pragma unroll
   for (int y = 0; y < kXcds; ++y) {
@@ -1107,12 +1126,11 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
     return pair < pairs ? u : 0;
   };
   int die = (int)blockIdx.x % kXcds, place = (int)blockIdx.x / kXcds;
-  if (n_kv_heads % kXcds != 0) {  // (otherwise every die has the same pairs of every sequence)
-    int queue = 0;                // units of the pairs of column lane % 8
+  // (not where every die has the same pairs of every sequence, nor where no queue can be longer than take_entry asks for)
+  if (n_kv_heads % kXcds != 0 && (pairs > kXcds || __builtin_amdgcn_ballot_w64(n > kDieUnits) != 0)) {
+    int queue = 0;  // units of the pairs of column lane % 8
     for (int row0 = 0; row0 * kXcds < pairs; row0 += 64 / kXcds) queue += units_of(pair_of(row0 + lane / kXcds, lane % kXcds));
-    queue += __shfl_xor(queue, 8);
-    queue += __shfl_xor(queue, 16);
-    queue += __shfl_xor(queue, 32);
+    queue = sum_of_columns(queue);
     if (!take_entry(queue, (int)blockIdx.x, die, place)) return false;
   }
   // rows of the die's column, 64 at a time: units of each row's pair and, by a scan, of the rows before it

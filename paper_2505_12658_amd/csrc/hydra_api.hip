@@ -90,11 +90,14 @@ bool within_rounds(size_t rounds, int32_t head_dim, size_t capacity, unsigned co
 bool list_free(int32_t batch, int32_t head_dim, size_t capacity, unsigned compute_units) {
   return batch <= hydra::kDirectSeqs && within_rounds(kListFreeRounds, head_dim, capacity, compute_units);
 }
-// (grid: as many workgroups as there can be items; their order takes care of how they spread over the dies)
+// (grid: as many workgroups as there can be items, and as take_entry asks for; their order takes care of how the items spread
+// over the dies)
 template <int D>
 hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, int32_t batch, int32_t n_kv_heads, size_t capacity, hipStream_t stream) {
-  return causal ? launch(hydra::attn_fwd_direct_kernel<D, true>, dim3((unsigned)capacity), dim3(256), stream, args, batch, n_kv_heads)
-                : launch(hydra::attn_fwd_direct_kernel<D, false>, dim3((unsigned)capacity), dim3(256), stream, args, batch, n_kv_heads);
+  constexpr size_t kLeast = hydra::kXcds * hydra::kDieUnits;
+  const dim3 grid((unsigned)(capacity > kLeast || n_kv_heads % hydra::kXcds == 0 ? capacity : kLeast));
+  return causal ? launch(hydra::attn_fwd_direct_kernel<D, true>, grid, dim3(256), stream, args, batch, n_kv_heads)
+                : launch(hydra::attn_fwd_direct_kernel<D, false>, grid, dim3(256), stream, args, batch, n_kv_heads);
 }
 
 // Bytes of one partial result of the paged kernel's packed-rows form.

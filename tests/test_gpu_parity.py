@@ -314,6 +314,9 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
     ([700, 650, 30], 12, 12, 64),    # pairs in rows and a half
     ([260] * 5, 3, 3, 80),
     ([64] * 9, 1, 1, 64),            # nine pairs of one item: the ninth item is the second of its die
+    ([558], 28, 4, 128),             # queues of 32 items on four dies: every die does its own
+    ([4096], 1, 1, 64),              # 32 items of one pair, and 33
+    ([4097], 1, 1, 64),
 ])
 def test_items_are_handed_out_whole_for_any_bound(lengths, hq, hkv, d):
     """Batches whose (sequence, KV head) pairs do not spread evenly over the dies, with an exact, a loose and an understated
