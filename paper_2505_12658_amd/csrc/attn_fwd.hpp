@@ -1055,7 +1055,9 @@ __device__ __forceinline__ int sum_of_columns(int x) {
 // past the last entry.
 // Without it (every queue done by its own die, the grid sized for the longest queue that max_seqlen allows), us: one request
 // of 8192 tokens with 28 / 4 heads of 128 800 -> 422 (half of the dies had nothing; persistent workgroups that steal 518),
-// with 8 / 1 heads 682 -> 155 (307); 12 requests of 200 .. 1047 tokens under a bound of 32 768 75.7 -> 59.7.
+// with 8 / 1 heads 682 -> 155 (307); 12 requests of 200 .. 1047 tokens under a bound of 32 768 75.7 -> 59.7.  Counting the
+// queues costs a workgroup some 0.1 us, seen in batches that were level without it (300, 1200 and 700 tokens, 28 / 4 heads,
+// 26.3 -> 26.6).
 __device__ __forceinline__ bool take_entry(int n, int t, int& die, int& place) {
   die = t % kXcds;
   place = t / kXcds;
