@@ -40,6 +40,7 @@ namespace paged {
 
 constexpr int kDecodeRows = 16;  // rows (new tokens x grouped heads) of a decode tile
 constexpr int kDecodeKeys = 32;  // keys per step
+constexpr int kUnits = 256;      // compute units
 
 // Floats of LDS per wave and row of partial output (padded: the rows of a wave start in different banks).
 template <int D>
@@ -50,6 +51,10 @@ template <int D>
 constexpr int kDecodeSlotFloats = kDecodeRows * kDecodeRowFloats<D> > kDecodeKeys * D / 2 ? kDecodeRows * kDecodeRowFloats<D> : kDecodeKeys * D / 2;
 template <int D>
 constexpr size_t kDecodeLdsPerWave = (kDecodeSlotFloats<D> + 2 * kDecodeRows) * sizeof(float);
+
+// (see attn_decode_kernel)
+constexpr int kOrderedKeys = 256;      // a batch without a context of more keys is not ordered by them
+constexpr int kDecodeShortKeys = 512;  // a batch without a context of as many does with four waves per workgroup
 
 #if defined(__HIP_DEVICE_COMPILE__)
 
@@ -214,7 +219,7 @@ struct DecodeWave {
 // otherwise a partial result for the combine kernel.  Called by all n_waves waves; lds: n_waves * kDecodeLdsPerWave<D>
 // bytes, 16-byte aligned.  Does nothing for a request that has no new tokens or more than kDecodeRows rows.
 template <int D>
-__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int b, int kv_head, int split) {
+__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int b, int kv_head, int q_start, int q_len, int kv_len, int split) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, h = lane >> 4;
@@ -222,20 +227,27 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   float* s_sum = s_max + n_waves * kDecodeRows;
   float* s_slots = s_sum + n_waves * kDecodeRows;
 
-  const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
-  const int q_start = cu[b];
-  const int q_len = cu[b + 1] - q_start;
-  int kv_len = lens[b];
-  const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;
-  if (kv_len > table_keys) kv_len = (int)table_keys;
-  if (q_len <= 0 || kv_len < q_len || q_len * a.group > kDecodeRows) return;
-  const int n_rows = q_len * a.group;
-
+  if (kv_len <= 0) return;
   const int n_halves = (kv_len + kDecodeKeys - 1) / kDecodeKeys;
   int begin, end, per_share, n_shares;
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   split_range(n_halves, per_share, split, begin, end);
   if (begin >= end) return;  // past the context's last share: the combine kernel knows and skips it
+
+  // Block-table entries of the wave's next 32 steps: lane 2 i + half has the entry of that half of step i
+  // (one load; the loop takes them from there lane by lane).  Ids are clamped to the cache, so that a corrupt
+  // table cannot make the loads leave it; entries past the context are not read.
+  const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
+  const int last_entry = (kv_len - 1) >> a.block_shift;
+  auto entries = [&](int first_step) {
+    const int key = (begin + wave + n_waves * (first_step + (lane >> 1))) * kDecodeKeys + 16 * (lane & 1);
+    int e = key >> a.block_shift;
+    return table[e < last_entry ? e : last_entry];
+  };
+  // (the first ones are asked for together with the request's rows)
+  int ids = entries(0);
+  if (q_len <= 0 || kv_len < q_len || q_len * a.group > kDecodeRows) return;
+  const int n_rows = q_len * a.group;
 
   // this lane's row
   const int row = m < n_rows ? m : n_rows - 1;
@@ -249,21 +261,10 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   w.init(a.k_cache, a.v_cache, a.n_kv_heads, kv_head, kv_len, a.block_shift, a.num_blocks, a.q + (int64_t)(q_start + token) * a.q_stride + head * D, c,
          (uint32_t)(uintptr_t)HYDRA_LDS_PTR(s_slots + wave * kDecodeSlotFloats<D>), lane);
   if (steps > 0) {
-    // Block-table entries of the wave's next 32 steps: lane 2 i + half has the entry of that half of step i
-    // (one load; the loop takes them from there lane by lane).  Ids are clamped to the cache, so that a corrupt
-    // table cannot make the loads leave it; entries past the context are not read.
-    const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
-    const int last_entry = (kv_len - 1) >> a.block_shift;
-    auto entries = [&](int first_step) {
-      const int key = (begin + wave + n_waves * (first_step + (lane >> 1))) * kDecodeKeys + 16 * (lane & 1);
-      int e = key >> a.block_shift;
-      e = e < last_entry ? e : last_entry;
-      const int id = table[e];
-      return id < 0 ? 0 : (id > w.last_block ? w.last_block : id);
-    };
-    int ids = entries(0);
     auto key_of = [&](int i) { return (begin + wave + n_waves * i) * kDecodeKeys; };
+    auto in_cache = [&](int id) { return id < 0 ? 0 : (id > w.last_block ? w.last_block : id); };
     auto id_of = [&](int i, int half) { return __builtin_amdgcn_readlane(ids, 2 * (i & 31) + half); };
+    ids = in_cache(ids);
 #pragma unroll
     for (int half = 0; half < 2; ++half) w.load_k(half, id_of(0, half), key_of(0) + 16 * half);
 #pragma unroll
@@ -273,7 +274,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
       w.stage_k();
       // (the loads of a step that does not exist are issued all the same, with nothing in range: a branch around
       // them would make the compiler wait for everything in flight where the paths meet again)
-      if ((i & 31) == 31) ids = entries(i + 1);
+      if ((i & 31) == 31) ids = in_cache(entries(i + 1));
       const int b0 = id_of(i + 1, 0), b1 = id_of(i + 1, 1), next = i + 1 < steps ? key_of(i + 1) : kv_len;
       w.load_k(0, b0, next);
       w.load_k(1, b1, next + 16);
@@ -340,6 +341,57 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   }
 }
 
+// The request of rank `rank` when the batch is ordered by context, longest first (in steps of kDecodeKeys; equal ones by
+// number), and its context.  Called by whole waves; every wave finds it for itself, without LDS or a barrier: the lengths
+// lie in REGS registers of its lanes, and a search over the bits of a length, highest first, counts with ballots how many
+// requests reach it (0.3 us; a search over single keys, with branches around the registers that a batch does not fill, 0.9).
+// False where the order would not matter: contexts within a quarter of each other, or none of kOrderedKeys.
+// any_long: some context has kDecodeShortKeys.
+template <int REGS>
+__device__ __forceinline__ bool request_of_rank(const PagedArgs& a, int rank, int table_keys, int& b, int& kv_len, bool& any_long) {
+  const int lane = threadIdx.x & 63;
+  int len[REGS], steps[REGS];
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) len[r] = a.kv_lens[r * 64 + lane < a.batch ? r * 64 + lane : a.batch - 1];
+  bool ragged = false, far = false, longer = false;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    const bool real = r * 64 + lane < a.batch;
+    len[r] = len[r] < table_keys ? len[r] : table_keys;
+    steps[r] = real ? (len[r] > 0 ? (len[r] + kDecodeKeys - 1) / kDecodeKeys : 0) : -1;
+    const int64_t first = __builtin_amdgcn_readfirstlane(steps[0]);
+    far = far || steps[r] > kOrderedKeys / kDecodeKeys;
+    longer = longer || len[r] >= kDecodeShortKeys;
+    ragged = ragged || (real && (steps[r] * 5 < first * 4 || steps[r] * 4 > first * 5));
+  }
+  any_long = __builtin_amdgcn_ballot_w64(longer) != 0;
+  if (__builtin_amdgcn_ballot_w64(far) == 0 || __builtin_amdgcn_ballot_w64(ragged) == 0) return false;
+  // the largest number of steps that more than `rank` requests reach: that of the request asked for
+  int v = 0;
+  for (int bit = 1 << (31 - __builtin_clz((table_keys + kDecodeKeys - 1) / kDecodeKeys)); bit > 0; bit >>= 1) {
+    int reach = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) reach += __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] >= (v | bit)));
+    v = reach > rank ? v | bit : v;
+  }
+  int skip = rank;  // requests of as many steps that come before it
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) skip -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] > v));
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    uint64_t here = __builtin_amdgcn_ballot_w64(steps[r] == v);
+    const int n = __builtin_popcountll(here);
+    if (skip >= 0 && skip < n) {
+      for (int i = 0; i < skip; ++i) here &= here - 1;
+      const int at = __builtin_ctzll(here);
+      b = r * 64 + at;
+      kv_len = __builtin_amdgcn_readlane(len[r], at);
+    }
+    skip -= n;
+  }
+  return true;
+}
+
 #endif  // __HIP_DEVICE_COMPILE__
 
 // Whether requests of `rows` rows take this form (the 16 keys of half a step lie in one cache block).
@@ -349,35 +401,76 @@ constexpr int kDecodeMinBlock = 16;
 
 // Waves per SIMD the kernel is built for (168 registers each).
 constexpr int kDecodeWavesPerSimd = 3;
-constexpr int kDecodeMaxWaves = 8;
-constexpr int kDecodeLongKeys = 768;   // a block table from which on asks for them
-constexpr int kDecodeShortKeys = 512;  // below which the longest context does without
+constexpr int kDecodeWaves = 4;        // waves of a workgroup: enough to keep a compute unit's memory path full
+constexpr int kDecodeMaxWaves = 8;     // the most: a unit then holds one workgroup at a time
+constexpr int kDecodeLongKeys = 768;   // a block table from which on a launch may ask for them
 constexpr int kDecodeWideTable = 4096; // keys in a row of the block table from which on the kernel looks for that
 
+// Batches of more pairs than compute units are taken in the order of their contexts: units are then level, whatever the order
+// of the requests in the batch, and no long context starts behind another one.  The first 256 workgroups, which the hardware
+// deals out one to a unit, take the 256 longest pairs from the shortest of them up, the ones behind them the others from the
+// longest down: so the second pair of a unit is the longer the shorter its first one is, and the very longest have a unit
+// for themselves.  us, in the order of the batch (with eight waves, see below) and so, 28 / 4 heads of 128: 96 requests of
+// 128 .. 1782 tokens 37.2 -> 29.5 (longest first from both ends 32), 125 44.1 -> 32, 80 33.9 -> 27.4, 70 of 900 .. 1800
+// 43.2 -> 34.6, 200 of 128 .. 1800 65.8 -> 50, 100 of 40 .. 407 12.1 -> 10.1; 32 / 32 heads: 14 of 300 .. 2000 50.8 -> 41.9, 33 of
+// 600 .. 1100 77.7 -> 76.8, 9 of 300 .. 3000, which the longest context holds up either way, 45.9 -> 46.6.
+// Not where no context has more than kOrderedKeys (the search costs what the order gains: 300 of 30 .. 200 tokens 14.4 -> 15.5),
+// and the batch has to fit four registers of a wave's lanes (eight: 500 of 20 .. 100 under a wide table 15.7 -> 17.0, without a search).
+constexpr int kOrderedMost = 256;  // requests
+inline bool decode_ordered(int64_t pairs, int n_splits, int batch, int64_t table_keys) {
+  return pairs > kUnits && n_splits == 1 && batch <= kOrderedMost && table_keys > kOrderedKeys;
+}
+// Eight waves are for one to two long pairs per unit: a unit that is done early then takes one of the remaining pairs.
+//   - In the order of the batch they are worth it throughout (96 requests of 128 .. 1782 tokens 39.7 -> 35.7 us with four heads).
+//   - Ordered, only where the second pairs are nearly as many as the first ones: 128 requests of 128 .. 1800 tokens 33.9 -> 32.2
+//     us, 120 31.9 -> 31.7, 110 30.9 -> 31.1, 96 29.6 -> 29.9, 66 24.8 -> 25.6.
+constexpr int kDecodeManyPairs = 464;
+inline int decode_waves(int64_t pairs, int n_splits, int64_t table_keys, bool ordered) {
+  return pairs > (ordered ? kDecodeManyPairs - 1 : kUnits) && pairs <= 2 * kUnits && n_splits == 1 && table_keys >= kDecodeLongKeys ? kDecodeMaxWaves : kDecodeWaves;
+}
+
 // grid = batch * n_kv_heads * n_splits workgroups, share-major (the first shares of all pairs, which every request
-// has, then the second shares, ...); dynamic LDS: waves * kDecodeLdsPerWave<D> bytes.
-template <int D>
-__global__ __launch_bounds__(64 * kDecodeMaxWaves) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd, kDecodeWavesPerSimd))) void attn_decode_kernel(
+// has, then the second shares, ...); dynamic LDS: WAVES * kDecodeLdsPerWave<D> bytes.
+template <int D, bool ORDERED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd, kDecodeWavesPerSimd))) void attn_decode_kernel(
     const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float s_decode[];
+  const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;  // (at most 2^30)
+  const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
   const int pairs = a.batch * a.n_kv_heads;
-  const int split = (int)blockIdx.x / pairs, pair = (int)blockIdx.x - split * pairs;
-  const int b = pair / a.n_kv_heads;
-  int waves = (int)blockDim.x >> 6;
-  // Eight waves are for long contexts, and the host knows only that the table allows them: in a batch without one, half of
-  // the waves leave, and the unit has room for a second workgroup (195 requests of at most 407 tokens under a table of
-  // 32 768 keys 13.1 -> 11.9 us, 100 of them 13.5 -> 11.9).  Only workgroups of short contexts look for a long one, and only
-  // where the table could be wider than the contexts (125 of 128 .. 1800 tokens under a tight one 42.4 us, looking 43.2).
-  if (waves == kDecodeMaxWaves && a.kv_lens[b] < kDecodeShortKeys && ((int64_t)a.max_blocks_per_seq << a.block_shift) >= kDecodeWideTable) {
-    bool far = false;
-    for (int r = (int)threadIdx.x & 63; r < a.batch; r += 64) far = far || a.kv_lens[r] >= kDecodeShortKeys;
-    if (__builtin_amdgcn_ballot_w64(far) == 0) {
-      waves = kDecodeMaxWaves / 2;
-      if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= waves) return;
+  const int split = ORDERED ? 0 : (int)blockIdx.x / pairs;
+  int pair = (int)blockIdx.x - split * pairs;
+  if (ORDERED && pair < kUnits) pair = kUnits - 1 - pair;
+  int b = pair / a.n_kv_heads;
+  const int kv_head = pair - b * a.n_kv_heads;
+  int q_start = cu[b], q_end = cu[b + 1], kv_len = lens[b];
+  bool any_long = true;
+  if constexpr (ORDERED) {
+    const int keys = (int)table_keys;
+    const bool found = a.batch <= 64    ? request_of_rank<1>(a, b, keys, b, kv_len, any_long)
+                       : a.batch <= 128 ? request_of_rank<2>(a, b, keys, b, kv_len, any_long)
+                                        : request_of_rank<4>(a, b, keys, b, kv_len, any_long);
+    if (found) {
+      q_start = cu[b];
+      q_end = cu[b + 1];
     }
+  } else if (WAVES > kDecodeWaves && kv_len < kDecodeShortKeys && table_keys >= kDecodeWideTable) {
+    any_long = false;
+    for (int r = (int)threadIdx.x & 63; r < a.batch; r += 64) any_long = any_long || a.kv_lens[r] >= kDecodeShortKeys;
+    any_long = __builtin_amdgcn_ballot_w64(any_long) != 0;
   }
-  run_decode<D>(a, s_decode, waves, b, pair - b * a.n_kv_heads, split);
+  // Eight waves are for long contexts, and the host knows only that the table allows them: in a batch without one, half of
+  // the waves leave, and the unit has room for a second workgroup (300 requests of at most 407 tokens under a table of
+  // 32 768 keys, one KV head).  In the order of the batch only workgroups of short contexts look for a long one, and only
+  // where the table could be wider than the contexts (125 of 128 .. 1800 tokens under a tight one 42.4 us, looking 43.2).
+  int waves = WAVES;
+  if (WAVES > kDecodeWaves && !any_long) {
+    waves = kDecodeWaves;
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= kDecodeWaves) return;
+  }
+  if (kv_len > table_keys) kv_len = (int)table_keys;
+  run_decode<D>(a, s_decode, waves, b, kv_head, q_start, q_end - q_start, kv_len, split);
 #else
   (void)a;
 #endif

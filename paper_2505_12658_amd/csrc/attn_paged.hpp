@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (q_len == 0 || q_len * a.group > kRows) return;
     if constexpr (kDecodeForm<D>) {
       if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
-        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, split);
+        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, a.cu_seqlens_q[b], q_len, kv_len, split);
         return;
       }
     }

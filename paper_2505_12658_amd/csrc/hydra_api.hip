@@ -162,13 +162,14 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t max_q_len, 
   bool launched = false;
   if constexpr (hydra::paged::kDecodeForm<D>) {
     if (decode_only) {
-      // Waves per workgroup: 4 keep a compute unit's memory path full.  With one to two workgroups per unit and long
-      // contexts 8, of which a unit holds one at a time: units that are done early then take the remaining pairs
-      // instead of some units holding two long contexts from the start (96 requests of 128 .. 1782 tokens, 4 KV heads:
-      // 39.7 -> 35.7 us; 195 of at most 407: 16.4 -> 20.4, hence the length, which the kernel checks once more).
       const int64_t keys = (int64_t)args.max_blocks_per_seq << args.block_shift;
-      const int waves = rows_wgs > 256 && rows_wgs <= 512 && args.n_splits == 1 && keys >= hydra::paged::kDecodeLongKeys ? hydra::paged::kDecodeMaxWaves : 4;
-      err = launch_lds(hydra::paged::attn_decode_kernel<D>, dim3(rows_wgs), dim3(64 * waves), waves * hydra::paged::kDecodeLdsPerWave<D>, s, args);
+      const bool ordered = hydra::paged::decode_ordered(rows_wgs, args.n_splits, args.batch, keys);
+      using hydra::paged::kDecodeMaxWaves, hydra::paged::kDecodeWaves, hydra::paged::attn_decode_kernel;
+      const bool eight = hydra::paged::decode_waves(rows_wgs, args.n_splits, keys, ordered) == kDecodeMaxWaves;
+      const int waves = eight ? kDecodeMaxWaves : kDecodeWaves;
+      err = launch_lds(ordered ? (eight ? attn_decode_kernel<D, true, kDecodeMaxWaves> : attn_decode_kernel<D, true, kDecodeWaves>)
+                               : (eight ? attn_decode_kernel<D, false, kDecodeMaxWaves> : attn_decode_kernel<D, false, kDecodeWaves>),
+                       dim3(rows_wgs), dim3(64 * waves), waves * hydra::paged::kDecodeLdsPerWave<D>, s, args);
       launched = true;
     }
   }

@@ -326,6 +326,48 @@ def test_decode_form(case):
     _check(_run_gpu(h, q, kc, vc, tables), want)
 
 
+ORDERED_CASES = [
+    # requests, KV heads, d, contexts (a function of the request's number), table keys: more pairs than compute units
+    (33, 8, 64, lambda i: 257 + 7 * i, 0),                               # one register of lengths; 264 pairs, the shortest of all orders
+    (64, 5, 128, lambda i: (0, 1, 31, 32, 33, 300, 1000)[i % 7], 0),     # many equal ones, and requests without context
+    (65, 4, 64, lambda i: 900 - 11 * i, 0),                              # two registers, one lane of the second; longest first already
+    (128, 3, 64, lambda i: 1 + 37 * i % 511, 4096),                      # a table wider than any context
+    (129, 2, 64, lambda i: 600 if i == 128 else 40 + i % 5, 0),          # four registers; one long context, the last one
+    (256, 2, 64, lambda i: 1 + 131 * i % 777, 0),                        # 512 pairs, eight waves
+    (256, 2, 64, lambda i: 1 + 131 * i % 511, 4096),                     # eight waves of which four leave
+    (116, 4, 128, lambda i: 40 * (i % 23), 0),                           # 464 pairs
+    (70, 16, 64, lambda i: 20 + 53 * i % 500, 0),                        # 1120 pairs: more than the chip holds at once
+    (80, 4, 64, lambda i: 1000 + i % 100, 0),                            # contexts within a quarter of each other
+    (257, 1, 64, lambda i: 1 + 131 * i % 777, 0),                        # one request too many
+]
+
+
+@pytest.mark.parametrize("case", ORDERED_CASES, ids=lambda c: f"n{c[0]}-k{c[1]}-d{c[2]}-t{c[4]}-{c[3](1)}")
+def test_pairs_in_the_order_of_their_contexts(case):
+    """Decode batches of more (request, KV head) pairs than compute units, whose workgroups find their pair by the rank of its
+    context: every row is there, against the oracle, and (where both launches have four waves per workgroup) with the bits of
+    the same requests in batches too small to be ordered."""
+    n, hkv, d, context, table_keys = case
+    kv_lens = [context(i) for i in range(n)]
+    h = si.HybridBatch("ordered", [1 if k else 0 for k in kv_lens], kv_lens, 2 * hkv, hkv, d, block_size=16, seed=n + hkv)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    if table_keys:
+        wide = np.full((n, table_keys // 16), -1, dtype=np.int32)
+        wide[:, : tables.shape[1]] = tables
+        tables = wide
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    _run_gpu(h, q, kc, vc, tables, out=out)
+    _check(out, _want(h, q, kc, vc, tables))
+    if 464 <= n * hkv <= 512 or n == 257:
+        return
+    size = 256 // hkv
+    for at in range(0, n, size):
+        part = si.HybridBatch("part", h.q_lens[at:at + size], kv_lens[at:at + size], 2 * hkv, hkv, d, block_size=16)
+        rows = slice(int(h.cu_seqlens_q[at]), int(h.cu_seqlens_q[at]) + part.total_q)
+        alone = _run_gpu(part, q[rows], kc, vc, np.ascontiguousarray(tables[at:at + size]), use_workspace=False)
+        assert torch.equal(alone.view(torch.int16), out[rows].view(torch.int16))
+
+
 def test_split_context_with_an_infinite_value():
     """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
     column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
