@@ -341,6 +341,39 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   }
 }
 
+// The lane of the set bit number n of a mask that has more than n.
+__device__ __forceinline__ int nth_lane(uint64_t mask, int n) {
+  const int lane = threadIdx.x & 63;
+  const int lower = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+  return __builtin_ctzll(__builtin_amdgcn_ballot_w64((mask >> lane & 1) != 0 && lower == n));
+}
+
+// The request of rank `rank` (register x 64 + lane), longest first and equal ones by number, of those whose length steps[]
+// holds; -1 in the other lanes.  A search over the bits of a length, highest first: ballots count how many requests reach it.
+template <int REGS>
+__device__ __forceinline__ int search_rank(const int (&steps)[REGS], int rank, int table_keys) {
+  // the largest number of steps that more than `rank` requests reach: that of the request asked for
+  int v = 0;
+  for (int bit = 1 << (31 - __builtin_clz((table_keys + kDecodeKeys - 1) / kDecodeKeys)); bit > 0; bit >>= 1) {
+    int reach = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) reach += __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] >= (v | bit)));
+    v = reach > rank ? v | bit : v;
+  }
+  int skip = rank;  // requests of as many steps that come before it
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) skip -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] > v));
+  int found = -1;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    const uint64_t here = __builtin_amdgcn_ballot_w64(steps[r] == v);
+    const int n = __builtin_popcountll(here);
+    if (skip >= 0 && skip < n) found = r * 64 + nth_lane(here, skip);
+    skip -= n;
+  }
+  return found;
+}
+
 // The request of rank `rank` when the batch is ordered by context, longest first (in steps of kDecodeKeys; equal ones by
 // number), and its context.  Called by whole waves; every wave finds it for itself, without LDS or a barrier: the lengths
 // lie in REGS registers of its lanes, and a search over the bits of a length, highest first, counts with ballots how many
@@ -366,29 +399,12 @@ __device__ __forceinline__ bool request_of_rank(const PagedArgs& a, int rank, in
   }
   any_long = __builtin_amdgcn_ballot_w64(longer) != 0;
   if (__builtin_amdgcn_ballot_w64(far) == 0 || __builtin_amdgcn_ballot_w64(ragged) == 0) return false;
-  // the largest number of steps that more than `rank` requests reach: that of the request asked for
-  int v = 0;
-  for (int bit = 1 << (31 - __builtin_clz((table_keys + kDecodeKeys - 1) / kDecodeKeys)); bit > 0; bit >>= 1) {
-    int reach = 0;
+  const int at = search_rank(steps, rank, table_keys);
+  if (at < 0) return true;  // (not for a rank that a request has)
+  b = at;
 #pragma unroll
-    for (int r = 0; r < REGS; ++r) reach += __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] >= (v | bit)));
-    v = reach > rank ? v | bit : v;
-  }
-  int skip = rank;  // requests of as many steps that come before it
-#pragma unroll
-  for (int r = 0; r < REGS; ++r) skip -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] > v));
-#pragma unroll
-  for (int r = 0; r < REGS; ++r) {
-    uint64_t here = __builtin_amdgcn_ballot_w64(steps[r] == v);
-    const int n = __builtin_popcountll(here);
-    if (skip >= 0 && skip < n) {
-      for (int i = 0; i < skip; ++i) here &= here - 1;
-      const int at = __builtin_ctzll(here);
-      b = r * 64 + at;
-      kv_len = __builtin_amdgcn_readlane(len[r], at);
-    }
-    skip -= n;
-  }
+  for (int r = 0; r < REGS; ++r)
+    if (at / 64 == r) kv_len = __builtin_amdgcn_readlane(len[r], at % 64);
   return true;
 }
 

@@ -575,29 +575,218 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
 
 #endif  // __HIP_DEVICE_COMPILE__
 
-// grid = batch * n_kv_heads * n_splits + n_tile_wgs workgroups, one-dimensional.
-//   - The first batch * n_kv_heads * n_splits run the packed-rows form (decode steps, chunks of a few tokens):
-//     n_splits workgroups per (request, KV head), each a share of the context; requests of the other form are
-//     left at once.
-//   - The last n_tile_wgs run the wave-tile form: workgroup w of them serves KV head w % n_kv_heads and group
-//     number w / n_kv_heads in the list of all groups of four wave tiles of all requests that take this form
-//     (q_len * group > 32), which it finds for itself: the 256 threads add up the groups of a slice of the
-//     requests each and a scan over the slices gives every request's place; the requests of this form (few:
-//     prefill chunks) are then ranked by context length in LDS and the groups counted off in that order, the
-//     longest context first and inside a request from the last token tile down (which sees the most keys).
-//     The host sizes n_tile_wgs from the total number of new tokens (it cannot see the lengths); workgroups past
-//     the last group leave at once.
-// The hardware starts workgroups in index order.  Measured on the hybrid benchmark batch (96 decode steps, 4
-// chunks): decode steps first and then the chunks' workgroups from the longest down, 82 us; chunks first in
-// batch order, 88 us (the decode steps then wait for the few free slots and the long ones among them end the
-// kernel); a grid with one row of workgroups per request (which made every decode request pay for the widest
-// chunk's row with workgroups that only looked at its length and left, and started a chunk that stood last in the
-// batch last), 95 us.
-// Both forms live in one kernel so that the decode requests and the prefill chunks of a batch run side by
-// side on the chip; two workgroups per compute unit (a wave keeps within 256 registers, a workgroup within
-// half of the LDS).
-constexpr int kFirstLayer = 256;  // compute units: workgroups i and i + 256 of a grid share one
-constexpr int kLongChain = 8;     // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
+// One-dimensional grid of workgroups of two kinds:
+//   - decode steps and chunks of a few tokens, in the decode form or the packed-rows form: n_splits workgroups per
+//     (request, KV head), each a share of the context;
+//   - prefill chunks, in the wave-tile form: a workgroup per group of four wave tiles and KV head.  The groups are counted
+//     off with the longest context first and inside a request from the last token tile down (which sees the most keys);
+//     neighbouring workgroups have the same group and the next KV head.
+// The host sizes the grid from the total number of new tokens (it cannot see the lengths); workgroups past the last group
+// leave at once.  Which work a workgroup has, it finds out for itself: find_work for batches of up to kOrderedMost requests;
+// for larger ones decode steps have the first batch * n_kv_heads * n_splits workgroups in the order of the requests, and a
+// chunk's workgroup finds its group by a scan over the requests in LDS (the 256 threads add up the groups of a slice of the
+// requests each, and the requests that have groups are ranked by context).
+// The hardware starts workgroups in index order.  Both kinds live in one kernel so that the decode requests and the prefill
+// chunks of a batch run side by side on the chip; two workgroups per compute unit (a wave keeps within 256 registers, a
+// workgroup within half of the LDS).
+constexpr int kFirstLayer = kUnits;  // workgroups i and i + 256 of a grid share a compute unit
+constexpr int kLongChain = 8;        // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
+constexpr int kStepUnits = 128;      // compute units that the chains leave to the decode steps
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// A workgroup's work: a share of a request's context for one KV head (f0 < 0), or a group of wave tiles of a request.
+struct Work {
+  int b, kv_head, q_start, q_len, kv_len, split, f0;
+};
+
+// This workgroup's work, found by every wave for itself from the lengths of the whole batch, which lie in REGS registers of its
+// lanes; false for workgroups that have none.
+// The order.  A key tile takes a chunk's workgroup 1.1 us on a unit of its own, 1.5 beside another chain and 2.2 beside a
+// decode step, which keeps the unit's memory path full.  So the chip is divided: on the first `units` compute units the
+// workgroups of both layers (ids i and i + 256) are decode steps, the longest first in all, paired like those of
+// attn_decode_kernel; on the others both are chains, the longest ones, a longer one with a shorter one.  What does not fit follows
+// behind, shorter decode steps before shorter chains.
+//   - The chains' part is as large as the groups of more than half of the longest chain need, since the kernel lasts as long as
+//     its longest chain and these cannot start late; where decode steps fill more than a layer and are not much longer than the
+//     chains (a decode step takes half as long per key, alone on its unit), at least what the decode steps leave of two layers.
+//   - Decode steps of less than a layer whose contexts are shorter than the chunks' are done early: then the chains of the second
+//     layer go beside them, and the longest have a unit for themselves (43 of 70 .. 708 tokens and 4 chunks of 192: 20.5 us, else 21.5).
+//   - Without long chains the decode steps are what the kernel waits for, and all units start with them.
+// Of split contexts only the shares that exist have a workgroup, so that chains start on the units that these leave free.
+// us before (requests in batch order, empty shares among them; of the chains as many as the decode steps left slots for, beside each
+// other) and now, 28 / 4 heads of 128: 96 decode steps of 180 .. 1800 tokens and 4 chunks of 512 63.8 -> 62, of 250 .. 2500 and 4 of
+// 200 62.4 -> 50.8; 70 of 200 .. 2000 and 2 of 300 46.1 -> 33.7; 36 of 246 .. 2466 and 3 of 352 38.0 -> 31.9; 72 of 136 .. 1366 and 4 of
+// 215 37.5 -> 28.6; 76 of 44 .. 441 and 4 of 72 15.6 -> 14.6; 20 of 240 .. 2408 and 4 of 68 21.1 -> 17.2; 5 of 97 .. 971 and 1 of 299
+// 12.0 -> 11.1 (a scan over the requests through LDS took longer); 42 of 72 .. 723 and 4 of 64 12.4 -> 12.7 (decode steps whose lengths
+// now come through the vector memory path; the largest loss of 96 mixes, their mean is 6 % faster).
+template <int REGS>
+__device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
+  const int lane = threadIdx.x & 63;
+  const int table_keys = (int)((int64_t)a.max_blocks_per_seq << a.block_shift);
+  int q_start[REGS], q_len[REGS], kv_len[REGS];
+  int steps[REGS], groups[REGS];  // of a request of the first kind / of the second
+  uint64_t chunks[REGS], any_chunk = 0, far_chunk = 0;
+  int n_steps = 0;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    const int at = r * 64 + lane < a.batch ? r * 64 + lane : a.batch - 1;
+    q_start[r] = a.cu_seqlens_q[at];
+    q_len[r] = a.cu_seqlens_q[at + 1];
+    kv_len[r] = a.kv_lens[at];
+  }
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    q_len[r] -= q_start[r];
+    kv_len[r] = kv_len[r] < table_keys ? kv_len[r] : table_keys;
+    if (r * 64 + lane >= a.batch || kv_len[r] < q_len[r]) q_len[r] = 0;  // (a context shorter than its new tokens is invalid)
+    const bool many = q_len[r] * a.group > kRows, chunk = many && a.n_tile_wgs > 0;
+    steps[r] = q_len[r] > 0 && !many ? (kv_len[r] + kDecodeKeys - 1) / kDecodeKeys : -1;
+    groups[r] = chunk ? (((q_len[r] + kRows - 1) / kRows) * a.group + kWavesPerGroup - 1) / kWavesPerGroup : 0;
+    n_steps += __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] > 0));
+    chunks[r] = __builtin_amdgcn_ballot_w64(chunk);
+    any_chunk |= chunks[r];
+    far_chunk |= __builtin_amdgcn_ballot_w64(chunk && kv_len[r] > kLongChain * kKvTileRows);
+  }
+  // workgroups of the first kind: one per share
+  int rows_wgs = n_steps * a.n_kv_heads, shares[REGS];
+  if (a.n_splits > 1) {
+    int sum = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) {
+      int per;
+      shares[r] = 0;
+      if (steps[r] > 0) share_plan(steps[r], a.n_splits, a.least_log2, per, shares[r]);
+      sum += shares[r];
+    }
+    rows_wgs = __builtin_amdgcn_readlane(wave_scan_add(sum), 63) * a.n_kv_heads;
+  }
+  const int id = (int)blockIdx.x;
+
+  // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
+  int units = kFirstLayer;
+  bool beside_steps = false;
+  if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
+    int longest = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r)
+      for (uint64_t left = chunks[r]; left != 0; left &= left - 1) {
+        const int kv = __builtin_amdgcn_readlane(kv_len[r], __builtin_ctzll(left));
+        longest = kv > longest ? kv : longest;
+      }
+    int far = 0;  // groups whose chains are longer than half of the longest
+    uint64_t longer = 0, far_longer = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) {
+      int tokens = kv_len[r] - longest / 2;
+      tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
+      far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
+      longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
+      far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
+    }
+    beside_steps = rows_wgs <= kFirstLayer && longer == 0;
+    if (far_chunk != 0 && !beside_steps) {
+      int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
+      if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
+      chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
+      units = kFirstLayer - chain_units;
+    }
+  }
+  if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
+  const int chain_units = kFirstLayer - units;
+
+  int step = -1, chain = -1;
+  if (id < units) {
+    step = id;
+  } else if (id < kFirstLayer || beside_steps) {
+    chain = id - units;
+  } else if (id < kFirstLayer + units) {
+    step = units + id - kFirstLayer;
+    if (step >= rows_wgs) chain = 2 * chain_units + step - (rows_wgs > units ? rows_wgs : units);
+  } else if (id < 2 * kFirstLayer) {
+    const int at = id - (kFirstLayer + units);  // (the longer the first chain of a unit, the shorter the second)
+    chain = 2 * chain_units - 8 - (at & ~7) + (at & 7);
+  } else {
+    step = 2 * units + id - 2 * kFirstLayer;
+    if (step >= rows_wgs) chain = id - (rows_wgs > units ? rows_wgs : units);
+  }
+
+  if (chain >= 0) {
+    const int target = chain / a.n_kv_heads;
+    w.kv_head = chain - target * a.n_kv_heads;
+    w.split = 0;
+    w.b = -1;
+    int before[REGS];  // groups ahead of this lane's chunk: those of chunks with longer contexts
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) before[r] = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r)
+      for (uint64_t left = chunks[r]; left != 0; left &= left - 1) {
+        const int j = __builtin_ctzll(left);
+        const int kv = __builtin_amdgcn_readlane(kv_len[r], j), n = __builtin_amdgcn_readlane(groups[r], j);
+#pragma unroll
+        for (int e = 0; e < REGS; ++e) before[e] += kv > kv_len[e] || (kv == kv_len[e] && r * 64 + j < e * 64 + lane) ? n : 0;
+      }
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) {
+      const uint64_t here = __builtin_amdgcn_ballot_w64(groups[r] > 0 && before[r] <= target && target < before[r] + groups[r]);
+      if (here != 0) {
+        const int j = __builtin_ctzll(here);
+        w.b = r * 64 + j;
+        w.q_start = __builtin_amdgcn_readlane(q_start[r], j);
+        w.q_len = __builtin_amdgcn_readlane(q_len[r], j);
+        w.kv_len = __builtin_amdgcn_readlane(kv_len[r], j);
+        w.f0 = (__builtin_amdgcn_readlane(groups[r], j) - 1 - (target - __builtin_amdgcn_readlane(before[r], j))) * kWavesPerGroup;
+      }
+    }
+    return w.b >= 0;  // (past the last group otherwise)
+  }
+
+  if (step >= rows_wgs) return false;
+  w.f0 = -1;
+  w.split = 0;
+  // ranked by context, or (where all of them start together, and where contexts are split: ranked, the second workgroups of the
+  // units with the longest shares had long ones too, 20 decode steps of 240 .. 2408 tokens and 4 chunks of 68 21.2 -> 23.3 us)
+  // just the request number `rank` of this kind
+  const bool ranked = rows_wgs > units && a.n_splits == 1;
+  uint64_t of_kind[REGS];
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) of_kind[r] = __builtin_amdgcn_ballot_w64(steps[r] > 0);
+  int pair = ranked && step < units ? units - 1 - step : step;  // (see attn_decode_kernel)
+  if (a.n_splits > 1) {
+    // share-major: the first shares of all pairs, then the second shares of those that have one, ...
+    for (;;) {
+      int n = 0;
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) n += __builtin_popcountll(of_kind[r]);
+      n *= a.n_kv_heads;
+      if (pair < n || n == 0) break;
+      pair -= n;
+      ++w.split;
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) of_kind[r] = __builtin_amdgcn_ballot_w64(shares[r] > w.split);
+    }
+  }
+  const int rank = pair / a.n_kv_heads;
+  w.kv_head = pair - rank * a.n_kv_heads;
+  w.b = ranked ? search_rank(steps, rank, table_keys) : -1;
+  int skip = rank;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) {
+    if (!ranked) {
+      const int n = __builtin_popcountll(of_kind[r]);
+      if (skip >= 0 && skip < n) w.b = r * 64 + nth_lane(of_kind[r], skip);
+      skip -= n;
+    }
+    if (w.b / 64 == r) {
+      w.q_start = __builtin_amdgcn_readlane(q_start[r], w.b % 64);
+      w.q_len = __builtin_amdgcn_readlane(q_len[r], w.b % 64);
+      w.kv_len = __builtin_amdgcn_readlane(kv_len[r], w.b % 64);
+    }
+  }
+  return true;
+}
+
+#endif  // __HIP_DEVICE_COMPILE__
 
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_paged_kernel(const PagedArgs a) {
@@ -617,155 +806,161 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kv_len > table_keys) kv_len = (int)table_keys;
     if (q_len < 0 || kv_len < q_len) q_len = 0;
   };
-  int b, kv_head, f0 = 0;
-  const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;
-  // This workgroup's place in the order above.  Where the decode steps fill the first layer of the chip (256 units) and
-  // part of the second, the second layer's remaining slots go to the longest chunk chains, and a chain that shares its
-  // unit with a decode step crawls: the decode step keeps the unit's memory path full (a key tile takes the chain 2.2 us
-  // instead of 1.5).  When the batch has long chains, those slots are moved: c chains end the first layer and c lie
-  // above them in the second, so that chains share units with chains and decode steps with decode steps (96 decode
-  // steps and 4 chunks of 512 with up to 3 chunks behind them: 71.3 -> 62 us; over 48 mixes +5 %, from +17 to -3).
-  // Without long chains the decode steps are what the kernel waits for, and they stay in front.
-  int place = (int)blockIdx.x;
-  {
-    int c = (kFirstLayer * 2 - n_rows_wgs) / 2;
-    c = (c < a.n_tile_wgs ? c : a.n_tile_wgs) & ~7;  // (places only change hands with ids that the grid has; a multiple of 8: KV heads keep their dies)
-    const int id = (int)blockIdx.x;
-    if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
-      bool far = false;
-      for (int r = (int)threadIdx.x; r < a.batch; r += 256) {
-        int q_len, kv_len;
+  int b, kv_head, q_start, q_len, kv_len, split = 0, f0 = -1;  // f0 < 0: the packed-rows form or the decode form
+  if (a.batch <= kOrderedMost) {
+    Work w;
+    if (!(a.batch <= 64 ? find_work<1>(a, w) : find_work<4>(a, w))) return;
+    b = w.b, kv_head = w.kv_head, q_start = w.q_start, q_len = w.q_len, kv_len = w.kv_len, split = w.split, f0 = w.f0;
+  } else {
+    const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;
+    // This workgroup's place: decode steps, then chains.  Where the decode steps fill the first layer of the chip (256 units) and
+    // part of the second, the second layer's remaining slots go to the longest chunk chains, and a chain that shares its
+    // unit with a decode step crawls: the decode step keeps the unit's memory path full (a key tile takes the chain 2.2 us
+    // instead of 1.5).  When the batch has long chains, those slots are moved: c chains end the first layer and c lie
+    // above them in the second, so that chains share units with chains and decode steps with decode steps (96 decode
+    // steps and 4 chunks of 512 with up to 3 chunks behind them: 71.3 -> 62 us; over 48 mixes +5 %, from +17 to -3).
+    // Without long chains the decode steps are what the kernel waits for, and they stay in front.
+    int place = (int)blockIdx.x;
+    {
+      int c = (kFirstLayer * 2 - n_rows_wgs) / 2;
+      c = (c < a.n_tile_wgs ? c : a.n_tile_wgs) & ~7;  // (places only change hands with ids that the grid has; a multiple of 8: KV heads keep their dies)
+      const int id = (int)blockIdx.x;
+      if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
+        bool far = false;
+        for (int r = (int)threadIdx.x; r < a.batch; r += 256) {
+          int q_len, kv_len;
+          lengths_of(r, q_len, kv_len);
+          far = far || (q_len * a.group > kRows && kv_len > kLongChain * kKvTileRows);
+        }
+        if (__syncthreads_or(far)) place = id < kFirstLayer ? n_rows_wgs + id - (kFirstLayer - c) : id - c;
+      }
+    }
+    if (place < n_rows_wgs) {
+      const int r = place;
+      // (share-major: the workgroups of the first shares, which every request has, lie next to each other and are dealt
+      // to all dies alike; the further shares, some of them empty when contexts differ in length, come behind them)
+      const int pairs = a.batch * a.n_kv_heads;
+      split = r / pairs;
+      const int pair = r - split * pairs;
+      b = pair / a.n_kv_heads;
+      kv_head = pair - b * a.n_kv_heads;
+      lengths_of(b, q_len, kv_len);
+      if (q_len == 0 || q_len * a.group > kRows) return;
+    } else{
+      // which group of which request: see above.  Thread i adds up requests [i * per, (i + 1) * per).
+      int* s_scan = reinterpret_cast<int*>(s_stats);  // [0..3] the waves' groups, [4..7] the waves' requests, [256] = request, [257] = group
+      const int target = (place - n_rows_wgs) / a.n_kv_heads;
+      kv_head = (place - n_rows_wgs) - target * a.n_kv_heads;
+      const int per = (a.batch + 255) / 256;
+      auto groups_of = [&](int r, int& kv_len) {
+        int q_len;
         lengths_of(r, q_len, kv_len);
-        far = far || (q_len * a.group > kRows && kv_len > kLongChain * kKvTileRows);
-      }
-      if (__syncthreads_or(far)) place = id < kFirstLayer ? n_rows_wgs + id - (kFirstLayer - c) : id - c;
-    }
-  }
-  if (place < n_rows_wgs) {
-    const int r = place;
-    // (share-major: the workgroups of the first shares, which every request has, lie next to each other and are dealt
-    // to all dies alike; the further shares, some of them empty when contexts differ in length, come behind them)
-    const int pairs = a.batch * a.n_kv_heads;
-    const int split = r / pairs, pair = r - split * pairs;
-    b = pair / a.n_kv_heads;
-    kv_head = pair - b * a.n_kv_heads;
-    int q_len, kv_len;
-    lengths_of(b, q_len, kv_len);
-    if (q_len == 0 || q_len * a.group > kRows) return;
-    if constexpr (kDecodeForm<D>) {
-      if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
-        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, a.cu_seqlens_q[b], q_len, kv_len, split);
-        return;
-      }
-    }
-    run_packed_rows<D>(a, smem, s_stats, a.block_tables + (int64_t)b * a.max_blocks_per_seq, a.cu_seqlens_q[b], q_len, kv_len, kv_head, b, split);
-    return;
-  }
-  {
-    // which group of which request: see above.  Thread i adds up requests [i * per, (i + 1) * per).
-    int* s_scan = reinterpret_cast<int*>(s_stats);  // [0..3] the waves' groups, [4..7] the waves' requests, [256] = request, [257] = group
-    const int target = (place - n_rows_wgs) / a.n_kv_heads;
-    kv_head = (place - n_rows_wgs) - target * a.n_kv_heads;
-    const int per = (a.batch + 255) / 256;
-    auto groups_of = [&](int r, int& kv_len) {
-      int q_len;
-      lengths_of(r, q_len, kv_len);
-      if (q_len * a.group <= kRows) return 0;
-      return (((q_len + kRows - 1) / kRows) * a.group + kWavesPerGroup - 1) / kWavesPerGroup;
-    };
-    const int first = (int)threadIdx.x * per, last = first + per < a.batch ? first + per : a.batch;
-    int mine = 0, mine_reqs = 0;  // groups, and requests that have groups, in this thread's slice
-    for (int r = first; r < last; ++r) {
-      int kv;
-      const int n = groups_of(r, kv);
-      mine += n;
-      mine_reqs += n > 0 ? 1 : 0;
-    }
-    const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
-    int incl = mine, incl_reqs = mine_reqs;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(incl, d), up_reqs = __shfl_up(incl_reqs, d);
-      if (lane_ >= d) {
-        incl += up;
-        incl_reqs += up_reqs;
-      }
-    }
-    if (lane_ == 63) {
-      s_scan[wave_] = incl;
-      s_scan[4 + wave_] = incl_reqs;
-    }
-    if (threadIdx.x == 0) s_scan[256] = -1;
-    __syncthreads();
-    int before = incl - mine, before_reqs = incl_reqs - mine_reqs;  // of the slices ahead of this thread's
-    for (int i = 0; i < wave_; ++i) {
-      before += s_scan[i];
-      before_reqs += s_scan[4 + i];
-    }
-    const int total_reqs = s_scan[4] + s_scan[5] + s_scan[6] + s_scan[7];
-    if (target >= s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3]) return;  // past the last group
-    // Requests with the longest contexts first: their workgroups run longest, and the kernel is as long as the
-    // last of them.  The requests of this form (few: prefill chunks) are gathered in LDS, ranked by context
-    // length, and the groups are counted off in that order.  (More than kMaxSorted of them: batch order.)
-    constexpr int kMaxSorted = 256;
-    if (total_reqs <= kMaxSorted) {
-      int* s_req = reinterpret_cast<int*>(smem);  // the tile stages are not in use yet
-      int* s_groups = s_req + kMaxSorted, *s_key = s_req + 2 * kMaxSorted;
-      int* s_sorted_req = s_req + 3 * kMaxSorted, *s_sorted_groups = s_req + 4 * kMaxSorted;
-      int k = before_reqs;
+        if (q_len * a.group <= kRows) return 0;
+        return (((q_len + kRows - 1) / kRows) * a.group + kWavesPerGroup - 1) / kWavesPerGroup;
+      };
+      const int first = (int)threadIdx.x * per, last = first + per < a.batch ? first + per : a.batch;
+      int mine = 0, mine_reqs = 0;  // groups, and requests that have groups, in this thread's slice
       for (int r = first; r < last; ++r) {
         int kv;
         const int n = groups_of(r, kv);
-        if (n > 0) {
-          s_req[k] = r;
-          s_groups[k] = n;
-          s_key[k] = kv;
-          ++k;
+        mine += n;
+        mine_reqs += n > 0 ? 1 : 0;
+      }
+      const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
+      int incl = mine, incl_reqs = mine_reqs;
+  #pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(incl, d), up_reqs = __shfl_up(incl_reqs, d);
+        if (lane_ >= d) {
+          incl += up;
+          incl_reqs += up_reqs;
         }
       }
-      __syncthreads();
-      if ((int)threadIdx.x < total_reqs) {
-        const int key = s_key[threadIdx.x];
-        int rank = 0;
-        for (int j = 0; j < total_reqs; ++j) rank += (s_key[j] > key || (s_key[j] == key && j < (int)threadIdx.x)) ? 1 : 0;
-        s_sorted_req[rank] = s_req[threadIdx.x];
-        s_sorted_groups[rank] = s_groups[threadIdx.x];
+      if (lane_ == 63) {
+        s_scan[wave_] = incl;
+        s_scan[4 + wave_] = incl_reqs;
       }
+      if (threadIdx.x == 0) s_scan[256] = -1;
       __syncthreads();
-      if (threadIdx.x == 0) {
-        int at = 0;
-        for (int e = 0; e < total_reqs; ++e) {
-          const int n = s_sorted_groups[e];
+      int before = incl - mine, before_reqs = incl_reqs - mine_reqs;  // of the slices ahead of this thread's
+      for (int i = 0; i < wave_; ++i) {
+        before += s_scan[i];
+        before_reqs += s_scan[4 + i];
+      }
+      const int total_reqs = s_scan[4] + s_scan[5] + s_scan[6] + s_scan[7];
+      if (target >= s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3]) return;  // past the last group
+      // Requests with the longest contexts first: their workgroups run longest, and the kernel is as long as the
+      // last of them.  The requests of this form (few: prefill chunks) are gathered in LDS, ranked by context
+      // length, and the groups are counted off in that order.  (More than kMaxSorted of them: batch order.)
+      constexpr int kMaxSorted = 256;
+      if (total_reqs <= kMaxSorted) {
+        int* s_req = reinterpret_cast<int*>(smem);  // the tile stages are not in use yet
+        int* s_groups = s_req + kMaxSorted, *s_key = s_req + 2 * kMaxSorted;
+        int* s_sorted_req = s_req + 3 * kMaxSorted, *s_sorted_groups = s_req + 4 * kMaxSorted;
+        int k = before_reqs;
+        for (int r = first; r < last; ++r) {
+          int kv;
+          const int n = groups_of(r, kv);
+          if (n > 0) {
+            s_req[k] = r;
+            s_groups[k] = n;
+            s_key[k] = kv;
+            ++k;
+          }
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < total_reqs) {
+          const int key = s_key[threadIdx.x];
+          int rank = 0;
+          for (int j = 0; j < total_reqs; ++j) rank += (s_key[j] > key || (s_key[j] == key && j < (int)threadIdx.x)) ? 1 : 0;
+          s_sorted_req[rank] = s_req[threadIdx.x];
+          s_sorted_groups[rank] = s_groups[threadIdx.x];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+          int at = 0;
+          for (int e = 0; e < total_reqs; ++e) {
+            const int n = s_sorted_groups[e];
+            if (target < at + n) {
+              s_scan[256] = s_sorted_req[e];
+              s_scan[257] = n - 1 - (target - at);  // from the last group down
+              break;
+            }
+            at += n;
+          }
+        }
+      } else if (target >= before && target < before + mine) {
+        int at = before;
+        for (int r = first; r < last; ++r) {
+          int kv;
+          const int n = groups_of(r, kv);
           if (target < at + n) {
-            s_scan[256] = s_sorted_req[e];
-            s_scan[257] = n - 1 - (target - at);  // from the last group down
+            s_scan[256] = r;
+            s_scan[257] = n - 1 - (target - at);
             break;
           }
           at += n;
         }
       }
-    } else if (target >= before && target < before + mine) {
-      int at = before;
-      for (int r = first; r < last; ++r) {
-        int kv;
-        const int n = groups_of(r, kv);
-        if (target < at + n) {
-          s_scan[256] = r;
-          s_scan[257] = n - 1 - (target - at);
-          break;
-        }
-        at += n;
+      __syncthreads();
+      b = __builtin_amdgcn_readfirstlane(s_scan[256]);
+      if (b < 0) return;  // (cannot happen: the target was below the total)
+      f0 = __builtin_amdgcn_readfirstlane(s_scan[257]) * kWavesPerGroup;
+      __syncthreads();  // (the scan area is the packed-rows form's statistics area, the lists lie in the tile stages)
+    }
+    if (place >= n_rows_wgs) lengths_of(b, q_len, kv_len);
+    q_start = a.cu_seqlens_q[b];
+  }
+  if (f0 < 0) {
+    if constexpr (kDecodeForm<D>) {
+      if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
+        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, q_start, q_len, kv_len, split);
+        return;
       }
     }
-    __syncthreads();
-    b = s_scan[256];
-    if (b < 0) return;  // (cannot happen: the target was below the total)
-    f0 = s_scan[257] * kWavesPerGroup;
-    __syncthreads();  // (the scan area is the packed-rows form's statistics area, the lists lie in the tile stages)
+    run_packed_rows<D>(a, smem, s_stats, a.block_tables + (int64_t)b * a.max_blocks_per_seq, q_start, q_len, kv_len, kv_head, b, split);
+    return;
   }
-  const int64_t q_start = a.cu_seqlens_q[b];
-  int q_len, kv_len;
-  lengths_of(b, q_len, kv_len);
   const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
   const int n_tok_tiles = (q_len + kRows - 1) / kRows;
   const int n_wave_tiles = n_tok_tiles * a.group;
@@ -830,7 +1025,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   w.init(lane, a.scale_log2);
   int row = q0 + m;
   row = row < q_len ? row : q_len - 1;
-  w.load_q(0, a.q + (q_start + row) * a.q_stride + head * D, shift + row);
+  w.load_q(0, a.q + (int64_t)(q_start + row) * a.q_stride + head * D, shift + row);
   const int min_lim = shift + q0;  // smallest limit among the tile's tokens
 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -850,7 +1045,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     slots = next_slots;
   }
-  w.store_row(0, active && q0 + m < q_len ? a.out + ((q_start + q0 + m) * a.n_q_heads + head) * D : nullptr);
+  w.store_row(0, active && q0 + m < q_len ? a.out + ((int64_t)(q_start + q0 + m) * a.n_q_heads + head) * D : nullptr);
 #else
   (void)a;
 #endif

@@ -173,7 +173,12 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t max_q_len, 
       launched = true;
     }
   }
-  if (!launched) err = launch(hydra::paged::attn_paged_kernel<D>, dim3(rows_wgs + tile_wgs), dim3(256), s, args);
+  if (!launched) {
+    // (find_work deals out decode steps and chains over both layers of the chip, and may leave seven places of the first unused)
+    unsigned grid = rows_wgs + tile_wgs;
+    if (tile_wgs > 0 && args.batch <= hydra::paged::kOrderedMost) grid = grid + 7 < 2 * hydra::paged::kUnits ? 2 * hydra::paged::kUnits : grid + 7;
+    err = launch(hydra::paged::attn_paged_kernel<D>, dim3(grid), dim3(256), s, args);
+  }
   if (err == hipSuccess && args.n_splits > 1) {
     const int64_t rows = (int64_t)max_q_len * args.group;
     const int64_t pieces = (rows < hydra::paged::kRows ? rows : hydra::paged::kRows) * (D / 4);
@@ -482,7 +487,7 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
                                    (int64_t)max_blocks_per_seq * block_size, tile_wgs, head_dim, workspace_bytes, &args.least_log2);
   args.n_splits = splits;
   const int64_t rows_wgs = (int64_t)batch * n_kv_heads * splits;
-  if (tile_wgs + rows_wgs > (int64_t)0x7fffffff) return HYDRA_ERR_UNSUPPORTED;
+  if (tile_wgs + rows_wgs > (int64_t)0x7fffff00) return HYDRA_ERR_UNSUPPORTED;
   args.n_tile_wgs = (int32_t)tile_wgs;
   const bool decode_only = (int64_t)max_q_len * args.group <= hydra::paged::kDecodeRows && block_size >= hydra::paged::kDecodeMinBlock;
   hipStream_t s = static_cast<hipStream_t>(stream);

@@ -368,6 +368,50 @@ def test_pairs_in_the_order_of_their_contexts(case):
         assert torch.equal(alone.view(torch.int16), out[rows].view(torch.int16))
 
 
+def _mix(steps, chunks, every=None):
+    """q_lens, kv_lens of decode steps (their contexts) and chunks ((new tokens, context)), a chunk after every `every` steps."""
+    q, k, at = [], [], 0
+    every = every or max(1, len(steps) // max(1, len(chunks)))
+    for i, n in enumerate(steps):
+        q.append(1 if n else 0)
+        k.append(n)
+        if (i + 1) % every == 0 and at < len(chunks):
+            q.append(chunks[at][0])
+            k.append(chunks[at][1])
+            at += 1
+    for c, n in chunks[at:]:
+        q.append(c)
+        k.append(n)
+    return q, k
+
+
+MIXED_CASES = [
+    # (q_lens, kv_lens), Hq, Hkv, d: decode steps and chunks over the two layers of the chip
+    (_mix([], [(300, 900), (70, 70), (33, 1100)]), 4, 2, 64),                                       # chains only, some long
+    (_mix([50], [(40, 40)]), 2, 1, 64),                                                             # one of each, neither long
+    (_mix([10 + 9 * i for i in range(61)], [(64, 700), (96, 600), (40, 513)]), 4, 4, 64),           # 64 requests; steps short of a layer
+    (_mix([10 + 9 * i for i in range(62)], [(64, 700), (96, 512), (40, 513)]), 8, 8, 64),           # 65; steps past one layer, long chains
+    (_mix([5 + 7 * i % 400 for i in range(127)], [(200, 1100)]), 8, 4, 128),                        # 508 steps, chains longer than any of them
+    (_mix([300 + 7 * i % 900 for i in range(140)], [(200, 600), (64, 64)]), 8, 4, 64),              # 560 steps, steps longer than the chains
+    (_mix([(0, 33, 400)[i % 3] for i in range(200)], [(40, 40 + 20 * i) for i in range(56)]), 2, 1, 64),   # 256 requests, 56 chunks, many equal
+    (_mix([1 + 5 * i % 99 for i in range(250)], [(33, 700), (64, 64)] * 3 + [(50, 60)]), 4, 2, 64),  # 257 requests: one too many
+    (_mix([2100, 1700, 900], [(60, 60)]), 4, 1, 128),                                               # split contexts beside a chunk
+    (_mix([700] * 9, [(100, 700)] * 9), 4, 2, 80),                                                  # the other forms, all of one length
+]
+
+
+@pytest.mark.parametrize("case", MIXED_CASES, ids=lambda c: f"n{len(c[0][0])}-q{sum(c[0][0])}-kv{max(c[0][1])}-h{c[1]}k{c[2]}-d{c[3]}")
+def test_steps_and_chains_over_the_chip(case):
+    """Hybrid batches whose workgroups find their step or chain from the lengths of the whole batch: every row is there."""
+    (q_lens, kv_lens), hq, hkv, d = case
+    h = si.HybridBatch("mix", q_lens, kv_lens, hq, hkv, d, block_size=16, seed=len(q_lens))
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    want = _want(h, q, kc, vc, tables)
+    for kw in ({}, {"use_workspace": False}):
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        _check(_run_gpu(h, q, kc, vc, tables, out=out, **kw), want)
+
+
 def test_split_context_with_an_infinite_value():
     """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
     column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
