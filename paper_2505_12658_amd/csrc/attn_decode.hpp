@@ -461,6 +461,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDec
   int b = pair / a.n_kv_heads;
   const int kv_head = pair - b * a.n_kv_heads;
   int q_start = cu[b], q_end = cu[b + 1], kv_len = lens[b];
+  if constexpr (!ORDERED) asm volatile("" : "+s"(q_start), "+s"(q_end), "+s"(kv_len));  // (asked for together)
   bool any_long = true;
   if constexpr (ORDERED) {
     const int keys = (int)table_keys;
