@@ -72,10 +72,10 @@ inline WorkspaceLayout workspace_layout(int64_t batch, int64_t total_tokens, int
   return w;
 }
 
-// Workgroups of the prepass: one per 1024 places of the list, at least one per queue (its tail), at most 64.
+// Workgroups of the prepass: one per queue (its tail), and one per 1024 places of the list, at most 64.
 inline unsigned prepass_workgroups(size_t capacity) {
   const size_t g = (capacity + kPrepassThreads - 1) / kPrepassThreads;
-  return (unsigned)(g < (size_t)kXcds ? (size_t)kXcds : g > 64 ? 64 : g);
+  return (unsigned)(kXcds + (g > 64 ? 64 : g));
 }
 
 // queue of the pair with rank r (row r / 8): serpentine dealing
@@ -87,7 +87,8 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
                                                                          int32_t* __restrict__ queue_prefix_global, int rows,
                                                                          WorkItem* __restrict__ items,
                                                                          int capacity, int tail_items) {
-  __shared__ int s_len[kPrepassLdsSeqs];
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(16))) int s_len[kPrepassLdsSeqs];
   __shared__ int s_start[kPrepassLdsSeqs];
   __shared__ int s_sorted[kPrepassLdsSeqs];
   __shared__ int s_prefix[kPrepassLdsPrefix];
@@ -96,39 +97,68 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   __shared__ int s_queue_len[kXcds];
   __shared__ int s_queue_start[kXcds + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Every workgroup of the grid derives the ranking and the queue layout for itself (steps 1 and 2: a few
-  // microseconds, and no synchronisation between workgroups is needed); the places of the list are then shared
-  // out over the grid (step 3), and workgroup x < 8 also orders the tail of queue x (step 4).  Workgroup 0
-  // writes the control block.
+  // Every workgroup of the grid derives the ranking and the queue layout for itself (steps 1 and 2: two microseconds, and no
+  // synchronisation between workgroups is needed); then workgroup x < 8 orders the tail of queue x (step 4), and the other
+  // places of the list are shared out over the rest of the grid (step 3).  Workgroup 0 writes the control block.
+  // What bounds the kernel is latency: a read of cu_seqlens, five barriers and what lies between them.  So sequences and tail
+  // items are ranked by counting, eight lanes each with two 16-byte reads, and the scan over a queue goes through data-parallel
+  // primitives (with LDS counters that several threads add to, scans and a bitonic sort by LDS permutes, and the tails behind the items on
+  // the same workgroups, us: 48 sequences with 28 / 4 heads of 128 7.3 -> 4.7, 16 with 32 / 32 6.9 -> 4.6, 128 8.1 -> 4.8, 300 15.0 -> 11.5;
+  // ranked by every wave in its registers, without the first two barriers, 1 sequence 3.4 instead of 4.2, 48 5.6, 64 6.2).
   const bool leader = blockIdx.x == 0;
   if (leader && tid < kXcds) ctrl->queue_head[tid * kHeadStride] = ctrl->queue_head[tid * kHeadStride + kLeftAt] = 0;
   if (leader && tid == kXcds) ctrl->queues_left = 0;
 
-  // Small batches (the normal case) are handled entirely in LDS after one read of cu_seqlens;
-  // the global arrays are only used for what does not fit.
+  // Batches of what LDS holds need one read of cu_seqlens; the global arrays are only used for what does not fit.
   const bool in_lds = batch <= kPrepassLdsSeqs;
   int* sorted = in_lds ? s_sorted : sorted_seq;
-  for (int b = tid; b < batch && b < kPrepassLdsSeqs; b += kPrepassThreads) {
-    const int start = cu[b];
-    s_start[b] = start;
-    s_len[b] = cu[b + 1] - start;
-  }
-  __syncthreads();
+  int* queue_prefix = rows * kXcds <= kPrepassLdsPrefix ? s_prefix : queue_prefix_global;
+  const int n_pairs = batch * n_kv_heads;
   auto length_of = [&](int b) { return b < kPrepassLdsSeqs ? s_len[b] : cu[b + 1] - cu[b]; };
   auto start_of = [&](int b) { return b < kPrepassLdsSeqs ? s_start[b] : cu[b]; };
+  // Sum over eight neighbouring lanes (neighbours, pairs, halves of a row of eight mirrored), in all of them.
+  auto sum_of_eight = [](int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
+    return x;
+  };
+  constexpr int kParts = 8, kCounted = kPrepassThreads / kParts;  // eight lanes count for one sequence or item, up to kCounted of them
+  constexpr int kShare = kCounted / kParts;
+  static_assert(kShare % 4 == 0, "whole 16-byte reads");
+  const int counted = tid / kParts, part = tid % kParts;
 
-  // 1. rank the sequences by descending length (ties by index): count who precedes each sequence.  Batches of
-  // up to half the workgroup have several threads per sequence, each counting a share of the others.
-  if (batch <= kPrepassThreads / 2) {
-    int* s_rank = s_key;  // (unused until step 3)
+  // 1. rank the sequences by descending length (ties by index): count who precedes each sequence
+  const bool few = batch <= kCounted;
+  for (int b = tid; b < (few ? kCounted : batch) && b < kPrepassLdsSeqs; b += kPrepassThreads) {
+    const int start = b < batch ? cu[b] : 0;
+    s_start[b] = start;
+    s_len[b] = b < batch ? cu[b + 1] - start : -1;  // (precedes nobody)
+  }
+  __syncthreads();
+  if (few) {
+    const int mine = s_len[counted];
+    int rank = 0;
+#pragma unroll
+    for (int i = 0; i < kShare; i += 4) {
+      const int o = part * kShare + i;
+      const int4 others = *reinterpret_cast<const int4*>(s_len + o);
+      rank += (others.x > mine || (others.x == mine && o < counted) ? 1 : 0) + (others.y > mine || (others.y == mine && o + 1 < counted) ? 1 : 0) +
+              (others.z > mine || (others.z == mine && o + 2 < counted) ? 1 : 0) + (others.w > mine || (others.w == mine && o + 3 < counted) ? 1 : 0);
+    }
+    rank = sum_of_eight(rank);
+    if (part == 0 && counted < batch) s_sorted[rank] = counted;
+  } else if (batch <= kPrepassThreads / 2) {
+    // (several threads per sequence, each counting a share of the others)
+    int* s_rank = s_key;  // (unused until step 4)
     const int parts = kPrepassThreads / batch;
     if (tid < batch) s_rank[tid] = 0;
     __syncthreads();
-    const int b = tid / parts, part = tid - b * parts;
+    const int b = tid / parts, part_of_b = tid - b * parts;
     if (b < batch) {
       const int mine = s_len[b];
       int count = 0;
-      for (int o = part; o < batch; o += parts) {
+      for (int o = part_of_b; o < batch; o += parts) {
         const int other = s_len[o];
         count += (other > mine || (other == mine && o < b)) ? 1 : 0;
       }
@@ -152,8 +182,6 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   __syncthreads();
 
   // 2. per queue, the running item count over its pairs (one pair per row): wave x scans queue x
-  int* queue_prefix = rows * kXcds <= kPrepassLdsPrefix ? s_prefix : queue_prefix_global;
-  const int n_pairs = batch * n_kv_heads;
   if (wave < kXcds) {
     int carry = 0;
     for (int row0 = 0; row0 < rows; row0 += 64) {
@@ -161,14 +189,9 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
       const int r = pair_rank(row, wave);
       int n = 0;
       if (row < rows && r < n_pairs) n = items_of_sequence(length_of(sorted[r / n_kv_heads]), group);
-      int incl = n;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d);
-        if (lane >= d) incl += up;
-      }
+      const int incl = wave_scan_add(n);
       if (row < rows) queue_prefix[wave * rows + row] = carry + incl - n;
-      carry += __shfl(incl, 63);
+      carry += __builtin_amdgcn_readlane(incl, 63);
     }
     if (lane == 0) s_queue_len[wave] = carry;
   }
@@ -232,7 +255,7 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
     const int q_begin = s_queue_start[x], q_end = s_queue_start[x + 1];
     return q_end - tail_items > q_begin ? q_end - tail_items : q_begin;
   };
-  for (int p = blockIdx.x * kPrepassThreads + tid; p < total; p += gridDim.x * kPrepassThreads) {
+  for (int p = ((int)blockIdx.x - kXcds) * kPrepassThreads + tid; p < total && blockIdx.x >= kXcds; p += ((int)gridDim.x - kXcds) * kPrepassThreads) {
     int x = 0;
 #pragma unroll
     for (int q = 1; q < kXcds; ++q) x += p >= s_queue_start[q] ? 1 : 0;
@@ -247,7 +270,8 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   // shortest sequences, but every run still goes from its dearest item to its cheapest.  (Only a tail, sized by
   // the caller so that the K/V rows of the pairs in it fit the die's L2 together: sorted, the items of one pair
   // run apart in time, and rows that have left the L2 in between come from memory once per item instead of
-  // once per die.)  Workgroup x takes queue x: its items go to LDS with a sort key, and wave 0 sorts the keys
+  // once per die.)  Workgroup x takes queue x: its items go to LDS with a sort key (distinct; -1 = no item), and eight threads
+  // per item count the keys above its own.
   if (blockIdx.x >= kXcds) return;
   const int tail_x = tail_of(blockIdx.x), tail_n = s_queue_start[blockIdx.x + 1] - tail_x;
   __syncthreads();  // (s_key held the rank counters of step 1)
@@ -256,50 +280,22 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
     if (tid < tail_n) {
       int cost;
       s_tail[tid] = item_at(tail_x + tid, blockIdx.x, cost);
-      key = cost * kTailSort + (kTailSort - 1 - tid);  // distinct keys; equal costs keep their order
+      key = cost * kTailSort + (kTailSort - 1 - tid);  // equal costs keep their order
     }
     s_key[tid] = key;
   }
   __syncthreads();
-  // (distinct by construction, -1 = no item) with a bitonic network held in registers: lane l has the keys of
-  // places l, l + 64, ...
-  constexpr int kKeysPerLane = kTailSort / 64;
-  static_assert(kTailSort % 64 == 0 && (kTailSort & (kTailSort - 1)) == 0, "a power of two, whole registers");
-  if (wave == 0) {
-    int key[kKeysPerLane];
+  static_assert(kTailSort == kCounted, "one tail item per eight threads");
+  const int key = s_key[counted];
+  int place = 0;
 #pragma unroll
-    for (int r = 0; r < kKeysPerLane; ++r) key[r] = s_key[r * 64 + lane];
-#pragma unroll
-    for (int size = 2; size <= kTailSort; size <<= 1) {
-#pragma unroll
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        if (stride >= 64) {
-          const int rs = stride / 64;  // the partner sits in another register of the same lane
-#pragma unroll
-          for (int r = 0; r < kKeysPerLane; ++r) {
-            if (r & rs) continue;
-            const bool descending = ((r * 64) & size) == 0;
-            const int a = key[r], b = key[r | rs];
-            const bool swap = descending ? a < b : a > b;
-            key[r] = swap ? b : a;
-            key[r | rs] = swap ? a : b;
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < kKeysPerLane; ++r) {
-            const int other = __shfl_xor(key[r], stride);
-            const bool descending = (((r * 64 + lane) & size) == 0);
-            const bool first = (lane & stride) == 0;  // the earlier place of the pair
-            const int hi = key[r] > other ? key[r] : other, lo = key[r] > other ? other : key[r];
-            key[r] = (first == descending) ? hi : lo;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kKeysPerLane; ++r)
-      if (key[r] >= 0) items[tail_x + r * 64 + lane] = s_tail[kTailSort - 1 - (key[r] & (kTailSort - 1))];
+  for (int i = 0; i < kShare; i += 4) {
+    const int4 others = *reinterpret_cast<const int4*>(s_key + part * kShare + i);
+    place += (others.x > key ? 1 : 0) + (others.y > key ? 1 : 0) + (others.z > key ? 1 : 0) + (others.w > key ? 1 : 0);
   }
+  place = sum_of_eight(place);
+  if (key >= 0 && part == 0) items[tail_x + place] = s_tail[counted];
+#endif  // __HIP_DEVICE_COMPILE__
 }
 
 }  // namespace hydra

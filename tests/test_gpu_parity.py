@@ -585,3 +585,44 @@ def test_numbers_of_the_wrong_kind():
     hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, 40.0, 1, str(w.softmax_scale), out, ws)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+
+
+def _work_list(lengths, hq, hkv, d, causal):
+    """The work list as csrc/worklist.hpp describes it: entries (first token, length, first wave tile, KV head) of the eight queues."""
+    group = hq // hkv
+    starts = np.concatenate([[0], np.cumsum(lengths)])
+    order = sorted(range(len(lengths)), key=lambda b: (-lengths[b], b))
+    queues = [[] for _ in range(8)]
+    for r in range(len(lengths) * hkv):
+        b, head, row, at = order[r // hkv], r % hkv, r // 8, r % 8
+        tiles = -(-lengths[b] // 32) * group
+        n = -(-tiles // 4)
+        for j in range(n):
+            i = n - 1 - j if causal else j
+            keys = (min(4 * i + 3, tiles - 1) // group + 1) * 32 if causal else lengths[b]
+            queues[7 - at if row & 1 else at].append((-(-min(keys, lengths[b]) // 64), (int(starts[b]), lengths[b], 4 * i, head)))
+    tail = min(128, (3 << 20) // (128 * d * 4 // group))
+    return [[e for _, e in q[:-tail]] + [e for _, e in sorted(q[-tail:], key=lambda x: -x[0])] for q in queues]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,causal", [(1, 28, 4, 128, True), (3, 4, 4, 64, False), (64, 7, 1, 128, True), (127, 8, 2, 64, True),
+                                                   (128, 2, 2, 80, False), (129, 4, 1, 64, True), (512, 2, 1, 64, True), (513, 1, 1, 64, False)])
+def test_work_list(batch, hq, hkv, d, causal):
+    """Entry for entry, at both ends of every way of ranking the sequences, with equal and empty ones among them."""
+    import paper_2505_12658_amd as hydra
+
+    rng = np.random.default_rng(batch)
+    lengths = [int(x) for x in rng.integers(0, 700, size=batch)]
+    for i in range(0, batch - 1, 3):
+        lengths[i] = lengths[i + 1]
+    lengths[-1] = max(lengths[-1], 1)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32, device="cuda:0")
+    ws = hydra.hydra_attn_build_worklist(cu, sum(lengths), max(lengths), hq, hkv, d, causal)
+    torch.cuda.synchronize()
+    words = ws.cpu().numpy()[: ws.numel() // 4 * 4].view(np.int32)
+    want = _work_list(lengths, hq, hkv, d, causal)
+    assert words[0] == sum(len(q) for q in want)
+    assert words[1:10].tolist() == np.concatenate([[0], np.cumsum([len(q) for q in want])]).tolist()
+    at = (128 + 8 * 128 + 4 * batch + 32 * -(-batch * hkv // 8) + 15) // 16 * 4
+    got = words[at : at + 4 * words[0]].reshape(-1, 4).tolist()
+    assert got == [list(e) for q in want for e in q]
