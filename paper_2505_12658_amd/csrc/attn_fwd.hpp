@@ -50,9 +50,10 @@ struct TileGeom : RowGeom<D> {
   // D = 80: the third 32-column block of P V has 16 columns to spare.  The lanes that feed them read bf16 ones
   // from a constant area instead of the V tile, so the matrix unit delivers the softmax row sums in output
   // columns 80..95 and the vector unit does not have to add them up (16 additions per key block and wave).
-  // The area covers every offset a V fragment read adds to its lane address (ring slot, key block, step).
+  // The area covers every offset a V fragment read adds to its lane address (key block, step); the two ring slots have an
+  // address register each for that block, so that the area is one tile long and three workgroups fit a compute unit's LDS.
   static constexpr bool kSumsFromMatrixUnit = D == 80;
-  static constexpr int kOnesBytes = kSumsFromMatrixUnit ? (kRing - 1) * kTileBytes + 9 * 1024 : 0;
+  static constexpr int kOnesBytes = kSumsFromMatrixUnit ? 9 * 1024 : 0;
   static constexpr int kOnesAt = 2 * kRing * kTileBytes + 64;    // (+ slack behind the last V tile)
   static constexpr int kLdsBytes = kOnesAt + kOnesBytes;
 };
@@ -302,7 +303,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // head}, posted by the waves that noticed, acted upon by the whole workgroup at the top of its next round.
   if (threadIdx.x == 0) s_redo[0] = 0;
   if constexpr (G::kSumsFromMatrixUnit) {
-    static_assert((R - 1) * G::kTileBytes + kKvTileRows * ROWB - 8 * ROWB + 8 <= G::kOnesBytes, "a V fragment read stays inside the ones");
+    static_assert(kKvTileRows * ROWB - 8 * ROWB + 8 <= G::kOnesBytes, "a V fragment read stays inside the ones");
     for (int i = threadIdx.x * 16; i < G::kOnesBytes; i += 256 * 16)
       *reinterpret_cast<u32x4_t*>(HYDRA_LDS_BYTE(k_ring + G::kOnesAt + i)) = u32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
   }
@@ -504,6 +505,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // LDS read addresses: lane part + ring slot of the iteration's K tile / V tile; the key block
   // inside the tile and the step are immediates.  Advanced once per iteration.
   uint32_t k_addr[KS], v_addr[CC];
+  uint32_t v_last1 = 0;  // kSumsFromMatrixUnit: the last block's address for ring slot 1 (v_addr: slot 0)
   const uint32_t lds_base = k_ring;
 #pragma unroll
   for (int s = 0; s < KS; ++s) k_addr[s] = lds_base + m * ROWB + k_swizzle<D>(m, KS * hf + s) * 16;  // K tile 0
@@ -515,7 +517,8 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
       v_addr[cc] = lds_base + R * G::kTileBytes + r * ROWB + v_swizzle<D>(r, chunk) * 16 + 8 * (sl & 1);  // V ring, slot 0
     }
     if constexpr (G::kSumsFromMatrixUnit) {
-      // columns 80..95 (the upper 16 of the last block): ones (the area is long enough for either ring slot)
+      // columns 80..95 (the upper 16 of the last block): ones, whichever ring slot is read
+      v_last1 = grp == 1 ? lds_base + G::kOnesAt : v_addr[CC - 1] + G::kTileBytes;
       if (grp == 1) v_addr[CC - 1] = lds_base + G::kOnesAt;
     }
   }
@@ -529,7 +532,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
 #pragma unroll
     for (int s = 0; s < KS; ++s) k_addr[s] += dk;
 #pragma unroll
-    for (int cc = 0; cc < CC; ++cc) v_addr[cc] += dv;
+    for (int cc = 0; cc < CC; ++cc) v_addr[cc] += G::kSumsFromMatrixUnit && cc == CC - 1 && grp == 1 ? 0 : dv;
     k_pos = k_new;
     v_pos = v_new;
   };
@@ -563,7 +566,8 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // PV unit u = (s2, cc): the V^T fragment of 16 keys x 32 columns
   auto load_v_frag = [&](int rb, int u, int voff) -> bf16x8_t {
     const int cc = u % CC, s2 = u / CC;
-    const uint32_t at = v_addr[cc] + voff + rb * kKeyBlock * ROWB + s2 * 16 * ROWB;
+    const uint32_t tile = G::kSumsFromMatrixUnit && cc == CC - 1 ? (voff == 0 ? v_addr[cc] : v_last1) : v_addr[cc] + voff;
+    const uint32_t at = tile + rb * kKeyBlock * ROWB + s2 * 16 * ROWB;
     const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)HYDRA_LDS_BYTE(at));
     const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)HYDRA_LDS_BYTE(at + 8 * ROWB));
     typedef __attribute__((ext_vector_type(8))) short s16x8_t;
@@ -1013,7 +1017,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroups
 // Batches of a few items per workgroup slot run with one workgroup per item, dealt out by the hardware as slots fall
 // free, instead of persistent workgroups that claim: at so few rounds the claims, their start and their end cost more
 // than loading the next item's Q ahead wins (7 LLaVA requests, 3 rounds: 85.0 -> 78.3 us; at 6 rounds the two are
-// level, at 13 persistent workgroups win by 2 %).
+// level, at 13 persistent workgroups win by 2 %).  At head_dim 80, where three of these workgroups fit a compute unit and only
+// two persistent ones, this form is the faster one at every size.
 // The item comes from the work list when there is one.  Without one (the call that would have to build it first), and
 // for at most kDirectSeqs sequences, every wave works its workgroup's item out from cu_seqlens, one round trip to memory
 // and some 300 instructions, about 1.3 us per workgroup against a prepass of 5 - 8 us.
@@ -1159,7 +1164,7 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
 #endif  // __HIP_DEVICE_COMPILE__
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroupsPerCu<D>, kWorkgroupsPerCu<D>))) void attn_fwd_direct_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kDirectPerCu<D>, kDirectPerCu<D>))) void attn_fwd_direct_kernel(
     const AttnArgs a, const int batch, const int n_kv_heads) {  // batch 0: the item comes from the work list
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D>::kLdsBytes];

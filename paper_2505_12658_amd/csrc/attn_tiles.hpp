@@ -33,6 +33,13 @@ constexpr int kWavesPerItem = 4;   // wave tiles per work-list item
 template <int D>
 constexpr int kWorkgroupsPerCu = D == 64 ? 3 : 2;
 
+// The same where every workgroup has one item (attn_fwd_direct_kernel), which needs fewer registers than the persistent form,
+// whose cold branch spills when it is held to a third of the register file.  At head_dim 80 the loop fits 168 registers and 50 KB
+// of LDS: three waves per SIMD instead of two, bit-identical results, 16 heads of 80, us: 65 536 tokens in images of 256 .. 4096
+// 856 -> 793, 25 000 296 -> 272, 12 000 122.6 -> 115.0, 6 000 81.8 -> 75.1, 2 500 and fewer (one item per compute unit) equal.
+template <int D>
+constexpr int kDirectPerCu = D <= 80 ? 3 : 2;
+
 // One work-list entry, written by the device prepass from cu_seqlens; it carries everything the
 // kernel needs, so a workgroup starts its loads after a single dependent read.
 //   x = first packed token of the sequence, y = sequence length (0: empty entry past the end of

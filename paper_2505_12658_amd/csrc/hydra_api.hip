@@ -84,8 +84,12 @@ hipError_t launch_attn(bool causal, const hydra::AttnArgs& args, unsigned comput
 // rounds) 71 -> 63 (66); 8 LLaVA requests (3 rounds) 102.6 -> 96.1 (95.4).
 constexpr size_t kDirectRounds = 6, kListFreeRounds = 4;
 bool within_rounds(size_t rounds, int32_t head_dim, size_t capacity, unsigned compute_units) {
-  const unsigned per_cu = head_dim == 64 ? hydra::kWorkgroupsPerCu<64> : head_dim == 80 ? hydra::kWorkgroupsPerCu<80> : hydra::kWorkgroupsPerCu<128>;
+  const unsigned per_cu = head_dim == 64 ? hydra::kDirectPerCu<64> : head_dim == 80 ? hydra::kDirectPerCu<80> : hydra::kDirectPerCu<128>;
   return capacity <= rounds * per_cu * compute_units;
+}
+// (head_dim 80 at any size: see kDirectPerCu; up to a million items, since a launch has fewer than 2^32 threads)
+bool direct_form(int32_t head_dim, size_t capacity, unsigned compute_units) {
+  return within_rounds(kDirectRounds, head_dim, capacity, compute_units) || (head_dim == 80 && capacity <= (size_t)1 << 20);
 }
 bool list_free(int32_t batch, int32_t head_dim, size_t capacity, unsigned compute_units) {
   return batch <= hydra::kDirectSeqs && within_rounds(kListFreeRounds, head_dim, capacity, compute_units);
@@ -326,7 +330,7 @@ int launch_packed(const void* q, const void* k, const void* v, void* out, int64_
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
-  if (workgroups_per_cu == 0 && (!with_list || within_rounds(kDirectRounds, head_dim, lay.capacity, cus))) {
+  if (workgroups_per_cu == 0 && (!with_list || direct_form(head_dim, lay.capacity, cus))) {
     const int32_t seqs = with_list ? 0 : batch;
     switch (head_dim) {
       case 64: err = launch_direct<64>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;

@@ -317,6 +317,7 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
     ([558], 28, 4, 128),             # queues of 32 items on four dies: every die does its own
     ([4096], 1, 1, 64),              # 32 items of one pair, and 33
     ([4097], 1, 1, 64),
+    ([20] * 700, 8, 8, 80),          # 5600 items: more rounds than other head dimensions do with a workgroup per item
 ])
 def test_items_are_handed_out_whole_for_any_bound(lengths, hq, hkv, d):
     """Batches whose (sequence, KV head) pairs do not spread evenly over the dies, with an exact, a loose and an understated
