@@ -279,6 +279,9 @@ def test_worklist_covers_every_tile_once_and_ends_with_cheap_items(hq, hkv, d, c
     ([100] * 65, 2, 2, 64, False),                               # one sequence too many: the work list
     ([0, 70, 0, 70, 33, 0], 8, 2, 80, True),                     # empty sequences in between
     ([64] * 24, 14, 2, 128, True),                               # equal lengths (not ranked)
+    ([33] * 37, 5, 5, 64, False),                                # the same, with one pair in the last row
+    ([300] * 11, 7, 1, 128, True),                               # 18 items for every pair, three pairs in the last row
+    ([1] * 64, 3, 1, 128, True),
     ([900, 1, 1, 32, 700, 33], 7, 1, 128, True),                 # one KV head: one pair per die and row
 ])
 def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
