@@ -244,9 +244,11 @@ using NextRB = std::integral_constant<int, N>;  // key block the following step 
 
 // LDS fragments are requested this many work units (one K or V^T fragment and the matrix instructions it feeds)
 // ahead of their use.  Each unit of distance keeps one more K and one more V^T fragment (8 registers) in flight.
-// (A distance of three was measured at head_dim 80 and 128, which have the registers: no faster.)
+// Two at head_dim 128, where two waves share a SIMD (three: no faster; one: 558 tokens 14.8 -> 15.1 us, larger batches level).
+// One where three waves do, which cover the LDS latency for each other: 16 heads of 80, 65 536 tokens in images of 256 .. 4096
+// 796 -> 791 us, 32 images of 577 tokens with 16 heads of 64 62.6 -> 62.3, one image equal.
 template <int D>
-constexpr int kFragsAhead = 2;
+constexpr int kFragsAhead = D <= 80 ? 1 : 2;
 
 #if defined(__HIP_DEVICE_COMPILE__)
 // LDS fragments of the first PF QK units and the first PF PV units of a pipeline step.
