@@ -111,10 +111,13 @@ struct DecodeWave {
     kv_len = kv_len_;
     block_shift = block_shift_;
     last_block = num_blocks - 1;
-    row_max = kLowest;
-    row_sum = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) q[s] = *reinterpret_cast<const bf16x8_t*>(q_row + (4 * s + h) * 8);
+    restart();
+  }
+  __device__ __forceinline__ void restart() {  // before the first key of a stream
+    row_max = kLowest;
+    row_sum = 0.f;
 #pragma unroll
     for (int u = 0; u < CW; ++u) o[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
@@ -216,16 +219,21 @@ struct DecodeWave {
 };
 
 // One workgroup's share of one (request, KV head): all of it, its output included, when the context fits one share,
-// otherwise a partial result for the combine kernel.  Called by all n_waves waves; lds: n_waves * kDecodeLdsPerWave<D>
-// bytes, 16-byte aligned.  Does nothing for a request that has no new tokens or more than kDecodeRows rows.
-template <int D>
-__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int b, int kv_head, int q_start, int q_len, int kv_len, int split) {
+// otherwise a partial result for the combine kernel.  Called by all n_waves waves; lds: kDecodeLdsPerWave<D> bytes per wave
+// (PER_WAVE 2: twice as many), 16-byte aligned.  Does nothing for a request that has no new tokens or more than kDecodeRows rows.
+// The keys of a share are dealt out to n_streams streams, block by block, each with a running maximum, a sum and an output of
+// its own until the merge: so the number of streams is part of the result.  It is n_waves, or with PER_WAVE 2 also twice that:
+// a wave then walks its first stream and goes on with its second one, whose first block is in flight by then.
+template <int D, int PER_WAVE = 1>
+__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int n_streams, int b, int kv_head, int q_start, int q_len, int kv_len,
+                                           int split) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, h = lane >> 4;
   float* s_max = lds;
-  float* s_sum = s_max + n_waves * kDecodeRows;
-  float* s_slots = s_sum + n_waves * kDecodeRows;
+  float* s_sum = s_max + PER_WAVE * n_waves * kDecodeRows;
+  float* s_slots = s_sum + PER_WAVE * n_waves * kDecodeRows;
+  const bool two = PER_WAVE == 2 && n_streams > n_waves;  // (else as with PER_WAVE 1)
 
   if (kv_len <= 0) return;
   const int n_halves = (kv_len + kDecodeKeys - 1) / kDecodeKeys;
@@ -239,8 +247,15 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   // table cannot make the loads leave it; entries past the context are not read.
   const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
   const int last_entry = (kv_len - 1) >> a.block_shift;
+  auto steps_of = [&](int stream) { return begin + stream < end ? (end - begin - stream + n_streams - 1) / n_streams : 0; };
+  const int steps0 = steps_of(wave), steps = two ? steps0 + steps_of(wave + n_waves) : steps0;  // of the first stream, of all
+  auto key_of = [&](int i) {
+    int block = wave + n_streams * i;
+    if (PER_WAVE == 2 && two && i >= steps0) block = wave + n_waves + n_streams * (i - steps0);
+    return (begin + block) * kDecodeKeys;
+  };
   auto entries = [&](int first_step) {
-    const int key = (begin + wave + n_waves * (first_step + (lane >> 1))) * kDecodeKeys + 16 * (lane & 1);
+    const int key = key_of(first_step + (lane >> 1)) + 16 * (lane & 1);
     int e = key >> a.block_shift;
     return table[e < last_entry ? e : last_entry];
   };
@@ -256,12 +271,29 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   const int lim = kv_len - q_len + token;  // largest visible key
   const float c = a.scale_log2;
 
-  const int steps = begin + wave < end ? (end - begin - wave + n_waves - 1) / n_waves : 0;
   DecodeWave<D> w;
   w.init(a.k_cache, a.v_cache, a.n_kv_heads, kv_head, kv_len, a.block_shift, a.num_blocks, a.q + (int64_t)(q_start + token) * a.q_stride + head * D, c,
-         (uint32_t)(uintptr_t)HYDRA_LDS_PTR(s_slots + wave * kDecodeSlotFloats<D>), lane);
+         (uint32_t)(uintptr_t)HYDRA_LDS_PTR(s_slots + (wave + (PER_WAVE - 1) * n_waves) * kDecodeSlotFloats<D>), lane);
+  // A stream's rows' maximum, sum and unnormalised output, for the merge.  (The wave's stage of K is the last slot it writes.)
+  constexpr int RF = kDecodeRowFloats<D>;
+  constexpr int CW = DecodeWave<D>::CW;
+  auto leave = [&](int stream) {
+    const float total_own = over_row_lanes(w.row_sum, [](float x, float y) { return x + y; });
+    if (h == 0) {
+      s_max[stream * kDecodeRows + m] = w.row_max;
+      s_sum[stream * kDecodeRows + m] = total_own;
+    }
+    if (m < n_rows) {
+      float* mine = s_slots + stream * kDecodeSlotFloats<D> + m * RF;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < CW; u += 4)  // columns (4 h + r) CW + u ..
+          *reinterpret_cast<f32x4_t*>(mine + (4 * h + r) * CW + u) = f32x4_t{w.o[u][r], w.o[u + 1][r], w.o[u + 2][r], w.o[u + 3][r]};
+    }
+  };
+  if (PER_WAVE == 2 && two && steps0 == 0) leave(wave);
   if (steps > 0) {
-    auto key_of = [&](int i) { return (begin + wave + n_waves * i) * kDecodeKeys; };
     auto in_cache = [&](int id) { return id < 0 ? 0 : (id > w.last_block ? w.last_block : id); };
     auto id_of = [&](int i, int half) { return __builtin_amdgcn_readlane(ids, 2 * (i & 31) + half); };
     ids = in_cache(ids);
@@ -286,42 +318,47 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
       __builtin_amdgcn_sched_barrier(0);
       w.load_v(0, b0, next);
       w.load_v(1, b1, next + 16);
+      if (PER_WAVE == 2 && two && i + 1 == steps0) {
+        __builtin_amdgcn_sched_barrier(0);
+        leave(wave);
+        w.restart();
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
 
-  // ---- merge: every wave leaves its rows' maximum, sum and unnormalised output ----
-  constexpr int RF = kDecodeRowFloats<D>;
-  constexpr int CW = DecodeWave<D>::CW;
+  // ---- merge ----
   __builtin_amdgcn_sched_barrier(0);
-  const float total_own = over_row_lanes(w.row_sum, [](float x, float y) { return x + y; });
-  if (h == 0) {
-    s_max[wave * kDecodeRows + m] = w.row_max;
-    s_sum[wave * kDecodeRows + m] = total_own;
-  }
-  if (m < n_rows) {
-    float* mine = s_slots + wave * kDecodeSlotFloats<D> + m * RF;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int u = 0; u < CW; u += 4)  // columns (4 h + r) CW + u ..
-        *reinterpret_cast<f32x4_t*>(mine + (4 * h + r) * CW + u) = f32x4_t{w.o[u][r], w.o[u + 1][r], w.o[u + 2][r], w.o[u + 3][r]};
-  }
+  leave(two ? wave + n_waves : wave);
   __syncthreads();
   const bool whole = n_shares == 1;  // the context is one share: this workgroup writes the output
   constexpr int kCols = D / 4;
   for (int i = threadIdx.x; i < n_rows * kCols; i += 64 * n_waves) {
     const int r = i / kCols, col = (i - r * kCols) * 4;
+    // (four streams at a time, so that their reads are in flight together; there are four or eight)
     float top = s_max[r];
-    for (int o = 1; o < n_waves; ++o) top = fmaxf(top, s_max[o * kDecodeRows + r]);
+    for (int o = 0; o < n_streams; o += 4)
+#pragma unroll
+      for (int e = o; e < o + 4; ++e) top = fmaxf(top, s_max[e * kDecodeRows + r]);
     float total = 0.f;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int o = 0; o < n_waves; ++o) {
-      // (a wave that saw no key of this row still holds the initial maximum: weight 0)
-      const float weight = fast_exp2((s_max[o * kDecodeRows + r] - top) * c);
-      total += weight * s_sum[o * kDecodeRows + r];
-      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(s_slots + o * kDecodeSlotFloats<D> + r * RF + col);
+    for (int o = 0; o < n_streams; o += 4) {
+      float own_top[4], own_sum[4];
+      f32x4_t v[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += weight * v[e];
+      for (int e = 0; e < 4; ++e) {
+        own_top[e] = s_max[(o + e) * kDecodeRows + r];
+        own_sum[e] = s_sum[(o + e) * kDecodeRows + r];
+        v[e] = *reinterpret_cast<const f32x4_t*>(s_slots + (o + e) * kDecodeSlotFloats<D> + r * RF + col);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        // (a stream that saw no key of this row still holds the initial maximum: weight 0)
+        const float weight = fast_exp2((own_top[e] - top) * c);
+        total += weight * own_sum[e];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[x] += weight * v[e][x];
+      }
     }
     if (whole) {
       const int tok = r / a.group, hd = kv_head * a.group + (r - tok * a.group);
@@ -418,36 +455,41 @@ constexpr int kDecodeMinBlock = 16;
 // Waves per SIMD the kernel is built for (168 registers each).
 constexpr int kDecodeWavesPerSimd = 3;
 constexpr int kDecodeWaves = 4;        // waves of a workgroup: enough to keep a compute unit's memory path full
-constexpr int kDecodeMaxWaves = 8;     // the most: a unit then holds one workgroup at a time
-constexpr int kDecodeLongKeys = 768;   // a block table from which on a launch may ask for them
+constexpr int kDecodeMaxStreams = 8;   // as many waves: a unit then holds one workgroup at a time
 constexpr int kDecodeWideTable = 4096; // keys in a row of the block table from which on the kernel looks for that
 
 // Batches of more pairs than compute units are taken in the order of their contexts: units are then level, whatever the order
 // of the requests in the batch, and no long context starts behind another one.  The first 256 workgroups, which the hardware
 // deals out one to a unit, take the 256 longest pairs from the shortest of them up, the ones behind them the others from the
 // longest down: so the second pair of a unit is the longer the shorter its first one is, and the very longest have a unit
-// for themselves.  us, in the order of the batch (with eight waves, see below) and so, 28 / 4 heads of 128: 96 requests of
-// 128 .. 1782 tokens 37.2 -> 29.5 (longest first from both ends 32), 125 44.1 -> 32, 80 33.9 -> 27.4, 70 of 900 .. 1800
-// 43.2 -> 34.6, 200 of 128 .. 1800 65.8 -> 50, 100 of 40 .. 407 12.1 -> 10.1; 32 / 32 heads: 14 of 300 .. 2000 50.8 -> 41.9, 33 of
-// 600 .. 1100 77.7 -> 76.8, 9 of 300 .. 3000, which the longest context holds up either way, 45.9 -> 46.6.
+// for themselves.  us, in the order of the batch and so (the same bits), 28 / 4 heads of 128: 96 requests of 128 .. 1800 tokens
+// 39.4 -> 31.8, 125 43.4 -> 33.6, 80 31.6 -> 28.2, 70 of 900 .. 1800 44.3 -> 37.4, 200 of 128 .. 1800 60.9 -> 46.9, 100 of 40 .. 407
+// 12.8 -> 10.3; 32 / 32 heads: 14 of 300 .. 2000 43.7 -> 36.4, 33 of 600 .. 1100 equal, 9 of 300 .. 3000, which the longest context
+// holds up either way, 34.5 -> 35.0.
 // Not where no context has more than kOrderedKeys (the search costs what the order gains: 300 of 30 .. 200 tokens 14.4 -> 15.5),
 // and the batch has to fit four registers of a wave's lanes (eight: 500 of 20 .. 100 under a wide table 15.7 -> 17.0, without a search).
 constexpr int kOrderedMost = 256;  // requests
 inline bool decode_ordered(int64_t pairs, int n_splits, int batch, int64_t table_keys) {
   return pairs > kUnits && n_splits == 1 && batch <= kOrderedMost && table_keys > kOrderedKeys;
 }
-// Eight waves are for one to two long pairs per unit: a unit that is done early then takes one of the remaining pairs.
-//   - In the order of the batch they are worth it throughout (96 requests of 128 .. 1782 tokens 39.7 -> 35.7 us with four heads).
-//   - Ordered, only where the second pairs are nearly as many as the first ones: 128 requests of 128 .. 1800 tokens 33.9 -> 32.2
-//     us, 120 31.9 -> 31.7, 110 30.9 -> 31.1, 96 29.6 -> 29.9, 66 24.8 -> 25.6.
-constexpr int kDecodeManyPairs = 464;
-inline int decode_waves(int64_t pairs, int n_splits, int64_t table_keys, bool ordered) {
-  return pairs > (ordered ? kDecodeManyPairs - 1 : kUnits) && pairs <= 2 * kUnits && n_splits == 1 && table_keys >= kDecodeLongKeys ? kDecodeMaxWaves : kDecodeWaves;
+// Long contexts of one to two pairs per unit are dealt out to eight streams, others to four.  The number says how the sums are
+// put together (run_decode), so it follows from the batch alone and not from the order it is taken in.
+constexpr int kDecodeLongKeys = 768;   // a block table from which on contexts count as long
+inline int decode_streams(int64_t pairs, int n_splits, int64_t table_keys) {
+  return pairs > kUnits && pairs <= 2 * kUnits && n_splits == 1 && table_keys >= kDecodeLongKeys ? kDecodeMaxStreams : kDecodeWaves;
 }
+// Eight streams are eight waves where a unit should hold one pair at a time, so that one that is done early takes one of the
+// remaining pairs.  In the order of the batch that is everywhere (96 requests of 128 .. 1782 tokens 35.7 us, 39.7 with four waves
+// and four streams), in the order of the contexts where the second pairs are nearly as many as the first ones.  Otherwise four
+// waves have two streams each, and two pairs share a unit.  us, eight waves and four, 28 / 4 heads of 128: 96 of 360 .. 900 23.0 and
+// 21.4, 80 of 1000 .. 1099 36.3 and 34.8, 70 of 900 .. 1800 38.6 and 37.4, 96 of 128 .. 1800 31.5 and 31.8; from 464 pairs on: 116 of
+// 90 .. 900 16.5 and 17.4, 128 of 200 .. 2000 36.1 and 38.8, of 630 .. 900 33.9 and 32.9.
+constexpr int kDecodeManyPairs = 464;
+inline int decode_waves(int64_t pairs, int streams, bool ordered) { return ordered && pairs < kDecodeManyPairs ? kDecodeWaves : streams; }
 
 // grid = batch * n_kv_heads * n_splits workgroups, share-major (the first shares of all pairs, which every request
-// has, then the second shares, ...); dynamic LDS: WAVES * kDecodeLdsPerWave<D> bytes.
-template <int D, bool ORDERED, int WAVES>
+// has, then the second shares, ...); dynamic LDS: STREAMS * kDecodeLdsPerWave<D> bytes.
+template <int D, bool ORDERED, int WAVES, int STREAMS>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd, kDecodeWavesPerSimd))) void attn_decode_kernel(
     const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -472,22 +514,21 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDec
       q_start = cu[b];
       q_end = cu[b + 1];
     }
-  } else if (WAVES > kDecodeWaves && kv_len < kDecodeShortKeys && table_keys >= kDecodeWideTable) {
+    any_long = any_long || keys < kDecodeWideTable;
+  } else if (STREAMS > kDecodeWaves && kv_len < kDecodeShortKeys && table_keys >= kDecodeWideTable) {
     any_long = false;
     for (int r = (int)threadIdx.x & 63; r < a.batch; r += 64) any_long = any_long || a.kv_lens[r] >= kDecodeShortKeys;
     any_long = __builtin_amdgcn_ballot_w64(any_long) != 0;
   }
-  // Eight waves are for long contexts, and the host knows only that the table allows them: in a batch without one, half of
-  // the waves leave, and the unit has room for a second workgroup (300 requests of at most 407 tokens under a table of
-  // 32 768 keys, one KV head).  In the order of the batch only workgroups of short contexts look for a long one, and only
-  // where the table could be wider than the contexts (125 of 128 .. 1800 tokens under a tight one 42.4 us, looking 43.2).
-  int waves = WAVES;
-  if (WAVES > kDecodeWaves && !any_long) {
-    waves = kDecodeWaves;
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= kDecodeWaves) return;
-  }
+  // Eight streams are for long contexts, and the host knows only that the table allows them: a batch without one has four, and
+  // where there are eight waves half of them leave, and the unit has room for a second workgroup (300 requests of at most 407
+  // tokens under a table of 32 768 keys, one KV head).  In the order of the batch only workgroups of short contexts look for a
+  // long one, and in either order only a table that could be wider than the contexts counts for nothing (125 of 128 .. 1800
+  // tokens under a tight one 42.4 us, looking 43.2).
+  const int streams = STREAMS > kDecodeWaves && !any_long ? kDecodeWaves : STREAMS;
+  if (WAVES > streams && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= streams) return;
   if (kv_len > table_keys) kv_len = (int)table_keys;
-  run_decode<D>(a, s_decode, waves, b, kv_head, q_start, q_end - q_start, kv_len, split);
+  run_decode<D, STREAMS / WAVES>(a, s_decode, WAVES < streams ? WAVES : streams, streams, b, kv_head, q_start, q_end - q_start, kv_len, split);
 #else
   (void)a;
 #endif

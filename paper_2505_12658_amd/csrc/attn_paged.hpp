@@ -954,7 +954,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (f0 < 0) {
     if constexpr (kDecodeForm<D>) {
       if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
-        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, b, kv_head, q_start, q_len, kv_len, split);
+        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, kWavesPerGroup, b, kv_head, q_start, q_len, kv_len, split);
         return;
       }
     }

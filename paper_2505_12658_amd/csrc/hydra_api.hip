@@ -168,12 +168,13 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, u
     if (decode_only) {
       const int64_t keys = (int64_t)args.max_blocks_per_seq << args.block_shift;
       const bool ordered = hydra::paged::decode_ordered(rows_wgs, args.n_splits, args.batch, keys);
-      using hydra::paged::kDecodeMaxWaves, hydra::paged::kDecodeWaves, hydra::paged::attn_decode_kernel;
-      const bool eight = hydra::paged::decode_waves(rows_wgs, args.n_splits, keys, ordered) == kDecodeMaxWaves;
-      const int waves = eight ? kDecodeMaxWaves : kDecodeWaves;
-      err = launch_lds(ordered ? (eight ? attn_decode_kernel<D, true, kDecodeMaxWaves> : attn_decode_kernel<D, true, kDecodeWaves>)
-                               : (eight ? attn_decode_kernel<D, false, kDecodeMaxWaves> : attn_decode_kernel<D, false, kDecodeWaves>),
-                       dim3(rows_wgs), dim3(64 * waves), waves * hydra::paged::kDecodeLdsPerWave<D>, s, args);
+      using hydra::paged::kDecodeMaxStreams, hydra::paged::kDecodeWaves, hydra::paged::attn_decode_kernel;
+      constexpr int kFour = kDecodeWaves, kEight = kDecodeMaxStreams;
+      const int streams = hydra::paged::decode_streams(rows_wgs, args.n_splits, keys), waves = hydra::paged::decode_waves(rows_wgs, streams, ordered);
+      void (*kernel)(hydra::paged::PagedArgs) = attn_decode_kernel<D, false, kFour, kFour>;
+      if (ordered) kernel = streams == kFour ? attn_decode_kernel<D, true, kFour, kFour> : waves == kFour ? attn_decode_kernel<D, true, kFour, kEight> : attn_decode_kernel<D, true, kEight, kEight>;
+      else if (streams == kEight) kernel = attn_decode_kernel<D, false, kEight, kEight>;
+      err = launch_lds(kernel, dim3(rows_wgs), dim3(64 * waves), streams * hydra::paged::kDecodeLdsPerWave<D>, s, args);
       launched = true;
     }
   }

@@ -345,7 +345,7 @@ ORDERED_CASES = [
 @pytest.mark.parametrize("case", ORDERED_CASES, ids=lambda c: f"n{c[0]}-k{c[1]}-d{c[2]}-t{c[4]}-{c[3](1)}")
 def test_pairs_in_the_order_of_their_contexts(case):
     """Decode batches of more (request, KV head) pairs than compute units, whose workgroups find their pair by the rank of its
-    context: every row is there, against the oracle, and (where both launches have four waves per workgroup) with the bits of
+    context: every row is there, against the oracle, and (where both launches deal the keys out to four streams) with the bits of
     the same requests in batches too small to be ordered."""
     n, hkv, d, context, table_keys = case
     kv_lens = [context(i) for i in range(n)]
@@ -358,14 +358,56 @@ def test_pairs_in_the_order_of_their_contexts(case):
     out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
     _run_gpu(h, q, kc, vc, tables, out=out)
     _check(out, _want(h, q, kc, vc, tables))
-    if 464 <= n * hkv <= 512 or n == 257:
-        return
+    keys = 16 * tables.shape[1]
+    if (256 < n * hkv <= 512 and keys >= 768 and not (keys >= 4096 and max(kv_lens) < 512)) or n == 257:
+        return  # eight streams: test_bits_of_a_decode_batch_whatever_its_order
     size = 256 // hkv
     for at in range(0, n, size):
         part = si.HybridBatch("part", h.q_lens[at:at + size], kv_lens[at:at + size], 2 * hkv, hkv, d, block_size=16)
         rows = slice(int(h.cu_seqlens_q[at]), int(h.cu_seqlens_q[at]) + part.total_q)
         alone = _run_gpu(part, q[rows], kc, vc, np.ascontiguousarray(tables[at:at + size]), use_workspace=False)
         assert torch.equal(alone.view(torch.int16), out[rows].view(torch.int16))
+
+
+STREAM_CASES = [
+    # requests, KV heads, d, contexts, table keys: 257 to 512 pairs, at most 256 requests
+    (65, 4, 128, lambda i: 900 - 11 * i, 0),                                  # four waves with two streams each
+    (86, 3, 64, lambda i: (0, 1, 31, 33, 128, 129, 256, 257, 1000)[i % 9], 0),  # streams of no, one and many blocks
+    (80, 4, 128, lambda i: 1000 + i % 100, 0),                                # near enough to each other to stay in batch order
+    (33, 14, 64, lambda i: 700 + 97 * i % 800, 0),                            # 462 pairs
+    (116, 4, 64, lambda i: 40 + 50 * (i % 23), 0),                            # 464 pairs: eight waves
+    (256, 2, 64, lambda i: 1 + 131 * i % 777, 0),                             # 512 pairs
+    (128, 3, 128, lambda i: 1 + 37 * i % 511, 1024),                          # a table wider than any context
+    (128, 3, 64, lambda i: 1 + 37 * i % 511, 4096),                           # and one so wide that short contexts have four streams
+    (128, 3, 64, lambda i: 512 if i == 77 else 1 + 37 * i % 511, 4096),       # one context too long for that
+]
+
+
+@pytest.mark.parametrize("case", STREAM_CASES, ids=lambda c: f"n{c[0]}-k{c[1]}-d{c[2]}-t{c[4]}-{c[3](1)}-{c[3](77)}")
+def test_bits_of_a_decode_batch_whatever_its_order(case):
+    """How the keys of a context are dealt out to partial sums is settled by the number of pairs and the lengths, not by the
+    order the pairs are taken in: the KV heads of a batch one after the other, as that many requests of one KV head (too many
+    to be ordered), give the same bits."""
+    n, hkv, d, context, table_keys = case
+    kv_lens = [context(i) for i in range(n)]
+    q_lens = [1 if k else 0 for k in kv_lens]
+    h = si.HybridBatch("heads", q_lens, kv_lens, 2 * hkv, hkv, d, block_size=16, seed=n + hkv)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    if table_keys:
+        wide = np.full((n, table_keys // 16), -1, dtype=np.int32)
+        wide[:, : tables.shape[1]] = tables
+        tables = wide
+    out = _run_gpu(h, q, kc, vc, tables)
+    _check(out, _want(h, q, kc, vc, tables))
+    blocks = kc.shape[0]
+    one = si.HybridBatch("requests", q_lens * hkv, kv_lens * hkv, 2, 1, d, block_size=16)
+
+    def by_head(t, heads):  # [.., heads of every KV head, d] -> one KV head after the other along the first dimension
+        return torch.cat([t[..., g * heads:(g + 1) * heads, :] for g in range(hkv)]).contiguous()
+
+    tables_one = np.concatenate([np.where(tables >= 0, tables + g * blocks, -1) for g in range(hkv)]).astype(np.int32)
+    got = _run_gpu(one, by_head(q, 2), by_head(kc, 1), by_head(vc, 1), tables_one)
+    assert torch.equal(by_head(out, 2).view(torch.int16), got.view(torch.int16))
 
 
 def _mix(steps, chunks, every=None):
