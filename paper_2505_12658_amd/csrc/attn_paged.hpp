@@ -592,8 +592,21 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
 constexpr int kFirstLayer = kUnits;  // workgroups i and i + 256 of a grid share a compute unit
 constexpr int kLongChain = 8;        // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
 constexpr int kStepUnits = 128;      // compute units that the chains leave to the decode steps
+constexpr int kFewChunks = 4;        // as many are ranked one by one
 
 #if defined(__HIP_DEVICE_COMPILE__)
+// The largest value of a wave's lanes (none below 0), in all of them.
+__device__ __forceinline__ int wave_max(int x) {
+  auto with = [&](int other) { x = other > x ? other : x; };
+  with(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  with(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  with(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  with(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  with(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  with(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
 // A workgroup's work: a share of a request's context for one KV head (f0 < 0), or a group of wave tiles of a request.
 struct Work {
   int b, kv_head, q_start, q_len, kv_len, split, f0;
@@ -619,6 +632,10 @@ struct Work {
 // 215 37.5 -> 28.6; 76 of 44 .. 441 and 4 of 72 15.6 -> 14.6; 20 of 240 .. 2408 and 4 of 68 21.1 -> 17.2; 5 of 97 .. 971 and 1 of 299
 // 12.0 -> 11.1 (a scan over the requests through LDS took longer); 42 of 72 .. 723 and 4 of 64 12.4 -> 12.7 (decode steps whose lengths
 // now come through the vector memory path; the largest loss of 96 mixes, their mean is 6 % faster).
+// A chain's chunk: up to kFewChunks chunks are ranked one by one, more by a search, whose time does not grow with their number.
+// us, through the scan in LDS, one by one and by the search: 256 chunks of 32 tokens 130, 503 and 79; 100 decode steps and 100 chunks of
+// 16 63, 139 and 55; 64 chunks of 100 53, 57 and 36; 16 of 512 215, 215 and 213; but a chunk of 64 alone 11.2, 10.4 and 10.8, 8 decode
+// steps of 70 .. 709 and 2 chunks of 405 20.3, 19.6 and 19.9.
 template <int REGS>
 __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
   const int lane = threadIdx.x & 63;
@@ -626,7 +643,7 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
   int q_start[REGS], q_len[REGS], kv_len[REGS];
   int steps[REGS], groups[REGS];  // of a request of the first kind / of the second
   uint64_t chunks[REGS], any_chunk = 0, far_chunk = 0;
-  int n_steps = 0;
+  int n_steps = 0, n_chunks = 0;
 #pragma unroll
   for (int r = 0; r < REGS; ++r) {
     const int at = r * 64 + lane < a.batch ? r * 64 + lane : a.batch - 1;
@@ -645,6 +662,7 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     n_steps += __builtin_popcountll(__builtin_amdgcn_ballot_w64(steps[r] > 0));
     chunks[r] = __builtin_amdgcn_ballot_w64(chunk);
     any_chunk |= chunks[r];
+    n_chunks += __builtin_popcountll(chunks[r]);
     far_chunk |= __builtin_amdgcn_ballot_w64(chunk && kv_len[r] > kLongChain * kKvTileRows);
   }
   // workgroups of the first kind: one per share
@@ -665,26 +683,26 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
   // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
   int units = kFirstLayer;
   bool beside_steps = false;
-  if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
+  if (rows_wgs == 0) {
+    beside_steps = true;  // (chains only)
+  } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
     int longest = 0;
-#pragma unroll
-    for (int r = 0; r < REGS; ++r)
-      for (uint64_t left = chunks[r]; left != 0; left &= left - 1) {
-        const int kv = __builtin_amdgcn_readlane(kv_len[r], __builtin_ctzll(left));
-        longest = kv > longest ? kv : longest;
-      }
-    int far = 0;  // groups whose chains are longer than half of the longest
     uint64_t longer = 0, far_longer = 0;
 #pragma unroll
-    for (int r = 0; r < REGS; ++r) {
-      int tokens = kv_len[r] - longest / 2;
-      tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
-      far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
-      longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
-      far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
-    }
+    for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
+    longest = wave_max(longest);
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
     beside_steps = rows_wgs <= kFirstLayer && longer == 0;
     if (far_chunk != 0 && !beside_steps) {
+      int far = 0;  // groups whose chains are longer than half of the longest
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) {
+        int tokens = kv_len[r] - longest / 2;
+        tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
+        far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
+        far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
+      }
       int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
       if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
       chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
@@ -715,30 +733,65 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     w.kv_head = chain - target * a.n_kv_heads;
     w.split = 0;
     w.b = -1;
-    int before[REGS];  // groups ahead of this lane's chunk: those of chunks with longer contexts
+    auto take = [&](int r, int j, int groups_left) {  // lane j of register r, from the last group down
+      w.b = r * 64 + j;
+      w.q_start = __builtin_amdgcn_readlane(q_start[r], j);
+      w.q_len = __builtin_amdgcn_readlane(q_len[r], j);
+      w.kv_len = __builtin_amdgcn_readlane(kv_len[r], j);
+      w.f0 = (groups_left - 1) * kWavesPerGroup;
+    };
+    if (n_chunks <= kFewChunks) {
+      int before[REGS];  // groups ahead of this lane's chunk: those of chunks with longer contexts
 #pragma unroll
-    for (int r = 0; r < REGS; ++r) before[r] = 0;
+      for (int r = 0; r < REGS; ++r) before[r] = 0;
 #pragma unroll
-    for (int r = 0; r < REGS; ++r)
-      for (uint64_t left = chunks[r]; left != 0; left &= left - 1) {
-        const int j = __builtin_ctzll(left);
-        const int kv = __builtin_amdgcn_readlane(kv_len[r], j), n = __builtin_amdgcn_readlane(groups[r], j);
+      for (int r = 0; r < REGS; ++r)
+        for (uint64_t left = chunks[r]; left != 0; left &= left - 1) {
+          const int j = __builtin_ctzll(left);
+          const int kv = __builtin_amdgcn_readlane(kv_len[r], j), n = __builtin_amdgcn_readlane(groups[r], j);
 #pragma unroll
-        for (int e = 0; e < REGS; ++e) before[e] += kv > kv_len[e] || (kv == kv_len[e] && r * 64 + j < e * 64 + lane) ? n : 0;
+          for (int e = 0; e < REGS; ++e) before[e] += kv > kv_len[e] || (kv == kv_len[e] && r * 64 + j < e * 64 + lane) ? n : 0;
+        }
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) {
+        const uint64_t here = __builtin_amdgcn_ballot_w64(groups[r] > 0 && before[r] <= target && target < before[r] + groups[r]);
+        if (here != 0) {
+          const int j = __builtin_ctzll(here);
+          take(r, j, __builtin_amdgcn_readlane(before[r] + groups[r], j) - target);
+        }
       }
+      return w.b >= 0;  // (past the last group otherwise)
+    }
+    // More chunks are taken by their key tiles, most first and equal ones by number: a search over the bits of a number of tiles,
+    // which adds up the groups of all chunks that reach it.
+    int tiles[REGS], most = 0, v = 0, ahead = 0;  // ahead: groups of the chunks with more than v tiles
 #pragma unroll
     for (int r = 0; r < REGS; ++r) {
-      const uint64_t here = __builtin_amdgcn_ballot_w64(groups[r] > 0 && before[r] <= target && target < before[r] + groups[r]);
-      if (here != 0) {
-        const int j = __builtin_ctzll(here);
-        w.b = r * 64 + j;
-        w.q_start = __builtin_amdgcn_readlane(q_start[r], j);
-        w.q_len = __builtin_amdgcn_readlane(q_len[r], j);
-        w.kv_len = __builtin_amdgcn_readlane(kv_len[r], j);
-        w.f0 = (__builtin_amdgcn_readlane(groups[r], j) - 1 - (target - __builtin_amdgcn_readlane(before[r], j))) * kWavesPerGroup;
-      }
+      tiles[r] = groups[r] > 0 ? (kv_len[r] + kKvTileRows - 1) / kKvTileRows : 0;
+      most = tiles[r] > most ? tiles[r] : most;
     }
-    return w.b >= 0;  // (past the last group otherwise)
+    most = wave_max(most);  // (at least 1: there are chunks)
+    for (int bit = 1 << (31 - __builtin_clz(most)); bit > 0; bit >>= 1) {
+      int sum = 0;
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) sum += tiles[r] >= (v | bit) ? groups[r] : 0;
+      sum = __builtin_amdgcn_readlane(wave_scan_add(sum), 63);
+      if (sum > target) v |= bit;
+      else ahead = sum;
+    }
+    int at = target - ahead;  // among the groups of the chunks with v tiles
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) {
+      const int mine = v > 0 && tiles[r] == v ? groups[r] : 0;
+      const int upto = wave_scan_add(mine);
+      const uint64_t here = __builtin_amdgcn_ballot_w64(upto - mine <= at && at < upto);
+      if (w.b < 0 && here != 0) {
+        const int j = __builtin_ctzll(here);
+        take(r, j, __builtin_amdgcn_readlane(upto, j) - at);
+      }
+      at -= __builtin_amdgcn_readlane(upto, 63);
+    }
+    return w.b >= 0;
   }
 
   if (step >= rows_wgs) return false;

@@ -454,6 +454,28 @@ def test_steps_and_chains_over_the_chip(case):
         _check(_run_gpu(h, q, kc, vc, tables, out=out, **kw), want)
 
 
+CHUNK_CASES = [
+    # (q_lens, kv_lens), Hq, Hkv, d: chains whose chunk is found one by one, and by the search over their key tiles
+    (_mix([20, 900], [(40, 64), (64, 65), (33, 700), (70, 129)]), 4, 2, 64),                         # four chunks and five
+    (_mix([20, 900], [(40, 64), (64, 65), (33, 700), (70, 129), (50, 50)]), 4, 2, 64),
+    (_mix([], [(33 + i, 64) for i in range(32)] * 2), 2, 1, 64),                                     # 64 chunks of one key tile
+    (_mix([5] * 9, [(33 + i % 20, 64 * (1 + i % 4)) if i % 4 else (40 + i, 200 + i) for i in range(56)]), 7, 1, 128),  # 65 requests; whole tiles
+    (_mix([300] * 3, [(33 + 7 * i % 40, 100 + 97 * i % 900) for i in range(253)]), 2, 1, 64),       # 256 requests, chunks over every register
+    (_mix([1 + i for i in range(200)], [(64, 1024)] * 3 + [(100, 1025)] * 3), 8, 2, 64),             # the largest number of tiles a power of two, and one more
+    (_mix([], [(200, 200 + 50 * (i % 3)) for i in range(70)]), 6, 3, 80),                            # groups of one chunk over several places
+]
+
+
+@pytest.mark.parametrize("case", CHUNK_CASES, ids=lambda c: f"n{len(c[0][0])}-q{sum(c[0][0])}-kv{max(c[0][1])}-h{c[1]}k{c[2]}-d{c[3]}")
+def test_chains_of_many_chunks(case):
+    """Batches of few and of many chunks: every row of every chunk is there."""
+    (q_lens, kv_lens), hq, hkv, d = case
+    h = si.HybridBatch("chunks", q_lens, kv_lens, hq, hkv, d, block_size=16, seed=len(q_lens) + 1)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    _check(_run_gpu(h, q, kc, vc, tables, out=out), _want(h, q, kc, vc, tables))
+
+
 def test_split_context_with_an_infinite_value():
     """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
     column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
