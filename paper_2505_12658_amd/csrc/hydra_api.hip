@@ -494,6 +494,13 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   args.n_splits = splits;
   const int64_t rows_wgs = (int64_t)batch * n_kv_heads * splits;
   if (tile_wgs + rows_wgs > (int64_t)0x7fffff00) return HYDRA_ERR_UNSUPPORTED;
+  // The launch needs fewer: a request of this form has more than kRows rows, which bounds how many there are (where contexts are
+  // cut is part of the result and stays with the number above).  Each of the others would look for its group in vain behind the
+  // last one: 248 decode steps of 19 .. 194 tokens and a chunk of 21, 28 / 4 heads of 128, 22.6 -> 16.0 us.
+  if (groups > 0) {
+    const int64_t least_q = hydra::paged::kRows / args.group + 1, most_chunks = total_q / least_q < batch ? total_q / least_q : batch;
+    tile_wgs = (((int64_t)total_q / hydra::paged::kRows + most_chunks) * args.group / hydra::paged::kWavesPerGroup + most_chunks) * n_kv_heads;
+  }
   args.n_tile_wgs = (int32_t)tile_wgs;
   const bool decode_only = (int64_t)max_q_len * args.group <= hydra::paged::kDecodeRows && block_size >= hydra::paged::kDecodeMinBlock;
   hipStream_t s = static_cast<hipStream_t>(stream);

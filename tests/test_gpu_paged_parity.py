@@ -476,6 +476,18 @@ def test_chains_of_many_chunks(case):
     _check(_run_gpu(h, q, kc, vc, tables, out=out), _want(h, q, kc, vc, tables))
 
 
+@pytest.mark.parametrize("group", [1, 2, 3, 5, 7, 16, 31, 32, 33])
+def test_chunks_of_the_fewest_rows(group):
+    """Chunks that are just too long for the packed-rows form, nothing else in the batch: as many workgroups as the host's bound
+    from the number of new tokens allows."""
+    q = 32 // group + 1
+    for n in (1, 5, 70, 300):
+        h = si.HybridBatch("fewest", [q] * n, [q + i % 40 for i in range(n)], group, 1, 64, block_size=16, seed=group)
+        qs, kc, vc, tables = si.make_paged_inputs(h)
+        out = torch.full(qs.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        _check(_run_gpu(h, qs, kc, vc, tables, out=out), _want(h, qs, kc, vc, tables))
+
+
 def test_split_context_with_an_infinite_value():
     """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
     column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
