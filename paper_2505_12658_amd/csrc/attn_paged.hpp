@@ -594,6 +594,22 @@ constexpr int kLongChain = 8;        // key tiles from which on a chunk's workgr
 constexpr int kStepUnits = 128;      // compute units that the chains leave to the decode steps
 constexpr int kFewChunks = 4;        // as many are ranked one by one
 
+// Context up to which a hybrid batch keeps the order of its requests.  To order it costs every workgroup up to 2 us where the
+// lengths fill REGS = 4 registers (129 to 256 requests), 0.5 where they fill two, 0.3 with one, paid once per round of workgroups;
+// it saves a part of the longest context's time.  So the limit grows with the pairs, and is in keys of head_dim 128 (a key of 64 takes
+// half as long).  us, the order of the batch and ordered, 28 / 4 heads of 128 if not said: 248 decode steps of 19 .. 194 tokens and
+// a chunk of 21 14.9 and 16.0, 250 of 160 .. 320 and 3 of 167 33.3 and 38.3, 177 of 362 .. 724 and 3 of 59 36.7 and 35.1, 232 of 1151 ..
+// 2303 and 2 of 24 133.6 and 122.4; 203 of 20 .. 204 and 8 of 34 with 16 heads of 64 29.3 and 37.1; 102 of 17 .. 112 and one of 60 7.3
+// and 8.2, 88 of 108 .. 217 and 3 of 129 15.5 and 16.7, 95 of 125 .. 1253 and 3 of 22 29.6 and 24.2; 32 of 167 .. 334 and 10 of 40 with
+// 16 / 8 heads of 80 12.6 and 14.5, 45 of 128 .. 1288 and 6 of 410 with 32 heads 97.1 and 90.2.
+template <int REGS, int D>
+constexpr int order_limit(int pairs) {
+  constexpr int kLeast = REGS == 1 ? 256 : REGS == 2 ? 640 : 1024;
+  pairs = pairs < (1 << 20) ? pairs : 1 << 20;  // (32 bits hold what follows)
+  const int keys = REGS == 1 ? pairs / 4 : REGS == 2 ? pairs * 3 / 4 : pairs * 4 / 3;
+  return (keys > kLeast ? keys : kLeast) * 128 / D;
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)
 // The largest value of a wave's lanes (none below 0), in all of them.
 __device__ __forceinline__ int wave_max(int x) {
@@ -614,7 +630,9 @@ struct Work {
 
 // This workgroup's work, found by every wave for itself from the lengths of the whole batch, which lie in REGS registers of its
 // lanes; false for workgroups that have none.
-// The order.  A key tile takes a chunk's workgroup 1.1 us on a unit of its own, 1.5 beside another chain and 2.2 beside a
+// Batches without a context beyond order_limit keep the order of their requests: decode steps in the first batch * n_kv_heads *
+// n_splits workgroups, which need only their own request's lengths, and the chains behind them.
+// The order of the others.  A key tile takes a chunk's workgroup 1.1 us on a unit of its own, 1.5 beside another chain and 2.2 beside a
 // decode step, which keeps the unit's memory path full.  So the chip is divided: on the first `units` compute units the
 // workgroups of both layers (ids i and i + 256) are decode steps, the longest first in all, paired like those of
 // attn_decode_kernel; on the others both are chains, the longest ones, a longer one with a shorter one.  What does not fit follows
@@ -636,21 +654,50 @@ struct Work {
 // us, through the scan in LDS, one by one and by the search: 256 chunks of 32 tokens 130, 503 and 79; 100 decode steps and 100 chunks of
 // 16 63, 139 and 55; 64 chunks of 100 53, 57 and 36; 16 of 512 215, 215 and 213; but a chunk of 64 alone 11.2, 10.4 and 10.8, 8 decode
 // steps of 70 .. 709 and 2 chunks of 405 20.3, 19.6 and 19.9.
-template <int REGS>
+template <int REGS, int D>
 __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, id = (int)blockIdx.x;
   const int table_keys = (int)((int64_t)a.max_blocks_per_seq << a.block_shift);
+  const int pairs = a.batch * a.n_kv_heads;
+  // this workgroup's place in the order of the batch
+  auto in_batch_order = [&]() {
+    w.split = a.n_splits > 1 ? id / pairs : 0;
+    const int pair = id - w.split * pairs;
+    w.b = pair / a.n_kv_heads;
+    w.kv_head = pair - w.b * a.n_kv_heads;
+    const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
+    int start = cu[w.b], end = cu[w.b + 1], len = lens[w.b];
+    asm volatile("" : "+s"(start), "+s"(end), "+s"(len));  // (asked for together)
+    w.q_start = start;
+    w.q_len = end - start;
+    w.kv_len = len < table_keys ? len : table_keys;
+    w.f0 = -1;
+    return w.q_len > 0 && w.kv_len >= w.q_len && w.q_len * a.group <= kRows;
+  };
+  const int limit = order_limit<REGS, D>(pairs);
+  bool ordered = table_keys > limit;  // (a table this narrow says it without a look at the lengths)
+  if (!ordered && id < pairs * a.n_splits) return in_batch_order();
+
   int q_start[REGS], q_len[REGS], kv_len[REGS];
-  int steps[REGS], groups[REGS];  // of a request of the first kind / of the second
-  uint64_t chunks[REGS], any_chunk = 0, far_chunk = 0;
-  int n_steps = 0, n_chunks = 0;
+#pragma unroll
+  for (int r = 0; r < REGS; ++r) kv_len[r] = a.kv_lens[r * 64 + lane < a.batch ? r * 64 + lane : a.batch - 1];
 #pragma unroll
   for (int r = 0; r < REGS; ++r) {
     const int at = r * 64 + lane < a.batch ? r * 64 + lane : a.batch - 1;
     q_start[r] = a.cu_seqlens_q[at];
     q_len[r] = a.cu_seqlens_q[at + 1];
-    kv_len[r] = a.kv_lens[at];
   }
+  if (REGS > 1 && ordered) {  // (the look costs what it saves where the lengths fill one register)
+    bool far = false;         // (requests past the last one repeat it)
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) far = far || kv_len[r] > limit;
+    ordered = __builtin_amdgcn_ballot_w64(far) != 0;
+    if (!ordered && id < pairs * a.n_splits) return in_batch_order();
+  }
+
+  int steps[REGS], groups[REGS];  // of a request of the first kind / of the second
+  uint64_t chunks[REGS], any_chunk = 0, far_chunk = 0;
+  int n_steps = 0, n_chunks = 0;
 #pragma unroll
   for (int r = 0; r < REGS; ++r) {
     q_len[r] -= q_start[r];
@@ -665,67 +712,69 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     n_chunks += __builtin_popcountll(chunks[r]);
     far_chunk |= __builtin_amdgcn_ballot_w64(chunk && kv_len[r] > kLongChain * kKvTileRows);
   }
-  // workgroups of the first kind: one per share
-  int rows_wgs = n_steps * a.n_kv_heads, shares[REGS];
-  if (a.n_splits > 1) {
-    int sum = 0;
-#pragma unroll
-    for (int r = 0; r < REGS; ++r) {
-      int per;
-      shares[r] = 0;
-      if (steps[r] > 0) share_plan(steps[r], a.n_splits, a.least_log2, per, shares[r]);
-      sum += shares[r];
-    }
-    rows_wgs = __builtin_amdgcn_readlane(wave_scan_add(sum), 63) * a.n_kv_heads;
-  }
-  const int id = (int)blockIdx.x;
 
-  // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
-  int units = kFirstLayer;
-  bool beside_steps = false;
-  if (rows_wgs == 0) {
-    beside_steps = true;  // (chains only)
-  } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
-    int longest = 0;
-    uint64_t longer = 0, far_longer = 0;
-#pragma unroll
-    for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
-    longest = wave_max(longest);
-#pragma unroll
-    for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
-    beside_steps = rows_wgs <= kFirstLayer && longer == 0;
-    if (far_chunk != 0 && !beside_steps) {
-      int far = 0;  // groups whose chains are longer than half of the longest
+  int step = -1, chain = -1, units = kFirstLayer, rows_wgs = 0, shares[REGS];
+  if (!ordered) {
+    chain = id - pairs * a.n_splits;
+  } else {
+    // workgroups of the first kind: one per share
+    rows_wgs = n_steps * a.n_kv_heads;
+    if (a.n_splits > 1) {
+      int sum = 0;
 #pragma unroll
       for (int r = 0; r < REGS; ++r) {
-        int tokens = kv_len[r] - longest / 2;
-        tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
-        far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
-        far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
+        int per;
+        shares[r] = 0;
+        if (steps[r] > 0) share_plan(steps[r], a.n_splits, a.least_log2, per, shares[r]);
+        sum += shares[r];
       }
-      int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
-      if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
-      chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
-      units = kFirstLayer - chain_units;
+      rows_wgs = __builtin_amdgcn_readlane(wave_scan_add(sum), 63) * a.n_kv_heads;
     }
-  }
-  if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
-  const int chain_units = kFirstLayer - units;
+    // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
+    bool beside_steps = false;
+    if (rows_wgs == 0) {
+      beside_steps = true;  // (chains only)
+    } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
+      int longest = 0;
+      uint64_t longer = 0, far_longer = 0;
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
+      longest = wave_max(longest);
+#pragma unroll
+      for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
+      beside_steps = rows_wgs <= kFirstLayer && longer == 0;
+      if (far_chunk != 0 && !beside_steps) {
+        int far = 0;  // groups whose chains are longer than half of the longest
+#pragma unroll
+        for (int r = 0; r < REGS; ++r) {
+          int tokens = kv_len[r] - longest / 2;
+          tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
+          far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
+          far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
+        }
+        int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
+        if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
+        chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
+        units = kFirstLayer - chain_units;
+      }
+    }
+    if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
+    const int chain_units = kFirstLayer - units;
 
-  int step = -1, chain = -1;
-  if (id < units) {
-    step = id;
-  } else if (id < kFirstLayer || beside_steps) {
-    chain = id - units;
-  } else if (id < kFirstLayer + units) {
-    step = units + id - kFirstLayer;
-    if (step >= rows_wgs) chain = 2 * chain_units + step - (rows_wgs > units ? rows_wgs : units);
-  } else if (id < 2 * kFirstLayer) {
-    const int at = id - (kFirstLayer + units);  // (the longer the first chain of a unit, the shorter the second)
-    chain = 2 * chain_units - 8 - (at & ~7) + (at & 7);
-  } else {
-    step = 2 * units + id - 2 * kFirstLayer;
-    if (step >= rows_wgs) chain = id - (rows_wgs > units ? rows_wgs : units);
+    if (id < units) {
+      step = id;
+    } else if (id < kFirstLayer || beside_steps) {
+      chain = id - units;
+    } else if (id < kFirstLayer + units) {
+      step = units + id - kFirstLayer;
+      if (step >= rows_wgs) chain = 2 * chain_units + step - (rows_wgs > units ? rows_wgs : units);
+    } else if (id < 2 * kFirstLayer) {
+      const int at = id - (kFirstLayer + units);  // (the longer the first chain of a unit, the shorter the second)
+      chain = 2 * chain_units - 8 - (at & ~7) + (at & 7);
+    } else {
+      step = 2 * units + id - 2 * kFirstLayer;
+      if (step >= rows_wgs) chain = id - (rows_wgs > units ? rows_wgs : units);
+    }
   }
 
   if (chain >= 0) {
@@ -764,12 +813,14 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     }
     // More chunks are taken by their key tiles, most first and equal ones by number: a search over the bits of a number of tiles,
     // which adds up the groups of all chunks that reach it.
-    int tiles[REGS], most = 0, v = 0, ahead = 0;  // ahead: groups of the chunks with more than v tiles
+    int tiles[REGS], most = 0, all = 0, v = 0, ahead = 0;  // ahead: groups of the chunks with more than v tiles
 #pragma unroll
     for (int r = 0; r < REGS; ++r) {
       tiles[r] = groups[r] > 0 ? (kv_len[r] + kKvTileRows - 1) / kKvTileRows : 0;
       most = tiles[r] > most ? tiles[r] : most;
+      all += groups[r];
     }
+    if (target >= __builtin_amdgcn_readlane(wave_scan_add(all), 63)) return false;  // past the last group
     most = wave_max(most);  // (at least 1: there are chunks)
     for (int bit = 1 << (31 - __builtin_clz(most)); bit > 0; bit >>= 1) {
       int sum = 0;
@@ -862,7 +913,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int b, kv_head, q_start, q_len, kv_len, split = 0, f0 = -1;  // f0 < 0: the packed-rows form or the decode form
   if (a.batch <= kOrderedMost) {
     Work w;
-    if (!(a.batch <= 64 ? find_work<1>(a, w) : find_work<4>(a, w))) return;
+    if (!(a.batch <= 64 ? find_work<1, D>(a, w) : a.batch <= 128 ? find_work<2, D>(a, w) : find_work<4, D>(a, w))) return;
     b = w.b, kv_head = w.kv_head, q_start = w.q_start, q_len = w.q_len, kv_len = w.kv_len, split = w.split, f0 = w.f0;
   } else {
     const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;

@@ -488,6 +488,37 @@ def test_chunks_of_the_fewest_rows(group):
         _check(_run_gpu(h, qs, kc, vc, tables, out=out), _want(h, qs, kc, vc, tables))
 
 
+ORDER_CASES = [
+    # (q_lens, kv_lens), Hq, Hkv, d, table keys: batches that keep the order of their requests, and such that do not
+    (_mix([30 + i for i in range(60)], [(40, 100), (9, 50)]), 8, 8, 64, 0),            # a narrow table says it
+    (_mix([30 + i for i in range(60)], [(40, 100), (9, 50)]), 8, 8, 64, 4096),         # one register: a wide table does not
+    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 1024 + 64), (64, 64)]), 4, 2, 128, 4096),   # two registers, ordered by one chunk
+    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 640), (64, 64)]), 4, 2, 128, 4096),         # the limit, and one key more
+    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 641), (64, 64)]), 4, 2, 128, 4096),
+    (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1024), (33, 40)] * 4), 8, 4, 128, 0),          # four registers: 832 pairs, limit 1109
+    (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1110), (33, 40)] * 4), 8, 4, 128, 0),
+    (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1024), (33, 40)] * 4), 8, 4, 128, 4096),
+    (_mix([1900, 40, 700, 2500], [(40, 300), (9, 11)]), 2, 1, 64, 0),                   # split contexts
+    (_mix([600, 40, 700, 30] * 20, [(40, 300)]), 8, 1, 64, 0),                          # 81 pairs, contexts cut in batch order
+]
+
+
+@pytest.mark.parametrize("case", ORDER_CASES, ids=lambda c: f"n{len(c[0][0])}-kv{max(c[0][1])}-h{c[1]}k{c[2]}-d{c[3]}-t{c[4]}")
+def test_hybrid_batches_in_either_order(case):
+    """Hybrid batches on both sides of the rule that keeps the order of the requests: every row is there."""
+    (q_lens, kv_lens), hq, hkv, d, table_keys = case
+    h = si.HybridBatch("order", q_lens, kv_lens, hq, hkv, d, block_size=16, seed=len(q_lens) + 2)
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    want = _want(h, q, kc, vc, tables)
+    if table_keys:
+        wide = np.full((len(q_lens), table_keys // 16), -1, dtype=np.int32)
+        wide[:, : tables.shape[1]] = tables
+        tables = wide
+    for kw in ({}, {"use_workspace": False}):
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        _check(_run_gpu(h, q, kc, vc, tables, out=out, **kw), want)
+
+
 def test_split_context_with_an_infinite_value():
     """A context of fewer shares than the launch has, whose last key holds an infinite V component: infinite in the output
     column it belongs to (the shares that do not exist must not turn it into NaN), everything else against the oracle."""
