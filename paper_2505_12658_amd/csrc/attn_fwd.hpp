@@ -244,11 +244,13 @@ using NextRB = std::integral_constant<int, N>;  // key block the following step 
 
 // LDS fragments are requested this many work units (one K or V^T fragment and the matrix instructions it feeds)
 // ahead of their use.  Each unit of distance keeps one more K and one more V^T fragment (8 registers) in flight.
-// Two at head_dim 128, where two waves share a SIMD (three: no faster; one: 558 tokens 14.8 -> 15.1 us, larger batches level).
-// One where three waves do, which cover the LDS latency for each other: 16 heads of 80, 65 536 tokens in images of 256 .. 4096
-// 796 -> 791 us, 32 images of 577 tokens with 16 heads of 64 62.6 -> 62.3, one image equal.
-template <int D>
-constexpr int kFragsAhead = D <= 80 ? 1 : 2;
+// Two in kernels built for two waves per SIMD (three: no faster; one: head_dim 128, 558 tokens 14.8 -> 15.1 us, larger batches level;
+// head_dim 80 with one workgroup per compute unit asked for, 48 requests with 28 / 4 heads 210.8 -> 213.9, 65 536 tokens in images of
+// 256 .. 4096 with 16 heads 1059 -> 1064; head_dim 64 from cache pages level).  One in kernels built for three, whose waves cover the
+// LDS latency for each other: the same images with a workgroup per item 796 -> 791, 32 images of 577 tokens with 16 heads of 64
+// 62.6 -> 62.3, one image equal (but 180.4 instead of 178.8 where one workgroup per unit is asked for, 48 requests with 28 / 4 heads of 64).
+template <int WAVES_PER_SIMD>
+constexpr int kFragsAhead = WAVES_PER_SIMD >= 3 ? 1 : 2;
 
 #if defined(__HIP_DEVICE_COMPILE__)
 // LDS fragments of the first PF QK units and the first PF PV units of a pipeline step.
@@ -268,10 +270,14 @@ constexpr float kMaxRowSum = 1.0995116e12f;  // 2^40: largest row sum (relative 
 struct PackedSource {
   static constexpr bool kPaged = false, kOneItem = false;
   template <int D>
+  static constexpr int kWavesPerSimd = kWorkgroupsPerCu<D>;  // that the kernel is built for
+  template <int D>
   struct Gather {};  // (the paged source's K/V gatherer; the packed rows use two TileLoaders)
 };
 struct DirectSource {
   static constexpr bool kPaged = false, kOneItem = true;
+  template <int D>
+  static constexpr int kWavesPerSimd = kDirectPerCu<D>;
   template <int D>
   struct Gather {};
   int64_t q_start;   // first token of the sequence
@@ -292,7 +298,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   constexpr int ROWB = G::kRowBytes;
   constexpr int NQ = KS;      // QK work units per key block: step s = one K fragment read + 2 MFMAs (qs = 0, 1)
   constexpr int NP = 2 * CC;  // PV work units per key block: (s2, cc) = one V^T fragment + 2 MFMAs
-  constexpr int PF = kFragsAhead<D>;
+  constexpr int PF = kFragsAhead<Src::template kWavesPerSimd<D>>;
   // LDS: K ring then V ring; tile t of either lives in ring slot t % kRing.
   constexpr int R = G::kRing, PD = G::kPrefetch;
   const uint32_t k_ring = (uint32_t)(uintptr_t)HYDRA_LDS_PTR(smem);  // LDS byte addresses
@@ -1004,7 +1010,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
 #endif  // __HIP_DEVICE_COMPILE__
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWorkgroupsPerCu<D>, kWorkgroupsPerCu<D>))) void attn_fwd_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PackedSource::kWavesPerSimd<D>, PackedSource::kWavesPerSimd<D>))) void attn_fwd_kernel(const AttnArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D>::kLdsBytes];
   __shared__ __attribute__((aligned(16))) int s_claim[4];
@@ -1185,7 +1191,7 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
 #endif  // __HIP_DEVICE_COMPILE__
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kDirectPerCu<D>, kDirectPerCu<D>))) void attn_fwd_direct_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DirectSource::kWavesPerSimd<D>, DirectSource::kWavesPerSimd<D>))) void attn_fwd_direct_kernel(
     const AttnArgs a, const int batch, const int n_kv_heads) {  // batch 0: the item comes from the work list
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D>::kLdsBytes];

@@ -36,6 +36,8 @@
 namespace hydra {
 namespace paged {
 
+constexpr int kPagedWavesPerSimd = 2;  // that attn_paged_kernel is built for
+
 template <int D>
 struct StageGeom : RowGeom<D> {
   using RowGeom<D>::kTileBytes;
@@ -145,6 +147,8 @@ __device__ __forceinline__ void issue_tile_loads(const TileSlots<D, KEYS, STEP>&
 // head_dim 80 (a row is not a whole fraction of 1024 bytes) and smaller blocks take the plain loop further down.
 struct PagedSource {
   static constexpr bool kPaged = true, kOneItem = true;
+  template <int D>
+  static constexpr int kWavesPerSimd = kPagedWavesPerSimd;
   const PagedArgs* args;
   const int32_t* table;  // the request's row of the block table
   int64_t q_start;       // first new token of the request in the packed q / out
@@ -893,7 +897,7 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
 #endif  // __HIP_DEVICE_COMPILE__
 
 template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_paged_kernel(const PagedArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWavesPerSimd, kPagedWavesPerSimd))) void attn_paged_kernel(const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using G = StageGeom<D>;
   constexpr int kLds = G::kLdsBytes > TileGeom<D>::kLdsBytes ? G::kLdsBytes : TileGeom<D>::kLdsBytes;
