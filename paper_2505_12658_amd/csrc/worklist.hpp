@@ -100,10 +100,10 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   // Every workgroup of the grid derives the ranking and the queue layout for itself (steps 1 and 2: two microseconds, and no
   // synchronisation between workgroups is needed); then workgroup x < 8 orders the tail of queue x (step 4), and the other
   // places of the list are shared out over the rest of the grid (step 3).  Workgroup 0 writes the control block.
-  // What bounds the kernel is latency: a read of cu_seqlens, five barriers and what lies between them.  So sequences and tail
+  // What bounds the kernel is latency: a read of cu_seqlens, five barriers (seven for 129 to 512 sequences) and what lies between them.  So sequences and tail
   // items are ranked by counting, eight lanes each with two 16-byte reads, and the scan over a queue goes through data-parallel
   // primitives (with LDS counters that several threads add to, scans and a bitonic sort by LDS permutes, and the tails behind the items on
-  // the same workgroups, us: 48 sequences with 28 / 4 heads of 128 7.3 -> 4.7, 16 with 32 / 32 6.9 -> 4.6, 128 8.1 -> 4.8, 300 15.0 -> 11.5;
+  // the same workgroups, us: 48 sequences with 28 / 4 heads of 128 7.0 -> 4.3, 16 with 32 / 32 6.6 -> 4.2, 128 7.8 -> 4.4, 300 17.5 -> 12.6;
   // ranked by every wave in its registers, without the first two barriers, 1 sequence 3.4 instead of 4.2, 48 5.6, 64 6.2).
   const bool leader = blockIdx.x == 0;
   if (leader && tid < kXcds) ctrl->queue_head[tid * kHeadStride] = ctrl->queue_head[tid * kHeadStride + kLeftAt] = 0;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kPrepassThreads) void build_worklist_kernel(const i
   // per item count the keys above its own.
   if (blockIdx.x >= kXcds) return;
   const int tail_x = tail_of(blockIdx.x), tail_n = s_queue_start[blockIdx.x + 1] - tail_x;
-  __syncthreads();  // (s_key held the rank counters of step 1)
+  // (s_key held the rank counters of step 1, which were last read three barriers ago)
   if (tid < kTailSort) {
     int key = -1;
     if (tid < tail_n) {
