@@ -415,6 +415,8 @@ __device__ __forceinline__ int search_rank(const int (&steps)[REGS], int rank, i
 // number), and its context.  Called by whole waves; every wave finds it for itself, without LDS or a barrier: the lengths
 // lie in REGS registers of its lanes, and a search over the bits of a length, highest first, counts with ballots how many
 // requests reach it (0.3 us; a search over single keys, with branches around the registers that a batch does not fill, 0.9).
+// A request without new tokens ranks by the context it has left, and its workgroups leave at once (96 slots, a third of them idle with
+// 1500 .. 1800 old tokens, 20.4 us in the order of the batch, 18.0 so).
 // False where the order would not matter: contexts within a quarter of each other, or none of kOrderedKeys.
 // any_long: some context has kDecodeShortKeys.
 template <int REGS>

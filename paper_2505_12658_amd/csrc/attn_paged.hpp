@@ -1165,8 +1165,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
 // workgroup) are skipped.  A thread adds up its columns over the shares.  It runs on an idle chip, and latency is all it costs,
 // most of it launch and instruction fetch; so it asks for everything it needs at once, the records of all shares of the launch
 // (whose places follow from the grid) together with the lengths that say which of them exist: one round trip to memory.
-// Records behind the lengths and now, us with the cache write, 28 / 4 heads of 128: 4 decode steps of 300 .. 1500 tokens 10.2 -> 10.0,
-// 1 of 5000 12.3 -> 11.8, 8 of 16 384 48.4 -> 48.1, 12 of 1000 .. 3700 18.0 -> 17.7.
+// Records behind the lengths and now, us of both kernels, 28 / 4 heads of 128: 4 decode steps of 300 .. 1500 tokens 7.84 -> 7.65, 1 of
+// 5000 10.17 -> 9.81, 12 of 1000 .. 3700 16.5 -> 16.1, 8 of 16 384 and 30 of 100 .. 1400 equal; with the caches and the workspace out of
+// every cache 12.74 -> 12.65, 14.80 -> 14.48, 21.5 -> 21.2 (records that no share wrote are read all the same).
 // With one workgroup per (request, KV head) a request of more than 8 rows of 128 took its trips two to four times: 30 requests of 4
 // new tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2, 28 / 2 heads, 18.9 -> 15.9.
 constexpr int kMaxSplits = 16;

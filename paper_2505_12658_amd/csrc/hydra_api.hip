@@ -80,14 +80,19 @@ hipError_t launch_attn(bool causal, const hydra::AttnArgs& args, unsigned comput
 
 // How a batch of up to `capacity` items runs: one workgroup per item up to kDirectRounds rounds of the chip's workgroup
 // slots, and up to kListFreeRounds without a work list if the call would have to build it (attn_fwd_direct_kernel).
-// us per call: 4 images of 577 tokens 27.5 -> 13.9, 14 images 45.1 -> 31.9 (36.7 with the list built), 32 images (3.5
-// rounds) 71 -> 63 (66); 8 LLaVA requests (3 rounds) 102.6 -> 96.1 (95.4).
+// us per call with persistent workgroups and so: 4 images of 577 tokens 27.5 -> 13.9, 14 images 45.1 -> 31.9, 32 images 71 -> 63.
+// us per call without a list and with one built first, by rounds: 16 heads of 64, 14 images of 577 tokens (1.5 rounds) 32.8 and 35.9, 26
+// (2.7) 53.6 and 56.4, 30 (3.1) 60.3 and 62.9, 34 (3.5) 68.5 and 69.6, 38 (4.0) 77.4 and 76.9; 16 heads of 80, 17 000 tokens in images
+// of 256 .. 4096 (2.9) 194.1 and 194.8, 19 000 (3.3) 204.3 and 207.6, 21 000 (3.6) 223.1 and 222.1, 23 000 (4.0) 243.3 and 243.5;
+// 28 / 4 heads of 128, 6 requests (1.5) 28.2 and 30.6, 10 (2.5) 41.6 and 41.3, 14 (3.4) 54.1 and 53.6, 18 (4.3) 66.3 and 65.7; 32 / 32
+// heads of 128, 2 requests of 700 tokens (0.8) 18.4 and 21.7, 3 (1.1) 27.4 and 26.2, 4 (1.5) 33.8 and 32.3, 5 (1.9) 38.2 and 39.6.
 constexpr size_t kDirectRounds = 6, kListFreeRounds = 4;
 bool within_rounds(size_t rounds, int32_t head_dim, size_t capacity, unsigned compute_units) {
   const unsigned per_cu = head_dim == 64 ? hydra::kDirectPerCu<64> : head_dim == 80 ? hydra::kDirectPerCu<80> : hydra::kDirectPerCu<128>;
   return capacity <= rounds * per_cu * compute_units;
 }
-// (head_dim 80 at any size: see kDirectPerCu; up to a million items, since a launch has fewer than 2^32 threads)
+// (head_dim 80 beyond that too: see kDirectPerCu.  Measured up to 640 000 items, 40 000 images of 16 tokens with 16 heads, 4782 us with
+// persistent workgroups, 4136 so; longer lists than a million stay with those.)
 bool direct_form(int32_t head_dim, size_t capacity, unsigned compute_units) {
   return within_rounds(kDirectRounds, head_dim, capacity, compute_units) || (head_dim == 80 && capacity <= (size_t)1 << 20);
 }
