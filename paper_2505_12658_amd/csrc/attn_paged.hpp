@@ -604,14 +604,14 @@ constexpr int kFewChunks = 4;        // as many are ranked one by one
 // half as long).  us, the order of the batch and ordered, 28 / 4 heads of 128 if not said: 248 decode steps of 19 .. 194 tokens and
 // a chunk of 21 14.9 and 16.0, 250 of 160 .. 320 and 3 of 167 33.3 and 38.3, 177 of 362 .. 724 and 3 of 59 36.7 and 35.1, 232 of 1151 ..
 // 2303 and 2 of 24 133.6 and 122.4; 203 of 20 .. 204 and 8 of 34 with 16 heads of 64 29.3 and 37.1; 102 of 17 .. 112 and one of 60 7.3
-// and 8.2, 88 of 108 .. 217 and 3 of 129 15.5 and 16.7, 95 of 125 .. 1253 and 3 of 22 29.6 and 24.2; 32 of 167 .. 334 and 10 of 40 with
+// and 8.2, 88 of 108 .. 217 and 3 of 129 15.5 and 16.7, 84 of 49 .. 494 and one of 27 14.5 and 10.8, 95 of 125 .. 1253 and 3 of 22 29.6
+// and 24.2, but 111 of 37 .. 375 and 4 of 111 17.5 and 19.0, 120 of 61 .. 615 and 4 of 100 21.2 and 23.4; 32 of 167 .. 334 and 10 of 40 with
 // 16 / 8 heads of 80 12.6 and 14.5, 45 of 128 .. 1288 and 6 of 410 with 32 heads 97.1 and 90.2.
-template <int REGS, int D>
-constexpr int order_limit(int pairs) {
-  constexpr int kLeast = REGS == 1 ? 256 : REGS == 2 ? 640 : 1024;
-  pairs = pairs < (1 << 20) ? pairs : 1 << 20;  // (32 bits hold what follows)
-  const int keys = REGS == 1 ? pairs / 4 : REGS == 2 ? pairs * 3 / 4 : pairs * 4 / 3;
-  return (keys > kLeast ? keys : kLeast) * 128 / D;
+inline int order_keys(int64_t batch, int64_t pairs, int64_t table_keys, int head_dim) {
+  const int64_t least = batch <= 64 ? 256 : batch <= 128 ? 440 : 1024, by_pairs = batch <= 64 ? pairs / 4 : batch <= 128 ? pairs * 3 / 4 : pairs * 4 / 3;
+  const int64_t keys = (by_pairs > least ? by_pairs : least) * 128 / head_dim;
+  if (table_keys <= keys) return kNeverOrdered;  // (a table this narrow says it without a look at the lengths,
+  return batch <= 64 ? 0 : (int)keys;            // and the look costs what it saves where these fill one register)
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -634,7 +634,7 @@ struct Work {
 
 // This workgroup's work, found by every wave for itself from the lengths of the whole batch, which lie in REGS registers of its
 // lanes; false for workgroups that have none.
-// Batches without a context beyond order_limit keep the order of their requests: decode steps in the first batch * n_kv_heads *
+// Batches without a context beyond order_keys keep the order of their requests: decode steps in the first batch * n_kv_heads *
 // n_splits workgroups, which need only their own request's lengths, and the chains behind them.
 // The order of the others.  A key tile takes a chunk's workgroup 1.1 us on a unit of its own, 1.5 beside another chain and 2.2 beside a
 // decode step, which keeps the unit's memory path full.  So the chip is divided: on the first `units` compute units the
@@ -658,7 +658,7 @@ struct Work {
 // us, through the scan in LDS, one by one and by the search: 256 chunks of 32 tokens 130, 503 and 79; 100 decode steps and 100 chunks of
 // 16 63, 139 and 55; 64 chunks of 100 53, 57 and 36; 16 of 512 215, 215 and 213; but a chunk of 64 alone 11.2, 10.4 and 10.8, 8 decode
 // steps of 70 .. 709 and 2 chunks of 405 20.3, 19.6 and 19.9.
-template <int REGS, int D>
+template <int REGS>
 __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
   const int lane = threadIdx.x & 63, id = (int)blockIdx.x;
   const int table_keys = (int)((int64_t)a.max_blocks_per_seq << a.block_shift);
@@ -678,8 +678,7 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     w.f0 = -1;
     return w.q_len > 0 && w.kv_len >= w.q_len && w.q_len * a.group <= kRows;
   };
-  const int limit = order_limit<REGS, D>(pairs);
-  bool ordered = table_keys > limit;  // (a table this narrow says it without a look at the lengths)
+  bool ordered = a.order_keys != kNeverOrdered;
   if (!ordered && id < pairs * a.n_splits) return in_batch_order();
 
   int q_start[REGS], q_len[REGS], kv_len[REGS];
@@ -691,10 +690,10 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     q_start[r] = a.cu_seqlens_q[at];
     q_len[r] = a.cu_seqlens_q[at + 1];
   }
-  if (REGS > 1 && ordered) {  // (the look costs what it saves where the lengths fill one register)
-    bool far = false;         // (requests past the last one repeat it)
+  if (REGS > 1 && ordered) {
+    bool far = false;  // (requests past the last one repeat it)
 #pragma unroll
-    for (int r = 0; r < REGS; ++r) far = far || kv_len[r] > limit;
+    for (int r = 0; r < REGS; ++r) far = far || kv_len[r] > a.order_keys;
     ordered = __builtin_amdgcn_ballot_w64(far) != 0;
     if (!ordered && id < pairs * a.n_splits) return in_batch_order();
   }
@@ -917,7 +916,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
   int b, kv_head, q_start, q_len, kv_len, split = 0, f0 = -1;  // f0 < 0: the packed-rows form or the decode form
   if (a.batch <= kOrderedMost) {
     Work w;
-    if (!(a.batch <= 64 ? find_work<1, D>(a, w) : a.batch <= 128 ? find_work<2, D>(a, w) : find_work<4, D>(a, w))) return;
+    if (!(a.batch <= 64 ? find_work<1>(a, w) : a.batch <= 128 ? find_work<2>(a, w) : find_work<4>(a, w))) return;
     b = w.b, kv_head = w.kv_head, q_start = w.q_start, q_len = w.q_len, kv_len = w.kv_len, split = w.split, f0 = w.f0;
   } else {
     const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;

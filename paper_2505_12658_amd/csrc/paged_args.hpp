@@ -8,6 +8,7 @@ namespace paged {
 
 constexpr int kRows = 32;          // new tokens (or packed rows) per wave tile
 constexpr int kWavesPerGroup = 4;  // wave tiles per workgroup
+constexpr int kNeverOrdered = 0x7fffffff;
 
 struct PagedArgs {
   const uint16_t* q;        // [total_q, n_q_heads, D] with token stride
@@ -35,6 +36,7 @@ struct PagedArgs {
   int32_t batch;
   int32_t most_rows;   // (new tokens x grouped heads) of a request at most, as the caller says
   int32_t n_tile_wgs;  // workgroups that the grid has for the wave-tile form (an upper bound from the host)
+  int32_t order_keys;  // a hybrid batch with a context of more keys is taken by its contexts (0: whatever they are, kNeverOrdered: not at all)
 };
 
 // One partial result of the packed-rows form: per row (32 rows) the maximum and the sum, then the

@@ -493,8 +493,8 @@ ORDER_CASES = [
     (_mix([30 + i for i in range(60)], [(40, 100), (9, 50)]), 8, 8, 64, 0),            # a narrow table says it
     (_mix([30 + i for i in range(60)], [(40, 100), (9, 50)]), 8, 8, 64, 4096),         # one register: a wide table does not
     (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 1024 + 64), (64, 64)]), 4, 2, 128, 4096),   # two registers, ordered by one chunk
-    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 640), (64, 64)]), 4, 2, 128, 4096),         # the limit, and one key more
-    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 641), (64, 64)]), 4, 2, 128, 4096),
+    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 440), (64, 64)]), 4, 2, 128, 4096),         # the limit, and one key more
+    (_mix([(0, 17, 300)[i % 3] for i in range(96)], [(40, 441), (64, 64)]), 4, 2, 128, 4096),
     (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1024), (33, 40)] * 4), 8, 4, 128, 0),          # four registers: 832 pairs, limit 1109
     (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1110), (33, 40)] * 4), 8, 4, 128, 0),
     (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1024), (33, 40)] * 4), 8, 4, 128, 4096),
