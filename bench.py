@@ -34,7 +34,7 @@ def profile_figures(workload: str):
     """Counter figures of the attention kernel on one workload, from the tracked rocprofv3 summary
     profiles/attn_fwd_<workload>.md: its `figures:` line is a JSON object written together with the tables
     (HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE passes scaled by the calibration copy, share of
-    cycles with the matrix pipe busy, kernel duration under the trace, the commit the profile was taken at).
+    cycles with the matrix pipe busy, the kernel and its duration under the trace, the commit the profile was taken at).
     Counters cannot be read inside a timed run, so the bench line carries them from there, with their source."""
     path = os.path.join(ROOT, "profiles", f"attn_fwd_{workload}.md")
     try:
@@ -230,7 +230,7 @@ def encode_beside_decode(dev, be: DeviceBatch, se, sd, n_sets: int, steps: int, 
     """The pairing the paper's two-stream experiment uses (Section 5.5: encode beside decode, context length 1024):
     encode attention (matrix-bound) on one stream, decode attention over the paged cache (memory-bound) on the
     other, as many decode launches per encode launch as take about the same time.  Three ways: one after the
-    other; launched together with the encode kernel at its own size (its persistent workgroups hold every
+    other; launched together with the encode kernel at its own size (its workgroups hold every
     compute unit's registers, so the decode kernel only gets what drains); launched together with the encode
     kernel at one workgroup per compute unit (hydra_attn_varlen_fwd_shared), so that both run on every compute unit."""
     import paper_2505_12658_amd as hydra
@@ -460,7 +460,7 @@ def main():
             "traffic": fig["traffic_bytes"] if fig else None,
             "traffic_over_algorithmic": fig["traffic_bytes"] / w.attention_min_bytes() if fig else None,
             "mfma_busy": fig["mfma_busy"] if fig else None,
-            "counters_from": {k: fig[k] for k in ("source", "commit", "kernel_avg_us_under_trace")} if fig else None,
+            "counters_from": {k: fig[k] for k in ("source", "kernel", "commit", "kernel_avg_us_under_trace")} if fig else None,
             "avg_kernel_us": attn_avg * 1e6,
             "median_kernel_us": float(np.median(attn_t)) * 1e6,
             "min_kernel_us": float(attn_t.min()) * 1e6,
@@ -507,7 +507,7 @@ def main():
             entry["traffic"] = ofig["traffic_bytes"] if ofig else None
             entry["traffic_over_algorithmic"] = ofig["traffic_bytes"] / ow.attention_min_bytes() if ofig else None
             entry["mfma_busy"] = ofig["mfma_busy"] if ofig else None
-            entry["counters_from"] = {k: ofig[k] for k in ("source", "commit", "kernel_avg_us_under_trace")} if ofig else None
+            entry["counters_from"] = {k: ofig[k] for k in ("source", "kernel", "commit", "kernel_avg_us_under_trace")} if ofig else None
             others.append(entry)
             del ob
             torch.cuda.empty_cache()
