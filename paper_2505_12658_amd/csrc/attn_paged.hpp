@@ -653,7 +653,8 @@ struct Work {
 // 200 62.4 -> 50.8; 70 of 200 .. 2000 and 2 of 300 46.1 -> 33.7; 36 of 246 .. 2466 and 3 of 352 38.0 -> 31.9; 72 of 136 .. 1366 and 4 of
 // 215 37.5 -> 28.6; 76 of 44 .. 441 and 4 of 72 15.6 -> 14.6; 20 of 240 .. 2408 and 4 of 68 21.1 -> 17.2; 5 of 97 .. 971 and 1 of 299
 // 12.0 -> 11.1 (a scan over the requests through LDS took longer); 42 of 72 .. 723 and 4 of 64 12.4 -> 12.7 (decode steps whose lengths
-// now come through the vector memory path; the largest loss of 96 mixes, their mean is 6 % faster).
+// now come through the vector memory path; the largest loss of 96 mixes, their mean is 6 % faster).  Split contexts of very
+// different lengths can lose more, since they are not ranked: 30 of 386 .. 3864 and one of 24 31.2 -> 33.7.
 // A chain's chunk: up to kFewChunks chunks are ranked one by one, more by a search, whose time does not grow with their number.
 // us, through the scan in LDS, one by one and by the search: 256 chunks of 32 tokens 130, 503 and 79; 100 decode steps and 100 chunks of
 // 16 63, 139 and 55; 64 chunks of 100 53, 57 and 36; 16 of 512 215, 215 and 213; but a chunk of 64 alone 11.2, 10.4 and 10.8, 8 decode
