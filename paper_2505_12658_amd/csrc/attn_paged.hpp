@@ -607,8 +607,13 @@ constexpr int kFewChunks = 4;        // as many are ranked one by one
 // and 8.2, 88 of 108 .. 217 and 3 of 129 15.5 and 16.7, 84 of 49 .. 494 and one of 27 14.5 and 10.8, 95 of 125 .. 1253 and 3 of 22 29.6
 // and 24.2, but 111 of 37 .. 375 and 4 of 111 17.5 and 19.0, 120 of 61 .. 615 and 4 of 100 21.2 and 23.4; 32 of 167 .. 334 and 10 of 40 with
 // 16 / 8 heads of 80 12.6 and 14.5, 45 of 128 .. 1288 and 6 of 410 with 32 heads 97.1 and 90.2.
-inline int order_keys(int64_t batch, int64_t pairs, int64_t table_keys, int head_dim) {
-  const int64_t least = batch <= 64 ? 256 : batch <= 128 ? 440 : 1024, by_pairs = batch <= 64 ? pairs / 4 : batch <= 128 ? pairs * 3 / 4 : pairs * 4 / 3;
+// Without chunks it costs less, and a batch of no more pairs than compute units gains nothing: 3 requests of 17 new tokens behind up to 189
+// keys, 16 heads of 64 under a table of 8192, 6.4 and 6.8; 97 of 3 behind 18 .. 176, 28 / 4 heads of 128, 10.2 and 8.8, 238 of 4 behind 36 .. 357
+// 26.6 and 24.6, 169 of 4 behind 100 .. 998 36.3 and 32.2; 183 of 2 behind 37 .. 375, 16 / 8 heads of 80, 26.8 and 28.5.
+inline int order_keys(int64_t batch, int64_t pairs, int64_t table_keys, int head_dim, int64_t tile_wgs) {
+  if (tile_wgs == 0 && pairs <= kUnits) return kNeverOrdered;
+  const int64_t least = tile_wgs == 0 ? 140 : batch <= 64 ? 256 : batch <= 128 ? 440 : 1024;
+  const int64_t by_pairs = tile_wgs == 0 || batch <= 64 ? pairs / 4 : batch <= 128 ? pairs * 3 / 4 : pairs * 4 / 3;
   const int64_t keys = (by_pairs > least ? by_pairs : least) * 128 / head_dim;
   if (table_keys <= keys) return kNeverOrdered;  // (a table this narrow says it without a look at the lengths,
   return batch <= 64 ? 0 : (int)keys;            // and the look costs what it saves where these fill one register)

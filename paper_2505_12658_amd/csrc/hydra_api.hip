@@ -507,7 +507,7 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
     tile_wgs = (((int64_t)total_q / hydra::paged::kRows + most_chunks) * args.group / hydra::paged::kWavesPerGroup + most_chunks) * n_kv_heads;
   }
   args.n_tile_wgs = (int32_t)tile_wgs;
-  args.order_keys = hydra::paged::order_keys(batch, (int64_t)batch * n_kv_heads, (int64_t)max_blocks_per_seq * block_size, head_dim);
+  args.order_keys = hydra::paged::order_keys(batch, (int64_t)batch * n_kv_heads, (int64_t)max_blocks_per_seq * block_size, head_dim, tile_wgs);
   const bool decode_only = (int64_t)max_q_len * args.group <= hydra::paged::kDecodeRows && block_size >= hydra::paged::kDecodeMinBlock;
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;

@@ -500,6 +500,14 @@ ORDER_CASES = [
     (_mix([1 + 3 * i % 500 for i in range(200)], [(64, 1024), (33, 40)] * 4), 8, 4, 128, 4096),
     (_mix([1900, 40, 700, 2500], [(40, 300), (9, 11)]), 2, 1, 64, 0),                   # split contexts
     (_mix([600, 40, 700, 30] * 20, [(40, 300)]), 8, 1, 64, 0),                          # 81 pairs, contexts cut in batch order
+    # no chunks: 280 pairs on both sides of 140 keys, 240 pairs, 1040 pairs, and few pairs whose contexts are cut
+    (([5] * 70, [5 + 2 * i % 136 for i in range(69)] + [140]), 16, 4, 128, 0),
+    (([5] * 70, [5 + 2 * i % 136 for i in range(69)] + [141]), 16, 4, 128, 0),
+    (([5] * 70, [5 + 2 * i % 136 for i in range(69)] + [141]), 16, 4, 128, 4096),
+    (([5] * 60, [5 + 7 * i % 400 for i in range(60)]), 16, 4, 128, 0),
+    (([2] * 130, [2 + 7 * i % 500 for i in range(130)]), 16, 8, 80, 0),
+    (([1] * 130, [7 * i % 90 + 1 for i in range(129)] + [700]), 16, 8, 80, 4096),
+    (([3, 0, 3, 3], [2000, 50, 3, 900]), 7, 1, 128, 0),
 ]
 
 
