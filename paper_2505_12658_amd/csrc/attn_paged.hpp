@@ -1167,14 +1167,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
 // Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch, parts), kCombineThreads threads;
 // parts: as many as give every thread 4 output columns of one row, for the most rows a request of the batch can have.
 // Requests that took the wave-tile form, have no new tokens, or whose context fits one share (already finished by one
-// workgroup) are skipped.  A thread adds up its columns over the shares.  It runs on an idle chip, and latency is all it costs,
-// most of it launch and instruction fetch; so it asks for everything it needs at once, the records of all shares of the launch
-// (whose places follow from the grid) together with the lengths that say which of them exist: one round trip to memory.
-// Records behind the lengths and now, us of both kernels, 28 / 4 heads of 128: 4 decode steps of 300 .. 1500 tokens 7.84 -> 7.65, 1 of
-// 5000 10.17 -> 9.81, 12 of 1000 .. 3700 16.5 -> 16.1, 8 of 16 384 and 30 of 100 .. 1400 equal; with the caches and the workspace out of
-// every cache 12.74 -> 12.65, 14.80 -> 14.48, 21.5 -> 21.2 (records that no share wrote are read all the same).
-// With one workgroup per (request, KV head) a request of more than 8 rows of 128 took its trips two to four times: 30 requests of 4
-// new tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2, 28 / 2 heads, 18.9 -> 15.9.
+// workgroup) are skipped.  A thread adds up its columns over the shares; it asks for everything it needs (every share's row
+// statistics and columns) before it uses any of it, so that behind the two lengths the kernel is one round trip to memory
+// long: it runs on an idle chip, and latency is all it costs (3.8 us after a decode of 4 requests, 4.6 us after one of
+// 8 x 16 384 keys, most of it launch and instruction fetch).  With one workgroup per (request, KV head) a request of more than
+// 8 rows of 128 took that trip two to four times: 30 requests of 4 new tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2,
+// 28 / 2 heads, 18.9 -> 15.9; decode steps unchanged.
+// The records of all shares asked for together with the lengths, whether they exist or not, cost what they gave: one request of 6000
+// tokens 10.9 -> 10.5 us of both kernels, 4 of 50 .. 300 under a table of 8192 keys 7.3 -> 7.1, but of contexts that are not cut 40 of
+// 100 .. 500 under such a table 9.3 -> 10.1, 16 of 50 .. 400 7.9 -> 8.4 (out of the caches 12.1 -> 13.6).
 constexpr int kMaxSplits = 16;
 constexpr int kCombineThreads = 256;
 
@@ -1183,32 +1184,9 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
 #if defined(__HIP_DEVICE_COMPILE__)
   const int b = blockIdx.y, kv_head = blockIdx.x;
   const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
-  int q_start = cu[b], q_end = cu[b + 1], kv_len = lens[b];
-  const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
-  constexpr int kColGroups = D / 4;
-  int i = (int)blockIdx.z * kCombineThreads + (int)threadIdx.x;
-  int row, col;
-  f32x4_t v[kMaxSplits];
-  float top[kMaxSplits], sum[kMaxSplits];
-  // (shares past the launch's last one re-read it: no branch between the loads.  What a share that this context does not have, or a
-  // row that the request does not have, left there is loaded too, and left out below.)
-  auto load = [&]() {
-    row = i / kColGroups;
-    col = (i - row * kColGroups) * 4;
-    const int at = row < kRows ? row : kRows - 1;
-#pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s) {
-      const float* rec = recs + (int64_t)(s < a.n_splits ? s : a.n_splits - 1) * kPartialFloats<D>;
-      top[s] = rec[at];
-      sum[s] = rec[kRows + at];
-      v[s] = *reinterpret_cast<const f32x4_t*>(rec + 2 * kRows + at * D + col);
-    }
-  };
-  if (a.most_rows < kRows && i >= a.most_rows * kColGroups) return;  // (of a row that no request has)
-  load();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" : "+s"(q_start), "+s"(q_end), "+s"(kv_len));  // (asked for together)
-  const int q_len = q_end - q_start;
+  const int q_start = cu[b];
+  const int q_len = cu[b + 1] - q_start;
+  int kv_len = lens[b];
   const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;
   if (kv_len > table_keys) kv_len = (int)table_keys;
   if (q_len <= 0 || kv_len < q_len || q_len * a.group > kRows) return;
@@ -1217,15 +1195,28 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
   int per_share, n_shares;
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   if (n_shares == 1) return;  // done by one workgroup, which wrote the output itself
-  while (i < n_rows * kColGroups) {
+  const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
+  constexpr int kColGroups = D / 4;
+  for (int i = (int)blockIdx.z * kCombineThreads + (int)threadIdx.x; i < n_rows * kColGroups; i += (int)gridDim.z * kCombineThreads) {
+    const int row = i / kColGroups, col = (i - row * kColGroups) * 4;
+    f32x4_t v[kMaxSplits];
+    float top[kMaxSplits], sum[kMaxSplits];
+    // (shares past the last one re-read it and are left out below: no branch between the loads)
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+      const float* rec = recs + (int64_t)(s < n_shares ? s : n_shares - 1) * kPartialFloats<D>;
+      top[s] = rec[row];
+      sum[s] = rec[kRows + row];
+      v[s] = *reinterpret_cast<const f32x4_t*>(rec + 2 * kRows + row * D + col);
+    }
     float best = top[0];
 #pragma unroll
-    for (int s = 1; s < kMaxSplits; ++s) best = fmaxf(best, s < n_shares ? top[s] : top[0]);
+    for (int s = 1; s < kMaxSplits; ++s) best = fmaxf(best, top[s]);
     float total = 0.f;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kMaxSplits; ++s) {
-      // (not by weight 0 alone: a share that does not exist may hold anything, an infinite V of the last one among it)
+      // (not by weight 0 alone: an infinite V in the last share would come out as NaN)
       const bool live = s < n_shares;
       const float w = live ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
       total += w * (live ? sum[s] : 0.f);
@@ -1239,8 +1230,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
     u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
                   __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2_t))};
     *reinterpret_cast<u32x2_t*>(a.out + ((int64_t)(q_start + token) * a.n_q_heads + head) * D + col) = pk;
-    i += (int)gridDim.z * kCombineThreads;
-    if (i < n_rows * kColGroups) load();
   }
 #else
   (void)a;

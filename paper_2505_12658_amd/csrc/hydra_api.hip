@@ -166,7 +166,7 @@ int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t til
 // Launches of attn_paged_fwd for one head dimension: the decode kernel when no request of the batch has more rows than
 // its form takes, otherwise the kernel that holds all forms; then the merge of split contexts.
 template <int D>
-hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, unsigned rows_wgs, unsigned tile_wgs, hipStream_t s) {
+hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t max_q_len, bool decode_only, unsigned rows_wgs, unsigned tile_wgs, hipStream_t s) {
   hipError_t err;
   bool launched = false;
   if constexpr (hydra::paged::kDecodeForm<D>) {
@@ -190,7 +190,8 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, bool decode_only, u
     err = launch(hydra::paged::attn_paged_kernel<D>, dim3(grid), dim3(256), s, args);
   }
   if (err == hipSuccess && args.n_splits > 1) {
-    const int64_t pieces = (int64_t)(args.most_rows < hydra::paged::kRows ? args.most_rows : hydra::paged::kRows) * (D / 4);
+    const int64_t rows = (int64_t)max_q_len * args.group;
+    const int64_t pieces = (rows < hydra::paged::kRows ? rows : hydra::paged::kRows) * (D / 4);
     const unsigned parts = (unsigned)((pieces + hydra::paged::kCombineThreads - 1) / hydra::paged::kCombineThreads);
     err = launch(hydra::paged::attn_paged_combine_kernel<D>, dim3((unsigned)args.n_kv_heads, (unsigned)args.batch, parts), dim3(hydra::paged::kCombineThreads), s, args);
   }
@@ -487,8 +488,6 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   if ((int64_t)max_q_len * args.group <= hydra::paged::kRows) groups = 0;  // every request takes the packed-rows form
   args.partials = static_cast<float*>(workspace);
   args.batch = batch;
-  const int64_t most_rows = (int64_t)max_q_len * args.group;
-  args.most_rows = (int32_t)(most_rows < 0x7fffffff ? most_rows : 0x7fffffff);
   // Workgroups of the wave-tile form: one per group of four wave tiles and KV head.  The request lengths are
   // on the device, so this is an upper bound from the total: a request of q new tokens has at most
   // (q / 32 + 1) * group / 4 + 1 groups.
@@ -512,9 +511,9 @@ int hydra_attn_paged_fwd(const void* q, void* out, int64_t q_token_stride, const
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t err;
   switch (head_dim) {
-    case 64: err = launch_paged<64>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
-    case 80: err = launch_paged<80>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
-    default: err = launch_paged<128>(args, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    case 64: err = launch_paged<64>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    case 80: err = launch_paged<80>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
+    default: err = launch_paged<128>(args, max_q_len, decode_only, (unsigned)rows_wgs, (unsigned)tile_wgs, s); break;
   }
   return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
 }

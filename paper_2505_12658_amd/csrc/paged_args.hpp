@@ -34,7 +34,6 @@ struct PagedArgs {
   int32_t least_log2;
   float* partials;  // [batch, n_kv_heads, n_splits] records of kPartialFloats<D> floats
   int32_t batch;
-  int32_t most_rows;   // (new tokens x grouped heads) of a request at most, as the caller says
   int32_t n_tile_wgs;  // workgroups that the grid has for the wave-tile form (an upper bound from the host)
   int32_t order_keys;  // a hybrid batch with a context of more keys is taken by its contexts (0: whatever they are, kNeverOrdered: not at all)
 };
