@@ -39,6 +39,7 @@ constexpr int kWorkgroupsPerCu = D == 64 ? 3 : 2;
 // 856 -> 793, 25 000 296 -> 272, 12 000 122.6 -> 115.0, 6 000 81.8 -> 75.1, 2 500 and fewer (one item per compute unit) equal.
 template <int D>
 constexpr int kDirectPerCu = D <= 80 ? 3 : 2;
+constexpr int kLdsPerUnit = 160 * 1024;  // bytes
 
 // One work-list entry, written by the device prepass from cu_seqlens; it carries everything the
 // kernel needs, so a workgroup starts its loads after a single dependent read.
@@ -108,7 +109,7 @@ __device__ __forceinline__ int v_swizzle(int row, int chunk) {
 }
 
 // Items of one (sequence, KV head).
-__device__ __forceinline__ int items_of_sequence(int len, int group) {
+__host__ __device__ __forceinline__ int items_of_sequence(int len, int group) {
   const int tok_tiles = (len + kWaveTileRows - 1) / kWaveTileRows;
   return (tok_tiles * group + kWavesPerItem - 1) / kWavesPerItem;
 }

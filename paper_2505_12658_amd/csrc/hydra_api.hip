@@ -99,14 +99,33 @@ bool direct_form(int32_t head_dim, size_t capacity, unsigned compute_units) {
 bool list_free(int32_t batch, int32_t head_dim, size_t capacity, unsigned compute_units) {
   return batch <= hydra::kDirectSeqs && within_rounds(kListFreeRounds, head_dim, capacity, compute_units);
 }
+// Whether a batch at head_dim 80 has about four items of short sequences per compute unit: then two of its workgroups share a unit
+// instead of three, which would leave the fourth alone with the unit's SIMDs.  Items are exact where all sequences have max_seqlen
+// tokens, and an average otherwise (half a wave tile and three eighths of an item of every sequence are padding).
+// us with three and with two, causal: 28 / 4 heads, sequences of 272 tokens, 832 items 17.9 and 17.2, 896 19.7 and 17.3, 960 20.5 and 18.2;
+// of 384, 840 20.7 and 19.3, 924 22.8 and 19.9; 16 heads, of 256, 800 21.9 and 22.0, 864 23.3 and 22.7, 992 26.9 and 23.1, 1056 27.1 and
+// 27.4; of 64 .. 448, 896 23.0 and 20.4; of 384, 864 23.6 and 23.1, 1056 26.5 and 28.6 (8 heads).  Bidirectional, where the items differ less:
+// 28 / 4 heads of 272, 832 21.9 and 22.7, 896 equal, 1024 24.0 and 23.2; 16 heads, of 64 .. 448, 896 26.9 and 24.9, 976 26.7 and 24.1;
+// but of 384 tokens with 28 / 4 heads 924 25.0 and 26.2.
+bool four_short_items(bool causal, int32_t batch, int32_t total_tokens, int32_t max_seqlen, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
+  const float most_tokens = causal ? 400.0f : 300.0f, least_items = causal ? 3.15f : 3.3f;
+  const float seqs = (float)batch, kv_heads = (float)n_kv_heads, units = (float)compute_units;
+  if ((float)total_tokens > most_tokens * seqs) return false;
+  const int32_t group = n_q_heads / n_kv_heads;
+  float items = kv_heads * ((float)group * ((float)total_tokens / hydra::kWaveTileRows + 0.5f * seqs) / hydra::kWavesPerItem + 0.375f * seqs);
+  if ((int64_t)max_seqlen * batch == total_tokens) items = kv_heads * seqs * (float)hydra::items_of_sequence(max_seqlen, group);
+  return items > least_items * units && items <= 4.0f * units;
+}
 // (grid: as many workgroups as there can be items, and as take_entry asks for; their order takes care of how the items spread
 // over the dies)
 template <int D>
-hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, int32_t batch, int32_t n_kv_heads, size_t capacity, hipStream_t stream) {
+hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, int32_t batch, int32_t n_kv_heads, size_t capacity, bool two_per_unit, hipStream_t stream) {
   constexpr size_t kLeast = hydra::kXcds * hydra::kDieUnits;
   const dim3 grid((unsigned)(capacity > kLeast || n_kv_heads % hydra::kXcds == 0 ? capacity : kLeast));
-  return causal ? launch(hydra::attn_fwd_direct_kernel<D, true>, grid, dim3(256), stream, args, batch, n_kv_heads)
-                : launch(hydra::attn_fwd_direct_kernel<D, false>, grid, dim3(256), stream, args, batch, n_kv_heads);
+  // (LDS that is asked for and not used, so that a third workgroup does not fit)
+  constexpr size_t kThird = hydra::kLdsPerUnit / 3;
+  const size_t pad = two_per_unit && hydra::TileGeom<D>::kLdsBytes < kThird ? kThird - hydra::TileGeom<D>::kLdsBytes : 0;
+  return launch_lds(causal ? hydra::attn_fwd_direct_kernel<D, true> : hydra::attn_fwd_direct_kernel<D, false>, grid, dim3(256), pad, stream, args, batch, n_kv_heads);
 }
 
 // Bytes of one partial result of the paged kernel's packed-rows form.
@@ -339,10 +358,11 @@ int launch_packed(const void* q, const void* k, const void* v, void* out, int64_
   hipError_t err;
   if (workgroups_per_cu == 0 && (!with_list || direct_form(head_dim, lay.capacity, cus))) {
     const int32_t seqs = with_list ? 0 : batch;
+    const bool two = head_dim == 80 && four_short_items(causal != 0, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads, cus);
     switch (head_dim) {
-      case 64: err = launch_direct<64>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
-      case 80: err = launch_direct<80>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
-      default: err = launch_direct<128>(causal != 0, args, seqs, n_kv_heads, lay.capacity, s); break;
+      case 64: err = launch_direct<64>(causal != 0, args, seqs, n_kv_heads, lay.capacity, false, s); break;
+      case 80: err = launch_direct<80>(causal != 0, args, seqs, n_kv_heads, lay.capacity, two, s); break;
+      default: err = launch_direct<128>(causal != 0, args, seqs, n_kv_heads, lay.capacity, false, s); break;
     }
     return err == hipSuccess ? HYDRA_OK : HYDRA_ERR_LAUNCH;
   }

@@ -591,6 +591,32 @@ def test_numbers_of_the_wrong_kind():
     assert torch.equal(out.view(torch.int16), want.view(torch.int16))
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,causal", [
+    ([256] * 30, 16, 16, False),                                    # 960 items, counted from max_seqlen
+    ([256] * 27, 16, 16, False),                                    # 864: just past the least for bidirectional batches
+    ([256] * 25, 16, 16, True),                                     # 800: three workgroups
+    ([256] * 26, 16, 16, True),                                     # 832: two
+    ([384] * 11, 28, 4, False),                                     # 924, too long where nothing is masked
+    ([40 + 13 * i % 400 for i in range(50)], 14, 2, True),          # an estimate
+    ([256] * 32, 16, 16, True),                                     # 1024
+])
+def test_four_short_items_per_unit(lengths, hq, hkv, causal):
+    """Batches at head_dim 80 on both sides of the rule that keeps a third workgroup off the compute units: every row is there,
+    with a list and without, and the bits do not depend on it (a looser bound on the lengths turns the count into an estimate)."""
+    hydra = _hydra()
+    w = si.Workload("short", lengths, hq, hkv, 80, causal, seed=len(lengths))
+    q, k, v = (t.to("cuda:0") for t in si.make_qkv(w))
+    cu = torch.from_numpy(w.cu_seqlens).to("cuda:0")
+    out = hydra.hydra_attn_varlen_fwd(q, k, v, cu, w.max_seqlen, causal, w.softmax_scale)
+    loose = hydra.hydra_attn_varlen_fwd(q, k, v, cu, 3 * w.max_seqlen, causal, w.softmax_scale)
+    ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, w.max_seqlen, hq, hkv, 80, causal)
+    listed = torch.empty_like(out)
+    hydra.hydra_attn_varlen_fwd_prebuilt(q, k, v, cu, w.max_seqlen, causal, w.softmax_scale, listed, ws)
+    torch.cuda.synchronize()
+    _check(out, reference.attn_varlen(_f64(q.cpu()), _f64(k.cpu()), _f64(v.cpu()), w.cu_seqlens, causal, w.softmax_scale))
+    assert torch.equal(out.view(torch.int16), loose.view(torch.int16)) and torch.equal(out.view(torch.int16), listed.view(torch.int16))
+
+
 def _work_list(lengths, hq, hkv, d, causal):
     """The work list as csrc/worklist.hpp describes it: entries (first token, length, first wave tile, KV head) of the eight queues."""
     group = hq // hkv
