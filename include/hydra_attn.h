@@ -125,6 +125,9 @@ int hydra_attn_varlen_fwd_prebuilt(const void* q, const void* k, const void* v, 
  *   workgroups_per_cu  >= 1 (otherwise HYDRA_ERR_INVALID_ARG); values above the kernel's own number
  *        (3 at head_dim 64, else 2) mean that number.  With 1, half (two thirds at head_dim 64) of every
  *        compute unit's registers and most of its LDS stay free for the other stream's kernels.
+ *        Batches of so few tokens that there is a compute unit for every 64 rows of a KV head's queries
+ *        run with one workgroup per compute unit at most whatever the value; it holds no more of
+ *        the registers than above, and 68, 93 or 132 KB of LDS at head_dim 64, 80 and 128.
  *
  * Results are bit-identical to hydra_attn_varlen_fwd_prebuilt for every value (work items are
  * independent; only their placement changes).  Everything else as for hydra_attn_varlen_fwd_prebuilt.

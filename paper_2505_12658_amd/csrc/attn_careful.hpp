@@ -57,10 +57,10 @@ __device__ __forceinline__ void issue_kv_tile_loads(const AttnArgs& a, uint32_t 
 // none of them is still in flight, or it would make the LDS reads of the packed kernel's hot loop wait for them.
 __device__ __forceinline__ void wait_for_tile_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// One work item, by one workgroup of 4 waves.  `lds`: LDS byte address of StageGeom<D>::kLdsBytes bytes that
+// One work item (of TILES wave tiles), by one workgroup of WAVES waves, of which the first four work.  `lds`: LDS byte address of StageGeom<D>::kLdsBytes bytes that
 // nothing else uses meanwhile (no load into them in flight).  Called by all threads of the workgroup; ends
 // with every wave's loads complete and a barrier.
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int TILES = kWavesPerItem, int WAVES = 4>
 __device__ __forceinline__ void run_item(const AttnArgs& a, int64_t seq_start, int seq_len, int f0, int kv_head, uint32_t lds) {
   using G = StageGeom<D>;
   constexpr int KS = G::kQkSteps;
@@ -81,18 +81,18 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, int64_t seq_start, i
 
   // this wave's tile
   int f = f0 + wave;
-  const bool active = f < n_wave_tiles;
-  if (!active) f = n_wave_tiles - 1;
+  const bool active = f < n_wave_tiles && wave < TILES;
+  if (!active) f = f < n_wave_tiles ? f : n_wave_tiles - 1;
   const int tok_tile = f / a.group;
   const int head = kv_head * a.group + (f - tok_tile * a.group);
   const int q0 = tok_tile * kRows;
-  const int f_last = (f0 + kWavesPerItem - 1 < n_wave_tiles ? f0 + kWavesPerItem - 1 : n_wave_tiles - 1);
+  const int f_last = (f0 + TILES - 1 < n_wave_tiles ? f0 + TILES - 1 : n_wave_tiles - 1);
   // K/V tiles the workgroup streams, and those this wave uses (keys below q0 + 32 under the causal mask)
   const int tiles_wg = CAUSAL ? ((f_last / a.group + 1) * kRows + kKvTileRows - 1) / kKvTileRows : n_kv_tiles;
   const int tiles_wave = active ? (CAUSAL ? (q0 + kRows + kKvTileRows - 1) / kKvTileRows : n_kv_tiles) : 0;
 
   // first K/V tile in flight before anything else
-  issue_kv_tile_loads<D>(a, lds, wave, lane, seq_start, seq_len, kv_head, 0);
+  if (WAVES == 4 || wave < 4) issue_kv_tile_loads<D>(a, lds, wave, lane, seq_start, seq_len, kv_head, 0);
 
   // Q fragments (B operand): lane (m, hf) holds query row q0 + m, columns hf*D/2 + 8*s .. +7
   bf16x8_t qf[KS];
@@ -131,7 +131,7 @@ __device__ __forceinline__ void run_item(const AttnArgs& a, int64_t seq_start, i
 
   for (int t = 0; t < tiles_wg; ++t) {
     const uint32_t stage = lds + (t & 1) * G::kStageBytes;
-    if (t + 1 < tiles_wg)
+    if (t + 1 < tiles_wg && (WAVES == 4 || wave < 4))
       issue_kv_tile_loads<D>(a, lds + ((t + 1) & 1) * G::kStageBytes, wave, lane, seq_start, seq_len, kv_head, (t + 1) * kKvTileRows);
 
     if (t < tiles_wave) {

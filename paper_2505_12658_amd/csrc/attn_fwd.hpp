@@ -40,7 +40,8 @@
 
 namespace hydra {
 
-template <int D>
+// TEAMS: sets of rings, one for each team of waves that works on a part of an item's keys.
+template <int D, int TEAMS = 1, int STAGE_ROWS = 0>
 struct TileGeom : RowGeom<D> {
   using RowGeom<D>::kTileBytes;
   // K tiles and V tiles each live in a ring of kRing LDS tiles; loads run kRing - 1 tiles ahead of use
@@ -54,8 +55,12 @@ struct TileGeom : RowGeom<D> {
   // address register each for that block, so that the area is one tile long and three workgroups fit a compute unit's LDS.
   static constexpr bool kSumsFromMatrixUnit = D == 80;
   static constexpr int kOnesBytes = kSumsFromMatrixUnit ? 9 * 1024 : 0;
-  static constexpr int kOnesAt = 2 * kRing * kTileBytes + 64;    // (+ slack behind the last V tile)
-  static constexpr int kLdsBytes = kOnesAt + kOnesBytes;
+  static constexpr int kTeamBytes = 2 * kRing * kTileBytes;         // K ring, V ring
+  static constexpr int kOnesAt = TEAMS * kTeamBytes + 64;           // (+ slack behind the last V tile)
+  static constexpr int kSumsAt = kOnesAt + kOnesBytes;              // the teams' references and sums, 512 bytes per wave tile
+  static constexpr int kSumsBytes = TEAMS > 1 ? TEAMS * kWavesPerItem * 512 : 0;
+  static constexpr int kQueriesAt = (kSumsAt + kSumsBytes + 1023) / 1024 * 1024;  // STAGE_ROWS rows of Q
+  static constexpr int kLdsBytes = STAGE_ROWS > 0 ? kQueriesAt + STAGE_ROWS * RowGeom<D>::kRowBytes : kSumsAt + kSumsBytes;
 };
 
 // Everything below uses gfx950-only types and builtins, so the host pass of hipcc only sees the
@@ -75,26 +80,29 @@ struct TileGeom : RowGeom<D> {
 // before the one that reads them, followed by the workgroup barrier.  Nothing relies on the order
 // in which direct-to-LDS loads complete: a load that misses to HBM was observed to land after a
 // younger one that hit in L2.
-template <int D>
+// WAVES: how many waves share a tile's loads; wave w of them issues loads w, w + WAVES, ...
+template <int D, int WAVES = kWavesPerItem>
 struct TileLoader {
   using G = TileGeom<D>;
-  static constexpr int kPerWave = (G::kLoadInstr + 3) / 4;
-  // When four load instructions cover a whole number of rows, the lane offsets of a wave's loads
+  static constexpr int kPerWave = (G::kLoadInstr + WAVES - 1) / WAVES;
+  // Where kPeriod of a wave's loads cover a whole multiple of 16 rows, lane offsets of loads kPeriod apart
   // differ by a constant (the swizzle repeats), which also goes into the scalar offset:
-  // one offset register instead of kPerWave.
-  static constexpr bool kUniformStep = (4 * 64) % G::kChunks == 0 && ((4 * 64) / G::kChunks) % 16 == 0;
-  static constexpr int kOffsets = kUniformStep ? 1 : kPerWave;
+  // kPeriod offset registers instead of kPerWave.
+  static constexpr int repeats_after(int loads) { return (loads * WAVES * 64) % (16 * G::kChunks) == 0 || loads >= kPerWave ? loads : repeats_after(loads + 1); }
+  static constexpr int kPeriod = repeats_after(1);
+  static constexpr bool kUniformStep = kPeriod == 1;
+  static constexpr int kOffsets = kPeriod;
   u32x4_t rsrc;                 // the sequence's rows of this KV head, from the first row to the end of the last
   uint32_t tile_off;            // bytes from the first row of the sequence to the first row of the next tile
   uint32_t tile_stride;         // bytes between first rows of consecutive tiles
   uint32_t lane_off[kOffsets];  // bytes from the first row of a tile
-  uint32_t step_bytes;          // kUniformStep: bytes between the rows of consecutive loads of this wave
+  uint32_t step_bytes;          // bytes between the rows of loads of this wave that are kPeriod apart
   int wave;
 
   template <bool IS_V>
   __device__ __forceinline__ void init(const uint16_t* base, int64_t stride, int64_t seq_start, int seq_len, int kv_head, int wave_, int lane) {
     wave = wave_;
-    __builtin_assume(wave >= 0 && wave < kWavesPerItem);
+    __builtin_assume(wave >= 0 && wave < WAVES);
     const uint32_t row_bytes = (uint32_t)(stride * 2);
     const uint64_t first_row = (uint64_t)(uintptr_t)(base + seq_start * stride + kv_head * D);
     rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)first_row);
@@ -103,10 +111,10 @@ struct TileLoader {
     rsrc[3] = 0x00020000u;
     tile_off = 0;
     tile_stride = __builtin_amdgcn_readfirstlane((uint32_t)kKvTileRows * row_bytes);
-    step_bytes = __builtin_amdgcn_readfirstlane((uint32_t)((4 * 64) / G::kChunks) * row_bytes);
+    step_bytes = __builtin_amdgcn_readfirstlane((uint32_t)(kPeriod * WAVES * 64 / G::kChunks) * row_bytes);
 #pragma unroll
     for (int u = 0; u < kOffsets; ++u) {
-      const int flat = (wave + 4 * u) * 64 + lane;
+      const int flat = (wave + WAVES * u) * 64 + lane;
       const int row = flat / G::kChunks, phys = flat % G::kChunks;
       const int chunk = IS_V ? v_swizzle<D>(row, phys) : k_swizzle<D>(row, phys);
       lane_off[u] = (uint32_t)row * row_bytes + chunk * 16;
@@ -115,14 +123,14 @@ struct TileLoader {
   // Issues load u (0 .. kPerWave - 1) of this wave's share of the next tile; lds_dst: LDS byte address
   // of the tile's ring slot.
   __device__ __forceinline__ void issue_piece(int u, uint32_t lds_dst) const {
-    const int instr = wave + 4 * u;
+    const int instr = wave + WAVES * u;
     if (instr < G::kLoadInstr) {
       // (m0 is reserved: the compiler only ever sets it immediately before an instruction of its own that reads it)
       const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_dst + instr * 1024);
-      const uint32_t soff = __builtin_amdgcn_readfirstlane(tile_off + (kUniformStep ? (uint32_t)u * step_bytes : 0u));
+      const uint32_t soff = __builtin_amdgcn_readfirstlane(tile_off + (uint32_t)(u / kPeriod) * step_bytes);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                    :
-                   : "s"(m0), "v"(lane_off[kUniformStep ? 0 : u]), "s"(rsrc), "s"(soff));
+                   : "s"(m0), "v"(lane_off[u % kPeriod]), "s"(rsrc), "s"(soff));
     }
   }
   // Issues all of this wave's loads of the next tile at once and moves on to the tile after it.
@@ -269,15 +277,25 @@ constexpr float kMaxRowSum = 1.0995116e12f;  // 2^40: largest row sum (relative 
 // attn_paged.hpp for that source).
 struct PackedSource {
   static constexpr bool kPaged = false, kOneItem = false;
+  static constexpr int kTeams = 1, kTiles = kWavesPerItem;
+  static constexpr int kLoaders = 0, kStageRows = 0;
   template <int D>
   static constexpr int kWavesPerSimd = kWorkgroupsPerCu<D>;  // that the kernel is built for
   template <int D>
   struct Gather {};  // (the paged source's K/V gatherer; the packed rows use two TileLoaders)
 };
+// TEAMS: 2 where the keys of an item are divided between two teams of waves; LOADERS: waves of each team that do nothing but load
+// tiles (see attn_fwd_direct_kernel).
+template <int TEAMS, int LOADERS>
 struct DirectSource {
   static constexpr bool kPaged = false, kOneItem = true;
+  static constexpr int kTeams = TEAMS, kTiles = kWavesPerItem / TEAMS, kLoaders = LOADERS;
+  static constexpr int kStageRows = LOADERS > 0 && kTiles > 2 ? kTiles * kWaveTileRows : 0;
+  static constexpr int kThreads = 64 * TEAMS * (kTiles + LOADERS);
+  // (what the compiler is told: two teams without loading waves are for calls that leave half of the registers to others)
+  static constexpr int kBound = TEAMS == 2 ? 512 : kThreads;
   template <int D>
-  static constexpr int kWavesPerSimd = kDirectPerCu<D>;
+  static constexpr int kWavesPerSimd = TEAMS == 1 && LOADERS == 0 ? kDirectPerCu<D> : 2;
   template <int D>
   struct Gather {};
   int64_t q_start;   // first token of the sequence
@@ -292,7 +310,9 @@ struct DirectSource {
 // recomputes the item with its own careful routine).
 template <int D, bool CAUSAL, class Src>
 __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src, unsigned char* smem, int* s_claim, int* s_redo) {
-  using G = TileGeom<D>;
+  constexpr int TEAMS = Src::kTeams, WT = Src::kTiles;  // teams of WT waves, one per wave tile of the item
+  constexpr int kLoaders = Src::kLoaders;               // more waves per team that load its K (one half) and its V tiles (the other)
+  using G = TileGeom<D, TEAMS, Src::kStageRows>;
   constexpr int KS = G::kQkSteps;
   constexpr int CC = G::kPvChunks;
   constexpr int ROWB = G::kRowBytes;
@@ -301,19 +321,22 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   constexpr int PF = kFragsAhead<Src::template kWavesPerSimd<D>>;
   // LDS: K ring then V ring; tile t of either lives in ring slot t % kRing.
   constexpr int R = G::kRing, PD = G::kPrefetch;
-  const uint32_t k_ring = (uint32_t)(uintptr_t)HYDRA_LDS_PTR(smem);  // LDS byte addresses
-  const uint32_t v_ring = k_ring + R * G::kTileBytes;
-
   const int lane_id = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool loader_wave = kLoaders > 0 && wave >= TEAMS * WT;
+  const int team = TEAMS == 1 ? 0 : loader_wave ? (wave - TEAMS * WT) / (kLoaders > 0 ? kLoaders : 1) : wave / WT, wave_tile = TEAMS == 1 ? wave : wave % WT;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)HYDRA_LDS_PTR(smem);  // LDS byte addresses
+  const uint32_t k_ring = lds0 + team * G::kTeamBytes;
+  const uint32_t v_ring = k_ring + R * G::kTileBytes;
+
   const int die = (int)blockIdx.x % kXcds;  // the die this workgroup runs on, whose queue is its own
   // s_redo: an item whose exponentials left the fast path's range: {flag, first token, length, first wave tile, KV
   // head}, posted by the waves that noticed, acted upon by the whole workgroup at the top of its next round.
   if (threadIdx.x == 0) s_redo[0] = 0;
   if constexpr (G::kSumsFromMatrixUnit) {
     static_assert(kKvTileRows * ROWB - 8 * ROWB + 8 <= G::kOnesBytes, "a V fragment read stays inside the ones");
-    for (int i = threadIdx.x * 16; i < G::kOnesBytes; i += 256 * 16)
-      *reinterpret_cast<u32x4_t*>(HYDRA_LDS_BYTE(k_ring + G::kOnesAt + i)) = u32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    for (int i = threadIdx.x * 16; i < G::kOnesBytes; i += (int)blockDim.x * 16)
+      *reinterpret_cast<u32x4_t*>(HYDRA_LDS_BYTE(lds0 + G::kOnesAt + i)) = u32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
   }
 
   // Wave 0 claims the items for the whole workgroup, one round ahead: the claim for the next
@@ -347,10 +370,12 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // an item's last iteration until the barrier before the next item's first key block.  The loads
   // of the NEXT item are issued as soon as the current item's last iteration is over, ahead of the
   // epilogue, so that their latency hides behind it.
-  static_assert(kWavesPerItem * kWaveTileRows * ROWB <= R * G::kTileBytes, "the Q tiles of the four waves fit the V ring");
+  static_assert(WT * kWaveTileRows * ROWB <= R * G::kTileBytes, "the Q tiles of a team's waves fit its V ring");
   constexpr int kRowInstr = kWaveTileRows * G::kChunks / 64;  // 64-lane instructions that cover a 32-row tile
   static_assert(kWaveTileRows * G::kChunks % 64 == 0, "whole instructions");
-  const uint32_t q_stage = v_ring + wave * (kWaveTileRows * ROWB);
+  // (with waves of their own for the loads the first V tile is on its way at the same time, into slot 0)
+  const uint32_t q_stage = (Src::kStageRows > 0 ? lds0 + G::kQueriesAt : lds0 + R * G::kTileBytes + (kLoaders > 0 ? G::kTileBytes : 0)) + wave_tile * (kWaveTileRows * ROWB);
+  static_assert(kLoaders == 0 || WT * kWaveTileRows * ROWB <= G::kTileBytes || Src::kStageRows == WT * kWaveTileRows, "... and slot 1");
   auto issue_q_loads = [&](int64_t seq_start, int seq_len, int q0, int head, int lane) {
     const uint64_t base = (uint64_t)(uintptr_t)(a.q + (seq_start + q0) * a.q_stride + head * D);
     const uint32_t q_row_bytes = (uint32_t)(a.q_stride * 2);
@@ -361,11 +386,13 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     rsrc[2] = __builtin_amdgcn_readfirstlane((uint32_t)(rows - 1) * q_row_bytes + D * 2);  // rows past the end arrive as zeros
     rsrc[3] = 0x00020000u;
 #pragma unroll
-    for (int i = 0; i < kRowInstr; ++i) {
-      const int flat = i * 64 + lane;
+    for (int i = 0; i < (kRowInstr + TEAMS - 1) / TEAMS; ++i) {
+      const int instr = i * TEAMS + team;  // (teams share the loads of the rows that they share)
+      if (TEAMS > 1 && instr >= kRowInstr) break;
+      const int flat = instr * 64 + lane;
       const int row = flat / G::kChunks, phys = flat % G::kChunks;
       const uint32_t off = (uint32_t)row * q_row_bytes + k_swizzle<D>(row, phys) * 16;
-      const uint32_t m0 = __builtin_amdgcn_readfirstlane(q_stage + i * 1024);
+      const uint32_t m0 = __builtin_amdgcn_readfirstlane(q_stage + instr * 1024);
       // (nt: Q is read once; marking its lines for early replacement leaves the L2 to the K/V rows that are re-read)
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" : : "s"(m0), "v"(off), "s"(rsrc));
     }
@@ -450,20 +477,26 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   const int n_wave_tiles = n_tok_tiles * a.group;
 
   // this wave's tile
-  int f = f0 + wave;
+  int f = f0 + wave_tile;
   const bool active = f < n_wave_tiles;
   if (!active) f = n_wave_tiles - 1;
   const int tok_tile = f / a.group;
   const int head = kv_head * a.group + (f - tok_tile * a.group);
   const int q0 = tok_tile * kWaveTileRows;
-  const int f_last = (f0 + kWavesPerItem - 1 < n_wave_tiles ? f0 + kWavesPerItem - 1 : n_wave_tiles - 1);
+  const int f_last = (f0 + WT - 1 < n_wave_tiles ? f0 + WT - 1 : n_wave_tiles - 1);
   // KV tiles (of 64 keys) the workgroup streams
   const int n_kv_tiles = (kv_len + kKvTileRows - 1) / kKvTileRows;
   const int causal_keys = shift + (f_last / a.group + 1) * kWaveTileRows;  // keys visible to the item's last query tile
-  const int W = CAUSAL && causal_keys < kv_len ? (causal_keys + kKvTileRows - 1) / kKvTileRows : n_kv_tiles;
-  // key blocks this wave consumes: keys [0, kv_end)
+  const int W_all = CAUSAL && causal_keys < kv_len ? (causal_keys + kKvTileRows - 1) / kKvTileRows : n_kv_tiles;
+  // ... of which this team takes tiles [first_tile, first_tile + W_own); W: the most that a team takes
+  const int W = (W_all + TEAMS - 1) / TEAMS, first_tile = team * W;
+  const int W_own = TEAMS == 1 || first_tile + W <= W_all ? W : (first_tile < W_all ? W_all - first_tile : 0);
+  const int key_base = first_tile * kKvTileRows;  // blocks, masks and limits count from here
+  // key blocks this wave consumes: of the keys [0, kv_end) those of its team's tiles
   const int kv_end = CAUSAL ? (shift + q0 + kWaveTileRows < kv_len ? shift + q0 + kWaveTileRows : kv_len) : kv_len;
-  const int NB = active ? (kv_end + kKeyBlock - 1) / kKeyBlock : 0;
+  int blocks = (kv_end - key_base + kKeyBlock - 1) / kKeyBlock;
+  if constexpr (TEAMS > 1) blocks = blocks < 0 ? 0 : blocks < 2 * W_own ? blocks : 2 * W_own;
+  const int NB = active ? blocks : 0;
 
   // Workgroup iterations: iteration 0 is the prologue (needs K(0)); iteration t >= 1 needs K tile t
   // and V tile t - 1 and runs, per wave, key-block steps 2t - 1 and 2t.  There are W + 1 of them.
@@ -472,23 +505,53 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // issued in iteration t is needed in iteration t + 1, so each iteration ends with a wait for all
   // of the wave's loads and a barrier.
   static_assert(PD == 1 && R == 2, "the iteration-end wait is for everything in flight");
+  if constexpr (kLoaders > 0) {
+    if (loader_wave) {
+      // K tile 0 is the computing waves' own; these start with K tile 1 and V tile 0, ahead of the item's first barrier.
+      constexpr int kEach = kLoaders / 2;
+      const int number = (wave - TEAMS * WT) % kLoaders;
+      const bool is_v = number >= kEach;
+      TileLoader<D, kEach> loader;
+      if (is_v) loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, number % kEach, lane);
+      else loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, number % kEach, lane);
+      const int ahead = is_v ? 0 : 1;  // iteration t loads K tile t + 1, V tile t
+      loader.tile_off = (first_tile + ahead) * loader.tile_stride;
+      const uint32_t ring = is_v ? v_ring : k_ring;
+      if (ahead < W_own) loader.issue_next(ring + ahead * G::kTileBytes);
+      __syncthreads();  // (the one behind K tile 0 and Q)
+      wait_all_loads();
+      __syncthreads();
+      for (int t = 1; t <= W; ++t) {
+        if (t + ahead < W_own) loader.issue_next(ring + ((t + ahead) % R) * G::kTileBytes);
+        wait_all_loads();
+        __syncthreads();
+      }
+      if constexpr (TEAMS > 1) __syncthreads();  // (the one between the teams' results and their sum)
+      break;
+    }
+  }
   // The loaders of the two sources have different shapes: two independent tile loaders for the packed rows, one
   // gatherer for the pages (a V tile comes from the pages its K tile came from one iteration earlier).
-  std::conditional_t<Src::kPaged, int, TileLoader<D>> k_loader, v_loader;
+  std::conditional_t<Src::kPaged, int, TileLoader<D, WT>> k_loader, v_loader;
   typename Src::template Gather<D> gather;
   if constexpr (Src::kPaged) {
     gather.init(src, kv_head, wave, lane);
   } else {
-    k_loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, wave, lane);
-    v_loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, wave, lane);
+    k_loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, wave_tile, lane);
+    v_loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, wave_tile, lane);
+    if constexpr (TEAMS > 1) {
+      k_loader.tile_off = first_tile * k_loader.tile_stride;
+      v_loader.tile_off = first_tile * v_loader.tile_stride;
+    }
   }
   // after the issue of iteration t, tile loads 0 .. 2(t+PD) are out; iteration t needs 0 .. 2t
   auto issue_loads = [&](int t) {
     if constexpr (Src::kPaged) {
       gather.issue(t - 1 + PD < W, v_ring + ((t - 1 + PD) % R) * G::kTileBytes, t + PD < W, k_ring + ((t + PD) % R) * G::kTileBytes);
     } else {
-      if (t - 1 + PD < W) v_loader.issue_next(v_ring + ((t - 1 + PD) % R) * G::kTileBytes);
-      if (t + PD < W) k_loader.issue_next(k_ring + ((t + PD) % R) * G::kTileBytes);
+      if constexpr (kLoaders > 0) return;
+      if (t - 1 + PD < W_own) v_loader.issue_next(v_ring + ((t - 1 + PD) % R) * G::kTileBytes);
+      if (t + PD < W_own) k_loader.issue_next(k_ring + ((t + PD) % R) * G::kTileBytes);
     }
   };
   if constexpr (Src::kPaged) gather.issue_first(k_ring); else k_loader.issue_next(k_ring);
@@ -500,11 +563,12 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   qreg_t qf[QS][KS];
   int q_lim[QS];  // largest visible key index for this lane's query of sub-tile qs
   wait_all_loads();  // Q (and this wave's part of K(0)) has landed
+  if constexpr (TEAMS > 1) __syncthreads();  // ... and the other waves' parts
 #pragma unroll
   for (int qs = 0; qs < QS; ++qs) {
     int row = q0 + 32 * qs + m;
     row = row < seq_len ? row : seq_len - 1;
-    q_lim[qs] = CAUSAL ? shift + row : kv_len - 1;
+    q_lim[qs] = (CAUSAL ? shift + row : kv_len - 1) - key_base;
 #pragma unroll
     for (int s = 0; s < KS; ++s)
       qf[qs][s] = *reinterpret_cast<const qreg_t*>(HYDRA_LDS_BYTE(q_stage + (32 * qs + m) * ROWB + k_swizzle<D>(32 * qs + m, KS * hf + s) * 16));
@@ -526,8 +590,8 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     }
     if constexpr (G::kSumsFromMatrixUnit) {
       // columns 80..95 (the upper 16 of the last block): ones, whichever ring slot is read
-      v_last1 = grp == 1 ? lds_base + G::kOnesAt : v_addr[CC - 1] + G::kTileBytes;
-      if (grp == 1) v_addr[CC - 1] = lds_base + G::kOnesAt;
+      v_last1 = grp == 1 ? lds0 + G::kOnesAt : v_addr[CC - 1] + G::kTileBytes;
+      if (grp == 1) v_addr[CC - 1] = lds0 + G::kOnesAt;
     }
   }
   // The address registers point at slot 0 of both rings from here through the hot loop, whose reads name
@@ -564,7 +628,10 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   float nref[QS];        // -reference * c of this lane's query row
   float row_sum[QS];     // this lane's half of the row sum
 #pragma unroll
-  for (int qs = 0; qs < QS; ++qs) row_sum[qs] = 0.f;
+  for (int qs = 0; qs < QS; ++qs) {
+    row_sum[qs] = 0.f;
+    if constexpr (TEAMS > 1) nref[qs] = -kLowest;  // (a wave tile none of whose keys are this team's)
+  }
 
   // LDS fragment reads; rb = key block inside the tile the address registers point at.
   // (koff / voff: ring slot of the tile, in bytes; constants where it matters, so they end up in the instruction)
@@ -594,7 +661,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
         if (key > q_lim[qs]) S[qs][r] = -__builtin_inff();
     }
   };
-  const int min_lim = CAUSAL ? shift + q0 : kv_len - 1;
+  const int min_lim = (CAUSAL ? shift + q0 : kv_len - 1) - key_base;
   auto needs_mask = [&](int j) { return j * kKeyBlock + kKeyBlock - 1 > min_lim; };
 
   // Softmax of a key block whose S holds the raw scores, in 16 * QS halves of an element pair (pair = half / 2:
@@ -742,15 +809,15 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   using WithQK = std::integral_constant<bool, true>;
   using LastStep = std::integral_constant<bool, false>;
 
-  __syncthreads();  // K(0) is complete; every wave has taken its Q out of the V ring
+  if constexpr (TEAMS == 1 || kLoaders == 0) __syncthreads();  // K(0) is complete; every wave has taken its Q out of the V ring
   // the rest of the prologue loads: V(0) K(1) V(1) ... K(PD)
   if constexpr (Src::kPaged) {
     gather.issue(0 < W, v_ring, 1 < W, k_ring + G::kTileBytes);
   } else {
 #pragma unroll
-    for (int n = 0; n < PD; ++n) {
-      if (n < W) v_loader.issue_next(v_ring + n * G::kTileBytes);
-      if (n + 1 < W) k_loader.issue_next(k_ring + (n + 1) * G::kTileBytes);
+    for (int n = 0; n < (kLoaders > 0 ? 0 : PD); ++n) {
+      if (n < W_own) v_loader.issue_next(v_ring + n * G::kTileBytes);
+      if (n + 1 < W_own) k_loader.issue_next(k_ring + (n + 1) * G::kTileBytes);
     }
   }
 
@@ -951,26 +1018,58 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // next item's first load (issued after the barrier at the top of the next round).  The stores go
   // through a buffer descriptor that ends with the tile's last valid row (rows past it are dropped
   // by the hardware).
-  static_assert(kWavesPerItem * kWaveTileRows * ROWB <= R * G::kTileBytes, "the output tiles of the four waves fit the K ring");
+  static_assert(WT * kWaveTileRows * ROWB <= R * G::kTileBytes, "the output tiles of a team's waves fit its K ring");
+  // Two teams: each has the references, sums and unnormalised outputs of its keys.  They exchange halves of the columns through
+  // their rings, in the order of the registers, and each finishes its half.
+  constexpr int kOut = G::kChunks / TEAMS;  // 16-byte pieces of an output row that a wave finishes
+  float o_mine[kOut][4];                    // (eight columns of a row are with lanes m and m + 32)
+  float total = row_sum[0];
+  if constexpr (TEAMS > 1) {
+    static_assert(QS == 1 && TEAMS == 2 && G::kChunks % 2 == 0, "one row per lane, halves of columns");
+    constexpr int kSlotBytes = kOut * 1024;
+    static_assert(WT * kSlotBytes <= R * G::kTileBytes, "what a team hands over fits its K ring");
+    const uint32_t slot = wave_tile * kSlotBytes + lane * 16, sums = lds0 + G::kSumsAt + wave_tile * 512 + lane * 8;
+    const uint32_t k_other = lds0 + (1 - team) * G::kTeamBytes;
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+      f32x4_t theirs;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lower = o_acc[0][i / 4][4 * (i % 4) + e], upper = o_acc[0][(i + kOut) / 4][4 * ((i + kOut) % 4) + e];
+        o_mine[i][e] = team == 0 ? lower : upper;
+        theirs[e] = team == 0 ? upper : lower;
+      }
+      *reinterpret_cast<f32x4_t*>(HYDRA_LDS_BYTE(k_ring + slot + i * 1024)) = theirs;
+    }
+    *reinterpret_cast<f32x2_t*>(HYDRA_LDS_BYTE(sums + team * (kWavesPerItem * 512))) = f32x2_t{-nref[0], row_sum[0]};
+    __syncthreads();
+    const f32x2_t rs = *reinterpret_cast<const f32x2_t*>(HYDRA_LDS_BYTE(sums + (1 - team) * (kWavesPerItem * 512)));
+    const float both = fmaxf(-nref[0], rs[0]), w_mine = fast_exp2(-nref[0] - both), w_theirs = fast_exp2(rs[0] - both);
+    total = row_sum[0] * w_mine + rs[1] * w_theirs;
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+      const f32x4_t x = *reinterpret_cast<const f32x4_t*>(HYDRA_LDS_BYTE(k_other + slot + i * 1024));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o_mine[i][e] = o_mine[i][e] * w_mine + x[e] * w_theirs;
+    }
+    // (each wave's staging area below lies in its own team's V ring: the other team may still be reading the K ring)
+  } else {
+#pragma unroll
+    for (int i = 0; i < kOut; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o_mine[i][e] = o_acc[0][i / 4][4 * (i % 4) + e];
+  }
   if (active) {
-    const uint32_t o_stage = k_ring + wave * (kWaveTileRows * ROWB);
+    const uint32_t o_stage = (TEAMS > 1 ? v_ring : k_ring) + wave_tile * (kWaveTileRows * ROWB);
+    if constexpr (!G::kSumsFromMatrixUnit) total = sum_with_other_half(total);
+    const float inv = 1.0f / total;
 #pragma unroll
-    for (int qs = 0; qs < QS; ++qs) {
-      const float total = G::kSumsFromMatrixUnit ? row_sum[qs] : sum_with_other_half(row_sum[qs]);
-      const float inv = 1.0f / total;
-      const int r_own = 32 * qs + m;
-#pragma unroll
-      for (int cc = 0; cc < CC; ++cc)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int chunk = 4 * cc + g4;  // columns 32cc + 8*g4 .. +7; this lane has 4*hf .. 4*hf+3 of them
-          if (chunk >= G::kChunks) continue;
-          f32x2_t x0 = {o_acc[qs][cc][4 * g4] * inv, o_acc[qs][cc][4 * g4 + 1] * inv};
-          f32x2_t x1 = {o_acc[qs][cc][4 * g4 + 2] * inv, o_acc[qs][cc][4 * g4 + 3] * inv};
-          u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(x0, bf16x2_t)),
-                        __builtin_bit_cast(uint32_t, __builtin_convertvector(x1, bf16x2_t))};
-          *reinterpret_cast<u32x2_t*>(HYDRA_LDS_BYTE(o_stage + r_own * ROWB + k_swizzle<D>(r_own, chunk) * 16 + 8 * hf)) = pk;
-        }
+    for (int i = 0; i < kOut; ++i) {  // columns 8 i .. 8 i + 7 of the wave's; this lane has 4 hf .. 4 hf + 3 of them
+      f32x2_t x0 = {o_mine[i][0] * inv, o_mine[i][1] * inv};
+      f32x2_t x1 = {o_mine[i][2] * inv, o_mine[i][3] * inv};
+      u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(x0, bf16x2_t)),
+                    __builtin_bit_cast(uint32_t, __builtin_convertvector(x1, bf16x2_t))};
+      *reinterpret_cast<u32x2_t*>(HYDRA_LDS_BYTE(o_stage + m * ROWB + k_swizzle<D>(m, i) * 16 + 8 * hf)) = pk;
     }
     const uint64_t base = (uint64_t)(uintptr_t)(a.out + ((seq_start + q0) * a.n_q_heads + head) * D);
     const uint32_t out_row_bytes = (uint32_t)a.n_q_heads * (D * 2);
@@ -981,11 +1080,11 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
     rsrc[2] = __builtin_amdgcn_readfirstlane((uint32_t)(rows - 1) * out_row_bytes + D * 2);
     rsrc[3] = 0x00020000u;
 #pragma unroll
-    for (int i = 0; i < kRowInstr; ++i) {
+    for (int i = 0; i < (kRowInstr + TEAMS - 1) / TEAMS; ++i) {
       const int flat = i * 64 + lane;
-      const int r = flat / G::kChunks, chunk = flat % G::kChunks;
+      const int r = flat / kOut, chunk = flat % kOut;
       const u32x4_t piece = *reinterpret_cast<const u32x4_t*>(HYDRA_LDS_BYTE(o_stage + r * ROWB + k_swizzle<D>(r, chunk) * 16));
-      const uint32_t off = (uint32_t)r * out_row_bytes + chunk * 16;
+      const uint32_t off = (uint32_t)r * out_row_bytes + (team * kOut + chunk) * 16;  // (r past the tile: out of the descriptor's range)
       // (a store of more than 8 bytes reads its data registers a little after it issues; the wait
       // states keep the next instruction from overwriting them: the compiler does not see this store)
       // (nt: the output is not read again by this kernel)
@@ -1030,6 +1129,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PackedSourc
 // The item comes from the work list when there is one.  Without one (the call that would have to build it first), and
 // for at most kDirectSeqs sequences, every wave works its workgroup's item out from cu_seqlens, one round trip to memory
 // and some 300 instructions, about 1.3 us per workgroup against a prepass of 4 - 5 us.
+// Forms.  TEAMS = 1, LOADERS = 0: as the persistent kernel, but one item.  Where the batch has a compute unit for every item, an item's
+// chain of key tiles is the kernel's length, and a wave alone on its SIMD spends half of an iteration issuing its share of the tile loads
+// (16 cycles of the compute unit per kilobyte, during which a wave issues nothing else) and in the LDS and matrix latencies that no
+// other wave covers.  LOADERS > 0: that many more waves per team issue the loads, half of them K tiles and half V tiles, the first of
+// them while Q is on its way: an iteration of 64 keys at head_dim 128 takes 0.8 us instead of 1.0.  TEAMS = 2: the workgroup has two
+// wave tiles instead of four, and each of two teams of two waves half of the key tiles, in rings of its own; the teams share the
+// loads of Q and merge their results through LDS, half of the columns by each (all by one: 0.3 to 0.6 us longer).  us with 4, 8 and 8
+// waves so: one image of 577 tokens with 16 heads of 64 9.45, 8.58, 6.58; a request of 558 tokens with 28 / 4 heads of 128 12.4, 11.3,
+// 8.9.  TEAMS = 2, LOADERS = 0 is the same split for calls that leave registers to others (10.5 us).
+// LOADERS change no bit of the result; two teams' P is rounded relative to a reference of each team (the relative error against 64 bits
+// goes down by 0.3 to 3 %).
+// Not kept: one copy of the iteration's code instead of two plus the last one's, 0.1 to 0.5 us longer; two teams of four waves without
+// loading waves, equal to one team with; two loading waves per team of four waves, three waves per SIMD, equal at head_dim 64, 4 to 7 %
+// faster at 80; two waves per wave tile that take the scores of every other key block each, exchange P through LDS and multiply half
+// of the columns each, 9.0 and 10.8 us: an iteration per key tile again, and 0.4 us of an iteration are latencies.
 constexpr int kDirectSeqs = 64;
 constexpr int kDieUnits = 32;  // compute units of a die
 
@@ -1129,6 +1243,15 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
     // 64 9.71 -> 9.49, 12 of them 28.0 -> 27.6; one request of 558 tokens, 28 / 4 heads of 128, 12.58 -> 12.28, of 2000 39.9 -> 39.7).
     const int n = __builtin_amdgcn_readfirstlane(units(first_len));
     if (n <= 0) return false;
+    if (pairs < kXcds && kXcds % pairs == 0 && n > kDieUnits) {
+      // one request: its pairs in turn, which gives each die one pair, or a part of one (through take_entry, whose counts take
+      // a workgroup half a microsecond: 28 / 4 heads of 128, 700 tokens 14.3 us, 13.8 so; in halved items 400 tokens 9.1 and 8.7)
+      kv_head = (int)blockIdx.x % pairs;
+      unit = (int)blockIdx.x / pairs;
+      seq_start = __builtin_amdgcn_readfirstlane(start);
+      seq_len = first_len;
+      return unit < n;
+    }
     if (n_kv_heads % kXcds != 0 && (pairs > kXcds || n > kDieUnits)) {
       const int rows = pairs / kXcds;
       if (!take_entry(n * (rows + (pair_of(rows, lane % kXcds) < pairs ? 1 : 0)), (int)blockIdx.x, die, place)) return false;
@@ -1190,34 +1313,40 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
 }
 #endif  // __HIP_DEVICE_COMPILE__
 
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DirectSource::kWavesPerSimd<D>, DirectSource::kWavesPerSimd<D>))) void attn_fwd_direct_kernel(
+template <int D, bool CAUSAL, int TEAMS, int LOADERS>
+__global__ __launch_bounds__((DirectSource<TEAMS, LOADERS>::kBound)) __attribute__((amdgpu_waves_per_eu(DirectSource<TEAMS, LOADERS>::template kWavesPerSimd<D>, DirectSource<TEAMS, LOADERS>::template kWavesPerSimd<D>))) void attn_fwd_direct_kernel(
     const AttnArgs a, const int batch, const int n_kv_heads) {  // batch 0: the item comes from the work list
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D>::kLdsBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[TileGeom<D, TEAMS, DirectSource<TEAMS, LOADERS>::kStageRows>::kLdsBytes];
   __shared__ __attribute__((aligned(16))) int s_claim[4];
   __shared__ __attribute__((aligned(16))) int s_redo[8];
-  DirectSource src;
-  if (batch == 0) {
+  DirectSource<TEAMS, LOADERS> src;
+  constexpr int TILES = src.kTiles, kShare = kWavesPerItem / TILES;  // wave tiles per workgroup, workgroups per entry of the list
+  if (batch == 0) {  // (an entry of the list is shared by kShare workgroups)
     const int lane = threadIdx.x & 63;
     const int first = a.ctrl->xcd_start[lane % kXcds];
     int die, place;
-    if (!take_entry(a.ctrl->xcd_start[lane % kXcds + 1] - first, (int)blockIdx.x, die, place)) return;
-    const WorkItem it = a.items[__builtin_amdgcn_readlane(first, die) + place];
+    if (!take_entry((a.ctrl->xcd_start[lane % kXcds + 1] - first) * kShare, (int)blockIdx.x, die, place)) return;
+    const WorkItem it = a.items[__builtin_amdgcn_readlane(first, die) + place / kShare];
     src.q_start = __builtin_amdgcn_readfirstlane(it.x);
     src.q_len = __builtin_amdgcn_readfirstlane(it.y);
-    src.f0 = __builtin_amdgcn_readfirstlane(it.z);
+    src.f0 = __builtin_amdgcn_readfirstlane(it.z) + place % kShare * TILES;
     src.kv_head = __builtin_amdgcn_readfirstlane(it.w);
+    if (kShare > 1 && src.f0 >= (src.q_len + kWaveTileRows - 1) / kWaveTileRows * a.group) return;
   } else {
     int start, item;
-    if (!find_unit(a.cu_seqlens, batch, n_kv_heads, [&](int len) { return items_of_sequence(len, a.group); }, start, src.q_len, src.kv_head, item)) return;
-    if (CAUSAL) item = items_of_sequence(src.q_len, a.group) - 1 - item;  // most expensive first
+    if (!find_unit(a.cu_seqlens, batch, n_kv_heads, [&](int len) { return items_of_sequence<TILES>(len, a.group); }, start, src.q_len, src.kv_head, item)) return;
+    if (CAUSAL) item = items_of_sequence<TILES>(src.q_len, a.group) - 1 - item;  // most expensive first
     src.q_start = start;
-    src.f0 = item * kWavesPerItem;
+    src.f0 = item * TILES;
   }
   if (attn_item_loop<D, CAUSAL>(a, src, smem, s_claim, s_redo)) {
+    if constexpr (TEAMS > 1) {  // (the other team's waves have stored parts of the rows that are stored again)
+      wait_all_loads();
+      __syncthreads();
+    }
     const uint32_t lds = (uint32_t)(uintptr_t)HYDRA_LDS_PTR(smem);
-    careful::run_item<D, CAUSAL>(a, src.q_start, src.q_len, src.f0, src.kv_head, lds);
+    careful::run_item<D, CAUSAL, TILES, DirectSource<TEAMS, LOADERS>::kThreads / 64>(a, src.q_start, src.q_len, src.f0, src.kv_head, lds);
   }
 #else
   (void)a;

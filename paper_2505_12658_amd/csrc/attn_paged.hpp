@@ -147,6 +147,8 @@ __device__ __forceinline__ void issue_tile_loads(const TileSlots<D, KEYS, STEP>&
 // head_dim 80 (a row is not a whole fraction of 1024 bytes) and smaller blocks take the plain loop further down.
 struct PagedSource {
   static constexpr bool kPaged = true, kOneItem = true;
+  static constexpr int kTeams = 1, kTiles = kWavesPerItem;
+  static constexpr int kLoaders = 0, kStageRows = 0;
   template <int D>
   static constexpr int kWavesPerSimd = kPagedWavesPerSimd;
   const PagedArgs* args;

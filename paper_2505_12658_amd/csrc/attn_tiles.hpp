@@ -108,10 +108,11 @@ __device__ __forceinline__ int v_swizzle(int row, int chunk) {
   else return chunk;
 }
 
-// Items of one (sequence, KV head).
+// Items of one (sequence, KV head), TILES wave tiles each.
+template <int TILES = kWavesPerItem>
 __host__ __device__ __forceinline__ int items_of_sequence(int len, int group) {
   const int tok_tiles = (len + kWaveTileRows - 1) / kWaveTileRows;
-  return (tok_tiles * group + kWavesPerItem - 1) / kWavesPerItem;
+  return (tok_tiles * group + TILES - 1) / TILES;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

@@ -311,6 +311,66 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
         assert torch.equal(listed.view(torch.int16), out.view(torch.int16)) and torch.equal(shared.view(torch.int16), out.view(torch.int16))
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
+    # two teams: every item of two wave tiles has a compute unit
+    ([65], 1, 1, 64, False),               # a key tile and one key more: the second team has one key
+    ([65], 3, 1, 128, True),               # ... that only the last row sees; wave tiles without keys of the second team
+    ([129, 70, 65], 2, 2, 80, True),       # tiles that do not divide by two; odd numbers of key blocks
+    ([191, 64, 130, 66], 7, 1, 128, True),
+    ([1000], 4, 4, 128, False),
+    ([2049], 3, 1, 64, True),
+    ([577], 16, 16, 64, False),
+    ([96, 160], 16, 8, 80, False),         # KV heads spread evenly over the dies
+    # loading waves: every item of four wave tiles has one
+    ([577, 577], 16, 16, 64, False),
+    ([640], 32, 32, 128, True),
+    ([700], 28, 4, 128, True),             # a single request: pairs in turn
+    ([1100], 16, 16, 80, False),
+    ([1400], 28, 4, 128, True),            # ... of more items than units
+])
+def test_a_unit_for_every_item(lengths, hq, hkv, d, causal):
+    """Batches so small that items have compute units of their own, on both sides of where items are halved and of where they
+    have waves that load: against the oracle, the same bits from a work list and for a call that shares the chip, and with keys far
+    out of the fast path's range at either end of the sequences.  Loading waves change no bit: the same sequences in a larger batch."""
+    hydra = _hydra()
+    w = si.custom(lengths, hq, hkv, d, causal, seed=3 * sum(lengths) + hq)
+    q, k, v = si.make_qkv(w)
+    dev = torch.device("cuda:0")
+    cu = torch.from_numpy(w.cu_seqlens).to(dev)
+
+    def bits(qd, kd, vd, cu, longest, how):
+        out = torch.full_like(qd, float("nan"))
+        if how == "plain":
+            hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, longest, causal, w.softmax_scale, out=out)
+        else:
+            ws = hydra.hydra_attn_build_worklist(cu, qd.shape[0], longest, hq, hkv, d, causal)
+            if how == "listed":
+                hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, longest, causal, w.softmax_scale, out, ws)
+            else:
+                hydra.hydra_attn_varlen_fwd_shared(qd, kd, vd, cu, longest, causal, w.softmax_scale, out, ws, how)
+        torch.cuda.synchronize()
+        return out
+
+    for planted in (None, 40, -2):
+        if planted is not None:
+            k = k.clone()
+            for b in range(w.batch):
+                k[w.cu_seqlens[b] + (planted if planted > 0 else lengths[b] + planted)] = 64.0  # (see test_large_scores_take_careful_path)
+        qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+        out = bits(qd, kd, vd, cu, w.max_seqlen, "plain")
+        _check(out, c_oracle.attn_varlen(_f64(q), _f64(k), _f64(v), w.cu_seqlens, causal, w.softmax_scale))
+        for longest, how in ((w.max_seqlen, "listed"), (3 * w.max_seqlen, "plain"), (w.max_seqlen, 1), (w.max_seqlen, 3)):
+            assert torch.equal(bits(qd, kd, vd, cu, longest, how).view(torch.int16), out.view(torch.int16)), (planted, how)
+        if planted is None and hq * sum(-(-L // 32) for L in lengths) > 512:
+            more = [*lengths, 900, 900, 900, 900, 900, 900]
+            big = si.custom(more, hq, hkv, d, causal, seed=1)
+            qb, kb, vb = (t.to(dev) for t in si.make_qkv(big))
+            for t, own in ((qb, qd), (kb, kd), (vb, vd)):
+                t[:w.total_tokens] = own
+            with_others = bits(qb, kb, vb, torch.from_numpy(big.cu_seqlens).to(dev), big.max_seqlen, "plain")[:w.total_tokens]
+            assert torch.equal(with_others.view(torch.int16), out.view(torch.int16))
+
+
 @pytest.mark.parametrize("lengths,hq,hkv,d", [
     ([1500], 7, 1, 128),             # one pair: seven dies have no queue of their own
     ([900, 40], 14, 2, 64),          # four pairs of two lengths
