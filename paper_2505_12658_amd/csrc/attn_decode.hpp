@@ -224,23 +224,24 @@ struct DecodeWave {
 // The keys of a share are dealt out to n_streams streams, block by block, each with a running maximum, a sum and an output of
 // its own until the merge: so the number of streams is part of the result.  It is n_waves, or with PER_WAVE 2 also twice that:
 // a wave then walks its first stream and goes on with its second one, whose first block is in flight by then.
+// thread: number among the threads of the n_waves waves.  Returns whether the waves met at a workgroup barrier (once) on the way.
 template <int D, int PER_WAVE = 1>
-__device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n_waves, int n_streams, int b, int kv_head, int q_start, int q_len, int kv_len,
-                                           int split) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__device__ __forceinline__ bool run_decode(const PagedArgs& a, float* lds, int n_waves, int n_streams, int b, int kv_head, int q_start, int q_len, int kv_len,
+                                           int split, int thread) {
+  const int lane = thread & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(thread >> 6);
   const int m = lane & 15, h = lane >> 4;
   float* s_max = lds;
   float* s_sum = s_max + PER_WAVE * n_waves * kDecodeRows;
   float* s_slots = s_sum + PER_WAVE * n_waves * kDecodeRows;
   const bool two = PER_WAVE == 2 && n_streams > n_waves;  // (else as with PER_WAVE 1)
 
-  if (kv_len <= 0) return;
+  if (kv_len <= 0) return false;
   const int n_halves = (kv_len + kDecodeKeys - 1) / kDecodeKeys;
   int begin, end, per_share, n_shares;
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   split_range(n_halves, per_share, split, begin, end);
-  if (begin >= end) return;  // past the context's last share: the combine kernel knows and skips it
+  if (begin >= end) return false;  // past the context's last share: the combine kernel knows and skips it
 
   // Block-table entries of the wave's next 32 steps: lane 2 i + half has the entry of that half of step i
   // (one load; the loop takes them from there lane by lane).  Ids are clamped to the cache, so that a corrupt
@@ -261,7 +262,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   };
   // (the first ones are asked for together with the request's rows)
   int ids = entries(0);
-  if (q_len <= 0 || kv_len < q_len || q_len * a.group > kDecodeRows) return;
+  if (q_len <= 0 || kv_len < q_len || q_len * a.group > kDecodeRows) return false;
   const int n_rows = q_len * a.group;
 
   // this lane's row
@@ -333,7 +334,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
   __syncthreads();
   const bool whole = n_shares == 1;  // the context is one share: this workgroup writes the output
   constexpr int kCols = D / 4;
-  for (int i = threadIdx.x; i < n_rows * kCols; i += 64 * n_waves) {
+  for (int i = thread; i < n_rows * kCols; i += 64 * n_waves) {
     const int r = i / kCols, col = (i - r * kCols) * 4;
     // (four streams at a time, so that their reads are in flight together; there are four or eight)
     float top = s_max[r];
@@ -376,6 +377,7 @@ __device__ __forceinline__ void run_decode(const PagedArgs& a, float* lds, int n
       *reinterpret_cast<f32x4_t*>(rec + 2 * kRows + r * D + col) = acc;
     }
   }
+  return true;
 }
 
 // The lane of the set bit number n of a mask that has more than n.
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDec
   const int streams = STREAMS > kDecodeWaves && !any_long ? kDecodeWaves : STREAMS;
   if (WAVES > streams && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= streams) return;
   if (kv_len > table_keys) kv_len = (int)table_keys;
-  run_decode<D, STREAMS / WAVES>(a, s_decode, WAVES < streams ? WAVES : streams, streams, b, kv_head, q_start, q_end - q_start, kv_len, split);
+  run_decode<D, STREAMS / WAVES>(a, s_decode, WAVES < streams ? WAVES : streams, streams, b, kv_head, q_start, q_end - q_start, kv_len, split, (int)threadIdx.x);
 #else
   (void)a;
 #endif

@@ -277,6 +277,8 @@ constexpr float kMaxRowSum = 1.0995116e12f;  // 2^40: largest row sum (relative 
 // attn_paged.hpp for that source).
 struct PackedSource {
   static constexpr bool kPaged = false, kOneItem = false;
+  template <int D, int WAVES>
+  using Loader = int;  // (of its loading waves: none)
   static constexpr int kTeams = 1, kTiles = kWavesPerItem;
   static constexpr int kLoaders = 0, kStageRows = 0;
   template <int D>
@@ -289,6 +291,10 @@ struct PackedSource {
 template <int TEAMS, int LOADERS>
 struct DirectSource {
   static constexpr bool kPaged = false, kOneItem = true;
+#if defined(__HIP_DEVICE_COMPILE__)
+  template <int D, int WAVES>
+  using Loader = TileLoader<D, WAVES>;
+#endif
   static constexpr int kTeams = TEAMS, kTiles = kWavesPerItem / TEAMS, kLoaders = LOADERS;
   static constexpr int kStageRows = LOADERS > 0 && kTiles > 2 ? kTiles * kWaveTileRows : 0;
   static constexpr int kThreads = 64 * TEAMS * (kTiles + LOADERS);
@@ -511,12 +517,20 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
       constexpr int kEach = kLoaders / 2;
       const int number = (wave - TEAMS * WT) % kLoaders;
       const bool is_v = number >= kEach;
-      TileLoader<D, kEach> loader;
-      if (is_v) loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, number % kEach, lane);
-      else loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, number % kEach, lane);
       const int ahead = is_v ? 0 : 1;  // iteration t loads K tile t + 1, V tile t
-      loader.tile_off = (first_tile + ahead) * loader.tile_stride;
       const uint32_t ring = is_v ? v_ring : k_ring;
+      typename Src::template Loader<D, kEach> loader;
+      if constexpr (Src::kPaged) {  // (K tile 0 as well)
+        loader.init(src, is_v, kv_head, number % kEach, lane);
+        if (!is_v) {
+          loader.issue_next(ring);
+          wait_all_loads();
+        }
+      } else {
+        if (is_v) loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, number % kEach, lane);
+        else loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, number % kEach, lane);
+        loader.tile_off = (first_tile + ahead) * loader.tile_stride;
+      }
       if (ahead < W_own) loader.issue_next(ring + ahead * G::kTileBytes);
       __syncthreads();  // (the one behind K tile 0 and Q)
       wait_all_loads();
@@ -535,7 +549,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   std::conditional_t<Src::kPaged, int, TileLoader<D, WT>> k_loader, v_loader;
   typename Src::template Gather<D> gather;
   if constexpr (Src::kPaged) {
-    gather.init(src, kv_head, wave, lane);
+    if constexpr (kLoaders == 0) gather.init(src, kv_head, wave, lane);
   } else {
     k_loader.template init<false>(a.k, a.k_stride, seq_start, seq_len, kv_head, wave_tile, lane);
     v_loader.template init<true>(a.v, a.v_stride, seq_start, seq_len, kv_head, wave_tile, lane);
@@ -547,14 +561,18 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   // after the issue of iteration t, tile loads 0 .. 2(t+PD) are out; iteration t needs 0 .. 2t
   auto issue_loads = [&](int t) {
     if constexpr (Src::kPaged) {
-      gather.issue(t - 1 + PD < W, v_ring + ((t - 1 + PD) % R) * G::kTileBytes, t + PD < W, k_ring + ((t + PD) % R) * G::kTileBytes);
+      if constexpr (kLoaders == 0) gather.issue(t - 1 + PD < W, v_ring + ((t - 1 + PD) % R) * G::kTileBytes, t + PD < W, k_ring + ((t + PD) % R) * G::kTileBytes);
     } else {
       if constexpr (kLoaders > 0) return;
       if (t - 1 + PD < W_own) v_loader.issue_next(v_ring + ((t - 1 + PD) % R) * G::kTileBytes);
       if (t + PD < W_own) k_loader.issue_next(k_ring + ((t + PD) % R) * G::kTileBytes);
     }
   };
-  if constexpr (Src::kPaged) gather.issue_first(k_ring); else k_loader.issue_next(k_ring);
+  if constexpr (Src::kPaged) {
+    if constexpr (kLoaders == 0) gather.issue_first(k_ring);
+  } else {
+    k_loader.issue_next(k_ring);
+  }
 
   if (!q_ahead) issue_q_loads(seq_start, seq_len, q0, head, lane);
   // Q fragments (B operand): lane (m, hf) holds query row q0 + 32*qs + m, columns hf*D/2 + 8*s .. +7, as
@@ -812,7 +830,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   if constexpr (TEAMS == 1 || kLoaders == 0) __syncthreads();  // K(0) is complete; every wave has taken its Q out of the V ring
   // the rest of the prologue loads: V(0) K(1) V(1) ... K(PD)
   if constexpr (Src::kPaged) {
-    gather.issue(0 < W, v_ring, 1 < W, k_ring + G::kTileBytes);
+    if constexpr (kLoaders == 0) gather.issue(0 < W, v_ring, 1 < W, k_ring + G::kTileBytes);
   } else {
 #pragma unroll
     for (int n = 0; n < (kLoaders > 0 ? 0 : PD); ++n) {

@@ -145,10 +145,12 @@ __device__ __forceinline__ void issue_tile_loads(const TileSlots<D, KEYS, STEP>&
 // covers it, and the next iteration's issue reads it lane by lane into scalar registers.  The V tile of an
 // iteration comes from the blocks its K tile came from one iteration earlier, so they are kept.
 // head_dim 80 (a row is not a whole fraction of 1024 bytes) and smaller blocks take the plain loop further down.
+// LOADERS: waves that do nothing but load tiles (see attn_item_loop).
+template <int LOADERS = 0>
 struct PagedSource {
   static constexpr bool kPaged = true, kOneItem = true;
   static constexpr int kTeams = 1, kTiles = kWavesPerItem;
-  static constexpr int kLoaders = 0, kStageRows = 0;
+  static constexpr int kLoaders = LOADERS, kStageRows = LOADERS > 0 ? kWavesPerItem * kWaveTileRows : 0;
   template <int D>
   static constexpr int kWavesPerSimd = kPagedWavesPerSimd;
   const PagedArgs* args;
@@ -251,6 +253,80 @@ struct PagedSource {
       if (has_k) issue_tile(next_tile, k_block, k_lo, k_hi, k_lane_off, k_dst);
 #pragma unroll
       for (int u = 0; u < kPerWave; ++u) v_block[u] = k_block[u];
+      ++next_tile;
+      lookup(next_tile);
+    }
+  };
+
+  // One of WAVES waves that load the K tiles, or the V tiles, of the item one after the other.
+  template <int D, int WAVES>
+  struct Loader {
+    using G = TileGeom<D>;
+    static constexpr int kPerWave = G::kLoadInstr / WAVES;
+    static constexpr int kRowsPerInstr = 1024 / G::kRowBytes;
+    static constexpr int kPeriod = kRowsPerInstr * WAVES % 16 == 0 ? 1 : 2;  // loads after which the swizzles repeat
+    static_assert(G::kLoadInstr % WAVES == 0 && 1024 % G::kRowBytes == 0 && kRowsPerInstr * WAVES * kPeriod % 16 == 0 && kPerWave <= 64, "whole rows per instruction");
+    uint32_t lo, hi;             // byte address of this KV head's part of cache row 0 (uniform)
+    uint32_t row_bytes;          // bytes between cache rows (uniform)
+    uint32_t lane_off[kPeriod];  // this lane's 16 bytes inside a load instruction's rows
+    const int32_t* table;
+    int kv_len, block_shift, last_block, last_entry, number, lane;
+    int next_tile;    // the next tile to issue, whose table entries `pending` holds
+    int32_t pending;  // lane u < kPerWave: table entry of this wave's load u of tile next_tile
+
+    __device__ __forceinline__ int first_key(int tile, int u) const { return tile * kKvTileRows + kRowsPerInstr * (number + WAVES * u); }
+    __device__ __forceinline__ void lookup(int tile) {
+      pending = 0;
+      if (lane < kPerWave) {
+        int entry = first_key(tile, lane) >> block_shift;
+        entry = entry < last_entry ? entry : last_entry;  // (tiles past the context are looked up but never loaded)
+        pending = table[entry];
+      }
+    }
+    __device__ __forceinline__ void init(const PagedSource& src, bool is_v, int kv_head, int number_, int lane_) {
+      const PagedArgs& a = *src.args;
+      number = number_;
+      lane = lane_;
+      table = src.table;
+      kv_len = src.kv_len;
+      block_shift = a.block_shift;
+      last_block = a.num_blocks - 1;
+      last_entry = a.max_blocks_per_seq - 1;
+      row_bytes = __builtin_amdgcn_readfirstlane((uint32_t)a.n_kv_heads * (D * 2));
+      const uint64_t base = (uint64_t)(uintptr_t)((is_v ? a.v_cache : a.k_cache) + (int64_t)kv_head * D);
+      lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+      hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+      const int in_instr = lane / G::kChunks, phys = lane % G::kChunks;
+#pragma unroll
+      for (int u = 0; u < kPeriod; ++u) {
+        const int row = kRowsPerInstr * (number + WAVES * u) + in_instr;
+        lane_off[u] = (uint32_t)in_instr * row_bytes + (is_v ? v_swizzle<D>(row, phys) : k_swizzle<D>(row, phys)) * 16;
+      }
+      next_tile = 0;
+      lookup(0);
+    }
+    __device__ __forceinline__ void issue_next(uint32_t lds_dst) {
+      int32_t block[kPerWave];  // (all in scalar registers before the first load goes out, see Gather::issue)
+#pragma unroll
+      for (int u = 0; u < kPerWave; ++u) {
+        const int b = __builtin_amdgcn_readlane(pending, u);
+        block[u] = b < 0 ? 0 : (b > last_block ? last_block : b);  // a corrupt table cannot make the loads leave the cache
+      }
+#pragma unroll
+      for (int u = 0; u < kPerWave; ++u) {
+        const int key = first_key(next_tile, u);
+        const uint32_t slot = ((uint32_t)block[u] << block_shift) + ((uint32_t)key & ((1u << block_shift) - 1u));
+        const uint64_t base = (((uint64_t)hi << 32) | lo) + (uint64_t)slot * row_bytes;
+        int valid = kv_len - key;
+        valid = valid > kRowsPerInstr ? kRowsPerInstr : valid;
+        u32x4_t rsrc;
+        rsrc[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
+        rsrc[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xffffu);
+        rsrc[2] = __builtin_amdgcn_readfirstlane(valid > 0 ? (uint32_t)(valid - 1) * row_bytes + D * 2 : 0u);
+        rsrc[3] = 0x00020000u;
+        const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_dst + (number + WAVES * u) * 1024);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(m0), "v"(lane_off[u % kPeriod]), "s"(rsrc));
+      }
       ++next_tile;
       lookup(next_tile);
     }
@@ -462,14 +538,15 @@ struct WaveTile {
 // workgroup barrier inside the loop; a wave's next half tile travels through registers while it computes on
 // the current one, see TileRegs), and the four partial results (maximum, sum, unnormalised output per row)
 // are merged through LDS at the end.
+// thread, result: see run_decode.
 template <int D>
-__device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned char* smem, float* s_stats, const int32_t* table, int64_t q_start,
-                                                int q_len, int kv_len, int kv_head, int request, int split) {
+__device__ __forceinline__ bool run_packed_rows(const PagedArgs& a, unsigned char* smem, float* s_stats, const int32_t* table, int64_t q_start,
+                                                int q_len, int kv_len, int kv_head, int request, int split, int thread) {
   using G = StageGeom<D>;
   using W = WaveTile<D, 1>;
   constexpr int kHalfKeys = kKvTileRows / 2;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = thread & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(thread >> 6);
   const int m = lane & 31;
   const int shift = kv_len - q_len;
   const int n_rows = q_len * a.group;
@@ -489,7 +566,7 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
   int per_share, n_shares;
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   split_range(n_halves, per_share, split, h_begin, h_end);
-  if (h_begin >= h_end) return;  // past the context's last share: the combine kernel knows and skips it
+  if (h_begin >= h_end) return false;  // past the context's last share: the combine kernel knows and skips it
   const bool whole = n_shares == 1;  // the context is one share: this workgroup writes the output
   // The rows of half tile h + 4 travel (into registers) while half tile h is computed on, and the block-table
   // look-up of half tile h + 8 travels behind them; its entries are not touched before the top of the next round.
@@ -524,7 +601,7 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
 #pragma unroll
     for (int i = 0; i < 16; ++i) mine[(cc * 16 + i) * 64 + lane] = w.o_acc[0][cc][i];
   __syncthreads();
-  if (wave != 0) return;
+  if (wave != 0) return true;
   float scale_of[kWavesPerGroup];
   {
     float top = s_stats[lane];
@@ -551,7 +628,7 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
     }
   if (whole) {
     w.store_row(0, valid ? a.out + ((q_start + token) * a.n_q_heads + head) * D : nullptr);
-    return;
+    return true;
   }
   // this share's partial result: the row's maximum, its sum (both halves of the row added up) and its
   // unnormalised output, for the combine kernel
@@ -577,6 +654,7 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
         }
       }
   }
+  return true;
 }
 
 #endif  // __HIP_DEVICE_COMPILE__
@@ -595,10 +673,20 @@ __device__ __forceinline__ void run_packed_rows(const PagedArgs& a, unsigned cha
 // The hardware starts workgroups in index order.  Both kinds live in one kernel so that the decode requests and the prefill
 // chunks of a batch run side by side on the chip; two workgroups per compute unit (a wave keeps within 256 registers, a
 // workgroup within half of the LDS).
+// Wide workgroups (512 threads, one to a compute unit) are for batches that wait for their chains: four waves compute a chain and
+// four load its tiles (attn_item_loop), so that a key tile takes 0.8 us instead of 1.1 (of which a third was the issue of the loads and
+// their latency behind it), 1.0 with the whole chip at work; two chains to a unit take 1.5 each, which is the better rate where
+// there is enough to fill the chip.  A wide workgroup has one decode step (share, packed-rows request) as long as the chip has units for
+// all places, else the shortest are second ones: the halves of its waves take one each.  us, four waves and eight, 28 / 4 heads of 128: a
+// chunk of 512 tokens alone 13.8 and 11.4, behind 1536 keys 41.2 and 30.3; 4 chunks of 128 14.1 and 11.6; 24 decode steps of 91 .. 916 and
+// 4 chunks of 158 17.1 and 14.4, 53 of 50 .. 508 and 4 of 286 28.4 and 22.7, 76 of 44 .. 441 and 4 of 72 14.7 and 12.1; the same bits.
 constexpr int kFirstLayer = kUnits;  // workgroups i and i + 256 of a grid share a compute unit
 constexpr int kLongChain = 8;        // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
 constexpr int kStepUnits = 128;      // compute units that the chains leave to the decode steps
 constexpr int kFewChunks = 4;        // as many are ranked one by one
+constexpr int kTrailing = 32;        // places at the end of a wide grid that are chains at least, if not all places fit the grid
+constexpr int kWideMost = 128;       // requests of a batch that wide workgroups take
+constexpr float kChainKeysPerStep = 2 * 32 * 0.9f;  // keys of a chain that take as long as a step of both of a wide workgroup's decode steps
 
 // Context up to which a hybrid batch keeps the order of its requests.  To order it costs every workgroup up to 2 us where the
 // lengths fill REGS = 4 registers (129 to 256 requests), 0.5 where they fill two, 0.3 with one, paid once per round of workgroups;
@@ -637,6 +725,7 @@ __device__ __forceinline__ int wave_max(int x) {
 // A workgroup's work: a share of a request's context for one KV head (f0 < 0), or a group of wave tiles of a request.
 struct Work {
   int b, kv_head, q_start, q_len, kv_len, split, f0;
+  int places, tail;  // of a chain, in wide workgroups: places that have work in all, and the first one from which on they are all chains
 };
 
 // This workgroup's work, found by every wave for itself from the lengths of the whole batch, which lie in REGS registers of its
@@ -666,13 +755,13 @@ struct Work {
 // us, through the scan in LDS, one by one and by the search: 256 chunks of 32 tokens 130, 503 and 79; 100 decode steps and 100 chunks of
 // 16 63, 139 and 55; 64 chunks of 100 53, 57 and 36; 16 of 512 215, 215 and 213; but a chunk of 64 alone 11.2, 10.4 and 10.8, 8 decode
 // steps of 70 .. 709 and 2 chunks of 405 20.3, 19.6 and 19.9.
-template <int REGS>
-__device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
-  const int lane = threadIdx.x & 63, id = (int)blockIdx.x;
+template <int REGS, bool WIDE>
+__device__ __forceinline__ bool find_work(const PagedArgs& a, int id, Work& w) {
+  const int lane = threadIdx.x & 63;
   const int table_keys = (int)((int64_t)a.max_blocks_per_seq << a.block_shift);
   const int pairs = a.batch * a.n_kv_heads;
   // this workgroup's place in the order of the batch
-  auto in_batch_order = [&]() {
+  auto in_batch_order = [&](int id) {
     w.split = a.n_splits > 1 ? id / pairs : 0;
     const int pair = id - w.split * pairs;
     w.b = pair / a.n_kv_heads;
@@ -687,7 +776,19 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     return w.q_len > 0 && w.kv_len >= w.q_len && w.q_len * a.group <= kRows;
   };
   bool ordered = a.order_keys != kNeverOrdered;
-  if (!ordered && id < pairs * a.n_splits) return in_batch_order();
+  // WIDE: two of the first kind to a workgroup, number i from the front and from the back, one for each half of its waves
+  const int half = WIDE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const int in_order = WIDE ? (pairs * a.n_splits + 1) / 2 : pairs * a.n_splits;
+  auto unit_in_order = [&]() {
+    if (!WIDE || half == 0) return in_batch_order(id);
+    const int other = pairs * a.n_splits - 1 - id;
+    return other > id && in_batch_order(other);
+  };
+  w.f0 = 0;
+  if (!ordered && id < in_order) {
+    w.f0 = -1;
+    return unit_in_order();
+  }
 
   int q_start[REGS], q_len[REGS], kv_len[REGS];
 #pragma unroll
@@ -703,7 +804,10 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
 #pragma unroll
     for (int r = 0; r < REGS; ++r) far = far || kv_len[r] > a.order_keys;
     ordered = __builtin_amdgcn_ballot_w64(far) != 0;
-    if (!ordered && id < pairs * a.n_splits) return in_batch_order();
+    if (!ordered && id < in_order) {
+      w.f0 = -1;
+      return unit_in_order();
+    }
   }
 
   int steps[REGS], groups[REGS];  // of a request of the first kind / of the second
@@ -724,9 +828,18 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     far_chunk |= __builtin_amdgcn_ballot_w64(chunk && kv_len[r] > kLongChain * kKvTileRows);
   }
 
-  int step = -1, chain = -1, units = kFirstLayer, rows_wgs = 0, shares[REGS];
+  int step = -1, chain = -1, units = kFirstLayer, rows_wgs = 0, firsts = 0, shares[REGS];
+  int chains = 0;  // (WIDE)
+  if constexpr (WIDE) {
+    int sum = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) sum += groups[r];
+    chains = __builtin_amdgcn_readlane(wave_scan_add(sum), 63) * a.n_kv_heads;
+  }
   if (!ordered) {
-    chain = id - pairs * a.n_splits;
+    chain = id - in_order;
+    w.places = in_order + chains;
+    w.tail = in_order;
   } else {
     // workgroups of the first kind: one per share
     rows_wgs = n_steps * a.n_kv_heads;
@@ -741,50 +854,87 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
       }
       rows_wgs = __builtin_amdgcn_readlane(wave_scan_add(sum), 63) * a.n_kv_heads;
     }
-    // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
-    bool beside_steps = false;
-    if (rows_wgs == 0) {
-      beside_steps = true;  // (chains only)
-    } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
-      int longest = 0;
-      uint64_t longer = 0, far_longer = 0;
+    if constexpr (WIDE) {
+      int keys = 0;
 #pragma unroll
-      for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
-      longest = wave_max(longest);
-#pragma unroll
-      for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
-      beside_steps = rows_wgs <= kFirstLayer && longer == 0;
-      if (far_chunk != 0 && !beside_steps) {
-        int far = 0;  // groups whose chains are longer than half of the longest
+      for (int r = 0; r < REGS; ++r) keys += steps[r] > 0 ? steps[r] : 0;
+      const int all_steps = __builtin_amdgcn_readlane(wave_scan_add(keys), 63);
+      // (numbers that shift the chains' places are multiples of 8: a KV head of a chunk keeps its dies)
+      // one of the first kind to a workgroup as far as the chip has compute units, the longest ones, and two for the rest
+      firsts = rows_wgs <= kUnits - chains ? rows_wgs : (rows_wgs + 1) / 2 > kUnits - chains ? (rows_wgs + 1) / 2 : kUnits - chains;
+      const int n_rows = (firsts + 7) & ~7;
+      int ahead = 0;
+      if (rows_wgs > 0 && firsts + chains > kUnits) {
+        // chains that last longer than a workgroup of the first kind go ahead of those, the others behind them
+        const int tokens_of = (int)((float)all_steps * (float)a.n_kv_heads / (float)rows_wgs * kChainKeysPerStep);
+        int far = 0;
 #pragma unroll
         for (int r = 0; r < REGS; ++r) {
-          int tokens = kv_len[r] - longest / 2;
+          int tokens = kv_len[r] - tokens_of;
           tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
           far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
-          far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
         }
-        int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
-        if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
-        chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
-        units = kFirstLayer - chain_units;
+        ahead = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads & ~7;
+        const int most = ((int)gridDim.x - n_rows - kTrailing) & ~7;  // (the grid has room for these)
+        ahead = ahead < most ? ahead : most;
       }
-    }
-    if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
-    const int chain_units = kFirstLayer - units;
-
-    if (id < units) {
-      step = id;
-    } else if (id < kFirstLayer || beside_steps) {
-      chain = id - units;
-    } else if (id < kFirstLayer + units) {
-      step = units + id - kFirstLayer;
-      if (step >= rows_wgs) chain = 2 * chain_units + step - (rows_wgs > units ? rows_wgs : units);
-    } else if (id < 2 * kFirstLayer) {
-      const int at = id - (kFirstLayer + units);  // (the longer the first chain of a unit, the shorter the second)
-      chain = 2 * chain_units - 8 - (at & ~7) + (at & 7);
+      w.places = n_rows + chains;
+      w.tail = ahead + n_rows;
+      if (id < ahead) {
+        chain = id;
+      } else if (id < ahead + n_rows) {
+        step = id - ahead;
+        if (step >= firsts) step = rows_wgs;  // (a place that only rounds the number up)
+        else if (half == 1) step = 2 * firsts - 1 - step;
+      } else {
+        chain = id - n_rows;
+      }
     } else {
-      step = 2 * units + id - 2 * kFirstLayer;
-      if (step >= rows_wgs) chain = id - (rows_wgs > units ? rows_wgs : units);
+      // (a multiple of 8, like everything that shifts the chains' places: a KV head of a chunk keeps its dies)
+      bool beside_steps = false;
+      if (rows_wgs == 0) {
+        beside_steps = true;  // (chains only)
+      } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
+        int longest = 0;
+        uint64_t longer = 0, far_longer = 0;
+  #pragma unroll
+        for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
+        longest = wave_max(longest);
+  #pragma unroll
+        for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
+        beside_steps = rows_wgs <= kFirstLayer && longer == 0;
+        if (far_chunk != 0 && !beside_steps) {
+          int far = 0;  // groups whose chains are longer than half of the longest
+  #pragma unroll
+          for (int r = 0; r < REGS; ++r) {
+            int tokens = kv_len[r] - longest / 2;
+            tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
+            far += groups[r] > 0 ? (int)((float)groups[r] * tokens / q_len[r]) : 0;
+            far_longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] - longest / 2 > longest);
+          }
+          int chain_units = __builtin_amdgcn_readlane(wave_scan_add(far), 63) * a.n_kv_heads / 2;
+          if (far_longer == 0 && rows_wgs > kFirstLayer && chain_units < (2 * kFirstLayer - rows_wgs) / 2) chain_units = (2 * kFirstLayer - rows_wgs) / 2;
+          chain_units = (chain_units < kFirstLayer - kStepUnits ? chain_units : kFirstLayer - kStepUnits) & ~7;
+          units = kFirstLayer - chain_units;
+        }
+      }
+      if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
+      const int chain_units = kFirstLayer - units;
+  
+      if (id < units) {
+        step = id;
+      } else if (id < kFirstLayer || beside_steps) {
+        chain = id - units;
+      } else if (id < kFirstLayer + units) {
+        step = units + id - kFirstLayer;
+        if (step >= rows_wgs) chain = 2 * chain_units + step - (rows_wgs > units ? rows_wgs : units);
+      } else if (id < 2 * kFirstLayer) {
+        const int at = id - (kFirstLayer + units);  // (the longer the first chain of a unit, the shorter the second)
+        chain = 2 * chain_units - 8 - (at & ~7) + (at & 7);
+      } else {
+        step = 2 * units + id - 2 * kFirstLayer;
+        if (step >= rows_wgs) chain = id - (rows_wgs > units ? rows_wgs : units);
+      }
     }
   }
 
@@ -856,17 +1006,17 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
     return w.b >= 0;
   }
 
-  if (step >= rows_wgs) return false;
   w.f0 = -1;
+  if (step >= rows_wgs) return false;
   w.split = 0;
   // ranked by context, or (where all of them start together, and where contexts are split: ranked, the second workgroups of the
   // units with the longest shares had long ones too, 20 decode steps of 240 .. 2408 tokens and 4 chunks of 68 21.2 -> 23.3 us)
   // just the request number `rank` of this kind
-  const bool ranked = rows_wgs > units && a.n_splits == 1;
+  const bool ranked = rows_wgs > (WIDE ? firsts : units) && a.n_splits == 1;
   uint64_t of_kind[REGS];
 #pragma unroll
   for (int r = 0; r < REGS; ++r) of_kind[r] = __builtin_amdgcn_ballot_w64(steps[r] > 0);
-  int pair = ranked && step < units ? units - 1 - step : step;  // (see attn_decode_kernel)
+  int pair = !WIDE && ranked && step < units ? units - 1 - step : step;  // (see attn_decode_kernel)
   if (a.n_splits > 1) {
     // share-major: the first shares of all pairs, then the second shares of those that have one, ...
     for (;;) {
@@ -903,15 +1053,82 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, Work& w) {
 
 #endif  // __HIP_DEVICE_COMPILE__
 
-template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWavesPerSimd, kPagedWavesPerSimd))) void attn_paged_kernel(const PagedArgs a) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  using G = StageGeom<D>;
-  constexpr int kLds = G::kLdsBytes > TileGeom<D>::kLdsBytes ? G::kLdsBytes : TileGeom<D>::kLdsBytes;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
-  __shared__ float s_stats[2 * kWavesPerGroup * 64];
-  if constexpr (kDecodeForm<D>) static_assert(kWavesPerGroup * kDecodeLdsPerWave<D> <= (size_t)kLds, "the decode form fits the tile stages");
+// LDS of a workgroup: the stages of the plain and the packed-rows form (of a wide one's halves, each its own), or the pipeline's rings.
+template <int D, bool WIDE>
+struct PagedLds {
+  static constexpr int kHalf = (StageGeom<D>::kLdsBytes + 1023) / 1024 * 1024;
+  static constexpr int kRows = (WIDE ? kHalf : 0) + StageGeom<D>::kLdsBytes, kRings = TileGeom<D, 1, WIDE ? kWavesPerItem * kWaveTileRows : 0>::kLdsBytes;
+  static constexpr int kBytes = kRows > kRings ? kRows : kRings;
+};
 
+#if defined(__HIP_DEVICE_COMPILE__)
+// A group of four wave tiles of a request (f0 .. f0 + 3 for one KV head) in the plain form: the first four waves of the workgroup.
+template <int D>
+__device__ __forceinline__ void run_plain(const PagedArgs& a, unsigned char* smem, int b, int kv_head, int q_start, int q_len, int kv_len, int f0) {
+  using G = StageGeom<D>;
+  const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
+  const int n_wave_tiles = (q_len + kRows - 1) / kRows * a.group;
+  const int shift = kv_len - q_len;  // keys that precede the first new token
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 31;
+
+  // this wave's tile
+  const bool works = wave < kWavesPerGroup;  // (not the loading waves of a wide workgroup)
+  int f = f0 + wave;
+  const bool active = works && f < n_wave_tiles;
+  if (!active) f = n_wave_tiles - 1;
+  const int tok_tile = f / a.group;
+  const int head = kv_head * a.group + (f - tok_tile * a.group);
+  const int q0 = tok_tile * kRows;
+  const int f_last = (f0 + kWavesPerGroup - 1 < n_wave_tiles ? f0 + kWavesPerGroup - 1 : n_wave_tiles - 1);
+  // keys visible to the last new token of a tile that starts at q: shift + min(q + 32, q_len)
+  auto keys_of_tile = [&](int q) { return shift + (q + kRows < q_len ? q + kRows : q_len); };
+  const int tiles_wg = (keys_of_tile((f_last / a.group) * kRows) + kKvTileRows - 1) / kKvTileRows;
+  const int tiles_wave = active ? (keys_of_tile(q0) + kKvTileRows - 1) / kKvTileRows : 0;
+
+  // first K/V tile in flight before anything else, and the second tile's block-table lookup behind it
+  TileSlots<D, kKvTileRows, kWavesPerGroup> slots, next_slots;
+  if (works) {
+    fetch_tile_slots(slots, a, table, wave, lane, kv_len, 0);
+    issue_tile_loads(slots, a, smem, wave, lane, kv_head);
+  }
+  if (works && 1 < tiles_wg) fetch_tile_slots(slots, a, table, wave, lane, kv_len, kKvTileRows);
+
+  WaveTile<D, 1> w;
+  w.init(lane, a.scale_log2);
+  int row = q0 + m;
+  row = row < q_len ? row : q_len - 1;
+  w.load_q(0, a.q + (int64_t)(q_start + row) * a.q_stride + head * D, shift + row);
+  const int min_lim = shift + q0;  // smallest limit among the tile's tokens
+
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  for (int t = 0; t < tiles_wg; ++t) {
+    unsigned char* stage = smem + (t & 1) * G::kStageBytes;
+    // tile t + 1 is fetched (its slots arrived during the previous iteration) and tile t + 2 is looked up
+    // while tile t is used
+    if (works && t + 1 < tiles_wg) issue_tile_loads(slots, a, smem + ((t + 1) & 1) * G::kStageBytes, wave, lane, kv_head);
+    if (works && t + 2 < tiles_wg) fetch_tile_slots(next_slots, a, table, wave, lane, kv_len, (t + 2) * kKvTileRows);
+    if (t < tiles_wave) {
+      const int kv0 = t * kKvTileRows;
+      w.template tile<2>(stage, kv0, kv0 + kKvTileRows - 1 > min_lim);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    slots = next_slots;
+  }
+  w.store_row(0, active && q0 + m < q_len ? a.out + ((int64_t)(q_start + q0 + m) * a.n_q_heads + head) * D : nullptr);
+}
+
+// A workgroup, from its place in the grid to its result.
+template <int D, bool WIDE>
+__device__ __forceinline__ void run_place(const PagedArgs& a, unsigned char* smem, float* s_stats) {
+  const int tid = (int)threadIdx.x;
+  using G = StageGeom<D>;
+  using Source = PagedSource<WIDE ? 4 : 0>;
+  constexpr int kHalfLds = PagedLds<D, WIDE>::kHalf;
   // new tokens and context of request b (context cut to what the table can describe; q_len 0: nothing to do,
   // also for a context shorter than its new tokens, which is invalid)
   auto lengths_of = [&](int b, int& q_len, int& kv_len) {
@@ -922,10 +1139,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
     if (q_len < 0 || kv_len < q_len) q_len = 0;
   };
   int b, kv_head, q_start, q_len, kv_len, split = 0, f0 = -1;  // f0 < 0: the packed-rows form or the decode form
-  if (a.batch <= kOrderedMost) {
+  int places = 0, tail = 0;
+  if (WIDE || a.batch <= kOrderedMost) {
     Work w;
-    if (!(a.batch <= 64 ? find_work<1>(a, w) : a.batch <= 128 ? find_work<2>(a, w) : find_work<4>(a, w))) return;
-    b = w.b, kv_head = w.kv_head, q_start = w.q_start, q_len = w.q_len, kv_len = w.kv_len, split = w.split, f0 = w.f0;
+    bool found;
+    if constexpr (WIDE) {
+      found = a.batch <= 64 ? find_work<1, true>(a, (int)blockIdx.x, w) : find_work<2, true>(a, (int)blockIdx.x, w);
+    } else {
+      found = a.batch <= 64 ? find_work<1, false>(a, (int)blockIdx.x, w) : a.batch <= 128 ? find_work<2, false>(a, (int)blockIdx.x, w) : find_work<4, false>(a, (int)blockIdx.x, w);
+    }
+    if (!found) {
+      if (WIDE && w.f0 < 0) __syncthreads();  // (the other half of the waves may have a decode step)
+      return;
+    }
+    b = w.b, kv_head = w.kv_head, q_start = w.q_start, q_len = w.q_len, kv_len = w.kv_len, split = w.split, f0 = w.f0, places = w.places, tail = w.tail;
   } else {
     const int n_rows_wgs = (int)gridDim.x - a.n_tile_wgs;
     // This workgroup's place: decode steps, then chains.  Where the decode steps fill the first layer of the chip (256 units) and
@@ -939,7 +1166,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
     {
       int c = (kFirstLayer * 2 - n_rows_wgs) / 2;
       c = (c < a.n_tile_wgs ? c : a.n_tile_wgs) & ~7;  // (places only change hands with ids that the grid has; a multiple of 8: KV heads keep their dies)
-      const int id = (int)blockIdx.x;
+      const int id = place;
       if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
         bool far = false;
         for (int r = (int)threadIdx.x; r < a.batch; r += 256) {
@@ -1067,26 +1294,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
     q_start = a.cu_seqlens_q[b];
   }
   if (f0 < 0) {
+    const int half = WIDE ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0, thread = tid - 256 * half;
+    unsigned char* const lds = smem + half * kHalfLds;
+    bool met;  // (the halves of a wide workgroup share one barrier)
     if constexpr (kDecodeForm<D>) {
       if (q_len * a.group <= kDecodeRows && (1 << a.block_shift) >= kDecodeMinBlock) {
-        run_decode<D>(a, reinterpret_cast<float*>(smem), kWavesPerGroup, kWavesPerGroup, b, kv_head, q_start, q_len, kv_len, split);
+        met = run_decode<D>(a, reinterpret_cast<float*>(lds), kWavesPerGroup, kWavesPerGroup, b, kv_head, q_start, q_len, kv_len, split, thread);
+        if (WIDE && !met) __syncthreads();
         return;
       }
     }
-    run_packed_rows<D>(a, smem, s_stats, a.block_tables + (int64_t)b * a.max_blocks_per_seq, q_start, q_len, kv_len, kv_head, b, split);
+    met = run_packed_rows<D>(a, lds, s_stats + half * (2 * kWavesPerGroup * 64), a.block_tables + (int64_t)b * a.max_blocks_per_seq, q_start, q_len, kv_len, kv_head, b, split,
+                             thread);
+    if (WIDE && !met) __syncthreads();
     return;
   }
   const int32_t* table = a.block_tables + (int64_t)b * a.max_blocks_per_seq;
-  const int n_tok_tiles = (q_len + kRows - 1) / kRows;
-  const int n_wave_tiles = n_tok_tiles * a.group;
-  if (f0 >= n_wave_tiles) return;  // (cannot happen: the group was counted from these lengths)
-  const int shift = kv_len - q_len;  // keys that precede the first new token
+  if (f0 >= (q_len + kRows - 1) / kRows * a.group) return;  // (cannot happen: the group was counted from these lengths)
+  bool redo = true;
 
   // The group runs on the packed kernel's pipeline when the cache layout allows (see PagedSource); if its row sums
   // leave that path's range, or the layout does not allow, the plain loop below computes (or recomputes) it.
   if constexpr (TileLoader<D>::kUniformStep) {
-    if ((1 << a.block_shift) >= PagedSource::Gather<D>::kRowsPerInstr && a.num_blocks <= (0x7fffffff >> a.block_shift)) {
-      PagedSource src;
+    if ((1 << a.block_shift) >= PagedSource<0>::Gather<D>::kRowsPerInstr && a.num_blocks <= (0x7fffffff >> a.block_shift)) {
+      Source src;
       src.args = &a;
       src.table = table;
       src.q_start = q_start;
@@ -1109,58 +1340,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPagedWaves
       fa.group = a.group;
       fa.scale_log2 = a.scale_log2;
       int* s_claim = reinterpret_cast<int*>(s_stats);  // (unused by a paged item; the redo flag lives behind it)
-      if (!attn_item_loop<D, true>(fa, src, smem, s_claim, s_claim + 8)) return;
+      if (!attn_item_loop<D, true>(fa, src, smem, s_claim, s_claim + 8)) {
+        if (!WIDE || places <= (int)gridDim.x) return;
+        redo = false;
+      }
     }
   }
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = lane & 31;
-
-  // this wave's tile
-  int f = f0 + wave;
-  const bool active = f < n_wave_tiles;
-  if (!active) f = n_wave_tiles - 1;
-  const int tok_tile = f / a.group;
-  const int head = kv_head * a.group + (f - tok_tile * a.group);
-  const int q0 = tok_tile * kRows;
-  const int f_last = (f0 + kWavesPerGroup - 1 < n_wave_tiles ? f0 + kWavesPerGroup - 1 : n_wave_tiles - 1);
-  // keys visible to the last new token of a tile that starts at q: shift + min(q + 32, q_len)
-  auto keys_of_tile = [&](int q) { return shift + (q + kRows < q_len ? q + kRows : q_len); };
-  const int tiles_wg = (keys_of_tile((f_last / a.group) * kRows) + kKvTileRows - 1) / kKvTileRows;
-  const int tiles_wave = active ? (keys_of_tile(q0) + kKvTileRows - 1) / kKvTileRows : 0;
-
-  // first K/V tile in flight before anything else, and the second tile's block-table lookup behind it
-  TileSlots<D, kKvTileRows, kWavesPerGroup> slots, next_slots;
-  fetch_tile_slots(slots, a, table, wave, lane, kv_len, 0);
-  issue_tile_loads(slots, a, smem, wave, lane, kv_head);
-  if (1 < tiles_wg) fetch_tile_slots(slots, a, table, wave, lane, kv_len, kKvTileRows);
-
-  WaveTile<D, 1> w;
-  w.init(lane, a.scale_log2);
-  int row = q0 + m;
-  row = row < q_len ? row : q_len - 1;
-  w.load_q(0, a.q + (int64_t)(q_start + row) * a.q_stride + head * D, shift + row);
-  const int min_lim = shift + q0;  // smallest limit among the tile's tokens
-
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-
-  for (int t = 0; t < tiles_wg; ++t) {
-    unsigned char* stage = smem + (t & 1) * G::kStageBytes;
-    // tile t + 1 is fetched (its slots arrived during the previous iteration) and tile t + 2 is looked up
-    // while tile t is used
-    if (t + 1 < tiles_wg) issue_tile_loads(slots, a, smem + ((t + 1) & 1) * G::kStageBytes, wave, lane, kv_head);
-    if (t + 2 < tiles_wg) fetch_tile_slots(next_slots, a, table, wave, lane, kv_len, (t + 2) * kKvTileRows);
-    if (t < tiles_wave) {
-      const int kv0 = t * kKvTileRows;
-      w.template tile<2>(stage, kv0, kv0 + kKvTileRows - 1 > min_lim);
+  if (redo) run_plain<D>(a, smem, b, kv_head, q_start, q_len, kv_len, f0);
+  if constexpr (WIDE) {
+    // The host sizes a wide grid for the chunks that it expects from their number of tokens (one for all that there can be would
+    // be mostly empty workgroups, 1.3 us of a compute unit each).  Places past its end are for the last workgroups, all of
+    // them chains, through the plain loop, whose code is here anyway.
+    const int last = (int)gridDim.x - 1 - (int)blockIdx.x, workers = (int)gridDim.x - tail;
+    for (int id = (int)gridDim.x + last; last < workers && id < places; id += workers) {
+      Work w;
+      if (!(a.batch <= 64 ? find_work<1, true>(a, id, w) : find_work<2, true>(a, id, w)) || w.f0 < 0) return;  // (cannot happen: a chain's place)
+      __syncthreads();
+      run_plain<D>(a, smem, w.b, w.kv_head, w.q_start, w.q_len, w.kv_len, w.f0);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    slots = next_slots;
   }
-  w.store_row(0, active && q0 + m < q_len ? a.out + ((int64_t)(q_start + q0 + m) * a.n_q_heads + head) * D : nullptr);
+}
+
+#endif
+
+template <int D, bool WIDE>
+__global__ __launch_bounds__(WIDE ? 512 : 256) __attribute__((amdgpu_waves_per_eu(kPagedWavesPerSimd, kPagedWavesPerSimd))) void attn_paged_kernel(const PagedArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[PagedLds<D, WIDE>::kBytes];
+  __shared__ float s_stats[(WIDE ? 2 : 1) * 2 * kWavesPerGroup * 64];
+  if constexpr (kDecodeForm<D>) static_assert(kWavesPerGroup * kDecodeLdsPerWave<D> <= (size_t)StageGeom<D>::kLdsBytes, "the decode form fits the tile stages");
+  run_place<D, WIDE>(a, smem, s_stats);
 #else
   (void)a;
 #endif

@@ -621,6 +621,46 @@ def test_shares_follow_the_contexts_not_the_table(q_lens, kv_lens, hq, hkv, d, b
         assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
+WIDE_CASES = [
+    # q_lens, kv_lens, Hq, Hkv, d, block_size
+    ([130], [130], 28, 4, 128, 16),                                              # chains alone
+    ([1, 130, 1, 200, 1], [60, 130, 1, 500, 33], 28, 4, 128, 16),                # a unit for everything
+    ([1] * 70 + [150, 150], [8 * i + 1 for i in range(70)] + [150, 300], 28, 4, 128, 16),     # two decode steps to a workgroup, not for all
+    ([1] * 101 + [250], [6 * i + 3 for i in range(101)] + [700], 5, 5, 64, 16),               # ... for all but one, an odd number
+    ([64] + [33] * 20, [64] + [33 + 20 * i for i in range(20)], 64, 4, 64, 16),               # more chains than the grid expects
+    ([64] + [33] * 30, [64] + [33] * 30, 28, 4, 128, 16),
+    ([3, 1, 90, 4, 2], [100, 40, 190, 4, 77], 8, 1, 128, 16),                    # 24 and 32 rows beside 8
+    ([1, 2, 100, 1], [50, 200, 100, 9], 8, 2, 64, 8),                            # blocks that the decode form does not take
+    ([1, 70, 1], [30, 140, 200], 4, 2, 128, 4),
+    ([0, 1, 100, 5, 0, 1], [4, 20, 140, 5, 0, 90], 7, 1, 128, 16),               # requests without new tokens
+    ([1] * 127 + [300], [64] * 127 + [300], 4, 2, 64, 16),                       # two registers of lengths
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: f"n{len(c[0])}-q{sum(c[0])}-kv{max(c[1])}-h{c[2]}k{c[3]}-d{c[4]}-b{c[5]}")
+@pytest.mark.parametrize("planted", [False, True])
+def test_hybrid_batches_in_wide_workgroups(case, planted):
+    """Hybrid batches whose chunks are long against the contexts run in workgroups of eight waves, under a block table that allows
+    far longer contexts in workgroups of four: the oracle, and the same bits (without splits, which follow the table) unless
+    keys far out of the fast path's range or chains past the end of the grid take the plain form."""
+    q_lens, kv_lens, hq, hkv, d, bs = case
+    h = si.HybridBatch("wide", q_lens, kv_lens, hq, hkv, d, block_size=bs, seed=sum(q_lens))
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    if planted:
+        kc = kc.clone()
+        for b, L in enumerate(kv_lens):
+            if L > 50:
+                kc[tables[b, 45 // bs], 45 % bs] = 64.0
+    far = np.full((h.batch, 32768 // bs), -1, dtype=np.int32)
+    far[:, : tables.shape[1]] = tables
+    want = _want(h, q, kc, vc, tables)
+    wide, narrow = _run_gpu(h, q, kc, vc, tables, use_workspace=False), _run_gpu(h, q, kc, vc, far, use_workspace=False)
+    _check(wide, want)
+    _check(narrow, want)
+    if len(q_lens) < 20 or q_lens[1] != 33:
+        assert torch.equal(wide.view(torch.int16), narrow.view(torch.int16))
+
+
 @pytest.mark.parametrize("longest", [407, 511, 512])
 def test_short_contexts_under_a_wide_table(longest):
     """Between 257 and 512 (request, KV head) pairs under a table of 8192 keys: launched with eight waves per workgroup, of which
