@@ -1375,23 +1375,108 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) __attribute__((amdgpu_waves_per_e
 #endif
 }
 
-// Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch, parts), kCombineThreads threads;
+// Merges the partial results of split contexts (n_splits > 1).  grid = (n_kv_heads, batch, parts), kCombineThreads<GROUPS> threads;
 // parts: as many as give every thread 4 output columns of one row, for the most rows a request of the batch can have.
 // Requests that took the wave-tile form, have no new tokens, or whose context fits one share (already finished by one
-// workgroup) are skipped.  A thread adds up its columns over the shares; it asks for everything it needs (every share's row
-// statistics and columns) before it uses any of it, so that behind the two lengths the kernel is one round trip to memory
-// long: it runs on an idle chip, and latency is all it costs (3.8 us after a decode of 4 requests, 4.6 us after one of
-// 8 x 16 384 keys, most of it launch and instruction fetch).  With one workgroup per (request, KV head) a request of more than
-// 8 rows of 128 took that trip two to four times: 30 requests of 4 new tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2,
-// 28 / 2 heads, 18.9 -> 15.9; decode steps unchanged.
+// workgroup) are skipped.
+// The kernel runs on an idle chip, and latency is all it costs, most of it the launch, the lengths and the fetch of its own code.  So it
+// asks for everything it needs (every share's row statistics and columns) before it uses any of it, one round trip to memory behind the
+// lengths; and it has little code on any way through: GROUPS threads have the same columns, each with every GROUPS-th share, up to EACH
+// of them, in code for 2, 4 or EACH, and the first adds up what they have through LDS.  us of both kernels, with one thread for all of up
+// to 16 shares and so, 28 / 4 heads of 128: 4 requests of 300 .. 1500 tokens 7.7 -> 6.9, 8 of 750 .. 1500 9.3 -> 8.6, 32 of 750 .. 1500
+// (2 shares) 18.8 -> 17.6, 4 of 8000 .. 16000 22.3 -> 21.5; two shares for each of eight waves instead of four for each of four 7.1 where
+// four have 6.9, four for each of sixteen 9.5 where eight for each of eight have 8.5, which take 8.2 with the shorter ways beside the long one.
+// With one workgroup per (request, KV head) a request of more than 8 rows of 128 took that trip two to four times: 30 requests of 4 new
+// tokens, 28 / 4 heads of 128, 29.1 -> 27.2 us; 20 of 2, 28 / 2 heads, 18.9 -> 15.9.
 // The records of all shares asked for together with the lengths, whether they exist or not, cost what they gave: one request of 6000
 // tokens 10.9 -> 10.5 us of both kernels, 4 of 50 .. 300 under a table of 8192 keys 7.3 -> 7.1, but of contexts that are not cut 40 of
 // 100 .. 500 under such a table 9.3 -> 10.1, 16 of 50 .. 400 7.9 -> 8.4 (out of the caches 12.1 -> 13.6).
-constexpr int kMaxSplits = 16;
-constexpr int kCombineThreads = 256;
+// Shares of a context.  16 left a lone request with a quarter of the chip: 28 / 4 heads of 128, one of 16 384 tokens 18.5 -> 11.3 us, of 5000
+// 10.2 -> 8.2, two of 16 000 19.0 -> 15.5; beside chunks there are 16 still (choose_splits).
+constexpr int kMaxSplits = 64;
+template <int GROUPS>
+constexpr int kCombineThreads = GROUPS > 4 ? 64 * GROUPS : 256;
+template <int GROUPS>
+constexpr int kCombinePieces = kCombineThreads<GROUPS> / GROUPS;  // of 4 columns of a row that a workgroup does
 
-template <int D>
-__global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(const PagedArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int D, int GROUPS, int EACH>
+__device__ __forceinline__ void merge_shares(const PagedArgs& a, const float* recs, int n_shares, int q_start, int kv_head, int n_rows) {
+  constexpr int kColGroups = D / 4, kPieces = kCombinePieces<GROUPS>;
+  static_assert(kPieces % 64 == 0, "whole waves");
+  const int group = GROUPS == 1 ? 0 : (int)threadIdx.x / kPieces, piece = (int)threadIdx.x % kPieces;
+  const int pieces = n_rows * kColGroups;
+  for (int base = (int)blockIdx.z * kPieces; base < pieces; base += (int)gridDim.z * kPieces) {
+    const int i = base + piece;
+    if (GROUPS == 1 && i >= pieces) return;
+    const int row = i < pieces ? i / kColGroups : 0, col = (i % kColGroups) * 4;
+    f32x4_t v[EACH];
+    float top[EACH], sum[EACH];
+    // (shares past the last one re-read it and are left out below: no branch between the loads)
+#pragma unroll
+    for (int s = 0; s < EACH; ++s) {
+      const int share = s * GROUPS + group;
+      const float* rec = recs + (int64_t)(share < n_shares ? share : n_shares - 1) * kPartialFloats<D>;
+      top[s] = rec[row];
+      sum[s] = rec[kRows + row];
+      v[s] = *reinterpret_cast<const f32x4_t*>(rec + 2 * kRows + row * D + col);
+    }
+    float best = top[0];
+#pragma unroll
+    for (int s = 1; s < EACH; ++s) best = fmaxf(best, top[s]);
+    float total = 0.f;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < EACH; ++s) {
+      // (not by weight 0 alone: an infinite V in the last share would come out as NaN)
+      const bool live = s * GROUPS + group < n_shares;
+      const float w = live ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
+      total += w * (live ? sum[s] : 0.f);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += w * (live ? v[s][e] : 0.f);
+    }
+    if constexpr (GROUPS > 1) {
+      __shared__ f32x4_t s_acc[GROUPS][kPieces];
+      __shared__ f32x2_t s_stat[GROUPS][kPieces];
+      s_acc[group][piece] = acc;
+      s_stat[group][piece] = f32x2_t{best, total};
+      __syncthreads();
+      if (group == 0) {
+        f32x2_t stat[GROUPS];
+        f32x4_t part[GROUPS];
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+          stat[g] = s_stat[g][piece];
+          part[g] = s_acc[g][piece];
+        }
+#pragma unroll
+        for (int g = 1; g < GROUPS; ++g) best = fmaxf(best, stat[g][0]);
+        total = 0.f;
+        acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+          const float w = g < n_shares ? fast_exp2((stat[g][0] - best) * a.scale_log2) : 0.f;
+          total += w * stat[g][1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] += w * part[g][e];
+        }
+      }
+      __syncthreads();  // (before the next pieces' results)
+      if (group != 0 || i >= pieces) continue;
+    }
+    const float inv = 1.0f / total;
+    const int token = row / a.group;
+    const int head = kv_head * a.group + (row - token * a.group);
+    const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
+    u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
+                  __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2_t))};
+    *reinterpret_cast<u32x2_t*>(a.out + ((int64_t)(q_start + token) * a.n_q_heads + head) * D + col) = pk;
+  }
+}
+#endif
+
+template <int D, int GROUPS, int EACH>
+__global__ __launch_bounds__(kCombineThreads<GROUPS>) void attn_paged_combine_kernel(const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const int b = blockIdx.y, kv_head = blockIdx.x;
   const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
@@ -1407,41 +1492,9 @@ __global__ __launch_bounds__(kCombineThreads) void attn_paged_combine_kernel(con
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   if (n_shares == 1) return;  // done by one workgroup, which wrote the output itself
   const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
-  constexpr int kColGroups = D / 4;
-  for (int i = (int)blockIdx.z * kCombineThreads + (int)threadIdx.x; i < n_rows * kColGroups; i += (int)gridDim.z * kCombineThreads) {
-    const int row = i / kColGroups, col = (i - row * kColGroups) * 4;
-    f32x4_t v[kMaxSplits];
-    float top[kMaxSplits], sum[kMaxSplits];
-    // (shares past the last one re-read it and are left out below: no branch between the loads)
-#pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s) {
-      const float* rec = recs + (int64_t)(s < n_shares ? s : n_shares - 1) * kPartialFloats<D>;
-      top[s] = rec[row];
-      sum[s] = rec[kRows + row];
-      v[s] = *reinterpret_cast<const f32x4_t*>(rec + 2 * kRows + row * D + col);
-    }
-    float best = top[0];
-#pragma unroll
-    for (int s = 1; s < kMaxSplits; ++s) best = fmaxf(best, top[s]);
-    float total = 0.f;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < kMaxSplits; ++s) {
-      // (not by weight 0 alone: an infinite V in the last share would come out as NaN)
-      const bool live = s < n_shares;
-      const float w = live ? fast_exp2((top[s] - best) * a.scale_log2) : 0.f;
-      total += w * (live ? sum[s] : 0.f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] += w * (live ? v[s][e] : 0.f);
-    }
-    const float inv = 1.0f / total;
-    const int token = row / a.group;
-    const int head = kv_head * a.group + (row - token * a.group);
-    const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
-    u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
-                  __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2_t))};
-    *reinterpret_cast<u32x2_t*>(a.out + ((int64_t)(q_start + token) * a.n_q_heads + head) * D + col) = pk;
-  }
+  if (EACH > 2 && n_shares <= 2 * GROUPS) merge_shares<D, GROUPS, 2>(a, recs, n_shares, q_start, kv_head, n_rows);
+  else if (EACH > 4 && n_shares <= 4 * GROUPS) merge_shares<D, GROUPS, 4>(a, recs, n_shares, q_start, kv_head, n_rows);
+  else merge_shares<D, GROUPS, EACH>(a, recs, n_shares, q_start, kv_head, n_rows);
 #else
   (void)a;
 #endif

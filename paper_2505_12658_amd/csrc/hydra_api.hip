@@ -204,7 +204,9 @@ PagedSplits paged_splits(int32_t batch, int32_t n_kv_heads, int32_t max_blocks_p
 // *least_log2: half tiles up to which a context is not cut further (share_plan).  Beside chunks 512 keys, as above; otherwise
 // one half tile per wave, and more where shares are few and long anyway, since short contexts then only add to the merge
 // (30 requests of 100 .. 1400 tokens in 2 shares: 14.4 us with 4 half tiles, 14.0 with 16).
-int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t tile_wgs, int32_t head_dim, size_t workspace_bytes, int32_t* least_log2) {
+int choose_splits(PagedSplits s, int64_t pairs, int64_t keys, int64_t tile_wgs, int32_t head_dim, size_t workspace_bytes, int32_t* least_log2) {
+  // (beside chunks as many shares as were measured there)
+  if (tile_wgs > 0) s = {s.once < 16 ? s.once : 16, s.twice < 16 ? s.twice : 16};
   auto layers = [&](int64_t n) { return (pairs * n + 255) / 256; };  // shares on the busiest unit, of 1 / n of a context
   int64_t n = layers(s.twice) * s.once * 10 < layers(s.once) * s.twice * 9 ? s.twice : s.once;
   int32_t beside_chunks = 0;
@@ -219,6 +221,10 @@ int choose_splits(const PagedSplits& s, int64_t pairs, int64_t keys, int64_t til
   if (n < 2) n = 1;
   const int64_t halves = (keys < 2048 ? keys : 2048) / 32 / n;
   *least_log2 = beside_chunks != 0 ? beside_chunks : halves < 8 ? 2 : halves < 16 ? 3 : 4;
+  // No more than the longest context that the table describes can have: fewer empty workgroups, and a shorter merge.  (Where contexts
+  // are cut stays the same.  Beside chunks the number has a say in where they go: left.)
+  const int64_t most = ((keys + 31) / 32 + ((int64_t)1 << *least_log2) - 1) >> *least_log2;
+  if (tile_wgs == 0 && n > most) n = most;
   return (int)n;
 }
 
@@ -295,8 +301,18 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t total_q, in
   if (err == hipSuccess && args.n_splits > 1) {
     const int64_t rows = (int64_t)max_q_len * args.group;
     const int64_t pieces = (rows < hydra::paged::kRows ? rows : hydra::paged::kRows) * (D / 4);
-    const unsigned parts = (unsigned)((pieces + hydra::paged::kCombineThreads - 1) / hydra::paged::kCombineThreads);
-    err = launch(hydra::paged::attn_paged_combine_kernel<D>, dim3((unsigned)args.n_kv_heads, (unsigned)args.batch, parts), dim3(hydra::paged::kCombineThreads), s, args);
+    // (a merge with as little code as the number of shares allows: see the kernel)
+    auto merge = [&](auto groups, auto each) {
+      constexpr int kGroups = decltype(groups)::value, kPieces = hydra::paged::kCombinePieces<kGroups>;
+      return launch(hydra::paged::attn_paged_combine_kernel<D, kGroups, decltype(each)::value>,
+                    dim3((unsigned)args.n_kv_heads, (unsigned)args.batch, (unsigned)((pieces + kPieces - 1) / kPieces)),
+                    dim3(hydra::paged::kCombineThreads<kGroups>), s, args);
+    };
+    using std::integral_constant;
+    if (args.n_splits <= 2) err = merge(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    else if (args.n_splits <= 4) err = merge(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    else if (args.n_splits <= 16) err = merge(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+    else err = merge(integral_constant<int, 8>{}, integral_constant<int, 8>{});
   }
   return err;
 }

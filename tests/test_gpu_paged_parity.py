@@ -575,6 +575,45 @@ def test_merge_of_requests_with_many_rows(d, rows):
     _check(_run_gpu(h, q, kc, vc, tables), _want(h, q, kc, vc, tables))
 
 
+@pytest.mark.parametrize("q_lens,kv_lens,hq,hkv,d,most", [
+    ([1], [8192], 7, 1, 128, 64),                                          # 64 shares: eight for each of eight waves
+    ([1] * 4, [8192, 128 * 33 + 1, 4096, 4097], 16, 1, 64, 64),            # 64, 34, 32 and 33 shares
+    ([1] * 4, [4096, 128 * 17 + 1, 2048, 128], 7, 1, 128, 64),             # 32, 18, 16 and one
+    ([1] * 3, [2177, 1100, 1025], 8, 1, 64, 64),                           # a table for 18 shares: 18, 9 and 9
+    ([1] * 5, [1000, 513, 512, 257, 256], 28, 2, 128, 51),                 # a table for 8: 8, 5, 4, 3 and 2
+    ([1] * 3, [700, 257, 129], 4, 2, 64, 64),                              # a table for 6: 6, 3 and 2
+    ([1] * 16, [1500, 700, 300, 40] * 4, 8, 4, 64, 8),                     # 4 shares of 256 units, room for 8
+    ([1] * 16, [1500, 700, 300, 40] * 4, 8, 8, 64, 4),                     # 2
+    ([1] * 2, [250, 130], 4, 4, 128, 0),                                   # too short to be cut
+    ([8, 3, 0, 1], [6000, 4100, 900, 2200], 4, 1, 128, 64),                # 32 rows, in the other form of the first kernel
+    ([4, 1], [3000, 5000], 8, 1, 80, 64),
+    ([1] * 20, [4096] * 10 + [1500] * 10, 4, 1, 128, 25),                  # 12 shares of 256 units, room for 25
+])
+def test_number_of_shares(q_lens, kv_lens, hq, hkv, d, most):
+    """Contexts of few requests in up to 64 shares, around the numbers where the merge takes another way, over a workspace of NaN; and
+    with an infinity in the last key's V, which one share has alone."""
+    import paper_2505_12658_amd as hydra
+
+    h = si.HybridBatch("shares", q_lens, kv_lens, hq, hkv, d, block_size=16, seed=len(q_lens))
+    q, kc, vc, tables = si.make_paged_inputs(h)
+    need = hydra.hydra_attn_paged_workspace_bytes(h.batch, hkv, d, tables.shape[1], 16)
+    assert need == most * h.batch * hkv * (2 * 32 + 32 * d) * 4
+    want = _want(h, q, kc, vc, tables)
+    for records in sorted({most, most // 2, min(most, 16)}):
+        ws = torch.full((max(records * h.batch * hkv * (2 * 32 + 32 * d), 4),), float("nan"), device="cuda:0")
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        _check(_run_gpu(h, q, kc, vc, tables, out=out, workspace=ws), want)
+    if q_lens[0] > 1:  # (its other tokens multiply the infinity by 0)
+        return
+    last = kv_lens[0] - 1
+    vc = vc.clone()
+    vc[int(tables[0][last // 16]), last % 16, 0, 5] = float("inf")
+    got = _run_gpu(h, q, kc, vc, tables).cpu()
+    assert (got[0, :hq // hkv, 5] == float("inf")).all()
+    got[0, :hq // hkv, 5] = torch.from_numpy(want[0, :hq // hkv, 5])
+    _check(got, want)
+
+
 @pytest.mark.parametrize("kv_lens,chunk,split", [
     ([1000, 120, 430], 128, False),     # the chunk's chain of key tiles is what the kernel waits for
     ([2500, 700, 90], 60, True),        # contexts far longer than the chunk
