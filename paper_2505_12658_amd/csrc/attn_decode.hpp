@@ -267,7 +267,7 @@ __device__ __forceinline__ bool run_decode(const PagedArgs& a, float* lds, int n
 
   // this lane's row
   const int row = m < n_rows ? m : n_rows - 1;
-  const int token = row / a.group;
+  const int token = quotient(row, a.group);
   const int head = kv_head * a.group + (row - token * a.group);
   const int lim = kv_len - q_len + token;  // largest visible key
   const float c = a.scale_log2;
@@ -362,7 +362,7 @@ __device__ __forceinline__ bool run_decode(const PagedArgs& a, float* lds, int n
       }
     }
     if (whole) {
-      const int tok = r / a.group, hd = kv_head * a.group + (r - tok * a.group);
+      const int tok = quotient(r, a.group), hd = kv_head * a.group + (r - tok * a.group);
       const float inv = 1.0f / total;
       const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
       const u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
@@ -491,21 +491,39 @@ inline int decode_streams(int64_t pairs, int n_splits, int64_t table_keys) {
 constexpr int kDecodeManyPairs = 464;
 inline int decode_waves(int64_t pairs, int streams, bool ordered) { return ordered && pairs < kDecodeManyPairs ? kDecodeWaves : streams; }
 
-// grid = batch * n_kv_heads * n_splits workgroups, share-major (the first shares of all pairs, which every request
-// has, then the second shares, ...); dynamic LDS: STREAMS * kDecodeLdsPerWave<D> bytes.
+#if defined(__HIP_DEVICE_COMPILE__)
+// All arguments in one trip to memory.  (Left to itself the compiler asks for each group of them where it is first used and waits there.)
+// us of the decode kernel and the merge so, and then without integer divisions on the way to the first load (`quotient`, and a grid that
+// says which request and head), 28 / 4 heads of 128: 4 requests of 300 .. 1500 tokens 6.86 -> 6.62 -> 6.39, 16 of 400 .. 800 9.5 -> 9.3 -> 8.9,
+// 4 of 150 .. 300 (not cut) 5.40 -> 5.34 -> 5.05, one of 16 384 11.3 -> 11.1 -> 10.7, 8 of 16 384 45.3 -> 45.2 -> 44.9.  (The block table
+// asked for together with the lengths, where a context is not cut: no faster.)
+__device__ __forceinline__ void ask_for_arguments(const PagedArgs& a) {
+  asm volatile("" : : "s"(a.q), "s"(a.out), "s"(a.q_stride), "s"(a.k_cache), "s"(a.v_cache), "s"(a.block_tables), "s"(a.cu_seqlens_q), "s"(a.kv_lens),
+               "s"(a.max_blocks_per_seq), "s"(a.num_blocks), "s"(a.block_shift), "s"(a.n_q_heads), "s"(a.n_kv_heads), "s"(a.group), "s"(a.scale_log2),
+               "s"(a.n_splits), "s"(a.least_log2), "s"(a.partials), "s"(a.batch));
+}
+#endif
+
+// grid = (n_kv_heads, batch, n_splits) workgroups: share-major (the first shares of all pairs, which every request
+// has, then the second shares, ...).  Ordered: batch * n_kv_heads.  Dynamic LDS: STREAMS * kDecodeLdsPerWave<D> bytes.
 template <int D, bool ORDERED, int WAVES, int STREAMS>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kDecodeWavesPerSimd, kDecodeWavesPerSimd))) void attn_decode_kernel(
     const PagedArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) float s_decode[];
+  ask_for_arguments(a);
   const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;  // (at most 2^30)
   const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
-  const int pairs = a.batch * a.n_kv_heads;
-  const int split = ORDERED ? 0 : (int)blockIdx.x / pairs;
-  int pair = (int)blockIdx.x - split * pairs;
-  if (ORDERED && pair < kUnits) pair = kUnits - 1 - pair;
-  int b = pair / a.n_kv_heads;
-  const int kv_head = pair - b * a.n_kv_heads;
+  int split = 0, b, kv_head;
+  if constexpr (ORDERED) {
+    const int id = (int)blockIdx.x, pair = id < kUnits ? kUnits - 1 - id : id;
+    b = quotient(pair, a.n_kv_heads);
+    kv_head = pair - b * a.n_kv_heads;
+  } else {
+    split = (int)blockIdx.z;
+    b = (int)blockIdx.y;
+    kv_head = (int)blockIdx.x;
+  }
   int q_start = cu[b], q_end = cu[b + 1], kv_len = lens[b];
   if constexpr (!ORDERED) asm volatile("" : "+s"(q_start), "+s"(q_end), "+s"(kv_len));  // (asked for together)
   bool any_long = true;

@@ -556,7 +556,7 @@ __device__ __forceinline__ bool run_packed_rows(const PagedArgs& a, unsigned cha
   int r = m;
   const bool valid = r < n_rows;
   r = valid ? r : n_rows - 1;
-  const int token = r / a.group;
+  const int token = quotient(r, a.group);
   const int head = kv_head * a.group + (r - token * a.group);
   w.load_q(0, a.q + (q_start + token) * a.q_stride + head * D, shift + token);
 
@@ -1369,6 +1369,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) __attribute__((amdgpu_waves_per_e
   __shared__ __attribute__((aligned(1024))) unsigned char smem[PagedLds<D, WIDE>::kBytes];
   __shared__ float s_stats[(WIDE ? 2 : 1) * 2 * kWavesPerGroup * 64];
   if constexpr (kDecodeForm<D>) static_assert(kWavesPerGroup * kDecodeLdsPerWave<D> <= (size_t)StageGeom<D>::kLdsBytes, "the decode form fits the tile stages");
+  ask_for_arguments(a);
+  asm volatile("" : : "s"(a.n_tile_wgs), "s"(a.order_keys));
   run_place<D, WIDE>(a, smem, s_stats);
 #else
   (void)a;
@@ -1383,7 +1385,7 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) __attribute__((amdgpu_waves_per_e
 // asks for everything it needs (every share's row statistics and columns) before it uses any of it, one round trip to memory behind the
 // lengths; and it has little code on any way through: GROUPS threads have the same columns, each with every GROUPS-th share, up to EACH
 // of them, in code for 2, 4 or EACH, and the first adds up what they have through LDS.  us of both kernels, with one thread for all of up
-// to 16 shares and so, 28 / 4 heads of 128: 4 requests of 300 .. 1500 tokens 7.7 -> 6.9, 8 of 750 .. 1500 9.3 -> 8.6, 32 of 750 .. 1500
+// to 16 shares and so (before ask_for_arguments and `quotient`), 28 / 4 heads of 128: 4 requests of 300 .. 1500 tokens 7.7 -> 6.9, 8 of 750 .. 1500 9.3 -> 8.6, 32 of 750 .. 1500
 // (2 shares) 18.8 -> 17.6, 4 of 8000 .. 16000 22.3 -> 21.5; two shares for each of eight waves instead of four for each of four 7.1 where
 // four have 6.9, four for each of sixteen 9.5 where eight for each of eight have 8.5, which take 8.2 with the shorter ways beside the long one.
 // With one workgroup per (request, KV head) a request of more than 8 rows of 128 took that trip two to four times: 30 requests of 4 new
@@ -1391,8 +1393,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) __attribute__((amdgpu_waves_per_e
 // The records of all shares asked for together with the lengths, whether they exist or not, cost what they gave: one request of 6000
 // tokens 10.9 -> 10.5 us of both kernels, 4 of 50 .. 300 under a table of 8192 keys 7.3 -> 7.1, but of contexts that are not cut 40 of
 // 100 .. 500 under such a table 9.3 -> 10.1, 16 of 50 .. 400 7.9 -> 8.4 (out of the caches 12.1 -> 13.6).
-// Shares of a context.  16 left a lone request with a quarter of the chip: 28 / 4 heads of 128, one of 16 384 tokens 18.5 -> 11.3 us, of 5000
-// 10.2 -> 8.2, two of 16 000 19.0 -> 15.5; beside chunks there are 16 still (choose_splits).
+// Shares of a context.  16 left a lone request with a quarter of the chip: 28 / 4 heads of 128, one of 16 384 tokens 18.5 -> 11.3 us (10.7 now), of
+// 5000 10.2 -> 8.2 (7.6), two of 16 000 19.0 -> 15.5 (14.9); beside chunks there are 16 still (choose_splits).
 constexpr int kMaxSplits = 64;
 template <int GROUPS>
 constexpr int kCombineThreads = GROUPS > 4 ? 64 * GROUPS : 256;
@@ -1401,12 +1403,12 @@ constexpr int kCombinePieces = kCombineThreads<GROUPS> / GROUPS;  // of 4 column
 
 #if defined(__HIP_DEVICE_COMPILE__)
 template <int D, int GROUPS, int EACH>
-__device__ __forceinline__ void merge_shares(const PagedArgs& a, const float* recs, int n_shares, int q_start, int kv_head, int n_rows) {
+__device__ __forceinline__ void merge_shares(const PagedArgs& a, const float* recs, int n_shares, int q_start, int kv_head, int n_rows, int parts) {
   constexpr int kColGroups = D / 4, kPieces = kCombinePieces<GROUPS>;
   static_assert(kPieces % 64 == 0, "whole waves");
   const int group = GROUPS == 1 ? 0 : (int)threadIdx.x / kPieces, piece = (int)threadIdx.x % kPieces;
   const int pieces = n_rows * kColGroups;
-  for (int base = (int)blockIdx.z * kPieces; base < pieces; base += (int)gridDim.z * kPieces) {
+  for (int base = (int)blockIdx.z * kPieces; base < pieces; base += parts * kPieces) {
     const int i = base + piece;
     if (GROUPS == 1 && i >= pieces) return;
     const int row = i < pieces ? i / kColGroups : 0, col = (i % kColGroups) * 4;
@@ -1465,7 +1467,7 @@ __device__ __forceinline__ void merge_shares(const PagedArgs& a, const float* re
       if (group != 0 || i >= pieces) continue;
     }
     const float inv = 1.0f / total;
-    const int token = row / a.group;
+    const int token = quotient(row, a.group);
     const int head = kv_head * a.group + (row - token * a.group);
     const f32x2_t a0 = {acc[0] * inv, acc[1] * inv}, a1 = {acc[2] * inv, acc[3] * inv};
     u32x2_t pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2_t)),
@@ -1480,9 +1482,12 @@ __global__ __launch_bounds__(kCombineThreads<GROUPS>) void attn_paged_combine_ke
 #if defined(__HIP_DEVICE_COMPILE__)
   const int b = blockIdx.y, kv_head = blockIdx.x;
   const const_table_t cu = (const_table_t)(uintptr_t)a.cu_seqlens_q, lens = (const_table_t)(uintptr_t)a.kv_lens;
-  const int q_start = cu[b];
-  const int q_len = cu[b + 1] - q_start;
-  int kv_len = lens[b];
+  int parts = (int)gridDim.z;
+  asm volatile("" : "+s"(parts));
+  ask_for_arguments(a);
+  int q_start = cu[b], q_end = cu[b + 1], kv_len = lens[b];
+  asm volatile("" : "+s"(q_start), "+s"(q_end), "+s"(kv_len));  // (asked for together)
+  const int q_len = q_end - q_start;
   const int64_t table_keys = (int64_t)a.max_blocks_per_seq << a.block_shift;
   if (kv_len > table_keys) kv_len = (int)table_keys;
   if (q_len <= 0 || kv_len < q_len || q_len * a.group > kRows) return;
@@ -1492,9 +1497,9 @@ __global__ __launch_bounds__(kCombineThreads<GROUPS>) void attn_paged_combine_ke
   share_plan(n_halves, a.n_splits, a.least_log2, per_share, n_shares);
   if (n_shares == 1) return;  // done by one workgroup, which wrote the output itself
   const float* recs = a.partials + ((int64_t)b * a.n_kv_heads + kv_head) * a.n_splits * kPartialFloats<D>;
-  if (EACH > 2 && n_shares <= 2 * GROUPS) merge_shares<D, GROUPS, 2>(a, recs, n_shares, q_start, kv_head, n_rows);
-  else if (EACH > 4 && n_shares <= 4 * GROUPS) merge_shares<D, GROUPS, 4>(a, recs, n_shares, q_start, kv_head, n_rows);
-  else merge_shares<D, GROUPS, EACH>(a, recs, n_shares, q_start, kv_head, n_rows);
+  if (EACH > 2 && n_shares <= 2 * GROUPS) merge_shares<D, GROUPS, 2>(a, recs, n_shares, q_start, kv_head, n_rows, parts);
+  else if (EACH > 4 && n_shares <= 4 * GROUPS) merge_shares<D, GROUPS, 4>(a, recs, n_shares, q_start, kv_head, n_rows, parts);
+  else merge_shares<D, GROUPS, EACH>(a, recs, n_shares, q_start, kv_head, n_rows, parts);
 #else
   (void)a;
 #endif

@@ -277,7 +277,8 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t total_q, in
       void (*kernel)(hydra::paged::PagedArgs) = attn_decode_kernel<D, false, kFour, kFour>;
       if (ordered) kernel = streams == kFour ? attn_decode_kernel<D, true, kFour, kFour> : waves == kFour ? attn_decode_kernel<D, true, kFour, kEight> : attn_decode_kernel<D, true, kEight, kEight>;
       else if (streams == kEight) kernel = attn_decode_kernel<D, false, kEight, kEight>;
-      err = launch_lds(kernel, dim3(rows_wgs), dim3(64 * waves), streams * hydra::paged::kDecodeLdsPerWave<D>, s, args);
+      const dim3 grid = ordered ? dim3(rows_wgs) : dim3((unsigned)args.n_kv_heads, (unsigned)args.batch, (unsigned)args.n_splits);
+      err = launch_lds(kernel, grid, dim3(64 * waves), streams * hydra::paged::kDecodeLdsPerWave<D>, s, args);
       launched = true;
     }
   }

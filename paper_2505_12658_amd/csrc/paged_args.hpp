@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_tiles.hpp"
+
 namespace hydra {
 namespace paged {
 
@@ -55,8 +57,8 @@ __device__ __forceinline__ void share_plan(int n_halves, int n_splits, int least
   const int most = (n_halves + (1 << least_log2) - 1) >> least_log2;
   const int k = n_splits < most ? n_splits : most;
   if (k < 2) return;
-  per = (n_halves + k - 1) / k;
-  shares = (n_halves + per - 1) / per;
+  per = quotient(n_halves + k - 1, k);
+  shares = quotient(n_halves + per - 1, per);
 }
 // half tiles [begin, end) of share s (empty past the last share)
 __device__ __forceinline__ void split_range(int n_halves, int per, int s, int& begin, int& end) {

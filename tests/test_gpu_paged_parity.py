@@ -614,6 +614,25 @@ def test_number_of_shares(q_lens, kv_lens, hq, hkv, d, most):
     _check(got, want)
 
 
+def test_more_than_a_million_pairs():
+    """20 requests of one key with 60 000 heads: (request, KV head) pairs on both sides of 2^20, where their division takes another way.
+    Each output row is the request's V row."""
+    import paper_2505_12658_amd as hydra
+
+    dev, batch, heads, d = torch.device("cuda:0"), 20, 60000, 64
+    gen = torch.Generator(device=dev).manual_seed(3)
+    table = torch.full((batch, 17), -1, dtype=torch.int32, device=dev)
+    table[:, 0] = torch.randperm(batch, generator=gen, device=dev).to(torch.int32)
+    q = torch.ones((batch, heads, d), dtype=torch.bfloat16, device=dev)
+    kc = torch.ones((batch, 16, heads, d), dtype=torch.bfloat16, device=dev)
+    vc = torch.full_like(kc, float("nan"))
+    rows = torch.randn((batch, heads, d), generator=gen, device=dev).to(torch.bfloat16)
+    vc[table[:, 0].long(), 0] = rows
+    out = hydra.hydra_attn_paged_fwd(q, kc, vc, table, torch.arange(batch + 1, dtype=torch.int32, device=dev),
+                                     torch.ones(batch, dtype=torch.int32, device=dev), 1, 0.125)
+    assert torch.equal(out.view(torch.int16), rows.view(torch.int16))
+
+
 @pytest.mark.parametrize("kv_lens,chunk,split", [
     ([1000, 120, 430], 128, False),     # the chunk's chain of key tiles is what the kernel waits for
     ([2500, 700, 90], 60, True),        # contexts far longer than the chunk
