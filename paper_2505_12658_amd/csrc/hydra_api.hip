@@ -151,16 +151,11 @@ bool loading_waves(bool causal, int32_t batch, int32_t total_tokens, int32_t max
          items_estimate(4, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads) <= (causal && batch == 1 ? 1.5f : 1.0f) * (float)compute_units;
 }
 
-// Grid: as many workgroups as there can be items (a sequence of L tokens has at most (L + 31) / 32 * group wave tiles and pads less than
-// an item), and as take_entry asks for; their order takes care of how the items spread over the dies.
 // listed: the items come from the work list, whose entries, four wave tiles or the rest of a sequence, the workgroups share.
 template <int D, int TEAMS, int LOADERS>
 hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, bool listed, int32_t batch, int32_t total_tokens, int32_t n_kv_heads, bool two_per_unit, hipStream_t stream) {
   using Source = hydra::DirectSource<TEAMS, LOADERS>;
-  constexpr int64_t kLeast = hydra::kXcds * hydra::kDieUnits;
-  const int64_t wave_tiles = ((int64_t)total_tokens + (hydra::kWaveTileRows - 1) * (int64_t)batch) / hydra::kWaveTileRows * args.group;
-  const int64_t per = listed ? hydra::kWavesPerItem : Source::kTiles, most = (wave_tiles + (per - 1) * batch) / per * (per / Source::kTiles) * n_kv_heads;
-  const dim3 grid((unsigned)(most > kLeast || n_kv_heads % hydra::kXcds == 0 ? most : kLeast));
+  const dim3 grid((unsigned)hydra::direct_workgroups(Source::kTiles, listed ? hydra::kWavesPerItem : Source::kTiles, batch, total_tokens, args.group, n_kv_heads));
   // (LDS that is asked for and not used, so that a third workgroup does not fit)
   constexpr size_t kThird = hydra::kLdsPerUnit / 3, kLds = hydra::TileGeom<D, TEAMS, Source::kStageRows>::kLdsBytes;
   const size_t pad = two_per_unit && kLds < kThird ? kThird - kLds : 0;

@@ -371,6 +371,28 @@ def test_a_unit_for_every_item(lengths, hq, hkv, d, causal):
             assert torch.equal(with_others.view(torch.int16), out.view(torch.int16))
 
 
+@pytest.mark.parametrize("batch,hkv", [(2, 1), (4, 1), (2, 2), (1, 2), (1, 4)])
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_few_pairs_of_one_length(batch, hkv, d, causal):
+    """Two or four (sequence, KV head) pairs of one length with more than 32 items each, in halved items, with loading waves and without:
+    the oracle, and the same bits from a work list, over outputs of NaN."""
+    hydra = _hydra()
+    dev = torch.device("cuda:0")
+    group, pairs = 16, batch * hkv
+    for tiles in (5, 40 // pairs, 80 // pairs):  # of 32 tokens: 40 items of two wave tiles per pair; 160 of four together; 320
+        w = si.custom([32 * tiles - 7] * batch, group * hkv, hkv, d, causal, seed=tiles + 10 * pairs + batch)
+        q, k, v = si.make_qkv(w)
+        qd, kd, vd, cu = q.to(dev), k.to(dev), v.to(dev), torch.from_numpy(w.cu_seqlens).to(dev)
+        out, listed = torch.full_like(qd, float("nan")), torch.full_like(qd, float("nan"))
+        hydra.hydra_attn_varlen_fwd(qd, kd, vd, cu, w.max_seqlen, causal, w.softmax_scale, out=out)
+        ws = hydra.hydra_attn_build_worklist(cu, w.total_tokens, w.max_seqlen, w.n_q_heads, hkv, d, causal)
+        hydra.hydra_attn_varlen_fwd_prebuilt(qd, kd, vd, cu, w.max_seqlen, causal, w.softmax_scale, listed, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(listed.view(torch.int16), out.view(torch.int16)), tiles
+        _check(out, c_oracle.attn_varlen(_f64(q), _f64(k), _f64(v), w.cu_seqlens, causal, w.softmax_scale))
+
+
 @pytest.mark.parametrize("lengths,hq,hkv,d", [
     ([1500], 7, 1, 128),             # one pair: seven dies have no queue of their own
     ([900, 40], 14, 2, 64),          # four pairs of two lengths
