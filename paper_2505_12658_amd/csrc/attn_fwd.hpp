@@ -344,7 +344,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   if (threadIdx.x == 0) s_redo[0] = 0;
   if constexpr (G::kSumsFromMatrixUnit) {
     static_assert(kKvTileRows * ROWB - 8 * ROWB + 8 <= G::kOnesBytes, "a V fragment read stays inside the ones");
-    for (int i = threadIdx.x * 16; i < G::kOnesBytes; i += (int)blockDim.x * 16)
+    for (int i = threadIdx.x * 16; i < G::kOnesBytes; i += 64 * TEAMS * (WT + kLoaders) * 16)
       *reinterpret_cast<u32x4_t*>(HYDRA_LDS_BYTE(lds0 + G::kOnesAt + i)) = u32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
   }
 
@@ -490,8 +490,9 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   const bool active = f < n_wave_tiles;
   if (!active) f = n_wave_tiles - 1;
   // (head_dim 64 and a reciprocal: 32 images of 577 tokens with 16 heads 59.4 -> 59.0 us, 9 of them 19.2 -> 19.1; two teams: causal requests of 200 tokens
-  // 6.83 -> 6.68, but one image 6.53 -> 6.59; head_dim 128 with four wave tiles, a request of 1000 tokens 16.0 -> 16.3)
-  constexpr bool kByReciprocal = TEAMS > 1 ? CAUSAL : D == 64;
+  // 6.83 -> 6.68, but one image 6.53 -> 6.59; head_dim 128 with four wave tiles, a request of 1000 tokens 16.0 -> 16.3.  One item per
+  // workgroup only: over many items the causal kernel of head_dim 64 would spill vector registers for it)
+  constexpr bool kByReciprocal = Src::kOneItem && !Src::kPaged && (TEAMS > 1 ? CAUSAL : D == 64);
   auto token_tile = [&](int flat) { return kByReciprocal ? quotient(flat, a.group) : flat / a.group; };
   const int tok_tile = token_tile(f);
   const int head = kv_head * a.group + (f - tok_tile * a.group);
