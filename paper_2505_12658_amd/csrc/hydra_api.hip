@@ -11,9 +11,12 @@
 #include "../../include/hydra_attn.h"
 #include "attn_fwd.hpp"
 #include "attn_paged.hpp"
+#include "batch_rules.hpp"
 #include "kv_write.hpp"
 #include "page_cache.hpp"
 #include "worklist.hpp"
+
+static_assert(hydra::rules::kTileTokens == hydra::kWaveTileRows && hydra::rules::kTileKeys == hydra::kKvTileRows, "the tiles that the kernels have");
 
 namespace {
 
@@ -100,18 +103,6 @@ bool direct_form(int32_t head_dim, size_t capacity, unsigned compute_units) {
 bool list_free(int32_t batch, int32_t head_dim, size_t capacity, unsigned compute_units) {
   return batch <= hydra::kDirectSeqs && within_rounds(kListFreeRounds, head_dim, capacity, compute_units);
 }
-// Items of `tiles` wave tiles in a batch: exact for one sequence and where all have max_seqlen tokens, otherwise an average (half a wave
-// tile and half of an item less half a tile of every sequence are padding; a sequence has a wave tile and an item at least).
-float items_estimate(int tiles, int32_t batch, int32_t total_tokens, int32_t max_seqlen, int32_t n_q_heads, int32_t n_kv_heads) {
-  const float seqs = (float)batch, kv_heads = (float)n_kv_heads, per_item = (float)tiles;
-  const int32_t group = n_q_heads / n_kv_heads;
-  if (batch == 1 || (int64_t)max_seqlen * batch == total_tokens) {
-    const int64_t tok_tiles = ((int64_t)(total_tokens / batch) + hydra::kWaveTileRows - 1) / hydra::kWaveTileRows;
-    return kv_heads * seqs * (float)((tok_tiles * group + tiles - 1) / tiles);
-  }
-  const float tok_tiles = fmaxf((float)total_tokens / hydra::kWaveTileRows + 0.5f * seqs, seqs);
-  return kv_heads * fmaxf((float)group * tok_tiles / per_item + 0.5f * (1.0f - 1.0f / per_item) * seqs, seqs);
-}
 // Whether a batch at head_dim 80 has about four items of short sequences per compute unit: then two of its workgroups share a unit
 // instead of three, which would leave the fourth alone with the unit's SIMDs.  Items are exact where all sequences have max_seqlen
 // tokens, and an average otherwise (half a wave tile and three eighths of an item of every sequence are padding).
@@ -122,35 +113,13 @@ float items_estimate(int tiles, int32_t batch, int32_t total_tokens, int32_t max
 // but of 384 tokens with 28 / 4 heads 924 25.0 and 26.2.
 bool four_short_items(bool causal, int32_t batch, int32_t total_tokens, int32_t max_seqlen, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
   const float most_tokens = causal ? 400.0f : 300.0f, least_items = causal ? 3.15f : 3.3f;
-  const float units = (float)compute_units;
-  if ((float)total_tokens > most_tokens * (float)batch) return false;
-  const float items = items_estimate(hydra::kWavesPerItem, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads);
+  const float seqs = (float)batch, kv_heads = (float)n_kv_heads, units = (float)compute_units;
+  if ((float)total_tokens > most_tokens * seqs) return false;
+  const int32_t group = n_q_heads / n_kv_heads;
+  float items = kv_heads * ((float)group * ((float)total_tokens / hydra::kWaveTileRows + 0.5f * seqs) / hydra::kWavesPerItem + 0.375f * seqs);
+  if ((int64_t)max_seqlen * batch == total_tokens) items = kv_heads * seqs * (float)hydra::items_of_sequence(max_seqlen, group);
   return items > least_items * units && items <= 4.0f * units;
 }
-// How a batch is taken whose items have a compute unit each, or nearly: then the length of an item's chain of key tiles is all that
-// counts (attn_fwd_direct_kernel).
-// Whether its items are two wave tiles, whose keys two teams of waves divide.  This is part of the result (each team's P is
-// rounded relative to a reference of its own), so it follows from the sizes that every call on the batch has in common, and calls that
-// share the chip take it as well.
-// us with items of four wave tiles, with loading waves as well (below), and so: one image of 577 tokens with 16 heads of 64 (160 items of
-// two wave tiles) 9.45, 8.58 and 6.58; one of 1000 with 16 heads of 80 (256) 16.8, 15.4 and 12.9; requests with 28 / 4 heads of 128, of
-// 558 tokens (252) 12.4, 11.3 and 8.9, of 200 (100) 7.84, 7.38 and 6.88; with 32 / 32 heads, 500 tokens (256) 11.7, 11.0 and 8.6, 544
-// (288) 12.1, 11.3 and 12.3, 700 (352) 14.5, 13.2 and 16.1.  Neither pays for sequences of one key tile: 12 requests of 20 tokens with
-// 28 / 4 heads 5.4 and 5.9, 16 of 64 6.7 and (loading waves) 6.9.
-bool more_than_a_key_tile(int32_t batch, int32_t total_tokens) { return total_tokens > (int64_t)hydra::kKvTileRows * batch; }
-bool halved_items(int32_t batch, int32_t total_tokens, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
-  return more_than_a_key_tile(batch, total_tokens) && items_estimate(2, batch, total_tokens, 0, n_q_heads, n_kv_heads) <= (float)compute_units;
-}
-// Whether workgroups of four wave tiles get four waves more that load their tiles, so that a compute unit holds one: two images of 577
-// tokens with 16 heads of 64 (160 items) 9.67 -> 8.85 us, a request of 1000 with 28 / 4 heads (224) 18.4 -> 16.2, with 32 / 32 heads
-// (256) 20.0 -> 18.4; but four images (320) 13.8 -> 17.6, three requests of 500 with 28 / 4 heads (336) 14.0 -> 16.1.  One causal sequence
-// has few long items and many short ones, which find a unit when the first are through: 28 / 4 heads, 1500 tokens (332) 28.3 -> 23.9;
-// 32 / 32 heads, 1100 (288) 22.8 -> 19.3, 1300 (352) 31.0 -> 27.8, 1600 (416) 33.5 -> 35.7.
-bool loading_waves(bool causal, int32_t batch, int32_t total_tokens, int32_t max_seqlen, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
-  return more_than_a_key_tile(batch, total_tokens) &&
-         items_estimate(4, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads) <= (causal && batch == 1 ? 1.5f : 1.0f) * (float)compute_units;
-}
-
 // listed: the items come from the work list, whose entries, four wave tiles or the rest of a sequence, the workgroups share.
 template <int D, int TEAMS, int LOADERS>
 hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, bool listed, int32_t batch, int32_t total_tokens, int32_t n_kv_heads, bool two_per_unit, hipStream_t stream) {
@@ -455,12 +424,12 @@ int launch_packed(const void* q, const void* k, const void* v, void* out, int64_
   auto launch_for = [&](auto d) {
     constexpr int D = decltype(d)::value;
     const bool is_causal = causal != 0;
-    if (halved_items(batch, total_tokens, n_q_heads, n_kv_heads, cus)) {
+    if (hydra::rules::halved_items(batch, total_tokens, n_q_heads, n_kv_heads, cus)) {
       return workgroups_per_cu == 0 ? launch_direct<D, 2, 2>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, false, s)
                                     : launch_direct<D, 2, 0>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, false, s);
     }
     if (workgroups_per_cu != 0 || (with_list && !direct_form(head_dim, lay.capacity, cus))) return launch_attn<D>(is_causal, args, cus, workgroups_per_cu, s);
-    if (loading_waves(is_causal, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads, cus))
+    if (hydra::rules::loading_waves(is_causal, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads, cus))
       return launch_direct<D, 1, 4>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, false, s);
     const bool two = D == 80 && four_short_items(is_causal, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads, cus);
     return launch_direct<D, 1, 0>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, two, s);
