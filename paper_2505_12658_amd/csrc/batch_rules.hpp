@@ -31,10 +31,15 @@ inline int64_t items_most(int tiles, int32_t batch, int32_t total_tokens, int32_
 // 558 tokens (252) 12.4, 11.3 and 8.9, of 200 (100) 7.84, 7.38 and 6.88; with 32 / 32 heads, 500 tokens (256) 11.7, 11.0 and 8.6, 544
 // (288) 12.1, 11.3 and 12.3, 700 (352) 14.5, 13.2 and 16.1; several sequences, 16 heads of 64, 4 of 65 .. 300 (208) 6.90, 6.56 and 5.96,
 // 10 of 65 (320) 5.2, 5.2 and 8.6, 2 of 200 .. 600 (272) 10.1, 9.3 and 11.6.  Neither pays for sequences of one key tile: 12 requests of 20
-// tokens with 28 / 4 heads 5.4 and 5.9, 16 of 64 6.7 and (loading waves) 6.9.
+// tokens with 28 / 4 heads 5.4 and 5.9, 16 of 64 6.7 and (loading waves) 6.9.  With two key tiles a team has one, and what halving saves is
+// little; at head_dim 128 the workgroups' loads of Q and their merge take it back where they fill the chip: four wave tiles and halves,
+// 8 / 1 heads, of 66 tokens 96 items 6.15 and 5.93, 168 6.70 and 6.55, 204 6.99 and 7.37, 252 7.08 and 8.38, of 128 192 7.27 and 6.90, 256 7.27 and 8.14;
+// 28 / 4 heads, 5 of 66 (220) 6.77 and 7.04; 64 / 8 heads, 2 of 128 (256) 6.84 and 7.01; of 192, 240 8.23 and 8.01.
 inline bool more_than_a_key_tile(int32_t batch, int32_t total_tokens) { return total_tokens > (int64_t)kTileKeys * batch; }
-inline bool halved_items(int32_t batch, int32_t total_tokens, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
-  return more_than_a_key_tile(batch, total_tokens) && items_most(2, batch, total_tokens, 0, n_q_heads / n_kv_heads, n_kv_heads) <= (int64_t)compute_units;
+inline bool halved_items(int32_t head_dim, int32_t batch, int32_t total_tokens, int32_t n_q_heads, int32_t n_kv_heads, unsigned compute_units) {
+  const bool two_key_tiles = total_tokens <= 2 * kTileKeys * (int64_t)batch;
+  return more_than_a_key_tile(batch, total_tokens) &&
+         items_most(2, batch, total_tokens, 0, n_q_heads / n_kv_heads, n_kv_heads) * 4 <= (head_dim == 128 && two_key_tiles ? 3 : 4) * (int64_t)compute_units;
 }
 // Whether workgroups of four wave tiles get four waves more that load their tiles, so that a compute unit holds one: two images of 577
 // tokens with 16 heads of 64 (160 items) 9.67 -> 8.85 us, a request of 1000 with 28 / 4 heads (224) 18.4 -> 16.2, with 32 / 32 heads

@@ -424,7 +424,7 @@ int launch_packed(const void* q, const void* k, const void* v, void* out, int64_
   auto launch_for = [&](auto d) {
     constexpr int D = decltype(d)::value;
     const bool is_causal = causal != 0;
-    if (hydra::rules::halved_items(batch, total_tokens, n_q_heads, n_kv_heads, cus)) {
+    if (hydra::rules::halved_items(D, batch, total_tokens, n_q_heads, n_kv_heads, cus)) {
       return workgroups_per_cu == 0 ? launch_direct<D, 2, 2>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, false, s)
                                     : launch_direct<D, 2, 0>(is_causal, args, with_list, batch, total_tokens, n_kv_heads, false, s);
     }

@@ -2,8 +2,8 @@
 #include "../paper_2505_12658_amd/csrc/batch_rules.hpp"
 
 extern "C" {
-int halved_items(int batch, int total_tokens, int n_q_heads, int n_kv_heads, int compute_units) {
-  return hydra::rules::halved_items(batch, total_tokens, n_q_heads, n_kv_heads, (unsigned)compute_units);
+int halved_items(int head_dim, int batch, int total_tokens, int n_q_heads, int n_kv_heads, int compute_units) {
+  return hydra::rules::halved_items(head_dim, batch, total_tokens, n_q_heads, n_kv_heads, (unsigned)compute_units);
 }
 int loading_waves(int causal, int batch, int total_tokens, int max_seqlen, int n_q_heads, int n_kv_heads, int compute_units) {
   return hydra::rules::loading_waves(causal != 0, batch, total_tokens, max_seqlen, n_q_heads, n_kv_heads, (unsigned)compute_units);

@@ -22,7 +22,8 @@ def test_small_packed_batches_have_a_unit_for_every_item(batch_rules):
         if rng.random() < 0.3:
             lengths = [longest] * n
         total, causal = sum(lengths), rng.random() < 0.5
-        if batch_rules.halved_items(n, total, hq, hkv, UNITS):
+        d = rng.choice([64, 80, 128])
+        if batch_rules.halved_items(d, n, total, hq, hkv, UNITS):
             taken[0] += 1
             assert _items(lengths, hq, hkv, 2) <= UNITS, (lengths, hq, hkv)
         for bound in (max(lengths), 2 * longest):
@@ -31,5 +32,8 @@ def test_small_packed_batches_have_a_unit_for_every_item(batch_rules):
                 assert _items(lengths, hq, hkv, 4) <= (UNITS * 3 // 2 if causal and n == 1 else UNITS), (lengths, hq, hkv, causal)
     assert min(taken) > 500, taken
     # one image of 577 tokens, a request of 558; ten sequences of 65 tokens do not fit
-    assert batch_rules.halved_items(1, 577, 16, 16, UNITS) and batch_rules.halved_items(1, 558, 28, 4, UNITS)
-    assert not batch_rules.halved_items(10, 651, 16, 16, UNITS)
+    assert batch_rules.halved_items(64, 1, 577, 16, 16, UNITS) and batch_rules.halved_items(128, 1, 558, 28, 4, UNITS)
+    assert not batch_rules.halved_items(64, 10, 651, 16, 16, UNITS)
+    # sequences of two key tiles that would fill the chip with halves: not at head_dim 128
+    assert not batch_rules.halved_items(128, 5, 5 * 66 - 1, 28, 4, UNITS) and batch_rules.halved_items(128, 3, 3 * 66 - 1, 28, 4, UNITS)
+    assert batch_rules.halved_items(80, 7, 7 * 66 - 1, 16, 16, UNITS)
