@@ -26,6 +26,8 @@
  *   - The calls are re-entrant; there is no global mutable state.  Results are bit-identical
  *     from run to run (no floating-point atomics; the order of the work list never affects the
  *     value of any output element).
+ *     Which of its forms a call takes follows from the batch's sizes and the GPU's number of compute units, and is part of
+ *     the result: the same sequence may differ in the last places of its bf16 output from one batch to another.
  *   - Contents of device-side index arrays (cu_seqlens, slot_mapping) cannot be checked without
  *     a device synchronisation; violating their documented preconditions is undefined behaviour.
  */
@@ -125,9 +127,12 @@ int hydra_attn_varlen_fwd_prebuilt(const void* q, const void* k, const void* v, 
  *   workgroups_per_cu  >= 1 (otherwise HYDRA_ERR_INVALID_ARG); values above the kernel's own number
  *        (3 at head_dim 64, else 2) mean that number.  With 1, half (two thirds at head_dim 64) of every
  *        compute unit's registers and most of its LDS stay free for the other stream's kernels.
- *        Batches of so few tokens that there is a compute unit for every 64 rows of a KV head's queries
- *        run with one workgroup per compute unit at most whatever the value; it holds no more of
- *        the registers than above, and 68, 93 or 132 KB of LDS at head_dim 64, 80 and 128.
+ *        Batches of so few tokens that there are compute units for every 64 rows of a KV head's queries (however the tokens
+ *        are divided among the sequences) start one workgroup for every 64 such rows, whatever the value: no
+ *        more workgroups than compute units; only at head_dim 64 do two fit one unit.  A workgroup has no more of the
+ *        registers than above, but 67, 92 and 131 KB of the 160 KB of LDS at head_dim 64, 80 and 128.  Beside one of
+ *        head_dim 128 workgroups of up to 29 KB find room: the paged call's decode kernel at head_dim 64 (18 KB), not at
+ *        head_dim 128 (34 KB), which runs on the units without such a workgroup and on the others when theirs is through.
  *
  * Results are bit-identical to hydra_attn_varlen_fwd_prebuilt for every value (work items are
  * independent; only their placement changes).  Everything else as for hydra_attn_varlen_fwd_prebuilt.

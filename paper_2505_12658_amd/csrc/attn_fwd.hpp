@@ -61,7 +61,8 @@ struct TileGeom : RowGeom<D> {
   static constexpr int kTeamBytes = 2 * kRing * kTileBytes;         // K ring, V ring
   static constexpr int kOnesAt = TEAMS * kTeamBytes + 64;           // (+ slack behind the last V tile)
   static constexpr int kSumsAt = kOnesAt + kOnesBytes;              // the teams' references and sums, 512 bytes per wave tile
-  static constexpr int kSumsBytes = TEAMS > 1 ? TEAMS * kWavesPerItem * 512 : 0;
+  static constexpr int kTeamSums = kWavesPerItem / TEAMS * 512;
+  static constexpr int kSumsBytes = TEAMS > 1 ? TEAMS * kTeamSums : 0;
   static constexpr int kQueriesAt = (kSumsAt + kSumsBytes + 1023) / 1024 * 1024;  // STAGE_ROWS rows of Q
   static constexpr int kLdsBytes = STAGE_ROWS > 0 ? kQueriesAt + STAGE_ROWS * RowGeom<D>::kRowBytes : kSumsAt + kSumsBytes;
 };
@@ -1067,9 +1068,9 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
       }
       *reinterpret_cast<f32x4_t*>(HYDRA_LDS_BYTE(k_ring + slot + i * 1024)) = theirs;
     }
-    *reinterpret_cast<f32x2_t*>(HYDRA_LDS_BYTE(sums + team * (kWavesPerItem * 512))) = f32x2_t{-nref[0], row_sum[0]};
+    *reinterpret_cast<f32x2_t*>(HYDRA_LDS_BYTE(sums + team * G::kTeamSums)) = f32x2_t{-nref[0], row_sum[0]};
     __syncthreads();
-    const f32x2_t rs = *reinterpret_cast<const f32x2_t*>(HYDRA_LDS_BYTE(sums + (1 - team) * (kWavesPerItem * 512)));
+    const f32x2_t rs = *reinterpret_cast<const f32x2_t*>(HYDRA_LDS_BYTE(sums + (1 - team) * G::kTeamSums));
     const float both = fmaxf(-nref[0], rs[0]), w_mine = fast_exp2(-nref[0] - both), w_theirs = fast_exp2(rs[0] - both);
     total = row_sum[0] * w_mine + rs[1] * w_theirs;
 #pragma unroll
@@ -1163,7 +1164,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PackedSourc
 // wave tiles instead of four, and each of two teams of two waves half of the key tiles, in rings of its own; the teams share the
 // loads of Q and merge their results through LDS, half of the columns by each (all by one: 0.3 to 0.6 us longer).  us with 4, 8 and 8
 // waves so: one image of 577 tokens with 16 heads of 64 9.45, 8.58, 6.58; a request of 558 tokens with 28 / 4 heads of 128 12.4, 11.3,
-// 8.9.  TEAMS = 2, LOADERS = 0 is the same split for calls that leave registers to others (10.5 us).
+// 8.9.  TEAMS = 2, LOADERS = 0 is the same split for calls that leave registers to others (10.5 us).  It leaves
+// less of the LDS, at head_dim 128 too little for a decode workgroup of the same head_dim.  us per call alone, and of it and of a stream
+// of decode steps beside it, as persistent workgroups and so: 200 tokens with 28 / 4 heads of 128 beside 64 of 128 .. 1800 tokens 8.4,
+// 15.6 + 26.2 and 6.6, 9.0 + 29.5; 558 tokens beside 32 of 400 .. 1200 13.1, 15.5 + 18.6 and 10.1, 13.3 + 17.0; 577 with 16 heads of 64 beside
+// 33 of 600 .. 1100 with 32 / 32 heads of 128 10.7, 37.3 + 79.8 and 7.4, 42.5 + 78.2.  Both streams together are done earlier, or 1 % later,
+// in eleven of twelve such pairs, in the last one named 4 % later.
 // LOADERS change no bit of the result; two teams' P is rounded relative to a reference of each team (the relative error against 64 bits
 // goes down by 0.3 to 3 %).
 // Not kept: one copy of the iteration's code instead of two plus the last one's, 0.1 to 0.5 us longer; two teams of four waves without

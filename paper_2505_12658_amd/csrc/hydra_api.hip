@@ -120,6 +120,10 @@ bool four_short_items(bool causal, int32_t batch, int32_t total_tokens, int32_t 
   if ((int64_t)max_seqlen * batch == total_tokens) items = kv_heads * seqs * (float)hydra::items_of_sequence(max_seqlen, group);
   return items > least_items * units && items <= 4.0f * units;
 }
+// (what the header tells callers of hydra_attn_varlen_fwd_shared about these workgroups' LDS, with 128 bytes for the kernel's own words)
+template <int D>
+constexpr bool shared_lds_within(int kilobytes) { return hydra::TileGeom<D, 2, hydra::DirectSource<2, 0>::kStageRows>::kLdsBytes + 128 <= kilobytes * 1024; }
+static_assert(shared_lds_within<64>(67) && shared_lds_within<80>(92) && shared_lds_within<128>(131), "as the header says");
 // listed: the items come from the work list, whose entries, four wave tiles or the rest of a sequence, the workgroups share.
 template <int D, int TEAMS, int LOADERS>
 hipError_t launch_direct(bool causal, const hydra::AttnArgs& args, bool listed, int32_t batch, int32_t total_tokens, int32_t n_kv_heads, bool two_per_unit, hipStream_t stream) {
