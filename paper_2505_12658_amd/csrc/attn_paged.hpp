@@ -679,13 +679,13 @@ __device__ __forceinline__ bool run_packed_rows(const PagedArgs& a, unsigned cha
 // there is enough to fill the chip.  A wide workgroup has one decode step (share, packed-rows request) as long as the chip has units for
 // all places, else the shortest are second ones: the halves of its waves take one each.  us, four waves and eight, 28 / 4 heads of 128: a
 // chunk of 512 tokens alone 13.8 and 11.4, behind 1536 keys 41.2 and 30.3; 4 chunks of 128 14.1 and 11.6; 24 decode steps of 91 .. 916 and
-// 4 chunks of 158 17.1 and 14.4, 53 of 50 .. 508 and 4 of 286 28.4 and 22.7, 76 of 44 .. 441 and 4 of 72 14.7 and 12.1; the same bits.
+// 4 chunks of 158 17.1 and 14.4, 53 of 50 .. 508 and 4 of 286 28.4 and 22.7, 76 of 44 .. 441 and 4 of 72 14.7 and 12.1; the same bits
+// (but for places that the grid does not have, see run_place).
 constexpr int kFirstLayer = kUnits;  // workgroups i and i + 256 of a grid share a compute unit
 constexpr int kLongChain = 8;        // key tiles from which on a chunk's workgroups are kept apart from the decode steps'
 constexpr int kStepUnits = 128;      // compute units that the chains leave to the decode steps
 constexpr int kFewChunks = 4;        // as many are ranked one by one
 constexpr int kTrailing = 32;        // places at the end of a wide grid that are chains at least, if not all places fit the grid
-constexpr int kWideMost = 128;       // requests of a batch that wide workgroups take
 constexpr float kChainKeysPerStep = 2 * 32 * 0.9f;  // keys of a chain that take as long as a step of both of a wide workgroup's decode steps
 
 // Context up to which a hybrid batch keeps the order of its requests.  To order it costs every workgroup up to 2 us where the
@@ -897,15 +897,15 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, int id, Work& w) {
       } else if (far_chunk != 0 || (any_chunk != 0 && id >= kFirstLayer)) {
         int longest = 0;
         uint64_t longer = 0, far_longer = 0;
-  #pragma unroll
+#pragma unroll
         for (int r = 0; r < REGS; ++r) longest = groups[r] > 0 && kv_len[r] > longest ? kv_len[r] : longest;
         longest = wave_max(longest);
-  #pragma unroll
+#pragma unroll
         for (int r = 0; r < REGS; ++r) longer |= __builtin_amdgcn_ballot_w64(steps[r] > 0 && kv_len[r] > longest);
         beside_steps = rows_wgs <= kFirstLayer && longer == 0;
         if (far_chunk != 0 && !beside_steps) {
           int far = 0;  // groups whose chains are longer than half of the longest
-  #pragma unroll
+#pragma unroll
           for (int r = 0; r < REGS; ++r) {
             int tokens = kv_len[r] - longest / 2;
             tokens = tokens < 0 ? 0 : tokens < q_len[r] ? tokens : q_len[r];
@@ -920,7 +920,7 @@ __device__ __forceinline__ bool find_work(const PagedArgs& a, int id, Work& w) {
       }
       if (any_chunk != 0 && units > rows_wgs) units = (rows_wgs + 7) & ~7;
       const int chain_units = kFirstLayer - units;
-  
+
       if (id < units) {
         step = id;
       } else if (id < kFirstLayer || beside_steps) {
@@ -1210,7 +1210,7 @@ __device__ __forceinline__ void run_place(const PagedArgs& a, unsigned char* sme
       }
       const int lane_ = threadIdx.x & 63, wave_ = threadIdx.x >> 6;
       int incl = mine, incl_reqs = mine_reqs;
-  #pragma unroll
+#pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
         const int up = __shfl_up(incl, d), up_reqs = __shfl_up(incl_reqs, d);
         if (lane_ >= d) {
@@ -1348,9 +1348,9 @@ __device__ __forceinline__ void run_place(const PagedArgs& a, unsigned char* sme
   }
   if (redo) run_plain<D>(a, smem, b, kv_head, q_start, q_len, kv_len, f0);
   if constexpr (WIDE) {
-    // The host sizes a wide grid for the chunks that it expects from their number of tokens (one for all that there can be would
-    // be mostly empty workgroups, 1.3 us of a compute unit each).  Places past its end are for the last workgroups, all of
-    // them chains, through the plain loop, whose code is here anyway.
+    // The host sizes a wide grid for the places that it takes the batch to have (wide_grid).  One that has more, because its chunks are
+    // not the whole ones that their tokens look like or because some requests have no new token, leaves the places past the grid's
+    // end to the last workgroups, all of them chains, through the plain loop, whose code is here anyway (and which gives other last bits).
     const int last = (int)gridDim.x - 1 - (int)blockIdx.x, workers = (int)gridDim.x - tail;
     for (int id = (int)gridDim.x + last; last < workers && id < places; id += workers) {
       Work w;

@@ -16,7 +16,9 @@
 #include "page_cache.hpp"
 #include "worklist.hpp"
 
-static_assert(hydra::rules::kTileTokens == hydra::kWaveTileRows && hydra::rules::kTileKeys == hydra::kKvTileRows, "the tiles that the kernels have");
+static_assert(hydra::rules::kTileTokens == hydra::kWaveTileRows && hydra::rules::kTileKeys == hydra::kKvTileRows && hydra::rules::kTileTokens == hydra::paged::kRows &&
+                  hydra::rules::kChainTiles == hydra::paged::kWavesPerGroup && hydra::rules::kUnits == hydra::paged::kUnits && hydra::rules::kTrailing == hydra::paged::kTrailing,
+              "what the kernels have");
 
 namespace {
 
@@ -196,39 +198,6 @@ int choose_splits(PagedSplits s, int64_t pairs, int64_t keys, int64_t tile_wgs, 
   return (int)n;
 }
 
-// Hybrid batches in workgroups of eight waves (attn_paged_kernel<D, true>): whether, and in how many.
-// They pay where the batch waits for its chains.  us, workgroups of four waves and of eight, 28 / 4 heads of 128 if not said:
-//   more places than two rounds of the chip keep its units full either way, and two chains share a unit better than one has it: 96
-//   decode steps of 128 .. 1800 tokens and 4 chunks of 512 (648 places) 55.7 and 58.4, 16 chunks of 512 (1792) 55.4 and 68.2, 16 steps and
-//   2 chunks of 300 with 32 / 32 heads (480) 28.5 and 30.3; but 4 chunks of 512 alone (456) 48.5 and 40.0, 23 of 61 .. 619 and 3 of 428
-//   (352) 34.1 and 27.6, 55 of 171 .. 1712 and 4 of 308 (406) 32.8 and 32.2;
-//   where contexts are far longer than the chunks, decode steps are what it waits for: 36 of 246 .. 2466 and 3 of 352 34.6 and
-//   36.7, 59 of 51 .. 512 and one of 104 9.4 and 10.1, 63 of 42 .. 423 and 3 of 62 11.2 and 11.6, 30 of 113 .. 1138 and 3 of 168 16.4 and 16.9;
-//   with a unit for every place from longer ones on: 25 of 114 .. 1142 and 4 of 102 13.3 and 12.0, 6 of 49 .. 492 and 2 of 97 9.5 and 8.4,
-//   42 of 72 .. 723 and 4 of 64 11.9 and 12.2; whatever they are where chains are most of the places: a chunk of 512 behind 1536
-//   keys 41.6 and 30.3;
-//   shares of split contexts are not ranked, and two to a workgroup can be two long ones: 20 of 240 .. 2408 and 4 of 68 17.0 and 20.7.
-struct WideGrid {
-  bool use;
-  unsigned workgroups;
-};
-WideGrid wide_grid(const hydra::paged::PagedArgs& args, int32_t total_q, int32_t max_q_len, unsigned rows_wgs, int head_dim) {
-  using hydra::paged::kRows, hydra::paged::kWavesPerGroup, hydra::paged::kUnits;
-  // The lengths are on the device: the chunks that are expected have max_q_len tokens each, and are as many as there are tokens for.
-  const int64_t groups = (((int64_t)max_q_len + kRows - 1) / kRows * args.group + kWavesPerGroup - 1) / kWavesPerGroup;
-  const int64_t chunks = max_q_len > 1 && total_q > args.batch ? ((int64_t)total_q - args.batch + max_q_len - 2) / (max_q_len - 1) : 1;
-  const int64_t chains = groups * chunks * args.n_kv_heads, pairs_of_rows = ((int64_t)rows_wgs + 1) / 2, chunk_tokens = (int64_t)total_q - args.batch;
-  const int64_t table_keys = (int64_t)args.max_blocks_per_seq << args.block_shift;
-  const bool all_at_once = (int64_t)rows_wgs + chains <= kUnits;
-  bool use = args.batch <= hydra::paged::kWideMost && (1 << args.block_shift) >= 1024 / (2 * head_dim) && args.num_blocks <= (0x7fffffff >> args.block_shift);
-  use = use && (all_at_once || args.n_splits == 1 || rows_wgs <= chains) && pairs_of_rows + chains <= 470;
-  use = use && ((int64_t)rows_wgs * 2 <= chains || table_keys * 10 <= chunk_tokens * (all_at_once ? 28 : 20));
-  // (find_work rounds two numbers of places up to multiples of 8)
-  int64_t wgs = pairs_of_rows + chains + chains / 4 + 16 + hydra::paged::kTrailing;
-  if (wgs < kUnits + 16) wgs = kUnits + 16;
-  return {use, (unsigned)(wgs < 0x7fffff00 ? wgs : 0x7fffff00)};
-}
-
 // Launches of attn_paged_fwd for one head dimension: the decode kernel when no request of the batch has more rows than
 // its form takes, otherwise the kernel that holds all forms; then the merge of split contexts.
 template <int D>
@@ -253,11 +222,13 @@ hipError_t launch_paged(const hydra::paged::PagedArgs& args, int32_t total_q, in
   if (!launched) {
     unsigned grid = rows_wgs + tile_wgs;
     if constexpr (D != 80) {
-      const WideGrid g = wide_grid(args, total_q, max_q_len, rows_wgs, D);
-      bool wide = tile_wgs > 0 && g.use;
-      if (wide) {
-        const unsigned wgs = g.workgroups < grid + 16 ? g.workgroups : grid + 16;
-        err = launch(hydra::paged::attn_paged_kernel<D, true>, dim3(wgs), dim3(512), s, args);
+      // (the pipeline asks for rows of a cache block that are whole load instructions, and for row numbers of 32 bits)
+      const bool pipeline = (1 << args.block_shift) >= 1024 / (2 * D) && args.num_blocks <= (0x7fffffff >> args.block_shift);
+      const hydra::rules::Hybrid batch{args.batch, total_q, max_q_len, args.group, args.n_kv_heads, args.n_splits, (int64_t)args.max_blocks_per_seq << args.block_shift};
+      if (const hydra::rules::WideGrid g = hydra::rules::wide_grid(batch); tile_wgs > 0 && pipeline && g.use) {
+        hydra::paged::PagedArgs wide_args = args;
+        if (g.by_context) wide_args.order_keys = 0;
+        err = launch(hydra::paged::attn_paged_kernel<D, true>, dim3((unsigned)(g.workgroups < grid + 16 ? g.workgroups : grid + 16)), dim3(512), s, wide_args);
         launched = true;
       }
     }

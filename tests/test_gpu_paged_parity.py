@@ -1,6 +1,8 @@
 """GPU parity of attention over the paged KV cache: the HIP kernel, called through the C ABI, against
 the fp64 oracle on the same seeded bf16 inputs.  Same tolerance as the packed attention: max |diff| <=
 2e-2 and mean |diff| <= 2e-3 over all output elements."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -683,24 +685,28 @@ WIDE_CASES = [
     # q_lens, kv_lens, Hq, Hkv, d, block_size
     ([130], [130], 28, 4, 128, 16),                                              # chains alone
     ([1, 130, 1, 200, 1], [60, 130, 1, 500, 33], 28, 4, 128, 16),                # a unit for everything
+    ([200, 100, 50, 25, 12, 6], [200, 300, 50, 225, 12, 6], 28, 4, 128, 16),     # chunks of unequal lengths
     ([1] * 70 + [150, 150], [8 * i + 1 for i in range(70)] + [150, 300], 28, 4, 128, 16),     # two decode steps to a workgroup, not for all
-    ([1] * 101 + [250], [6 * i + 3 for i in range(101)] + [700], 5, 5, 64, 16),               # ... for all but one, an odd number
-    ([64] + [33] * 20, [64] + [33 + 20 * i for i in range(20)], 64, 4, 64, 16),               # more chains than the grid expects
-    ([64] + [33] * 30, [64] + [33] * 30, 28, 4, 128, 16),
+    ([1] * 101 + [250], [4 * i + 3 for i in range(101)] + [300], 5, 5, 64, 16),               # ... for all but one, an odd number
+    ([1] * 90 + [300, 101], [3 * i + 1 for i in range(90)] + [300, 301], 14, 2, 128, 16),     # ... in a grid for all that there can be
     ([3, 1, 90, 4, 2], [100, 40, 190, 4, 77], 8, 1, 128, 16),                    # 24 and 32 rows beside 8
     ([1, 2, 100, 1], [50, 200, 100, 9], 8, 2, 64, 8),                            # blocks that the decode form does not take
-    ([1, 70, 1], [30, 140, 200], 4, 2, 128, 4),
-    ([0, 1, 100, 5, 0, 1], [4, 20, 140, 5, 0, 90], 7, 1, 128, 16),               # requests without new tokens
+    ([1, 70, 1], [30, 140, 190], 4, 2, 128, 4),
+    ([0, 1, 100, 35, 0, 1, 40], [4, 220, 140, 35, 0, 90, 300], 7, 1, 128, 16),   # requests without new tokens
     ([1] * 127 + [300], [64] * 127 + [300], 4, 2, 64, 16),                       # two registers of lengths
+    # chunks that are not the whole ones that their tokens look like: more chains than the grid has places
+    ([101] + [5] * 50, [101] + [5 + 3 * i for i in range(50)], 28, 4, 128, 16),
+    ([1] * 20 + [101] + [5] * 50, [60] * 20 + [101] + [5 + 3 * i for i in range(50)], 28, 4, 128, 16),
+    ([1, 101, 1] + [5] * 50, [200, 101, 60] + [5 + 3 * i for i in range(50)], 28, 4, 64, 16),
 ]
 
 
 @pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: f"n{len(c[0])}-q{sum(c[0])}-kv{max(c[1])}-h{c[2]}k{c[3]}-d{c[4]}-b{c[5]}")
 @pytest.mark.parametrize("planted", [False, True])
-def test_hybrid_batches_in_wide_workgroups(case, planted):
-    """Hybrid batches whose chunks are long against the contexts run in workgroups of eight waves, under a block table that allows
-    far longer contexts in workgroups of four: the oracle, and the same bits (without splits, which follow the table) unless
-    keys far out of the fast path's range or chains past the end of the grid take the plain form."""
+def test_hybrid_batches_in_wide_workgroups(case, planted, batch_rules):
+    """Hybrid batches that run in workgroups of eight waves, which batches of more than 128 requests do not: the same requests with others
+    that have no new token.  The oracle, and the same bits (without splits, which follow the number of requests) unless
+    chains past the end of the grid take the plain form."""
     q_lens, kv_lens, hq, hkv, d, bs = case
     h = si.HybridBatch("wide", q_lens, kv_lens, hq, hkv, d, block_size=bs, seed=sum(q_lens))
     q, kc, vc, tables = si.make_paged_inputs(h)
@@ -709,13 +715,27 @@ def test_hybrid_batches_in_wide_workgroups(case, planted):
         for b, L in enumerate(kv_lens):
             if L > 50:
                 kc[tables[b, 45 // bs], 45 % bs] = 64.0
-    far = np.full((h.batch, 32768 // bs), -1, dtype=np.int32)
-    far[:, : tables.shape[1]] = tables
+    others = 129 - h.batch
+    padded = si.HybridBatch("narrow", q_lens + [0] * others, kv_lens + [0] * others, hq, hkv, d, block_size=bs)
+    padded_tables = np.full((padded.batch, tables.shape[1]), -1, dtype=np.int32)
+    padded_tables[: h.batch] = tables
+
+    rule = batch_rules.wide_workgroups
+    rule.restype, rule.argtypes = ctypes.c_int64, [ctypes.c_int] * 6 + [ctypes.c_int64]
+    group, keys = hq // hkv, tables.shape[1] * bs
+    workgroups = rule(h.batch, h.total_q, h.max_q_len, group, hkv, 1, keys)
+    assert workgroups > 0 and rule(padded.batch, h.total_q, h.max_q_len, group, hkv, 1, keys) == 0
+    chains = hkv * sum(-(-(-(-n // 32) * group) // 4) for n in q_lens if n * group > 32)
+    steps = hkv * sum(0 < n * group <= 32 for n in q_lens)
+    past_the_grid = chains > workgroups
+    assert past_the_grid or chains + max((steps + 1) // 2, min(steps, 256 - chains)) + 15 <= workgroups
+    assert past_the_grid == (case in WIDE_CASES[-3:])
+
     want = _want(h, q, kc, vc, tables)
-    wide, narrow = _run_gpu(h, q, kc, vc, tables, use_workspace=False), _run_gpu(h, q, kc, vc, far, use_workspace=False)
+    wide, narrow = _run_gpu(h, q, kc, vc, tables, use_workspace=False), _run_gpu(padded, q, kc, vc, padded_tables, use_workspace=False)
     _check(wide, want)
     _check(narrow, want)
-    if len(q_lens) < 20 or q_lens[1] != 33:
+    if not past_the_grid:
         assert torch.equal(wide.view(torch.int16), narrow.view(torch.int16))
 
 
