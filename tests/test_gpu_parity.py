@@ -311,6 +311,11 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
         assert torch.equal(listed.view(torch.int16), out.view(torch.int16)) and torch.equal(shared.view(torch.int16), out.view(torch.int16))
 
 
+UNITS = 256  # compute units
+HALVED = {((65,), 1, 1, 64), ((65,), 3, 1, 128), ((129, 70, 65), 2, 2, 80), ((191, 64, 130, 66), 7, 1, 128), ((1000,), 4, 4, 128), ((2049,), 3, 1, 64),
+          ((577,), 16, 16, 64), ((96, 160), 16, 8, 80)}
+
+
 @pytest.mark.parametrize("lengths,hq,hkv,d,causal", [
     # two teams: every item of two wave tiles has a compute unit
     ([65], 1, 1, 64, False),               # a key tile and one key more: the second team has one key
@@ -327,12 +332,20 @@ def test_one_workgroup_per_item(lengths, hq, hkv, d, causal):
     ([700], 28, 4, 128, True),             # a single request: pairs in turn
     ([1100], 16, 16, 80, False),
     ([1400], 28, 4, 128, True),            # ... of more items than units
+    ([65] * 9 + [66], 16, 16, 64, False),  # halves would not all have one
+    ([65, 66, 65, 65, 65], 28, 4, 128, True),  # they would, but two key tiles do not pay for them
+    # neither: items of four wave tiles that may not all have one
+    ([129, 130, 129, 129, 129], 32, 32, 128, True),
 ])
-def test_a_unit_for_every_item(lengths, hq, hkv, d, causal):
+def test_a_unit_for_every_item(lengths, hq, hkv, d, causal, batch_rules):
     """Batches so small that items have compute units of their own, on both sides of where items are halved and of where they
     have waves that load: against the oracle, the same bits from a work list and for a call that shares the chip, and with keys far
     out of the fast path's range at either end of the sequences.  Loading waves change no bit: the same sequences in a larger batch."""
     hydra = _hydra()
+    halved = batch_rules.halved_items(d, len(lengths), sum(lengths), hq, hkv, UNITS)
+    loading = batch_rules.loading_waves(int(causal), len(lengths), sum(lengths), max(lengths), hq, hkv, UNITS)
+    sizes = (tuple(lengths), hq, hkv, d)
+    assert halved == (sizes in HALVED) and loading == (halved or sizes != ((129, 130, 129, 129, 129), 32, 32, 128))
     w = si.custom(lengths, hq, hkv, d, causal, seed=3 * sum(lengths) + hq)
     q, k, v = si.make_qkv(w)
     dev = torch.device("cuda:0")
@@ -374,7 +387,7 @@ def test_a_unit_for_every_item(lengths, hq, hkv, d, causal):
 @pytest.mark.parametrize("batch,hkv", [(2, 1), (4, 1), (2, 2), (1, 2), (1, 4)])
 @pytest.mark.parametrize("d", [64, 80, 128])
 @pytest.mark.parametrize("causal", [False, True])
-def test_few_pairs_of_one_length(batch, hkv, d, causal):
+def test_few_pairs_of_one_length(batch, hkv, d, causal, batch_rules):
     """Two or four (sequence, KV head) pairs of one length with more than 32 items each, in halved items, with loading waves and without:
     the oracle, and the same bits from a work list, over outputs of NaN."""
     hydra = _hydra()
@@ -382,6 +395,9 @@ def test_few_pairs_of_one_length(batch, hkv, d, causal):
     group, pairs = 16, batch * hkv
     for tiles in (5, 40 // pairs, 80 // pairs):  # of 32 tokens: 40 items of two wave tiles per pair; 160 of four together; 320
         w = si.custom([32 * tiles - 7] * batch, group * hkv, hkv, d, causal, seed=tiles + 10 * pairs + batch)
+        sizes = (batch, w.total_tokens, w.max_seqlen, group * hkv, hkv, UNITS)
+        assert batch_rules.halved_items(d, batch, w.total_tokens, *sizes[3:]) == (tiles == 5)
+        assert batch_rules.loading_waves(int(causal), *sizes) == (tiles <= 40 // pairs or (causal and batch == 1))
         q, k, v = si.make_qkv(w)
         qd, kd, vd, cu = q.to(dev), k.to(dev), v.to(dev), torch.from_numpy(w.cu_seqlens).to(dev)
         out, listed = torch.full_like(qd, float("nan")), torch.full_like(qd, float("nan"))
