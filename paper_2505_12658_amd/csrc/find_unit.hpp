@@ -91,8 +91,8 @@ __device__ __forceinline__ bool find_unit(const int32_t* cu, int batch, int n_kv
     // 64 9.71 -> 9.49, 12 of them 28.0 -> 27.6; one request of 558 tokens, 28 / 4 heads of 128, 12.58 -> 12.28, of 2000 39.9 -> 39.7).
     const int n = __builtin_amdgcn_readfirstlane(units(first_len));
     if (n <= 0) return false;
-    if (batch == 1 && pairs < kXcds && kXcds % pairs == 0 && n > kDieUnits) {
-      // one request: its pairs in turn, which gives each die one pair, or a part of one (through take_entry, whose counts take
+    if (batch == 1 && pairs < kXcds && (pairs & (pairs - 1)) == 0 && n > kDieUnits) {
+      // one request of 1, 2 or 4 KV heads: its pairs in turn, which gives each die one pair, or a part of one (through take_entry, whose counts take
       // a workgroup half a microsecond: 28 / 4 heads of 128, 700 tokens 14.3 us, 13.8 so; in halved items 400 tokens 9.1 and 8.7)
       kv_head = (int)blockIdx.x % pairs;
       unit = (int)blockIdx.x / pairs;
