@@ -128,7 +128,8 @@ int hydra_attn_varlen_fwd_prebuilt(const void* q, const void* k, const void* v, 
  *        (3 at head_dim 64, else 2) mean that number.  With 1, half (two thirds at head_dim 64) of every
  *        compute unit's registers and most of its LDS stay free for the other stream's kernels.
  *        Batches of so few tokens that there are compute units for every 64 rows of a KV head's queries (however the tokens
- *        are divided among the sequences) start one workgroup for every 64 such rows, whatever the value: no
+ *        are divided among the sequences; sequences of 64 tokens and fewer apart, at head_dim 128 of 128 and fewer where
+ *        they take most of the units) start one workgroup for every 64 such rows, whatever the value: no
  *        more workgroups than compute units; only at head_dim 64 do two fit one unit.  A workgroup has no more of the
  *        registers than above, but 67, 92 and 131 KB of the 160 KB of LDS at head_dim 64, 80 and 128.  Beside one of
  *        head_dim 128 workgroups of up to 29 KB find room: the paged call's decode kernel at head_dim 64 (18 KB), not at

@@ -490,7 +490,7 @@ __device__ __forceinline__ bool attn_item_loop(const AttnArgs& a, const Src& src
   int f = f0 + wave_tile;
   const bool active = f < n_wave_tiles;
   if (!active) f = n_wave_tiles - 1;
-  // (head_dim 64 and a reciprocal: 32 images of 577 tokens with 16 heads 59.4 -> 59.0 us, 9 of them 19.2 -> 19.1; two teams: causal requests of 200 tokens
+  // (head_dim 64 and a reciprocal: 32 images of 577 tokens with 16 heads 59.4 -> 59.0 us in a run of its own, within the spread of others; two teams: causal requests of 200 tokens
   // 6.83 -> 6.68, but one image 6.53 -> 6.59; head_dim 128 with four wave tiles, a request of 1000 tokens 16.0 -> 16.3.  One item per
   // workgroup only: over many items the causal kernel of head_dim 64 would spill vector registers for it)
   constexpr bool kByReciprocal = Src::kOneItem && !Src::kPaged && (TEAMS > 1 ? CAUSAL : D == 64);

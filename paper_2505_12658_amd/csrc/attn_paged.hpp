@@ -1166,15 +1166,14 @@ __device__ __forceinline__ void run_place(const PagedArgs& a, unsigned char* sme
     {
       int c = (kFirstLayer * 2 - n_rows_wgs) / 2;
       c = (c < a.n_tile_wgs ? c : a.n_tile_wgs) & ~7;  // (places only change hands with ids that the grid has; a multiple of 8: KV heads keep their dies)
-      const int id = place;
-      if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && id >= kFirstLayer - c && id < n_rows_wgs + c) {
+      if (n_rows_wgs > kFirstLayer && n_rows_wgs < 2 * kFirstLayer && place >= kFirstLayer - c && place < n_rows_wgs + c) {
         bool far = false;
         for (int r = (int)threadIdx.x; r < a.batch; r += 256) {
           int q_len, kv_len;
           lengths_of(r, q_len, kv_len);
           far = far || (q_len * a.group > kRows && kv_len > kLongChain * kKvTileRows);
         }
-        if (__syncthreads_or(far)) place = id < kFirstLayer ? n_rows_wgs + id - (kFirstLayer - c) : id - c;
+        if (__syncthreads_or(far)) place = place < kFirstLayer ? n_rows_wgs + place - (kFirstLayer - c) : place - c;
       }
     }
     if (place < n_rows_wgs) {

@@ -1,4 +1,4 @@
-// Which form of a kernel a batch takes, where that follows from what the host knows of it: whole-number arithmetic on the sizes of a call,
+// Which form of a kernel a batch takes, where that follows from what the host knows of it: arithmetic on the sizes of a call,
 // compiled for the host only, so that a test can ask it for any batch.
 #pragma once
 #include <stdint.h>
