@@ -699,13 +699,21 @@ WIDE_CASES = [
     ([1] * 20 + [101] + [5] * 50, [60] * 20 + [101] + [5 + 3 * i for i in range(50)], 28, 4, 128, 16),
     ([1, 101, 1] + [5] * 50, [200, 101, 60] + [5 + 3 * i for i in range(50)], 28, 4, 64, 16),
 ]
+FOUR_WAVE_CASES = [
+    # of the same kind, but with more chains than pay, longer contexts, or chunks that the host cannot count on
+    ([1] * 101 + [250], [6 * i + 3 for i in range(101)] + [700], 5, 5, 64, 16),
+    ([64] + [33] * 20, [64] + [33 + 20 * i for i in range(20)], 64, 4, 64, 16),
+    ([64] + [33] * 30, [64] + [33] * 30, 28, 4, 128, 16),
+    ([1, 70, 1], [30, 140, 200], 4, 2, 128, 4),
+    ([0, 1, 100, 5, 0, 1], [4, 20, 140, 5, 0, 90], 7, 1, 128, 16),
+]
 
 
-@pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: f"n{len(c[0])}-q{sum(c[0])}-kv{max(c[1])}-h{c[2]}k{c[3]}-d{c[4]}-b{c[5]}")
+@pytest.mark.parametrize("case", WIDE_CASES + FOUR_WAVE_CASES, ids=lambda c: f"n{len(c[0])}-q{sum(c[0])}-kv{max(c[1])}-h{c[2]}k{c[3]}-d{c[4]}-b{c[5]}")
 @pytest.mark.parametrize("planted", [False, True])
 def test_hybrid_batches_in_wide_workgroups(case, planted, batch_rules):
-    """Hybrid batches that run in workgroups of eight waves, which batches of more than 128 requests do not: the same requests with others
-    that have no new token.  The oracle, and the same bits (without splits, which follow the number of requests) unless
+    """Hybrid batches on both sides of the rule for workgroups of eight waves, which batches of more than 128 requests never take: the same
+    requests with others that have no new token.  The oracle, and the same bits (without splits, which follow the number of requests) unless
     chains past the end of the grid take the plain form."""
     q_lens, kv_lens, hq, hkv, d, bs = case
     h = si.HybridBatch("wide", q_lens, kv_lens, hq, hkv, d, block_size=bs, seed=sum(q_lens))
@@ -724,11 +732,11 @@ def test_hybrid_batches_in_wide_workgroups(case, planted, batch_rules):
     rule.restype, rule.argtypes = ctypes.c_int64, [ctypes.c_int] * 6 + [ctypes.c_int64]
     group, keys = hq // hkv, tables.shape[1] * bs
     workgroups = rule(h.batch, h.total_q, h.max_q_len, group, hkv, 1, keys)
-    assert workgroups > 0 and rule(padded.batch, h.total_q, h.max_q_len, group, hkv, 1, keys) == 0
+    assert (workgroups > 0) == (case in WIDE_CASES) and rule(padded.batch, h.total_q, h.max_q_len, group, hkv, 1, keys) == 0
     chains = hkv * sum(-(-(-(-n // 32) * group) // 4) for n in q_lens if n * group > 32)
     steps = hkv * sum(0 < n * group <= 32 for n in q_lens)
-    past_the_grid = chains > workgroups
-    assert past_the_grid or chains + max((steps + 1) // 2, min(steps, 256 - chains)) + 15 <= workgroups
+    past_the_grid = 0 < workgroups < chains
+    assert workgroups == 0 or past_the_grid or chains + max((steps + 1) // 2, min(steps, 256 - chains)) + 15 <= workgroups
     assert past_the_grid == (case in WIDE_CASES[-3:])
 
     want = _want(h, q, kc, vc, tables)
